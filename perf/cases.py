@@ -340,4 +340,7 @@ def tolerance(case):
         return {"rel": 1e-6, "max": 4e-6}                    # 1.7e-7, 9e-7
     # scores: 2.3e-7 and 2.5e-6 between orders, up to 3e-6 of the mean against float64.  Two candidates within that
     # of each other may change places at the edge of a budget, which moves the rows between them: one head of 112.
-    return {"rel": 1e-6, "max": 1.2e-5, "differ": 0.01}
+    # Keys without a common direction leave a redundancy near 0, the difference of two equal sums of squares: 1.4e-6.
+    if c["keys"] == "iid":
+        return {"rel": 1e-5, "max": 4e-5, "differ": 0.01}
+    return {"rel": 2e-6, "max": 1.2e-5, "differ": 0.01}
