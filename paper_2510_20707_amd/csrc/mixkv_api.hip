@@ -10,11 +10,11 @@ namespace mixkv {
 int stream_chunk_keys(int dtype, int D);
 int max_adaptive_heads();
 bool mixsel_supported(const Shape &s);
-hipError_t launch_topsel(const Shape &s, const LayerOutTable &out, char *ws, const Workspace &w, int64_t unit0, int nunits,
+hipError_t launch_topsel(const Shape &s, const LayerOutTable &out, char *ws, const CandLists &cl, int64_t unit0, int nunits,
                          int cand_m, const int32_t *budgets, hipStream_t st);
 hipError_t launch_mixsel(const Shape &s, bool select, const LayerOutTable &out, char *ws, const Workspace &w,
                          int64_t unit0, int nunits, const LayerInTable &in, int gather_eb, int cand_m,
-                         const int32_t *budgets, hipStream_t st);
+                         const CandLists &cl, const int32_t *budgets, hipStream_t st);
 
 static size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
@@ -170,14 +170,22 @@ static mixkv_status run(const mixkv_params *params, const mixkv_layer_in *in, mi
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u)) return MIXKV_ERR_INVALID_ARG;
     if (workspace_bytes < w.total) return MIXKV_ERR_WORKSPACE_TOO_SMALL;
   }
-  const bool lists_fit = workspace && !(reinterpret_cast<uintptr_t>(workspace) & 255u) && workspace_bytes >= w.total;
+  const bool ws_given = workspace && !(reinterpret_cast<uintptr_t>(workspace) & 255u);
+  const bool lists_fit = ws_given && workspace_bytes >= w.total;
+  // Selection alone on a workspace of the full size has the per-key rows too: room for lists of any length.
+  Workspace w_full = w;
+  if (select_only) carve_workspace(s, units, &w_full);
+  const bool rows_fit = ws_given && workspace_bytes >= w_full.total;
+  int max_head_rows = s.B;                              // rows the best-endowed head keeps
   if (stage_budgets) {
     if (!params->head_budgets) return MIXKV_ERR_INVALID_ARG;
+    max_head_rows = s.W;
     for (int l = 0; l < n_layers; ++l) {
       int64_t sum = 0;
       for (int h = 0; h < s.hkv; ++h) {
         const int32_t b = params->head_budgets[(size_t)l * s.hkv + h];
         if (b < s.W || b > s.N) return MIXKV_ERR_INVALID_ARG;
+        if (b > max_head_rows) max_head_rows = b;
         sum += b;
       }
       if (sum > (int64_t)s.hkv * s.B) return MIXKV_ERR_INVALID_ARG;
@@ -224,6 +232,25 @@ static mixkv_status run(const mixkv_params *params, const mixkv_layer_in *in, mi
     if (upload_ints(params->head_budgets, n_layers * s.hkv, dst, stream) != hipSuccess) return MIXKV_ERR_HIP;
     budgets_dev = dst;
   }
+  // How the rows are mixed and selected.
+  //   Short rows (one workgroup holds a head's candidates): one fused kernel mixes the scores and selects; selection
+  //   alone runs the same code on the caller's scores.
+  //   Long rows: several workgroups per head, whose lists one workgroup per head merges.
+  // In fixed and per-head mode these write the head's final rows; in head-adaptive mode every head hands its
+  // best cand_m candidates to a split kernel.  Scores reach memory only if somebody reads them (the caller, or the
+  // kernels that rank whole rows: rows or budgets too long for the lists, or no workspace to hold them).
+  const bool do_select = (stages & kSelect) != 0, short_row = mixsel_supported(s);
+  const int best = do_select && s.adaptive ? adaptive_candidates(s) : 0;
+  const CandLists lists = rows_fit ? CandLists{w_full.araw, w_full.vnorm, s.Npad} : CandLists{w.cand_idx, w.cand_key, kMaxCandPerHead};
+  const bool lists_hold = rows_fit || (lists_fit && best <= kMaxCandPerHead);
+  const SegPlan cut_sel = (!short_row && rows_fit && do_select) ? plan_segments(s, s.adaptive ? best : max_head_rows - s.W) : SegPlan{0, 0, 0};
+  const SegPlan cut_mix = cut_sel.seg > 0 ? cut_sel : ((!short_row && (stages & kScore)) ? plan_segments(s, 0) : SegPlan{0, 0, 0});
+  const int cand_m = lists_hold && (short_row || cut_sel.seg > 0) ? best : 0;
+  const bool long_select = cut_sel.seg > 0 && (!s.adaptive || cand_m > 0);
+  const bool fused = (stages & kScore) && short_row;
+  const bool fused_select = fused && do_select && !s.adaptive;
+  const bool fused_gather = fused_select && (stages & kGather);   // the selecting workgroup also copies its rows
+  const bool topsel = select_only && short_row && (!s.adaptive || cand_m > 0);
   StageTimer timed;
   timed.stream = stream;
   timed.ms = stage_ms;
@@ -238,15 +265,6 @@ static mixkv_status run(const mixkv_params *params, const mixkv_layer_in *in, mi
     std::memset(&to, 0, sizeof(to));
     std::memset(&tl, 0, sizeof(tl));
     const int64_t unit0 = (int64_t)l0 * s.units_per_layer;
-    // One fused kernel mixes the scores and, in fixed-budget mode, selects; scores reach memory
-    // only if somebody reads them (the caller, or the separate selection kernels).
-    const bool fused = (stages & kScore) && mixsel_supported(s);
-    const bool fused_select = fused && (stages & kSelect) && !s.adaptive;
-    const bool fused_gather = fused_select && (stages & kGather);   // the selecting workgroup also copies its rows
-    // head-adaptive mode: the fused kernel hands every head's best candidates to a small split kernel
-    // selection alone: the same selection code on the caller's scores, one workgroup per head
-    const bool topsel = select_only && mixsel_supported(s) && (!s.adaptive || (lists_fit && adaptive_candidates(s) > 0));
-    const int cand_m = ((fused || topsel) && (stages & kSelect) && s.adaptive) ? adaptive_candidates(s) : 0;
     for (int l = 0; l < nl; ++l) {
       if (in) {
         const mixkv_layer_in &li = in[l0 + l];
@@ -256,7 +274,7 @@ static mixkv_status run(const mixkv_params *params, const mixkv_layer_in *in, mi
       }
       const mixkv_layer_out &lo = out[l0 + l];
       float *scores = lo.scores;
-      if (!scores && !fused_select && cand_m == 0)
+      if (!scores && !fused_select && !long_select && cand_m == 0)
         scores = reinterpret_cast<float *>(ws + w.scores) + (unit0 + (int64_t)l * s.units_per_layer) * s.N;
       to.l[l] = LayerOut{scores, lo.redundancy, lo.indices, lo.counts, lo.offsets, lo.K_out, lo.V_out};
     }
@@ -273,17 +291,28 @@ static mixkv_status run(const mixkv_params *params, const mixkv_layer_in *in, mi
             return launch_attn(s, params->dtype, ti, to, tl, ws, w, unit0, nunits, grid, slot0, stream);
           })) &&
           ok(timed(2, [&] {
-            return fused ? launch_mixsel(s, fused_select || cand_m > 0, to, ws, w, unit0, nunits, ti,
-                                         fused_gather ? eb : 0, cand_m, budgets_l0, stream)
-                         : launch_mix(s, ti, to, ws, w, unit0, nunits, stream);
+            if (fused)
+              return launch_mixsel(s, fused_select || cand_m > 0, to, ws, w, unit0, nunits, ti, fused_gather ? eb : 0, cand_m, lists, budgets_l0,
+                                   stream);
+            if (cut_mix.seg > 0) return launch_segmix(s, cut_mix, long_select, ti, to, ws, w, unit0, nunits, cand_m, budgets_l0, stream);
+            return launch_mix(s, ti, to, ws, w, unit0, nunits, stream);
           }));
     }
     if (result == MIXKV_OK && topsel)
-      ok(timed(3, [&] { return launch_topsel(s, to, ws, w, unit0, nunits, cand_m, budgets_l0, stream); }));
-    if (result == MIXKV_OK && (stages & kSelect) && !fused_select && !(topsel && !s.adaptive))
+      ok(timed(3, [&] { return launch_topsel(s, to, ws, lists, unit0, nunits, cand_m, budgets_l0, stream); }));
+    if (result == MIXKV_OK && long_select)
       ok(timed(3, [&] {
-        return cand_m > 0 ? launch_select_candidates(s, to, ws, w, unit0, nl, cand_m, stream) : launch_select(s, to, nl, budgets_l0, stream);
+        if (select_only) {
+          const hipError_t e = launch_segtop(s, cut_sel, to, ws, w_full, unit0, nunits, cand_m, budgets_l0, stream);
+          if (e != hipSuccess) return e;
+        }
+        const hipError_t e = launch_mergetop(s, cut_sel, to, ws, w_full, lists, unit0, nunits, cand_m, budgets_l0, stream);
+        return e != hipSuccess || cand_m == 0 ? e : launch_select_candidates(s, to, ws, lists, unit0, nl, cand_m, stream);
       }));
+    else if (result == MIXKV_OK && do_select && cand_m > 0)
+      ok(timed(3, [&] { return launch_select_candidates(s, to, ws, lists, unit0, nl, cand_m, stream); }));
+    else if (result == MIXKV_OK && do_select && !fused_select && !topsel && !long_select)
+      ok(timed(3, [&] { return launch_select(s, to, nl, budgets_l0, stream); }));
     if (result == MIXKV_OK && (stages & kGather) && !fused_gather)
       ok(timed(4, [&] { return launch_gather(s, params->dtype, ti, to, nl, stream); }));
     if (result != MIXKV_OK) break;

@@ -10,8 +10,8 @@ constexpr int kWave = 64;
 constexpr int kTileKeys = 32;          // keys per MFMA tile
 constexpr int kLayersPerLaunch = 32;   // pointer-table entries that fit in one kernel-argument block
 constexpr int kSelectThreads = 1024;
-constexpr int kMaxCandPerHead = 1024;   // head-adaptive budgets: candidates a head hands to the budget split
-constexpr int kMaxCandPerGroup = 4096;  // ... and all heads of one (layer, batch item) together
+constexpr int kMaxCandPerHead = 1024;   // head-adaptive budgets: list length of the selection-only workspace layout
+constexpr int kMaxSegs = 32;            // segments a long row is cut into at most
 constexpr int kMaxStreamGrid = 1024;    // upper bound on the workgroups of a streaming kernel launch
 
 // Per-layer device pointers handed to the kernels by value.
@@ -63,11 +63,25 @@ struct Workspace {
   size_t vnorm;          // float  [units][Npad]             |V_i|
   size_t araw;           // float  [units][Npad]             window/group mean attention before pooling
   size_t sdiv;           // float  [units][Npad]             K_i . Kbar (the mix kernel applies -1/|K_i|)
-  size_t cand_idx;       // int32  [units][kMaxCandPerHead]  adaptive mode: every head's best candidates, ascending
-  size_t cand_key;       // uint32 [units][kMaxCandPerHead]  ... and their order-preserving keys
+  size_t cand_idx;       // int32  [units][kMaxCandPerHead]  adaptive mode, selection alone: every head's best
+  size_t cand_key;       // uint32 [units][kMaxCandPerHead]  candidates, ascending, and their order-preserving keys
   size_t scores;         // float  [units][N]                used when the caller passes no scores buffer
   size_t total;
 };
+
+// Where the heads' candidate lists for the head-adaptive split live: positions and order keys of unit u at
+// idx / key (byte offsets into the workspace) + u * stride entries.
+struct CandLists {
+  size_t idx, key;
+  int64_t stride;
+};
+
+// Bit 31 of a candidate-list entry: the candidate is one of its head's `floor` best.
+constexpr uint32_t kFloorFlag = 0x80000000u;
+
+// How a long row is cut over several workgroups: nseg segments of seg candidates, whose lists have `merge` entries
+// together (seg 0: the row cannot be cut).
+struct SegPlan { int seg, nseg, merge; };
 
 mixkv_status make_shape(const mixkv_params *p, Shape *s);
 void carve_workspace(const Shape &s, int64_t units, Workspace *w, bool select_only = false);
@@ -108,9 +122,20 @@ hipError_t launch_select(const Shape &s, const LayerOutTable &out, int nlayers, 
 // call neither synchronises nor depends on how the host memory was allocated).
 hipError_t upload_ints(const int32_t *host, int n, int32_t *dev, hipStream_t st);
 // Head-adaptive budget split from the per-head candidate lists (cand_m entries each) in the workspace.
-int adaptive_candidates(const Shape &s);   // cand_m, or 0 if the lists would be too long
-hipError_t launch_select_candidates(const Shape &s, const LayerOutTable &out, char *ws, const Workspace &w, int64_t unit0,
+int adaptive_candidates(const Shape &s);   // cand_m, 0 if no head keeps anything but its window
+hipError_t launch_select_candidates(const Shape &s, const LayerOutTable &out, char *ws, const CandLists &cl, int64_t unit0,
                                     int nlayers, int cand_m, hipStream_t st);
+hipError_t launch_split_stream(const Shape &s, const LayerOutTable &out, char *ws, const CandLists &cl, int64_t unit0, int nlayers,
+                               int cand_m, hipStream_t st);
+// Long rows (mixkv_longrow.hip): the cut for up to `keep` kept candidates per head, the mix (and with `select` the
+// segments' lists), the lists from scores in memory, and their merge.
+SegPlan plan_segments(const Shape &s, int keep);
+hipError_t launch_segmix(const Shape &s, const SegPlan &pl, bool select, const LayerInTable &in, const LayerOutTable &out, char *ws,
+                         const Workspace &w, int64_t unit0, int nunits, int cand_m, const int32_t *budgets, hipStream_t st);
+hipError_t launch_segtop(const Shape &s, const SegPlan &pl, const LayerOutTable &out, char *ws, const Workspace &w, int64_t unit0,
+                         int nunits, int cand_m, const int32_t *budgets, hipStream_t st);
+hipError_t launch_mergetop(const Shape &s, const SegPlan &pl, const LayerOutTable &out, char *ws, const Workspace &w, const CandLists &cl,
+                           int64_t unit0, int nunits, int cand_m, const int32_t *budgets, hipStream_t st);
 hipError_t launch_gather(const Shape &s, int dtype, const LayerInTable &in, const LayerOutTable &out, int nlayers,
                          hipStream_t st);
 

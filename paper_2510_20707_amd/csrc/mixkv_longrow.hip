@@ -1,0 +1,378 @@
+// Mixing and selection of long rows: several workgroups per head.
+//
+// A head's candidates are cut into segments of THREADS * EPT, one workgroup each.
+//   segstat_kernel   pools the segment's attention and takes its share of the head's statistics;
+//   segmix_kernel    folds the shares, forms the segment's mixed scores and, if a selection follows, hands the
+//                    segment's best `keep` candidates on as a list (ascending positions, with their order keys);
+//   segtop_kernel    the same lists from scores that are already in memory (mixkv_select);
+//   mergetop_kernel  one workgroup per head selects from the head's lists laid end to end.
+// A head that keeps `keep` candidates keeps none that is not among the `keep` best of its own segment, and the
+// lists hold equal scores in ascending position, so the result is the one a ranking of the whole row gives.
+//
+// Bound: HBM (four rows of floats per key, read by the statistics and again by the mix; the diversity and the
+// intrinsic score stay in registers from then on).  One 130 688-token prompt of 28 layers and 4 KV heads (234 MB of
+// rows, budget 128, head-adaptive): statistics 51 us (4.6 TB/s), mix and lists 83, merge 33, split 9.  One workgroup
+// per head for the mix and one per layer for the selection left most of the chip idle: 784 + 2 583 us.
+// At 32 768 tokens (448 heads) the three kernels take 155 us and mixsel_kernel, which holds a whole head, 150.
+//
+// Paper: Sec. 3.2 Eq. 2, Sec. 3.3 Eq. 5, Sec. 3.1 / Algorithm 1 (TopB), as in mixsel_kernel.
+#include "mixkv_topsel.h"
+
+namespace mixkv {
+
+constexpr int kHalo = 32;                // candidates on either side of a segment that the pooling window may reach
+constexpr int kMaxMerge = 1024 * 28;     // list entries mergetop_kernel can hold (LDS)
+
+// LDS slot of a float: four pad words per 32 keep every aligned group of four together and spread the groups of
+// owners a power of two apart over the banks.
+__device__ __forceinline__ int slot4(int i) { return i + ((i >> 5) << 2); }
+__host__ __device__ constexpr int slots4(int n) { return n + n / 32 * 4 + 4; }
+
+// Shares of a head's statistics, one per segment (in the rows that held the softmax offsets: the second pass was
+// their last reader).  Sums of intrinsic score and diversity are taken relative to the head's first candidate, so
+// that a range far from zero does not cost them their low bits.
+struct SegStat {
+  float sum_a, sum_v, sum_d, min_v, min_d, max_v, max_d;
+  float ref;                             // even segments: the intrinsic score of candidate 0, odd ones: its diversity
+};
+__device__ __forceinline__ SegStat *seg_stats(const Shape &s, char *ws, const Workspace &w, int64_t unit) {
+  static_assert(sizeof(SegStat) * kMaxSegs <= 256 * sizeof(float), "a head's shares fit its row of softmax offsets");
+  return reinterpret_cast<SegStat *>(reinterpret_cast<float *>(ws + w.nb) + unit * s.nb_rows);
+}
+
+// Loads the raw attention of the segment [s0, s0 + THREADS * EPT) and its halo into LDS (out-of-range
+// candidates hold the pooling's neutral element) and leaves the pooled values of the thread's candidates in
+// a[]: group g of four belongs to thread g % THREADS, so that all loads are coalesced.  Ends past its reads of LDS
+// only after the caller's next barrier.
+template <int THREADS, int EPT>
+__device__ __forceinline__ void load_pooled(const Shape &s, const float *araw, int s0, float (&a)[EPT], float *a_s) {
+  const int tid = threadIdx.x, Nc = s.Nc;
+  const bool pooled = s.pool != MIXKV_POOL_NONE && s.pool_k > 1, is_max = s.pool == MIXKV_POOL_MAX;
+  const float fill = is_max ? -INFINITY : 0.f;          // out-of-range taps: ignored by max, zero for avg
+  if (tid < 2 * kHalo) {
+    const int i = tid < kHalo ? s0 - kHalo + tid : s0 + THREADS * EPT + tid - kHalo;
+    const int li = tid < kHalo ? tid : THREADS * EPT + tid;
+    a_s[slot4(li)] = (pooled && i >= 0 && i < Nc) ? araw[i] : fill;
+  }
+#pragma unroll
+  for (int g = 0; g < EPT / 4; ++g) {
+    const int li = (g * THREADS + tid) * 4, i = s0 + li;
+    float4 r = make_float4(fill, fill, fill, fill);
+    if (i < Nc) {                                       // the rows are padded past the last group
+      r = *reinterpret_cast<const float4 *>(araw + i);
+      if (i + 1 >= Nc) r.y = fill;
+      if (i + 2 >= Nc) r.z = fill;
+      if (i + 3 >= Nc) r.w = fill;
+    }
+    a[4 * g] = r.x; a[4 * g + 1] = r.y; a[4 * g + 2] = r.z; a[4 * g + 3] = r.w;
+    *reinterpret_cast<float4 *>(&a_s[slot4(kHalo + li)]) = r;
+  }
+  __syncthreads();
+  if (!pooled) return;
+  const int hk = s.pool_k >> 1;
+  if (hk <= 3) {
+    // sliding window in registers over each group: its own values and the aligned groups on either side
+#pragma unroll
+    for (int g = 0; g < EPT / 4; ++g) {
+      const int li = kHalo + (g * THREADS + tid) * 4;
+      const float4 lo = *reinterpret_cast<const float4 *>(&a_s[slot4(li - 4)]);
+      const float4 hi = *reinterpret_cast<const float4 *>(&a_s[slot4(li + 4)]);
+      const float win[10] = {lo.y, lo.z, lo.w, a[4 * g], a[4 * g + 1], a[4 * g + 2], a[4 * g + 3], hi.x, hi.y, hi.z};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        float acc;
+        if (is_max) {
+          acc = win[3 + e];
+          if (hk >= 1) acc = fmaxf(acc, fmaxf(win[2 + e], win[4 + e]));
+          if (hk >= 2) acc = fmaxf(acc, fmaxf(win[1 + e], win[5 + e]));
+          if (hk >= 3) acc = fmaxf(acc, fmaxf(win[e], win[6 + e]));
+        } else {                                        // taps from left to right
+          acc = 0.f;
+          if (hk >= 3) acc += win[e];
+          if (hk >= 2) acc += win[1 + e];
+          if (hk >= 1) acc += win[2 + e];
+          acc += win[3 + e];
+          if (hk >= 1) acc += win[4 + e];
+          if (hk >= 2) acc += win[5 + e];
+          if (hk >= 3) acc += win[6 + e];
+          acc = acc / (float)s.pool_k;
+        }
+        a[4 * g + e] = acc;
+      }
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
+      const int li = kHalo + ((e >> 2) * THREADS + tid) * 4 + (e & 3);
+      float acc = a_s[slot4(li - hk)];
+      for (int j = li - hk + 1; j <= li + hk; ++j) acc = is_max ? fmaxf(acc, a_s[slot4(j)]) : acc + a_s[slot4(j)];
+      a[e] = is_max ? acc : acc / (float)s.pool_k;
+    }
+  }
+}
+
+template <int THREADS, int EPT>
+__global__ __launch_bounds__(THREADS) void segstat_kernel(Shape s, char *ws, Workspace w, int64_t unit0, int nseg) {
+  constexpr int SEG = THREADS * EPT, NW = THREADS / 64;
+  __shared__ __align__(16) float a_s[slots4(SEG + 2 * kHalo)];
+  __shared__ MsScratch sc;
+  const int ul = blockIdx.x / nseg, seg = blockIdx.x - ul * nseg, s0 = seg * SEG, tid = threadIdx.x;
+  const int64_t unit = unit0 + ul;
+  const UnitRows rows(s, ws, w, unit);
+  float4 v0, d0;
+  rows.load_vd(0, v0, d0);
+  const float vref = v0.x, dref = d0.x;
+  float st[7] = {0.f, 0.f, 0.f, INFINITY, INFINITY, -INFINITY, -INFINITY};   // sums a, v, d | min v, d | max v, d
+#pragma unroll
+  for (int g = 0; g < EPT / 4; ++g) {
+    const int i = s0 + (g * THREADS + tid) * 4;
+    float4 vr, dr;
+    rows.load_vd(i, vr, dr);
+    const float v4[4] = {vr.x, vr.y, vr.z, vr.w}, d4[4] = {dr.x, dr.y, dr.z, dr.w};
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (i + j < s.Nc) {
+        st[1] += v4[j] - vref; st[2] += d4[j] - dref;
+        st[3] = fminf(st[3], v4[j]); st[4] = fminf(st[4], d4[j]);
+        st[5] = fmaxf(st[5], v4[j]); st[6] = fmaxf(st[6], d4[j]);
+      }
+  }
+  float a[EPT];
+  load_pooled<THREADS, EPT>(s, rows.araw, s0, a, a_s);
+#pragma unroll
+  for (int e = 0; e < EPT; ++e)
+    if (s0 + ((e >> 2) * THREADS + tid) * 4 + (e & 3) < s.Nc) st[0] += a[e];
+  block_reduce_mixed<NW, 3, 2, 2>(st, sc);
+  if (tid == 0) seg_stats(s, ws, w, unit)[seg] = SegStat{st[0], st[1], st[2], st[3], st[4], st[5], st[6], (seg & 1) ? dref : vref};
+}
+
+// num / den to within half a unit in the last place, given rden = 1 / den
+__device__ __forceinline__ float quotient(float num, float den, float rden) {
+  const float q = num * rden;
+  return fmaf(fmaf(-q, den, num), rden, q);
+}
+
+// Candidates a head hands on from every segment: the rows it keeps besides the window (fixed and per-head
+// mode), or its candidates for the head-adaptive split.
+__device__ __forceinline__ int head_keep(const Shape &s, const int32_t *budgets, int layer, int h, int cand_m) {
+  return cand_m > 0 ? cand_m : (budgets ? budgets[layer * s.hkv + h] : s.B) - s.W;
+}
+
+// The segment's best min(keep, len) candidates, out of the scores in a_s (slot4(0) is candidate s0).
+template <int THREADS, int EPT>
+__device__ __forceinline__ void segment_list(const float *a_s, int s0, int len, int keep, int32_t *idx, uint32_t *ckey,
+                                             MsScratch &sc) {
+  const int base = threadIdx.x * EPT;
+  float a[EPT];
+#pragma unroll
+  for (int e = 0; e < EPT; e += 4) {
+    const float4 v = *reinterpret_cast<const float4 *>(&a_s[slot4(base + e)]);
+    a[e] = v.x; a[e + 1] = v.y; a[e + 2] = v.z; a[e + 3] = v.w;
+  }
+  top_select<THREADS, EPT>(a, len - base, s0 + base, min(keep, len), idx, ckey, 0, sc);
+}
+
+template <int THREADS, int EPT, bool SELECT>
+__global__ __launch_bounds__(THREADS) void segmix_kernel(Shape s, LayerInTable in, LayerOutTable out, char *ws, Workspace w,
+                                                         int64_t unit0, int nseg, int cand_m, const int32_t *budgets) {
+  constexpr int SEG = THREADS * EPT;
+  __shared__ __align__(16) float a_s[slots4(SEG + 2 * kHalo)];
+  __shared__ MsScratch sc;
+  const int ul = blockIdx.x / nseg, seg = blockIdx.x - ul * nseg, s0 = seg * SEG, tid = threadIdx.x, lane = tid & 63;
+  const int64_t unit = unit0 + ul;
+  const int layer = ul / s.units_per_layer, bh = ul - layer * s.units_per_layer, Nc = s.Nc;
+  const LayerOut O = out.l[layer];
+  const UnitRows rows(s, ws, w, unit);
+  if (tid == 0) { sc.ur[0] = 0xffffffffu; sc.ur[1] = 0u; }   // for the key range, read after later barriers
+
+  float v[EPT], d[EPT], a[EPT];
+#pragma unroll
+  for (int g = 0; g < EPT / 4; ++g) {
+    float4 vr, dr;
+    rows.load_vd(s0 + (g * THREADS + tid) * 4, vr, dr);
+    v[4 * g] = vr.x; v[4 * g + 1] = vr.y; v[4 * g + 2] = vr.z; v[4 * g + 3] = vr.w;
+    d[4 * g] = dr.x; d[4 * g + 1] = dr.y; d[4 * g + 2] = dr.z; d[4 * g + 3] = dr.w;
+  }
+  load_pooled<THREADS, EPT>(s, rows.araw, s0, a, a_s);
+
+  // ---- the head's statistics: lane l holds segment l's share, every wave folds them alike
+  const SegStat *shares = seg_stats(s, ws, w, unit);
+  SegStat x{0.f, 0.f, 0.f, INFINITY, INFINITY, -INFINITY, -INFINITY, 0.f};
+  if (lane < nseg) x = shares[lane];
+  const float sum_a = wave_reduce<WSum>(x.sum_a, 0.f), sum_v = wave_reduce<WSum>(x.sum_v, 0.f), sum_d = wave_reduce<WSum>(x.sum_d, 0.f);
+  const float vmin = wave_reduce<WMin>(x.min_v, INFINITY), dmin = wave_reduce<WMin>(x.min_d, INFINITY);
+  const float vmax = wave_reduce<WMax>(x.max_v, -INFINITY), dmax = wave_reduce<WMax>(x.max_d, -INFINITY);
+  const float vref = read_lane(x.ref, 0), dref = read_lane(x.ref, 1);
+  const float inv_n = 1.f / (float)Nc;
+  const float r = reinterpret_cast<const float *>(ws + w.rbar)[unit];
+  float wi, wd;
+  mix_weights(s.mix, r, s.mix == MIXKV_MIX_GIVEN_R ? in.l[layer].r_given[bh] : 0.f, wi, wd);
+  // mean((x - min) / den) = (sum(x - ref) + Nc (ref - min)) / (Nc den)
+  const float mean_ex = sum_a * inv_n;
+  const float vden = vmax - vmin + s.eps, dden = dmax - dmin + s.eps, rvden = 1.f / vden, rdden = 1.f / dden;
+  const float mean_in = (sum_v * inv_n + (vref - vmin)) / vden;
+  const float mean_dn = (sum_d * inv_n + (dref - dmin)) / dden;
+  const float f_in = rows.use_v ? mean_ex / (mean_in + s.eps) : 0.f;    // Sec. 3.2: scale VNorm to mean(s_ex)
+  const float mean_imp = rows.use_v ? mean_ex + f_in * mean_in : mean_ex;
+  const float f_div = mean_imp / (mean_dn + s.eps);                      // Sec. 3.3: scale diversity to mean(s_imp)
+  __syncthreads();                                      // the pooling is done with the raw attention: the scores replace it
+#pragma unroll
+  for (int g = 0; g < EPT / 4; ++g) {
+    float c[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int e = 4 * g + j;
+      const float imp = rows.use_v ? a[e] + quotient(v[e] - vmin, vden, rvden) * f_in : a[e];   // Eq. 2
+      c[j] = wi * imp + wd * (quotient(d[e] - dmin, dden, rdden) * f_div);                       // Eq. 5
+    }
+    *reinterpret_cast<float4 *>(&a_s[slot4((g * THREADS + tid) * 4)]) = make_float4(c[0], c[1], c[2], c[3]);
+  }
+  __syncthreads();
+  const int len = min(SEG, Nc - s0);
+  if (O.scores) {
+    float *scores = O.scores + (int64_t)bh * s.N;
+#pragma unroll
+    for (int k = 0; k < EPT; ++k) {
+      const int li = k * THREADS + tid;
+      if (li < len) scores[s0 + li] = a_s[slot4(li)];
+    }
+    if (seg == nseg - 1)
+      for (int i = Nc + tid; i < s.N; i += THREADS) scores[i] = INFINITY;
+  }
+  if constexpr (SELECT) {
+    // the list takes the place of the segment's own share of two rows that have been read
+    const int keep = head_keep(s, budgets, layer, bh % s.hkv, cand_m);
+    int32_t *idx = reinterpret_cast<int32_t *>(ws + w.sdiv) + unit * s.Npad + s0;
+    uint32_t *ckey = reinterpret_cast<uint32_t *>(ws + w.invnorm) + unit * s.Npad + s0;
+    if (keep > 0) segment_list<THREADS, EPT>(a_s, s0, len, keep, idx, ckey, sc);
+  }
+}
+
+template <int THREADS, int EPT>
+__global__ __launch_bounds__(THREADS) void segtop_kernel(Shape s, LayerOutTable out, char *ws, Workspace w, int64_t unit0,
+                                                         int nseg, int cand_m, const int32_t *budgets) {
+  constexpr int SEG = THREADS * EPT;
+  __shared__ __align__(16) float a_s[slots4(SEG)];
+  __shared__ MsScratch sc;
+  const int ul = blockIdx.x / nseg, seg = blockIdx.x - ul * nseg, s0 = seg * SEG, tid = threadIdx.x;
+  const int64_t unit = unit0 + ul;
+  const int layer = ul / s.units_per_layer, bh = ul - layer * s.units_per_layer, len = min(SEG, s.Nc - s0);
+  const float *scores = out.l[layer].scores + (int64_t)bh * s.N + s0;
+  if (tid == 0) { sc.ur[0] = 0xffffffffu; sc.ur[1] = 0u; }
+#pragma unroll
+  for (int k = 0; k < EPT; ++k) {
+    const int li = k * THREADS + tid;
+    a_s[slot4(li)] = li < len ? scores[li] : 0.f;
+  }
+  __syncthreads();
+  const int keep = head_keep(s, budgets, layer, bh % s.hkv, cand_m);
+  int32_t *idx = reinterpret_cast<int32_t *>(ws + w.sdiv) + unit * s.Npad + s0;
+  uint32_t *ckey = reinterpret_cast<uint32_t *>(ws + w.invnorm) + unit * s.Npad + s0;
+  if (keep > 0) segment_list<THREADS, EPT>(a_s, s0, len, keep, idx, ckey, sc);
+}
+
+// One workgroup per head: its rows (fixed and per-head mode) or its candidates for the head-adaptive split, out
+// of its segments' lists.  `seg` is the segment length the lists were made with.
+template <int THREADS, int EPT>
+__global__ __launch_bounds__(THREADS) void mergetop_kernel(Shape s, LayerOutTable out, char *ws, Workspace w, CandLists cl,
+                                                           int64_t unit0, int seg, int nseg, int cand_m, const int32_t *budgets) {
+  extern __shared__ __align__(16) float a_s[];
+  __shared__ MsScratch sc;
+  uint32_t *k_s = reinterpret_cast<uint32_t *>(a_s);
+  const int ul = blockIdx.x, tid = threadIdx.x;
+  const int64_t unit = unit0 + ul;
+  const int layer = ul / s.units_per_layer, bh = ul - layer * s.units_per_layer, h = bh % s.hkv, b = bh / s.hkv;
+  const LayerOut O = out.l[layer];
+  const int32_t *lidx = reinterpret_cast<const int32_t *>(ws + w.sdiv) + unit * s.Npad;
+  const uint32_t *lkey = reinterpret_cast<const uint32_t *>(ws + w.invnorm) + unit * s.Npad;
+  if (tid == 0) { sc.ur[0] = 0xffffffffu; sc.ur[1] = 0u; }
+  const int keep = head_keep(s, budgets, layer, h, cand_m), per = min(keep, seg);   // entries per list, the last one's may be fewer
+  const int n = per > 0 ? (nseg - 1) * per + min(per, s.Nc - (nseg - 1) * seg) : 0;
+  auto at = [&](int e) { const int g = e / per; return g * seg + (e - g * per); };
+  for (int e = tid; e < n; e += THREADS) k_s[slot4(e)] = lkey[at(e)];
+  __syncthreads();
+  const int base = tid * EPT;
+  uint32_t key[EPT];
+#pragma unroll
+  for (int e = 0; e < EPT; ++e) key[e] = base + e < n ? k_s[slot4(base + e)] : 0u;
+  auto pos = [&](int e) { return lidx[at(base + e)]; };
+  if (cand_m > 0) {
+    top_select_keys<THREADS, EPT>(key, n - base, cand_m, reinterpret_cast<int32_t *>(ws + cl.idx) + unit * cl.stride,
+                                  reinterpret_cast<uint32_t *>(ws + cl.key) + unit * cl.stride, s.floor_, sc, pos);
+    return;
+  }
+  int Bh, row0;
+  head_rows(s, budgets, layer, h, Bh, row0);
+  int32_t *idx = O.indices + (int64_t)b * s.hkv * s.B + row0;
+  if (keep > 0) top_select_keys<THREADS, EPT>(key, n - base, keep, idx, nullptr, 0, sc, pos);
+  finish_head(s, O, b, h, Bh, row0, idx, THREADS);
+}
+
+// ------------------------------------------------------------------------------------------------
+// launchers
+// ------------------------------------------------------------------------------------------------
+// The cut of a row of Nc candidates of which up to `keep` survive per head (0: no selection): the smallest
+// segments that give at most kMaxSegs of them, as long as the merge has no more than 16 384 entries to look at
+// (beyond that its one workgroup per head is the longer half); failing that the largest that fit it.
+SegPlan plan_segments(const Shape &s, int keep) {
+  SegPlan best{0, 0, 0};
+  for (int seg : {4096, 8192, 16384}) {
+    const int nseg = (s.Nc + seg - 1) / seg;
+    if (nseg < 2 || nseg > kMaxSegs) continue;
+    const int per = keep < seg ? keep : seg, last = s.Nc - (nseg - 1) * seg;
+    const int64_t n = (int64_t)(nseg - 1) * per + (per < last ? per : last);
+    if (n > kMaxMerge) continue;
+    best = SegPlan{seg, nseg, (int)n};
+    if (n <= 16384) break;
+  }
+  return best;
+}
+
+template <int THREADS, int EPT>
+static hipError_t launch_segmix_e(const Shape &s, const SegPlan &pl, bool select, const LayerInTable &in, const LayerOutTable &out,
+                                  char *ws, const Workspace &w, int64_t unit0, int nunits, int cand_m, const int32_t *budgets,
+                                  hipStream_t st) {
+  const dim3 grid((unsigned)(nunits * pl.nseg)), block(THREADS);
+  hipLaunchKernelGGL((segstat_kernel<THREADS, EPT>), grid, block, 0, st, s, ws, w, unit0, pl.nseg);
+  if (select) hipLaunchKernelGGL((segmix_kernel<THREADS, EPT, true>), grid, block, 0, st, s, in, out, ws, w, unit0, pl.nseg, cand_m, budgets);
+  else hipLaunchKernelGGL((segmix_kernel<THREADS, EPT, false>), grid, block, 0, st, s, in, out, ws, w, unit0, pl.nseg, 0, nullptr);
+  return hipGetLastError();
+}
+
+hipError_t launch_segmix(const Shape &s, const SegPlan &pl, bool select, const LayerInTable &in, const LayerOutTable &out, char *ws,
+                         const Workspace &w, int64_t unit0, int nunits, int cand_m, const int32_t *budgets, hipStream_t st) {
+  if (pl.seg == 4096) return launch_segmix_e<512, 8>(s, pl, select, in, out, ws, w, unit0, nunits, cand_m, budgets, st);
+  if (pl.seg == 8192) return launch_segmix_e<1024, 8>(s, pl, select, in, out, ws, w, unit0, nunits, cand_m, budgets, st);
+  return launch_segmix_e<1024, 16>(s, pl, select, in, out, ws, w, unit0, nunits, cand_m, budgets, st);
+}
+
+hipError_t launch_segtop(const Shape &s, const SegPlan &pl, const LayerOutTable &out, char *ws, const Workspace &w, int64_t unit0,
+                         int nunits, int cand_m, const int32_t *budgets, hipStream_t st) {
+  const dim3 grid((unsigned)(nunits * pl.nseg));
+  if (pl.seg == 4096) hipLaunchKernelGGL((segtop_kernel<512, 8>), grid, dim3(512), 0, st, s, out, ws, w, unit0, pl.nseg, cand_m, budgets);
+  else if (pl.seg == 8192) hipLaunchKernelGGL((segtop_kernel<1024, 8>), grid, dim3(1024), 0, st, s, out, ws, w, unit0, pl.nseg, cand_m, budgets);
+  else hipLaunchKernelGGL((segtop_kernel<1024, 16>), grid, dim3(1024), 0, st, s, out, ws, w, unit0, pl.nseg, cand_m, budgets);
+  return hipGetLastError();
+}
+
+template <int THREADS, int EPT>
+static hipError_t launch_mergetop_e(const Shape &s, const SegPlan &pl, const LayerOutTable &out, char *ws, const Workspace &w,
+                                    const CandLists &cl, int64_t unit0, int nunits, int cand_m, const int32_t *budgets, hipStream_t st) {
+  auto kern = mergetop_kernel<THREADS, EPT>;
+  static LdsLimitOnce once;
+  const hipError_t attr = once.raise(reinterpret_cast<const void *>(kern));
+  if (attr != hipSuccess) return attr;
+  hipLaunchKernelGGL(kern, dim3(nunits), dim3(THREADS), (size_t)slots4(pl.merge) * 4, st, s, out, ws, w,
+                     cl, unit0, pl.seg, pl.nseg, cand_m, budgets);
+  return hipGetLastError();
+}
+
+hipError_t launch_mergetop(const Shape &s, const SegPlan &pl, const LayerOutTable &out, char *ws, const Workspace &w, const CandLists &cl,
+                           int64_t unit0, int nunits, int cand_m, const int32_t *budgets, hipStream_t st) {
+  if (pl.merge <= 512 * 8) return launch_mergetop_e<512, 8>(s, pl, out, ws, w, cl, unit0, nunits, cand_m, budgets, st);
+  if (pl.merge <= 1024 * 8) return launch_mergetop_e<1024, 8>(s, pl, out, ws, w, cl, unit0, nunits, cand_m, budgets, st);
+  if (pl.merge <= 1024 * 16) return launch_mergetop_e<1024, 16>(s, pl, out, ws, w, cl, unit0, nunits, cand_m, budgets, st);
+  return launch_mergetop_e<1024, 32>(s, pl, out, ws, w, cl, unit0, nunits, cand_m, budgets, st);
+}
+
+}  // namespace mixkv

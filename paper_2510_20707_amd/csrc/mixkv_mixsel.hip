@@ -13,267 +13,14 @@
 // Paper: Sec. 3.2 Eq. 2 (importance = attention + scaled value norm), Sec. 3.3 (min-max and mean
 // matching of the diversity, Eq. 5 mix), Sec. 3.1 / Algorithm 1 (TopB with B' = B - W); Sec. 4.3 /
 // Table 4 for the variants (key-norm intrinsic score, un-weighted and one-sided mixes, given weights).
-#include <mutex>
-
-#include "mixkv_internal.h"
-#include "mixkv_wave.h"
+#include "mixkv_topsel.h"
 
 namespace mixkv {
-
-constexpr int kMsMaxThreads = 1024, kMsMaxWaves = kMsMaxThreads / 64;
-constexpr int kDigit = 11, kBins = 1 << kDigit;     // radix-select digit
-
-struct MsScratch {
-  float f[kMsMaxWaves][8];
-  float fr[8];
-  uint32_t ur[2];
-  int i[kMsMaxWaves + 1];
-  int hist[kBins];
-  int hist0[kBins];                      // the first round's histogram of a head, for a second threshold on the same keys
-  int bin, krem, cut;
-};
-
-// Block-wide reduction of NS sums, NMIN minima and NMAX maxima at once; every thread gets the
-// results back in place.  Fixed order: lanes in lane order inside a wave, then waves in wave order.
-template <int NW, int NS, int NMIN, int NMAX>
-__device__ __forceinline__ void block_reduce_mixed(float (&v)[NS + NMIN + NMAX], MsScratch &sc) {
-  constexpr int NV = NS + NMIN + NMAX;
-  static_assert(NV <= 8 && NW <= 16, "scratch holds eight values for sixteen waves");
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int k = 0; k < NV; ++k)
-    v[k] = k < NS ? wave_reduce<WSum>(v[k], 0.f)
-                  : (k < NS + NMIN ? wave_reduce<WMin>(v[k], INFINITY) : wave_reduce<WMax>(v[k], -INFINITY));
-  __syncthreads();                       // scratch may still be read from a previous call
-  if (lane == 0)
-#pragma unroll
-    for (int k = 0; k < NV; ++k) sc.f[wave][k] = v[k];
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < NV; ++k) {
-    // every wave folds the NW partials itself (one row of lanes), so no third barrier is needed
-    const float id = k < NS ? 0.f : (k < NS + NMIN ? INFINITY : -INFINITY);
-    float x = (lane & 15) < NW ? sc.f[lane & 15][k] : id;
-    x = k < NS ? row_scan_incl<WSum>(x, id) : (k < NS + NMIN ? row_scan_incl<WMin>(x, id) : row_scan_incl<WMax>(x, id));
-    v[k] = read_lane(x, 15);
-  }
-}
-
-// Block-wide minimum and maximum of unsigned keys through two LDS atomics per wave (integer
-// min / max do not depend on the order).  sc.ur must hold {0xffffffff, 0} from before an earlier
-// barrier of the kernel.
-__device__ __forceinline__ void block_minmax_u32(uint32_t &lo, uint32_t &hi, MsScratch &sc) {
-  const int lane = threadIdx.x & 63;
-  lo = wave_reduce<WMin>(lo, 0xffffffffu);
-  hi = wave_reduce<WMax>(hi, 0u);
-  if (lane == 0) { atomicMin(&sc.ur[0], lo); atomicMax(&sc.ur[1], hi); }
-  __syncthreads();
-  lo = sc.ur[0];
-  hi = sc.ur[1];
-}
-
-// Exclusive prefix sum of one int per thread (thread order); *total receives the block sum.
-__device__ __forceinline__ int read_lane_dyn(int x, int lane_uniform) {
-  return __builtin_amdgcn_readlane(x, __builtin_amdgcn_readfirstlane(lane_uniform));
-}
-
-template <int NW>
-__device__ __forceinline__ int block_scan_excl(int v, MsScratch &sc, int *total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int wtot;
-  const int inc = wave_scan_incl_add(v, &wtot);
-  __syncthreads();
-  if (lane == 0) sc.i[wave] = wtot;
-  __syncthreads();
-  const int x = (lane & 15) < NW ? sc.i[lane & 15] : 0;
-  const int y = row_scan_incl<WSum>(x, 0);              // inclusive over the waves, in every row of lanes
-  *total = read_lane(y, 15);
-  const int before = wave == 0 ? 0 : read_lane_dyn(y, wave - 1);
-  return before + inc - v;
-}
-
-__device__ __forceinline__ uint32_t order_key_u(float x) {
-  uint32_t u = __float_as_uint(x);
-  if (u == 0x80000000u) u = 0;                          // -0 and +0 are the same score
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-
-// One count into a shared histogram bin per lane, with the lanes that share the wave's most common
-// bin (as seen from its first active lane) merged into a single atomic.
-__device__ __forceinline__ void hist_add(int *hist, int bin, bool on) {
-  const unsigned long long act = __ballot(on);
-  if (act == 0) return;
-  const int first = __ffsll((long long)act) - 1;                  // wave-uniform
-  const int b0 = __builtin_amdgcn_readlane(bin, first);
-  const unsigned long long same = __ballot(on && bin == b0);
-  const int lane = threadIdx.x & 63;
-  if (lane == first) atomicAdd(&hist[b0], __popcll(same));
-  if (on && bin != b0) atomicAdd(&hist[bin], 1);
-}
-
-// Threshold of the k largest of a workgroup's keys (1 <= k <= number of valid keys): every thread holds
-// EPT keys, those with their bit set in `vmask` valid, and [kmin, kmax] is the range of all valid keys.  Most-significant-digit radix select from the first
-// bit in which the keys differ.  Returns tau, the k-th largest key, and in krem how many of the
-// keys equal to tau still belong to the k (0: all of them).  Ends behind a barrier: may be called again.
-// The first round counts every valid key and does not depend on k: FIRST = 1 keeps its histogram
-// aside, FIRST = 2 takes it from there (a second threshold on the same keys), 0 does neither.
-template <int THREADS, int EPT, int FIRST = 0>
-__device__ __forceinline__ uint32_t radix_threshold(const uint32_t (&key)[EPT], uint32_t vmask, uint32_t kmin, uint32_t kmax,
-                                                    int k, MsScratch &sc, int &krem) {
-  constexpr int NW = THREADS / 64;
-  const int tid = threadIdx.x;
-  // bits at and above `undecided` are common to all keys; digits of up to kDigit bits from there down
-  int undecided = kmin == kmax ? 0 : 32 - __clz((int)(kmin ^ kmax));
-  uint32_t prefix = undecided >= 32 ? 0u : (kmax >> undecided) << undecided;
-  bool all_equal = false, first = true;
-  while (undecided > 0) {
-    const int wbits = min(kDigit, undecided), shift = undecided - wbits;
-    const uint32_t himask = undecided >= 32 ? 0u : ~0u << undecided;
-    const bool saved = FIRST == 2 && first;             // this round's histogram is already in hist0
-    int *hist = saved ? sc.hist0 : sc.hist;
-    if (!saved) {
-      for (int i = tid; i < kBins; i += THREADS) sc.hist[i] = 0;
-      __syncthreads();
-#pragma unroll
-      for (int e = 0; e < EPT; ++e) {
-        const bool on = ((vmask >> e) & 1u) != 0 && (key[e] & himask) == (prefix & himask);
-        hist_add(sc.hist, (int)((key[e] >> shift) & ((1u << wbits) - 1u)), on);
-      }
-      __syncthreads();
-    }
-    // walk the bins from the top: thread t sums bins [kBins - (t+1)*BPT, kBins - t*BPT)
-    constexpr int BPT = (kBins + THREADS - 1) / THREADS;
-    int cnt = 0;
-#pragma unroll
-    for (int j = 0; j < BPT; ++j) {
-      const int bi = kBins - 1 - (tid * BPT + j);
-      const int c = bi >= 0 ? hist[bi] : 0;
-      if (FIRST == 1 && first && bi >= 0) sc.hist0[bi] = c;
-      cnt += c;
-    }
-    first = false;
-    int total;
-    const int excl = block_scan_excl<NW>(cnt, sc, &total);
-    if (excl < k && k <= excl + cnt) {
-      int run = excl;
-#pragma unroll
-      for (int j = 0; j < BPT; ++j) {
-        const int bi = kBins - 1 - (tid * BPT + j);
-        const int c = bi >= 0 ? hist[bi] : 0;
-        if (run < k && k <= run + c) { sc.bin = bi; sc.krem = k - run; sc.cut = c; }
-        run += c;
-      }
-    }
-    __syncthreads();
-    prefix |= (uint32_t)sc.bin << shift;
-    k = sc.krem;
-    undecided = shift;
-    const bool whole_bin = sc.cut == k && shift > 0 && prefix != 0;
-    __syncthreads();
-    // Every key of the bin is needed: the kept set is "all keys at or above the bin", whatever
-    // the lower digits are, so the remaining rounds can be skipped.
-    if (whole_bin) { prefix -= 1; all_equal = true; break; }
-  }
-  krem = all_equal ? 0 : k;
-  return prefix;
-}
-
-// Bit 31 of a candidate-list entry: the candidate is one of its head's `floor` best.
-constexpr uint32_t kFloorFlag = 0x80000000u;
-
-// TopB' of one head: the Bp >= 1 candidates with the largest scores, ties to the smaller index, out
-// of the EPT consecutive candidates base .. base + nvalid - 1 every thread holds in a[] (Sec. 3.1 /
-// Algorithm 1, TopB).  The kept positions go to idx[0, Bp) in ascending order.  With ckey not null
-// the list is a head's candidates for the head-adaptive split: the order keys go beside the
-// positions, and the head's `floor` <= Bp best carry kFloorFlag in their position word.
-// sc.ur must hold {0xffffffff, 0} from before an earlier barrier.
-template <int THREADS, int EPT>
-__device__ __forceinline__ void top_select(const float (&a)[EPT], int nvalid, int base, int Bp, int32_t *idx,
-                                           uint32_t *ckey, int floor, MsScratch &sc) {
-  constexpr int NW = THREADS / 64;
-  uint32_t key[EPT];
-  uint32_t kmin = 0xffffffffu, kmax = 0;
-#pragma unroll
-  for (int e = 0; e < EPT; ++e) {
-    key[e] = order_key_u(a[e]);
-    if (e < nvalid) { kmin = min(kmin, key[e]); kmax = max(kmax, key[e]); }
-  }
-  block_minmax_u32(kmin, kmax, sc);
-  const uint32_t vmask = nvalid >= EPT ? (EPT >= 32 ? 0xffffffffu : (1u << (EPT & 31)) - 1u)
-                                       : (nvalid <= 0 ? 0u : (1u << nvalid) - 1u);
-  int k;                             // of the keys equal to tau, the first k (by position) are kept
-  const bool flags = ckey != nullptr && floor > 0;
-  int kf = 0;
-  uint32_t tau, tauf = 0xffffffffu;
-  if (flags) {
-    tau = radix_threshold<THREADS, EPT, 1>(key, vmask, kmin, kmax, Bp, sc, k);
-    tauf = radix_threshold<THREADS, EPT, 2>(key, vmask, kmin, kmax, floor, sc, kf);
-  } else {
-    tau = radix_threshold<THREADS, EPT>(key, vmask, kmin, kmax, Bp, sc, k);
-  }
-  // one scan carries both counts: keys above tau (low half) and keys equal to tau (high half)
-  int ngt = 0, neq = 0, neqf = 0;
-#pragma unroll
-  for (int e = 0; e < EPT; ++e) {
-    const bool in = e < nvalid;
-    ngt += (in && key[e] > tau) ? 1 : 0;
-    neq += (in && key[e] == tau) ? 1 : 0;
-    neqf += (in && key[e] == tauf) ? 1 : 0;
-  }
-  int total;
-  const int packed = block_scan_excl<NW>(ngt | (neq << 16), sc, &total);
-  int seen = packed >> 16;                          // equal keys at smaller indices
-  int pos = (packed & 0xffff) + min(seen, k);       // kept entries at smaller indices
-  int seenf = flags ? block_scan_excl<NW>(neqf, sc, &total) : 0;
-#pragma unroll
-  for (int e = 0; e < EPT; ++e) {
-    if (e < nvalid) {
-      bool sel = key[e] > tau;
-      if (key[e] == tau) sel = seen++ < k;
-      bool inf = flags && key[e] > tauf;
-      if (flags && key[e] == tauf) inf = seenf++ < kf;
-      if (sel) {
-        if (pos < Bp) {
-          idx[pos] = (int32_t)((uint32_t)(base + e) | (inf ? kFloorFlag : 0u));
-          if (ckey) ckey[pos] = key[e];
-        }
-        ++pos;
-      }
-    }
-  }
-}
-
-// Rows head h of a layer keeps and its first row inside the batch item: B each, or the layer's
-// row of the budget table (per-head mode), the heads packed back to back.
-__device__ __forceinline__ void head_rows(const Shape &s, const int32_t *budgets, int layer, int h, int &Bh, int &row0) {
-  Bh = s.B;
-  row0 = h * s.B;
-  if (budgets) {
-    const int32_t *bl = budgets + layer * s.hkv;
-    row0 = 0;
-    for (int j = 0; j < h; ++j) row0 += bl[j];
-    Bh = bl[h];
-  }
-}
-
-// After the candidates of a head: the W window positions, the head's count and its offsets.
-__device__ __forceinline__ void finish_head(const Shape &s, const LayerOut &O, int b, int h, int Bh, int row0,
-                                            int32_t *idx, int threads) {
-  const int tid = threadIdx.x, Bp = Bh - s.W;
-  for (int wv = tid; wv < s.W; wv += threads) idx[Bp + wv] = s.Nc + wv;
-  if (tid == 0) {
-    O.counts[b * s.hkv + h] = Bh;
-    if (O.offsets) {
-      O.offsets[b * (s.hkv + 1) + h] = row0;
-      if (h == s.hkv - 1) O.offsets[b * (s.hkv + 1) + s.hkv] = row0 + Bh;
-    }
-  }
-}
 
 template <int THREADS, int EPT, bool SELECT>
 __global__ __launch_bounds__(THREADS) void mixsel_kernel(Shape s, LayerOutTable out, char *ws, Workspace w,
                                                            int64_t unit0, LayerInTable in, int gather_eb, int cand_m,
-                                                           const int32_t *budgets) {
+                                                           CandLists cl, const int32_t *budgets) {
   constexpr int NW = THREADS / 64;
   extern __shared__ float a_s[];                        // [Nc] raw window attention of this head
   __shared__ MsScratch sc;
@@ -281,14 +28,10 @@ __global__ __launch_bounds__(THREADS) void mixsel_kernel(Shape s, LayerOutTable 
   const int64_t unit = unit0 + ul;
   const int layer = ul / s.units_per_layer, bh = ul - layer * s.units_per_layer;
   const LayerOut O = out.l[layer];
-  const float *araw = reinterpret_cast<const float *>(ws + w.araw) + unit * s.Npad;
-  const float *vnorm = reinterpret_cast<const float *>(ws + w.vnorm) + unit * s.Npad;
-  const float *kdot = reinterpret_cast<const float *>(ws + w.sdiv) + unit * s.Npad;
-  const float *invn = reinterpret_cast<const float *>(ws + w.invnorm) + unit * s.Npad;
+  const UnitRows rows(s, ws, w, unit);
   const float r = reinterpret_cast<const float *>(ws + w.rbar)[unit];
   const int Nc = s.Nc, N = s.N, base = tid * EPT;
-  const bool use_v = s.intrinsic != MIXKV_INTRINSIC_NONE;      // an intrinsic score takes part (held in v[])
-  const bool knorm = s.intrinsic == MIXKV_INTRINSIC_KNORM;
+  const bool use_v = rows.use_v;
   const float inv_n = 1.f / (float)Nc;
   float wi, wd;
   mix_weights(s.mix, r, s.mix == MIXKV_MIX_GIVEN_R ? in.l[layer].r_given[bh] : 0.f, wi, wd);
@@ -305,24 +48,7 @@ __global__ __launch_bounds__(THREADS) void mixsel_kernel(Shape s, LayerOutTable 
   const int nvalid = Nc - base;             // consecutive ownership: candidates of this thread inside the row
   float a[EPT];
   float st[7] = {0.f, 0.f, 0.f, INFINITY, INFINITY, -INFINITY, -INFINITY};   // sums a, v, d | min v, d | max v, d
-  // intrinsic score and diversity of the four candidates from i on (zeros past the row)
-  auto load_vd = [&](int i, float4 &vr, float4 &dr) {
-    float4 kr = make_float4(0.f, 0.f, 0.f, 0.f), nr = kr;
-    vr = kr;
-    if (i < Nc) {
-      if (s.kstats) {                        // else nobody wrote them: the diversity is 0 and carries weight 0
-        kr = *reinterpret_cast<const float4 *>(kdot + i);
-        nr = *reinterpret_cast<const float4 *>(invn + i);
-      }
-      if (knorm) vr = make_float4(neg_key_norm(nr.x), neg_key_norm(nr.y), neg_key_norm(nr.z), neg_key_norm(nr.w));
-      else if (use_v) vr = *reinterpret_cast<const float4 *>(vnorm + i);
-    }
-    // s_div: a product rounded on its own.  The minimum is taken from the first reading and must
-    // cancel exactly against the second, so the compiler may not fuse the product into the
-    // subtraction that follows there (it may by default); the empty statements hide where it came from.
-    dr = make_float4(-kr.x * nr.x, -kr.y * nr.y, -kr.z * nr.z, -kr.w * nr.w);
-    asm("" : "+v"(dr.x), "+v"(dr.y), "+v"(dr.z), "+v"(dr.w));
-  };
+  auto load_vd = [&](int i, float4 &vr, float4 &dr) { rows.load_vd(i, vr, dr); };
   // The raw attention row goes to LDS with one pad word per 32 so that the accesses of
   // consecutive-range owners (a thread stride of EPT words) spread over the banks.
   auto slot = [](int i) { return i + (i >> 5); };
@@ -331,7 +57,7 @@ __global__ __launch_bounds__(THREADS) void mixsel_kernel(Shape s, LayerOutTable 
   for (int e4 = 0; e4 < EPT; e4 += 4) {
     const int i = cidx(e4);
     float4 ar = make_float4(0.f, 0.f, 0.f, 0.f), vr, dr;
-    if (i < Nc) ar = *reinterpret_cast<const float4 *>(araw + i);
+    if (i < Nc) ar = *reinterpret_cast<const float4 *>(rows.araw + i);
     load_vd(i, vr, dr);
     const float a4[4] = {ar.x, ar.y, ar.z, ar.w};
     const float v4[4] = {vr.x, vr.y, vr.z, vr.w}, d4[4] = {dr.x, dr.y, dr.z, dr.w};
@@ -463,8 +189,8 @@ __global__ __launch_bounds__(THREADS) void mixsel_kernel(Shape s, LayerOutTable 
   int Bh, row0;                                        // rows this head keeps, and its first row in the batch item
   head_rows(s, budgets, layer, h, Bh, row0);
   const int64_t out_row0 = (int64_t)b * s.hkv * s.B + row0;
-  int32_t *idx = cand ? reinterpret_cast<int32_t *>(ws + w.cand_idx) + unit * kMaxCandPerHead : O.indices + out_row0;
-  uint32_t *ckey = reinterpret_cast<uint32_t *>(ws + w.cand_key) + unit * kMaxCandPerHead;
+  int32_t *idx = cand ? reinterpret_cast<int32_t *>(ws + cl.idx) + unit * cl.stride : O.indices + out_row0;
+  uint32_t *ckey = reinterpret_cast<uint32_t *>(ws + cl.key) + unit * cl.stride;
   const int Bp = cand ? cand_m : Bh - s.W;
   if (Bp > 0) top_select<THREADS, EPT>(a, nvalid, base, Bp, idx, cand ? ckey : nullptr, s.floor_, sc);
   if (cand) return;
@@ -498,7 +224,7 @@ __global__ __launch_bounds__(THREADS) void mixsel_kernel(Shape s, LayerOutTable 
 // above: the head's final rows in fixed and per-head mode, or with cand_m > 0 its best cand_m
 // candidates with their keys for the head-adaptive split (Sec. 3.1 / Algorithm 1, TopB).
 template <int THREADS, int EPT>
-__global__ __launch_bounds__(THREADS) void topsel_kernel(Shape s, LayerOutTable out, char *ws, Workspace w, int64_t unit0,
+__global__ __launch_bounds__(THREADS) void topsel_kernel(Shape s, LayerOutTable out, char *ws, CandLists cl, int64_t unit0,
                                                            int cand_m, const int32_t *budgets) {
   extern __shared__ float a_s[];                        // [Nc] padded: the head's scores
   __shared__ MsScratch sc;
@@ -519,9 +245,9 @@ __global__ __launch_bounds__(THREADS) void topsel_kernel(Shape s, LayerOutTable 
   const int h = bh % s.hkv, b = bh / s.hkv;
   int Bh, row0;
   head_rows(s, budgets, layer, h, Bh, row0);
-  int32_t *idx = cand ? reinterpret_cast<int32_t *>(ws + w.cand_idx) + unit * kMaxCandPerHead
+  int32_t *idx = cand ? reinterpret_cast<int32_t *>(ws + cl.idx) + unit * cl.stride
                       : O.indices + (int64_t)b * s.hkv * s.B + row0;
-  uint32_t *ckey = cand ? reinterpret_cast<uint32_t *>(ws + w.cand_key) + unit * kMaxCandPerHead : nullptr;
+  uint32_t *ckey = cand ? reinterpret_cast<uint32_t *>(ws + cl.key) + unit * cl.stride : nullptr;
   const int Bp = cand ? cand_m : Bh - s.W;
   if (Bp > 0) top_select<THREADS, EPT>(a, nvalid, base, Bp, idx, ckey, s.floor_, sc);
   if (!cand) finish_head(s, O, b, h, Bh, row0, idx, THREADS);
@@ -532,21 +258,21 @@ __global__ __launch_bounds__(THREADS) void topsel_kernel(Shape s, LayerOutTable 
 // marked); a head keeps its floor, i.e. its f best, and the rest of the layer's pool goes to the
 // best remaining candidates of all heads together, ties to the smaller head, then the smaller
 // position.  A head can keep at most f + H * (B' - f) <= M candidates, so the lists hold every
-// candidate that can be kept and the result is the same as ranking all scores.  Thread t owns the
-// entries [4t, 4t + 4) of the H lists laid end to end: that order is the tie order, and the kept
+// candidate that can be kept and the result is the same as ranking all scores.  Thread t owns EPT
+// consecutive entries of the H lists laid end to end: that order is the tie order, and the kept
 // entries of a head come out in ascending position from one prefix sum.
-template <int THREADS>
-__global__ __launch_bounds__(THREADS) void candsplit_kernel(Shape s, LayerOutTable out, char *ws, Workspace w, int64_t unit0,
+template <int THREADS, int EPT>
+__global__ __launch_bounds__(THREADS) void candsplit_kernel(Shape s, LayerOutTable out, char *ws, CandLists cl, int64_t unit0,
                                                               int M) {
-  constexpr int NW = THREADS / 64, EPT = 4;
+  constexpr int NW = THREADS / 64;
   __shared__ MsScratch sc;
   __shared__ int hstart[65];                           // kept entries before each head's list; [H]: all
   const int tid = threadIdx.x, lb = blockIdx.x, layer = lb / s.batch, b = lb - layer * s.batch;
   const LayerOut O = out.l[layer];
   const int Nc = s.Nc, H = s.hkv, n = H * M, rest = H * (s.Bp - s.floor_);
   const int64_t unit = unit0 + (int64_t)lb * H;        // first head of this (layer, batch item)
-  const uint32_t *cidx = reinterpret_cast<const uint32_t *>(ws + w.cand_idx) + unit * kMaxCandPerHead;
-  const uint32_t *ckey = reinterpret_cast<const uint32_t *>(ws + w.cand_key) + unit * kMaxCandPerHead;
+  const uint32_t *cidx = reinterpret_cast<const uint32_t *>(ws + cl.idx) + unit * cl.stride;
+  const uint32_t *ckey = reinterpret_cast<const uint32_t *>(ws + cl.key) + unit * cl.stride;
   int32_t *idx = O.indices + (int64_t)b * H * s.B;
   if (tid == 0) { sc.ur[0] = 0xffffffffu; sc.ur[1] = 0u; }
   uint32_t key[EPT], pw[EPT];
@@ -556,10 +282,10 @@ __global__ __launch_bounds__(THREADS) void candsplit_kernel(Shape s, LayerOutTab
 #pragma unroll
   for (int j = 0; j < EPT; ++j) {
     const int e = tid * EPT + j;
-    head[j] = e / M;
+    head[j] = j == 0 ? e / M : head[j - 1] + (e >= (head[j - 1] + 1) * M ? 1 : 0);
     key[j] = 0; pw[j] = 0;
     if (e < n) {
-      const int at = head[j] * kMaxCandPerHead + (e - head[j] * M);
+      const int64_t at = head[j] * cl.stride + (e - head[j] * M);
       key[j] = ckey[at];
       pw[j] = cidx[at];
       inmask |= 1u << j;
@@ -611,33 +337,12 @@ __global__ __launch_bounds__(THREADS) void candsplit_kernel(Shape s, LayerOutTab
 
 // Largest sequence the fused kernel handles: 32 candidates per thread, and the raw attention row
 // must fit in LDS next to the scratch.
-constexpr int kMsMaxLds = 140 * 1024;
-
-// Raises a kernel's dynamic-LDS limit to kMsMaxLds the first time it is launched on a device.
-struct LdsLimitOnce {
-  static constexpr int kMaxDevices = 64;
-  std::mutex mu;
-  bool done[kMaxDevices] = {};
-  hipError_t raise(const void *kern) {
-    int dev = -1;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
-    std::lock_guard<std::mutex> lock(mu);
-    if (!done[dev]) {
-      e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, kMsMaxLds);
-      if (e != hipSuccess) return e;
-      done[dev] = true;
-    }
-    return hipSuccess;
-  }
-};
 bool mixsel_supported(const Shape &s) { return s.Nc <= kMsMaxThreads * 32 && (size_t)(s.Nc + s.Nc / 32 + 1) * 4 <= (size_t)kMsMaxLds; }
 
 template <int THREADS, int EPT>
 static hipError_t launch_mixsel_e(const Shape &s, bool select, const LayerOutTable &out, char *ws, const Workspace &w,
                                   int64_t unit0, int nunits, const LayerInTable &in, int gather_eb, int cand_m,
-                                  const int32_t *budgets, hipStream_t st) {
+                                  const CandLists &cl, const int32_t *budgets, hipStream_t st) {
   const size_t lds = (size_t)(s.Nc + s.Nc / 32 + 1) * 4;
   // The kernels may use more dynamic LDS than the default limit.  The limit is a property of the
   // kernel, shared by every stream and thread, so it is raised once, to the most mixsel_supported
@@ -648,13 +353,13 @@ static hipError_t launch_mixsel_e(const Shape &s, bool select, const LayerOutTab
     static LdsLimitOnce once;
     const hipError_t attr = once.raise(reinterpret_cast<const void *>(kern));
     if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL(kern, dim3(nunits), dim3(THREADS), lds, st, s, out, ws, w, unit0, in, gather_eb, cand_m, budgets);
+    hipLaunchKernelGGL(kern, dim3(nunits), dim3(THREADS), lds, st, s, out, ws, w, unit0, in, gather_eb, cand_m, cl, budgets);
   } else {
     auto kern = mixsel_kernel<THREADS, EPT, false>;
     static LdsLimitOnce once;
     const hipError_t attr = once.raise(reinterpret_cast<const void *>(kern));
     if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL(kern, dim3(nunits), dim3(THREADS), lds, st, s, out, ws, w, unit0, in, 0, 0, nullptr);
+    hipLaunchKernelGGL(kern, dim3(nunits), dim3(THREADS), lds, st, s, out, ws, w, unit0, in, 0, 0, cl, nullptr);
   }
   return hipGetLastError();
 }
@@ -665,47 +370,57 @@ static hipError_t launch_mixsel_e(const Shape &s, bool select, const LayerOutTab
 // workgroup keep the many block-wide steps cheap; long heads get more threads.
 hipError_t launch_mixsel(const Shape &s, bool select, const LayerOutTable &out, char *ws, const Workspace &w,
                          int64_t unit0, int nunits, const LayerInTable &in, int gather_eb, int cand_m,
-                         const int32_t *budgets, hipStream_t st) {
+                         const CandLists &cl, const int32_t *budgets, hipStream_t st) {
   const int nc = s.Nc;
-  if (nc <= 256 * 8) return launch_mixsel_e<256, 8>(s, select, out, ws, w, unit0, nunits, in, gather_eb, cand_m, budgets, st);
-  if (nc <= 512 * 8) return launch_mixsel_e<512, 8>(s, select, out, ws, w, unit0, nunits, in, gather_eb, cand_m, budgets, st);
-  if (nc <= 1024 * 8) return launch_mixsel_e<1024, 8>(s, select, out, ws, w, unit0, nunits, in, gather_eb, cand_m, budgets, st);
-  if (nc <= 1024 * 16) return launch_mixsel_e<1024, 16>(s, select, out, ws, w, unit0, nunits, in, gather_eb, cand_m, budgets, st);
-  return launch_mixsel_e<1024, 32>(s, select, out, ws, w, unit0, nunits, in, gather_eb, cand_m, budgets, st);
+  if (nc <= 256 * 8) return launch_mixsel_e<256, 8>(s, select, out, ws, w, unit0, nunits, in, gather_eb, cand_m, cl, budgets, st);
+  if (nc <= 512 * 8) return launch_mixsel_e<512, 8>(s, select, out, ws, w, unit0, nunits, in, gather_eb, cand_m, cl, budgets, st);
+  if (nc <= 1024 * 8) return launch_mixsel_e<1024, 8>(s, select, out, ws, w, unit0, nunits, in, gather_eb, cand_m, cl, budgets, st);
+  if (nc <= 1024 * 16) return launch_mixsel_e<1024, 16>(s, select, out, ws, w, unit0, nunits, in, gather_eb, cand_m, cl, budgets, st);
+  return launch_mixsel_e<1024, 32>(s, select, out, ws, w, unit0, nunits, in, gather_eb, cand_m, cl, budgets, st);
 }
 
 template <int THREADS, int EPT>
-static hipError_t launch_topsel_e(const Shape &s, const LayerOutTable &out, char *ws, const Workspace &w, int64_t unit0,
+static hipError_t launch_topsel_e(const Shape &s, const LayerOutTable &out, char *ws, const CandLists &cl, int64_t unit0,
                                   int nunits, int cand_m, const int32_t *budgets, hipStream_t st) {
   const size_t lds = (size_t)(s.Nc + s.Nc / 32 + 1) * 4;
   auto kern = topsel_kernel<THREADS, EPT>;
   static LdsLimitOnce once;
   const hipError_t attr = once.raise(reinterpret_cast<const void *>(kern));
   if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL(kern, dim3(nunits), dim3(THREADS), lds, st, s, out, ws, w, unit0, cand_m, budgets);
+  hipLaunchKernelGGL(kern, dim3(nunits), dim3(THREADS), lds, st, s, out, ws, cl, unit0, cand_m, budgets);
   return hipGetLastError();
 }
 
 // Selection on scores in memory for `nunits` units starting at unit0 (requires mixsel_supported):
 // final rows, or with cand_m > 0 every head's best cand_m candidates for the head-adaptive split.
-hipError_t launch_topsel(const Shape &s, const LayerOutTable &out, char *ws, const Workspace &w, int64_t unit0, int nunits,
+hipError_t launch_topsel(const Shape &s, const LayerOutTable &out, char *ws, const CandLists &cl, int64_t unit0, int nunits,
                          int cand_m, const int32_t *budgets, hipStream_t st) {
   const int nc = s.Nc;
-  if (nc <= 256 * 8) return launch_topsel_e<256, 8>(s, out, ws, w, unit0, nunits, cand_m, budgets, st);
-  if (nc <= 512 * 8) return launch_topsel_e<512, 8>(s, out, ws, w, unit0, nunits, cand_m, budgets, st);
-  if (nc <= 1024 * 8) return launch_topsel_e<1024, 8>(s, out, ws, w, unit0, nunits, cand_m, budgets, st);
-  if (nc <= 1024 * 16) return launch_topsel_e<1024, 16>(s, out, ws, w, unit0, nunits, cand_m, budgets, st);
-  return launch_topsel_e<1024, 32>(s, out, ws, w, unit0, nunits, cand_m, budgets, st);
+  if (nc <= 256 * 8) return launch_topsel_e<256, 8>(s, out, ws, cl, unit0, nunits, cand_m, budgets, st);
+  if (nc <= 512 * 8) return launch_topsel_e<512, 8>(s, out, ws, cl, unit0, nunits, cand_m, budgets, st);
+  if (nc <= 1024 * 8) return launch_topsel_e<1024, 8>(s, out, ws, cl, unit0, nunits, cand_m, budgets, st);
+  if (nc <= 1024 * 16) return launch_topsel_e<1024, 16>(s, out, ws, cl, unit0, nunits, cand_m, budgets, st);
+  return launch_topsel_e<1024, 32>(s, out, ws, cl, unit0, nunits, cand_m, budgets, st);
 }
 
-// The head-adaptive split of `nlayers` layers' candidate lists of M entries per head.
-hipError_t launch_select_candidates(const Shape &s, const LayerOutTable &out, char *ws, const Workspace &w, int64_t unit0,
-                                    int nlayers, int cand_m, hipStream_t st) {
-  const int n = cand_m * s.hkv, grid = nlayers * s.batch;
-  if (n <= 256 * 4) hipLaunchKernelGGL(candsplit_kernel<256>, dim3(grid), dim3(256), 0, st, s, out, ws, w, unit0, cand_m);
-  else if (n <= 512 * 4) hipLaunchKernelGGL(candsplit_kernel<512>, dim3(grid), dim3(512), 0, st, s, out, ws, w, unit0, cand_m);
-  else hipLaunchKernelGGL(candsplit_kernel<1024>, dim3(grid), dim3(1024), 0, st, s, out, ws, w, unit0, cand_m);
+// The head-adaptive split of `nlayers` layers' candidate lists of M entries per head: one workgroup per (layer, batch
+// item) with all entries in registers, or, past 16 of them per thread, streamed from memory.
+template <int THREADS, int EPT>
+static hipError_t launch_candsplit_e(const Shape &s, const LayerOutTable &out, char *ws, const CandLists &cl, int64_t unit0,
+                                     int grid, int cand_m, hipStream_t st) {
+  hipLaunchKernelGGL((candsplit_kernel<THREADS, EPT>), dim3(grid), dim3(THREADS), 0, st, s, out, ws, cl, unit0, cand_m);
   return hipGetLastError();
+}
+hipError_t launch_select_candidates(const Shape &s, const LayerOutTable &out, char *ws, const CandLists &cl, int64_t unit0,
+                                    int nlayers, int cand_m, hipStream_t st) {
+  const int64_t n = (int64_t)cand_m * s.hkv;
+  const int grid = nlayers * s.batch;
+  if (n <= 256 * 4) return launch_candsplit_e<256, 4>(s, out, ws, cl, unit0, grid, cand_m, st);
+  if (n <= 512 * 4) return launch_candsplit_e<512, 4>(s, out, ws, cl, unit0, grid, cand_m, st);
+  if (n <= 1024 * 4) return launch_candsplit_e<1024, 4>(s, out, ws, cl, unit0, grid, cand_m, st);
+  if (n <= 1024 * 8) return launch_candsplit_e<1024, 8>(s, out, ws, cl, unit0, grid, cand_m, st);
+  if (n <= 1024 * 16) return launch_candsplit_e<1024, 16>(s, out, ws, cl, unit0, grid, cand_m, st);
+  return launch_split_stream(s, out, ws, cl, unit0, nlayers, cand_m, st);
 }
 
 }  // namespace mixkv

@@ -196,10 +196,10 @@ __device__ int kth_equal_index(int rows, int n, uint32_t tau, int need, KeyFn ke
   return cut;
 }
 
-// Ordered compaction: writes the indices i in [0, n) with pred(i, scores[i]), ascending, to dst
+// Ordered compaction: writes value(i) for the i in [0, n) with pred(i), ascending, to dst
 // (at most `cap` of them, the size of the destination); returns the count.
-template <class Pred>
-__device__ int compact_ascending(int n, const float *scores, Pred pred, int32_t *dst, int cap, SelectScratch &sc) {
+template <class Pred, class Value>
+__device__ int compact_ascending(int n, Pred pred, Value value, int32_t *dst, int cap, SelectScratch &sc) {
   constexpr int U = 4;
   const WaveSeg g(n);
   int wtot = 0;
@@ -208,8 +208,7 @@ __device__ int compact_ascending(int n, const float *scores, Pred pred, int32_t 
 #pragma unroll
     for (int j = 0; j < U; ++j) {
       const int i = c0 + j * 64 + g.lane;
-      const float v = i < g.hi ? scores[i] : 0.f;
-      in[j] = i < g.hi && pred(i, v);
+      in[j] = i < g.hi && pred(i);
     }
 #pragma unroll
     for (int j = 0; j < U; ++j) wtot += __popcll(__ballot(in[j]));
@@ -221,14 +220,13 @@ __device__ int compact_ascending(int n, const float *scores, Pred pred, int32_t 
 #pragma unroll
     for (int j = 0; j < U; ++j) {
       const int i = c0 + j * 64 + g.lane;
-      const float v = i < g.hi ? scores[i] : 0.f;
-      in[j] = i < g.hi && pred(i, v);
+      in[j] = i < g.hi && pred(i);
     }
 #pragma unroll
     for (int j = 0; j < U; ++j) {
       const unsigned long long m = __ballot(in[j]);
       const int at = pos + lanes_below(m);
-      if (in[j] && at < cap) dst[at] = c0 + j * 64 + g.lane;
+      if (in[j] && at < cap) dst[at] = value(c0 + j * 64 + g.lane);
       pos += __popcll(m);
     }
   }
@@ -355,8 +353,8 @@ __global__ __launch_bounds__(kSelectThreads) void select_fixed_kernel(Shape s, L
     int need;
     radix_select(1, s.Nc, Bp, [&](int, int i, uint32_t &key) { return keyfn(i, key); }, sc, &tau, &need);
     const int cut = kth_equal_index(1, s.Nc, tau, need, [&](int, int i, uint32_t &key) { return keyfn(i, key); }, sc);
-    compact_ascending(s.Nc, scores, [&](int i, float v) { uint32_t k = order_key(v); return k > tau || (k == tau && i <= cut); },
-                      idx, Bp, sc);
+    compact_ascending(s.Nc, [&](int i) { const uint32_t k = order_key(scores[i]); return k > tau || (k == tau && i <= cut); },
+                      [](int i) { return i; }, idx, Bp, sc);
   }
   for (int wv = threadIdx.x; wv < s.W; wv += blockDim.x) idx[Bp + wv] = s.Nc + wv;
   if (threadIdx.x == 0) {
@@ -431,12 +429,12 @@ __global__ __launch_bounds__(kSelectThreads) void select_adaptive_kernel(Shape s
   int base = 0;
   for (int h = 0; h < H; ++h) {
     const float *sh = scores + (int64_t)h * s.N;
-    auto pred = [&](int i, float v) {
-      uint32_t key = order_key(v);
+    auto pred = [&](int i) {
+      const uint32_t key = order_key(sh[i]);
       if (in_floor(h, i, key)) return true;
       return rest > 0 && (key > tauR || (key == tauR && h * Nc + i <= cutR));
     };
-    const int cnt = compact_ascending(Nc, sh, pred, idx + base, H * s.B - base - s.W * (H - h), sc);
+    const int cnt = compact_ascending(Nc, pred, [](int i) { return i; }, idx + base, H * s.B - base - s.W * (H - h), sc);
     for (int wv = threadIdx.x; wv < s.W; wv += blockDim.x) idx[base + cnt + wv] = Nc + wv;
     if (threadIdx.x == 0) {
       O.counts[b * H + h] = cnt + s.W;
@@ -449,6 +447,54 @@ __global__ __launch_bounds__(kSelectThreads) void select_adaptive_kernel(Shape s
     offs[H] = base;
     for (int h = 0; h <= H; ++h) O.offsets[b * (H + 1) + h] = offs[h];
   }
+}
+
+// The head-adaptive split of candidate lists too long for the registers of one workgroup (candsplit_kernel has
+// the rules): the H lists of M entries are streamed a handful of times.
+__global__ __launch_bounds__(kSelectThreads) void split_stream_kernel(Shape s, LayerOutTable out, char *ws, CandLists cl,
+                                                                      int64_t unit0, int M) {
+  __shared__ SelectScratch sc;
+  const int lb = blockIdx.x, layer = lb / s.batch, b = lb - layer * s.batch, H = s.hkv, rest = H * (s.Bp - s.floor_);
+  const LayerOut O = out.l[layer];
+  const int64_t unit = unit0 + (int64_t)lb * H;        // first head of this (layer, batch item)
+  const uint32_t *cidx = reinterpret_cast<const uint32_t *>(ws + cl.idx) + unit * cl.stride;
+  const uint32_t *ckey = reinterpret_cast<const uint32_t *>(ws + cl.key) + unit * cl.stride;
+  int32_t *idx = O.indices + (int64_t)b * H * s.B;
+  uint32_t tau = 0xffffffffu;
+  int cut = -1;
+  if (rest > 0) {
+    auto keyfn = [&](int h, int i, uint32_t &key) {
+      key = ckey[h * cl.stride + i];
+      return !(cidx[h * cl.stride + i] & kFloorFlag);
+    };
+    int need;
+    radix_select(H, M, rest, keyfn, sc, &tau, &need);
+    cut = kth_equal_index(H, M, tau, need, keyfn, sc);
+  }
+  int base = 0;
+  for (int h = 0; h < H; ++h) {
+    const uint32_t *ih = cidx + h * cl.stride, *kh = ckey + h * cl.stride;
+    auto pred = [&](int i) {
+      if (ih[i] & kFloorFlag) return true;
+      return rest > 0 && (kh[i] > tau || (kh[i] == tau && h * M + i <= cut));
+    };
+    const int cnt = compact_ascending(M, pred, [&](int i) { return (int32_t)(ih[i] & ~kFloorFlag); }, idx + base,
+                                      H * s.B - base - s.W * (H - h), sc);
+    for (int wv = threadIdx.x; wv < s.W; wv += blockDim.x) idx[base + cnt + wv] = s.Nc + wv;
+    if (threadIdx.x == 0) {
+      O.counts[b * H + h] = cnt + s.W;
+      O.offsets[b * (H + 1) + h] = base;
+    }
+    base += cnt + s.W;
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) O.offsets[b * (H + 1) + H] = base;
+}
+
+hipError_t launch_split_stream(const Shape &s, const LayerOutTable &out, char *ws, const CandLists &cl, int64_t unit0, int nlayers,
+                               int cand_m, hipStream_t st) {
+  hipLaunchKernelGGL(split_stream_kernel, dim3(nlayers * s.batch), dim3(kSelectThreads), 0, st, s, out, ws, cl, unit0, cand_m);
+  return hipGetLastError();
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -511,12 +557,10 @@ hipError_t launch_gather(const Shape &s, int dtype, const LayerInTable &in, cons
   return hipGetLastError();
 }
 
-// Candidates a head has to hand to the budget split: its floor plus the whole shared pool; 0 if
-// that does not shorten the lists enough for the small kernel.
+// Candidates a head has to hand to the budget split: its floor plus the whole shared pool, as far as it has that many.
 int adaptive_candidates(const Shape &s) {
   const int64_t M = (int64_t)s.floor_ + (int64_t)s.hkv * (s.Bp - s.floor_);
-  if (M < 1 || M > s.Nc || M > kMaxCandPerHead || M * s.hkv > kMaxCandPerGroup) return 0;
-  return (int)M;
+  return (int)(M < s.Nc ? M : s.Nc);
 }
 
 int max_adaptive_heads() { return kMaxAdaptiveHeads; }

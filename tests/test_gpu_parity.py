@@ -328,6 +328,15 @@ def test_scoring_variants_adaptive_budgets_and_long_fallback():
     _run_and_check(wl, n_layers=1, budget=400, mix="sum", intrinsic="knorm")
 
 
+# Rows cut into segments: pooling windows that reach over the cuts (sliding window and generic loop), a last segment of
+# one candidate, key-norm scores, more than one batch item.
+@pytest.mark.parametrize("N,over", [(32768 + 32 + 1, dict(pool="avg", pool_kernel=5)), (33100, dict(pool="max", pool_kernel=31)),
+                                    (33001, dict(pool="avg", pool_kernel=9, intrinsic="knorm", budget=300)), (36864 + 33, dict(pool="none"))])
+def test_long_rows_pool_across_segments(N, over):
+    wl = WL["c2"].with_(name="long-pool", seq_len=N, batch=2, n_q_heads=2, n_kv_heads=1, text_suffix_start=N - 100)
+    _run_and_check(wl, n_layers=1, **over)
+
+
 def test_given_r_needs_the_weights():
     wl = WL["c1"]
     with pytest.raises(B.MixkvError) as e:

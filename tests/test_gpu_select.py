@@ -177,3 +177,44 @@ def test_per_head_budget_tables_are_validated_on_the_host():
         assert torch.all(out.indices == -7)                    # nothing was launched
     assert call(None)[0] == B.MIXKV_ERR_INVALID_ARG            # no table
     assert call(good, None)[0] == B.MIXKV_ERR_INVALID_ARG      # no workspace to stage it in
+
+
+# Rows beyond one workgroup's registers are cut into segments whose lists are merged, and head-adaptive lists may be
+# longer than the selection-only workspace holds, if the caller brings a workspace of the full size.  Cases: one
+# candidate past a segment, a last segment shorter than the lists, more kept than a segment holds, 8192- and
+# 16384-candidate segments, budgets whose split streams its lists from memory, a list that is the whole row, and
+# a budget too long for the merge.
+@pytest.mark.parametrize("kind", ["normal", "ties"])
+@pytest.mark.parametrize("mode,N,W,Bud,Hkv,floor", [
+    ("fixed", 32768 + 32 + 1, 32, 128, 2, 0), ("fixed", 9 * 4096 + 5 + 8, 8, 300, 1, 0), ("fixed", 40000, 16, 5000, 1, 0),
+    ("fixed", 140001, 32, 96, 2, 0), ("fixed", 300007, 32, 64, 1, 0), ("fixed", 70000, 32, 40000, 1, 0), ("fixed", 33000, 32, 32, 2, 0),
+    ("per_head", 50001, 32, 700, 3, 0), ("adaptive", 33000, 32, 128, 4, 24), ("adaptive", 66001, 8, 900, 4, 100),
+    ("adaptive", 3000, 32, 600, 4, 100), ("adaptive", 9001, 32, 1200, 8, 3), ("adaptive", 700, 4, 600, 5, 20),
+    ("adaptive", 20000, 32, 3000, 3, 2968)])
+def test_selection_on_a_full_workspace_is_bit_exact(kind, mode, N, W, Bud, Hkv, floor):
+    print(f"[case] select full workspace kind={kind} {mode} N={N} W={W} B={Bud} Hkv={Hkv} floor={floor}", flush=True)
+    rng = np.random.default_rng([7, N, Bud])
+    Bt = 2
+    s = _scores(kind, rng, Bt, Hkv, N, W)
+    if kind == "normal" and mode == "adaptive":
+        s[:, :, :N - W] *= np.linspace(0.5, 2.0, Hkv, dtype=np.float32)[None, :, None]
+    hb = np.array([[2 * Bud - W - (j % 2) * (2 * Bud - 2 * W) if j < Hkv - 1 else W for j in range(Hkv)]], dtype=np.int32)
+    p = B.make_params("bf16", Bt, Hkv, Hkv, 128, N, W, Bud, budget_mode=mode, budget_floor=floor,
+                      head_budgets=hb if mode == "per_head" else None)
+    out = B.alloc_layer_out(p, "cuda:0", redundancy=False, gather=False)
+    out.scores = torch.from_numpy(s).to("cuda:0")
+    out.indices.fill_(-1)
+    B.mixkv_select(p, [out], B.alloc_workspace(p, 1, "cuda:0"))
+    torch.cuda.synchronize()
+    idx = out.indices.cpu().numpy().reshape(Bt, Hkv * Bud)
+    cnt, off = out.counts.cpu().numpy(), out.offsets.cpu().numpy()
+    for b in range(Bt):
+        if mode == "adaptive":
+            bp = O.adaptive_budgets(s[b, :, :N - W].astype(np.float64), Bud, W, floor)
+        else:
+            bp = (hb[0] if mode == "per_head" else np.full(Hkv, Bud)) - W
+        np.testing.assert_array_equal(cnt[b], bp + W)
+        np.testing.assert_array_equal(off[b], np.concatenate([[0], np.cumsum(bp + W)]))
+        for h in range(Hkv):
+            want = O.select_unit(s[b, h, :N - W].astype(np.float64), int(bp[h]), N, W)
+            np.testing.assert_array_equal(idx[b, off[b, h]:off[b, h + 1]], want)
