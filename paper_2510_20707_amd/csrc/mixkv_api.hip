@@ -281,14 +281,19 @@ static mixkv_status run(const mixkv_params *params, const mixkv_layer_in *in, mi
     const int nunits = nl * s.units_per_layer;
     const int32_t *budgets_l0 = budgets_dev ? budgets_dev + (size_t)l0 * s.hkv : nullptr;
     if (result == MIXKV_OK && (stages & kScore)) {
-      const int grid = stream_grid(s, nunits, num_cus);
       const int64_t slot0 = (int64_t)(l0 / kLayersPerLaunch) * (kMaxStreamGrid + kLayersPerLaunch * s.units_per_layer);
-      const bool given_lse = in[0].window_lse != nullptr;
-      ok(timed(0, [&] { return launch_stats(s, params->dtype, ti, ws, w, unit0, nunits, grid, slot0, given_lse, stream); })) &&
+      const bool given_lse = in[0].window_lse != nullptr, keysplit = keysplit_supported(s, params->dtype);
+      const int grid = stream_grid(s, nunits, num_cus), ks_grid = keysplit_grid(s, params->dtype, nunits, num_cus);
+      const bool ks_stats = keysplit && !given_lse;
+      ok(timed(0, [&] {
+        return ks_stats ? launch_ks_stats(s, params->dtype, ti, ws, w, unit0, nunits, ks_grid, slot0, stream)
+                        : launch_stats(s, params->dtype, ti, ws, w, unit0, nunits, grid, slot0, given_lse, stream);
+      })) &&
           ok(timed(1, [&] {
-            hipError_t e = launch_fold(s, params->dtype, to, tl, ws, w, unit0, nunits, grid, s.nchunks, slot0, stream);
+            hipError_t e = launch_fold(s, params->dtype, to, tl, ws, w, unit0, nunits, ks_stats ? ks_grid : grid, s.nchunks, slot0, stream);
             if (e != hipSuccess) return e;
-            return launch_attn(s, params->dtype, ti, to, tl, ws, w, unit0, nunits, grid, slot0, stream);
+            return keysplit ? launch_ks_attn(s, params->dtype, ti, ws, w, unit0, nunits, ks_grid, stream)
+                            : launch_attn(s, params->dtype, ti, to, tl, ws, w, unit0, nunits, grid, slot0, stream);
           })) &&
           ok(timed(2, [&] {
             if (fused)

@@ -101,6 +101,13 @@ hipError_t launch_fold(const Shape &s, int dtype, const LayerOutTable &out, cons
                        int64_t unit0, int nunits, int grid, int items_per_unit, int64_t slot0, hipStream_t st);
 hipError_t launch_attn(const Shape &s, int dtype, const LayerInTable &in, const LayerOutTable &out, const LseTable &lse,
                        char *ws, const Workspace &w, int64_t unit0, int nunits, int grid, int64_t slot0, hipStream_t st);
+// The two passes for few query rows (mixkv_keysplit.hip); `grid` from keysplit_grid.
+bool keysplit_supported(const Shape &s, int dtype);
+int keysplit_grid(const Shape &s, int dtype, int nunits, int num_cus);
+hipError_t launch_ks_stats(const Shape &s, int dtype, const LayerInTable &in, char *ws, const Workspace &w, int64_t unit0, int nunits,
+                           int grid, int64_t slot0, hipStream_t st);
+hipError_t launch_ks_attn(const Shape &s, int dtype, const LayerInTable &in, char *ws, const Workspace &w, int64_t unit0, int nunits,
+                          int grid, hipStream_t st);
 hipError_t launch_mix(const Shape &s, const LayerInTable &in, const LayerOutTable &out, char *ws, const Workspace &w,
                       int64_t unit0, int nunits, hipStream_t st);
 // Weights of s_imp and of the scaled diversity in s_comp (Sec. 3.3, Eq. 5; Table 4's variants);

@@ -78,6 +78,19 @@ def test_ragged_shapes(dtype, D, N, W, Hq, Hkv, B):
     _run_and_check(wl, n_layers=2)
 
 
+# Few query rows: every wave takes whole key tiles of its own.  One and two query tiles, full and ragged; fewer tiles
+# than waves, a single tile, runs that end inside a tile; key statistics and value norms on and off.
+@pytest.mark.parametrize("dtype,D,N,W,Hq,Hkv,over", [
+    ("f32", 64, 1003, 16, 4, 2, {}), ("f32", 128, 515, 32, 2, 2, {}), ("f32", 128, 300, 33, 1, 1, {}), ("f32", 64, 90, 31, 4, 2, {}),
+    ("bf16", 64, 2049, 32, 4, 2, {}), ("bf16", 64, 40, 8, 8, 2, {}), ("bf16", 128, 1000, 8, 8, 2, dict(intrinsic="knorm")),
+    ("bf16", 128, 31, 5, 2, 1, dict(budget=7)), ("bf16", 128, 777, 32, 2, 2, dict(causal_window=False)), ("f32", 64, 130, 8, 2, 1, dict(mix="imp_only", intrinsic="none")),
+])
+def test_few_query_rows(dtype, D, N, W, Hq, Hkv, over):
+    wl = WL["c2"].with_(name="few-rows", dtype=dtype, head_dim=D, seq_len=N, window=W, n_q_heads=Hq, n_kv_heads=Hkv, batch=2,
+                        budget=min(N, W + 20), text_prefix=min(8, N // 4), text_suffix_start=N - min(8, N // 4))
+    _run_and_check(wl, n_layers=2, **over)
+
+
 @pytest.mark.parametrize("scale", [30.0, 150.0])
 def test_large_logits_move_the_softmax_offset_mid_run(scale):
     # Logits with a standard deviation of 30 and 150: at 150 a row meets keys far more than 88 above
