@@ -190,7 +190,7 @@ __global__ __launch_bounds__(kKsThreads, ks_wgs(DT, D)) void ks_stats_kernel(Sha
           float tmax = fmaxf(acc[0], acc[1]);
 #pragma unroll
           for (int i = 2; i < 16; i += 2) tmax = fmaxf(fmaxf(tmax, acc[i]), acc[i + 1]);
-          const float mn = fmaxf(m[q], tmax * c2);
+          const float mn = fmaxf(m[q], ceilf(tmax * c2));   // whole offsets: every rescaling, here and in the merges, is exact
           const float mu = (mn == -INFINITY) ? 0.f : mn;
           float s2[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
