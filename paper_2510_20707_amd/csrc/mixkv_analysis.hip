@@ -6,10 +6,9 @@
 // The N x N matrix is never formed.  With Xh the L2-normalised rows and S_a the sum of the rows
 // of block a, the mean of the matrix over block a x block b is S_a . S_b / (n_a n_b), and the sum
 // of all entries is |sum_a S_a|^2.  So one streaming pass over X produces the block sums
-// (blocksum_kernel, bound by HBM); blockgram_kernel forms their Gram matrix in LDS tiles and
-// redundancy_kernel folds them into the off-diagonal mean.
-#include "mixkv_internal.h"
-#include "mixkv_wave.h"
+// (blocksum_kernel, bound by HBM); blockgram_kernel forms their Gram matrix and folds them into the
+// off-diagonal mean.
+#include "mixkv_stream.h"
 
 namespace mixkv {
 
@@ -106,128 +105,114 @@ __global__ __launch_bounds__(256) void blocksum_kernel(AShape a, RowsInTable in,
   if (lane == 0) diag[(int64_t)ul * a.nb + blk] = dsum;
 }
 
-// Heat-map: one workgroup per (unit, 64 x 64 tile of the map).  The two sets of 64 block sums go
-// through LDS in slices of 64 dimensions (rows padded by four floats, so the 16 columns a wave
-// reads at once fall into different banks); every thread owns a 4 x 4 patch of the tile:
-// rows ty + 16 i, columns tx + 16 j.  M[a][b] = S_a . S_b / (n_a n_b).
-constexpr int kMapTile = 64, kMapSlice = 64;
+// Off-diagonal mean of one unit: the sum of all entries of the cosine matrix is |sum_a S_a|^2 and its trace sum_a
+// diag[a].  Partial sums are taken over interleaved blocks and folded in a fixed order, in double.
+constexpr int kMapThreads = 256;
 template <int D>
-__global__ __launch_bounds__(256) void blockgram_kernel(AShape a, SimOutTable out, const float *S) {
-  __shared__ float sa[kMapTile][kMapSlice + 4], sb[kMapTile][kMapSlice + 4];
-  const int tiles = (a.nb + kMapTile - 1) / kMapTile;
-  const int ul = blockIdx.x / (tiles * tiles), t = blockIdx.x - ul * tiles * tiles;
-  const int a0 = (t / tiles) * kMapTile, b0 = (t % tiles) * kMapTile;
+__device__ void redundancy_of(const AShape &a, const SimOutTable &out, const float *S, const float *diag, int ul) {
+  constexpr int PARTS = kMapThreads / D, U = 32;        // loads in flight
+  __shared__ double part[kMapThreads];
   const int layer = ul / a.units_per_layer, bh = ul - layer * a.units_per_layer;
-  float *map = out.l[layer].block_map;
-  if (!map) return;                                     // uniform over the workgroup
-  const float *Su = S + (int64_t)ul * a.nb * D;
-  const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
-  float acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
-  for (int d0 = 0; d0 < D; d0 += kMapSlice) {
-    if (d0 > 0) __syncthreads();
-    // 64 rows x 16 float4 per operand: four float4 per thread and operand, coalesced along d
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int e = tid + 256 * k, r = e >> 4, c = e & 15;
-      // rows past the last block read the last one (always in bounds) and are zeroed afterwards: a
-      // conditional load of either the row or a zero constant is compiled into a load from either the
-      // row or a copy of the constant in scratch memory
-      const int ra = min(a0 + r, a.nb - 1), rb = min(b0 + r, a.nb - 1);
-      float4 va = *reinterpret_cast<const float4 *>(Su + (int64_t)ra * D + d0 + 4 * c);
-      float4 vb = *reinterpret_cast<const float4 *>(Su + (int64_t)rb * D + d0 + 4 * c);
-      if (a0 + r >= a.nb) va = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (b0 + r >= a.nb) vb = make_float4(0.f, 0.f, 0.f, 0.f);
-      *reinterpret_cast<float4 *>(&sa[r][4 * c]) = va;
-      *reinterpret_cast<float4 *>(&sb[r][4 * c]) = vb;
-    }
-    __syncthreads();
-#pragma unroll 4
-    for (int d = 0; d < kMapSlice; d += 4) {
-      float4 x[4], y[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) x[i] = *reinterpret_cast<const float4 *>(&sa[ty + 16 * i][d]);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) y[j] = *reinterpret_cast<const float4 *>(&sb[tx + 16 * j][d]);
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          acc[i][j] = fmaf(x[i].x, y[j].x, acc[i][j]); acc[i][j] = fmaf(x[i].y, y[j].y, acc[i][j]);
-          acc[i][j] = fmaf(x[i].z, y[j].z, acc[i][j]); acc[i][j] = fmaf(x[i].w, y[j].w, acc[i][j]);
-        }
-    }
-  }
-  auto rows_of = [&](int blk) { return min(a.N, (blk + 1) * a.block) - blk * a.block; };
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int ba = a0 + ty + 16 * i;
-    if (ba >= a.nb) continue;
-    const float inv_na = 1.f / (float)rows_of(ba);
-    float *row = map + ((int64_t)bh * a.nb + ba) * a.nb;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int bb = b0 + tx + 16 * j;
-      if (bb < a.nb) row[bb] = acc[i][j] * inv_na / (float)rows_of(bb);
-    }
-  }
-}
-
-// Off-diagonal mean, one workgroup of 1024 threads per unit: the sum of all entries of the cosine
-// matrix is |sum_a S_a|^2 and its trace sum_a diag[a].  Partial sums are taken over interleaved
-// blocks and folded in a fixed order, in double.
-constexpr int kRedThreads = 1024;
-template <int D>
-__global__ __launch_bounds__(kRedThreads) void redundancy_kernel(AShape a, SimOutTable out, const float *S, const float *diag) {
-  constexpr int PARTS = kRedThreads / D;
-  __shared__ double part[kRedThreads];
-  const int ul = blockIdx.x, layer = ul / a.units_per_layer, bh = ul - layer * a.units_per_layer;
   float *red = out.l[layer].redundancy;
   if (!red) return;                                     // uniform over the workgroup
   const float *Su = S + (int64_t)ul * a.nb * D;
   const int tid = threadIdx.x, d = tid % D, pt = tid / D;
-  double t4[4] = {0.0, 0.0, 0.0, 0.0};                 // four loads in flight; folded in a fixed order
-  for (int bb = pt; bb < a.nb; bb += 4 * PARTS)
+  double t4[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int bb = pt; bb < a.nb; bb += U * PARTS) {
+    float x[U];
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-      if (bb + q * PARTS < a.nb) t4[q] += (double)Su[(int64_t)(bb + q * PARTS) * D + d];
+    for (int q = 0; q < U; ++q) {
+      const int at = bb + q * PARTS;
+      x[q] = Su[(int64_t)min(at, a.nb - 1) * D + d];
+      if (at >= a.nb) x[q] = 0.f;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int q = 0; q < U; ++q) t4[q & 3] += (double)x[q];
+  }
   part[tid] = (t4[0] + t4[1]) + (t4[2] + t4[3]);
   __syncthreads();
-  double sq = 0.0;
+  double share = 0.0;                                   // every thread's share of (all entries - trace)
   if (tid < D) {
     double v = 0.0;
 #pragma unroll
     for (int q = 0; q < PARTS; ++q) v += part[q * D + tid];
-    sq = v * v;
+    share = v * v;
   }
-  double tr = 0.0;
-  for (int bb = tid; bb < a.nb; bb += kRedThreads) tr += (double)diag[(int64_t)ul * a.nb + bb];
-  __syncthreads();
-  part[tid] = sq - tr;                                   // every thread's share of (all entries - trace)
-  __syncthreads();
-  // fold in two levels (32 x 32), each level in index order, so the LDS reads of a level overlap
-  double g = 0.0;
-  if (tid < 32) {
-    double v[32];
+  for (int bb = tid; bb < a.nb; bb += kMapThreads) share -= (double)diag[(int64_t)ul * a.nb + bb];
 #pragma unroll
-    for (int i = 0; i < 32; ++i) v[i] = part[tid * 32 + i];
-#pragma unroll
-    for (int i = 0; i < 32; ++i) g += v[i];
-  }
+  for (int o = 32; o >= 1; o >>= 1) share += __shfl_xor(share, o);
   __syncthreads();
-  if (tid < 32) part[tid] = g;
+  if ((tid & 63) == 0) part[tid >> 6] = share;
   __syncthreads();
   if (tid == 0) {
-    double v[32], off = 0.0;
+    double off = 0.0;
 #pragma unroll
-    for (int i = 0; i < 32; ++i) v[i] = part[i];
-#pragma unroll
-    for (int i = 0; i < 32; ++i) off += v[i];
+    for (int i = 0; i < kMapThreads / 64; ++i) off += part[i];
     const double n = (double)a.N;
     red[bh] = (float)(off / (n * (n - 1.0)));
+  }
+}
+
+// What follows from the block sums, in one launch: workgroups 0 .. nunits - 1 take a unit's off-diagonal mean each, the
+// others one 64 x 64 tile of a unit's heat-map, M[a][b] = S_a . S_b / (n_a n_b).  The two sets of 64 block sums
+// cross LDS as images of 32 rows and feed the fp32 matrix instructions, a 32 x 32 quadrant per wave.  Bound:
+// latency (loads, D / 2 matrix instructions, stores).  112 units of 128 blocks, D = 128: 13.5 us, against 15.2 (the
+// same tiles on the vector ALU) + 7.4 (a launch of its own for the means); fragments straight from memory, 32
+// rows of 32 bytes per load: 15 to 20.
+constexpr int kMapTile = 64;
+template <int D>
+__global__ __launch_bounds__(kMapThreads) void blockgram_kernel(AShape a, SimOutTable out, const float *S, const float *diag, int nunits) {
+  if ((int)blockIdx.x < nunits) {
+    redundancy_of<D>(a, out, S, diag, blockIdx.x);
+    return;
+  }
+  constexpr int DT = MIXKV_F32, NCHK = D / 8, PPR = D / 4, TILE = 32 * PPR, LOADS = TILE / kMapThreads;
+  __shared__ uint4 img[4 * TILE];                       // rows a0, a0 + 32, b0, b0 + 32
+  // workgroups go to the eight XCDs in turn: each XCD takes a contiguous eighth of the tiles, so that a unit's tiles
+  // share one L2
+  const int tiles = (a.nb + kMapTile - 1) / kMapTile, wg = blockIdx.x - nunits, per_xcd = (gridDim.x - nunits) / 8;
+  const int t = (wg & 7) * per_xcd + (wg >> 3);
+  if (t >= nunits * tiles * tiles) return;              // uniform over the workgroup
+  const int ul = t / (tiles * tiles), tt = t - ul * tiles * tiles, a0 = (tt / tiles) * kMapTile, b0 = (tt % tiles) * kMapTile;
+  const int layer = ul / a.units_per_layer, bh = ul - layer * a.units_per_layer;
+  float *map = out.l[layer].block_map;
+  if (!map) return;                                     // uniform over the workgroup
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, half = lane >> 5;
+  const uint4 *Su = reinterpret_cast<const uint4 *>(S + (int64_t)ul * a.nb * D);
+  // rows past the last block repeat it: their entries are not stored
+  uint4 v[4 * LOADS];
+#pragma unroll
+  for (int k = 0; k < 4 * LOADS; ++k) {
+    const int r = (k % LOADS * kMapThreads + tid) / PPR, piece = tid % PPR, g = k / LOADS;
+    v[k] = Su[(int64_t)min((g < 2 ? a0 : b0) + (g & 1) * 32 + r, a.nb - 1) * PPR + piece];
+  }
+#pragma unroll
+  for (int k = 0; k < 4 * LOADS; ++k) {
+    const int r = (k % LOADS * kMapThreads + tid) / PPR, piece = tid % PPR;
+    img[k / LOADS * TILE + r * PPR + (piece ^ tile_swz<DT, D>(r))] = v[k];
+  }
+  __syncthreads();
+  const uint4 *xa = img + (wave >> 1) * TILE, *yb = img + (2 + (wave & 1)) * TILE;
+  f32x16 acc;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+#pragma unroll
+  for (int c = 0; c < NCHK; ++c) {
+    Frag x, y;
+    x.q = read_key_frag<DT, D>(xa, 0, c, l32, half);
+    y.q = read_key_frag<DT, D>(yb, 0, c, l32, half);
+    acc = mma<DT>(x, y, acc);
+  }
+  auto rows_of = [&](int blk) { return (float)(min(a.N, (blk + 1) * a.block) - blk * a.block); };
+  const int bb = b0 + (wave & 1) * 32 + l32;
+  if (bb >= a.nb) return;
+  const float nb_b = rows_of(bb);
+  float *col = map + (int64_t)bh * a.nb * a.nb + bb;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int ba = a0 + (wave >> 1) * 32 + 8 * (i >> 2) + 4 * half + (i & 3);
+    if (ba < a.nb) col[(int64_t)ba * a.nb] = acc[i] * (1.f / rows_of(ba)) / nb_b;
   }
 }
 
@@ -300,19 +285,19 @@ mixkv_status mixkv_similarity(const mixkv_params *params, const mixkv_rows_in *i
     const int nunits = nl * a.units_per_layer;
     const size_t unit0 = (size_t)l0 * a.units_per_layer;
     float *Sg = S + unit0 * a.nb * a.D, *dg = diag + unit0 * a.nb;
-    const int tiles = (a.nb + kMapTile - 1) / kMapTile;
-    const dim3 grid_a((unsigned)(nunits * ((a.nb + 3) / 4))), grid_b((unsigned)(nunits * tiles * tiles)), grid_r(nunits);
+    bool any_map = false;
+    for (int l = 0; l < nl; ++l) any_map = any_map || to.l[l].block_map;
+    const int64_t tiles = any_map ? (a.nb + kMapTile - 1) / kMapTile : 0;
+    const dim3 grid_a((unsigned)(nunits * ((a.nb + 3) / 4))), grid_b((unsigned)(nunits + (nunits * tiles * tiles + 7) / 8 * 8));
     const bool bf = params->dtype == MIXKV_BF16;
     if (a.D == 128) {
       if (bf) hipLaunchKernelGGL((blocksum_kernel<MIXKV_BF16, 128>), grid_a, dim3(256), 0, stream, a, ti, Sg, dg, nunits);
       else hipLaunchKernelGGL((blocksum_kernel<MIXKV_F32, 128>), grid_a, dim3(256), 0, stream, a, ti, Sg, dg, nunits);
-      hipLaunchKernelGGL(blockgram_kernel<128>, grid_b, dim3(256), 0, stream, a, to, Sg);
-      hipLaunchKernelGGL(redundancy_kernel<128>, grid_r, dim3(kRedThreads), 0, stream, a, to, Sg, dg);
+      hipLaunchKernelGGL(blockgram_kernel<128>, grid_b, dim3(kMapThreads), 0, stream, a, to, Sg, dg, nunits);
     } else {
       if (bf) hipLaunchKernelGGL((blocksum_kernel<MIXKV_BF16, 64>), grid_a, dim3(256), 0, stream, a, ti, Sg, dg, nunits);
       else hipLaunchKernelGGL((blocksum_kernel<MIXKV_F32, 64>), grid_a, dim3(256), 0, stream, a, ti, Sg, dg, nunits);
-      hipLaunchKernelGGL(blockgram_kernel<64>, grid_b, dim3(256), 0, stream, a, to, Sg);
-      hipLaunchKernelGGL(redundancy_kernel<64>, grid_r, dim3(kRedThreads), 0, stream, a, to, Sg, dg);
+      hipLaunchKernelGGL(blockgram_kernel<64>, grid_b, dim3(kMapThreads), 0, stream, a, to, Sg, dg, nunits);
     }
     if (hipGetLastError() != hipSuccess) return MIXKV_ERR_HIP;
   }

@@ -108,3 +108,12 @@ def test_smallest_shapes():
     _check(wl, [lay], "K", 2)
     wl = WL["c1"].with_(name="tiny-sim3", seq_len=3, window=1, budget=2, n_q_heads=2, n_kv_heads=2, batch=3)
     _check(wl, [synth.make_layer(wl, 0)], "V", 2)
+
+
+# edges of the heat-map's 64 x 64 tiles and 32 x 32 quadrants, both row widths and types
+@pytest.mark.parametrize("dtype,D,N,block", [("f32", 64, 310, 10), ("f32", 128, 33, 1), ("bf16", 64, 650, 10), ("bf16", 128, 127, 2),
+                                             ("f32", 128, 645, 5), ("bf16", 128, 40, 40)])
+def test_heat_map_tile_edges(dtype, D, N, block):
+    wl = WL["c2"].with_(name="map-edges", dtype=dtype, head_dim=D, seq_len=N, window=8, budget=16, n_q_heads=3, n_kv_heads=3,
+                        text_prefix=4, text_suffix_start=N - 4)
+    _check(wl, [synth.make_layer(wl, 0)], "K", block)
