@@ -38,15 +38,17 @@ __global__ __launch_bounds__(THREADS) void mixsel_kernel(Shape s, LayerOutTable 
 
   // ---- load.  The first phases deal the candidates to the threads in groups of four, group
   // g * THREADS + tid to thread tid: consecutive lanes read consecutive 16 bytes (the per-unit rows
-  // are padded past Nc).  Only the attention stays in registers; the sums and extrema of the
-  // intrinsic score and the diversity are taken as they pass, and the mix reads the two a second
-  // time (from L2: the kernel before wrote them).  Three register arrays of EPT would not fit the
-  // 128 registers a 1024-thread workgroup leaves each lane at EPT = 32, and runs of EPT consecutive
-  // candidates per thread would touch one cache line per lane and load.  The selection does need
+  // are padded past Nc).  The sums and extrema of the intrinsic score and the diversity are taken as
+  // they pass.  Up to 16 candidates per thread all three rows stay in registers until the mix; at 32 they would not
+  // fit the 128 registers a 1024-thread workgroup leaves each lane, so only the attention does and the mix reads
+  // the two a second time (that reading cost 0.7 us at 8 per thread on 4 heads of 4096, 3 us at 16 on 256 heads of 16 384).
+  // Runs of EPT consecutive candidates per thread would touch one cache line per lane and load, but the selection needs
   // consecutive runs (ascending output from one prefix sum): s_comp reaches their owners through LDS.
   auto cidx = [&](int e) { return (((e >> 2) * THREADS + tid) << 2) + (e & 3); };
   const int nvalid = Nc - base;             // consecutive ownership: candidates of this thread inside the row
-  float a[EPT];
+  // up to 16 candidates per thread the other two fit beside it
+  constexpr bool KEEP = EPT <= 16;
+  float a[EPT], vk[KEEP ? EPT : 1], dk[KEEP ? EPT : 1];
   float st[7] = {0.f, 0.f, 0.f, INFINITY, INFINITY, -INFINITY, -INFINITY};   // sums a, v, d | min v, d | max v, d
   auto load_vd = [&](int i, float4 &vr, float4 &dr) { rows.load_vd(i, vr, dr); };
   // The raw attention row goes to LDS with one pad word per 32 so that the accesses of
@@ -64,6 +66,7 @@ __global__ __launch_bounds__(THREADS) void mixsel_kernel(Shape s, LayerOutTable 
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       a[e4 + j] = a4[j];
+      if constexpr (KEEP) { vk[e4 + j] = v4[j]; dk[e4 + j] = d4[j]; }
       if (i + j < Nc) {
         a_s[slot(i + j)] = a4[j];
         st[1] += v4[j]; st[2] += d4[j];
@@ -159,9 +162,16 @@ __global__ __launch_bounds__(THREADS) void mixsel_kernel(Shape s, LayerOutTable 
 #pragma unroll
   for (int e4 = 0; e4 < EPT; e4 += 4) {
     const int i = cidx(e4);
-    float4 vr, dr;
-    load_vd(i, vr, dr);
-    const float v4[4] = {vr.x, vr.y, vr.z, vr.w}, d4[4] = {dr.x, dr.y, dr.z, dr.w};
+    float v4[4], d4[4];
+    if constexpr (KEEP) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) { v4[j] = vk[e4 + j]; d4[j] = dk[e4 + j]; }
+    } else {
+      float4 vr, dr;
+      load_vd(i, vr, dr);
+      v4[0] = vr.x; v4[1] = vr.y; v4[2] = vr.z; v4[3] = vr.w;
+      d4[0] = dr.x; d4[1] = dr.y; d4[2] = dr.z; d4[3] = dr.w;
+    }
 #pragma unroll
     for (int j = 0; j < 4; ++j)
       if (i + j < Nc) a_s[slot(i + j)] = s_comp(a[e4 + j], v4[j], d4[j]);

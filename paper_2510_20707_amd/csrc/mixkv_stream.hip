@@ -327,7 +327,10 @@ __global__ __launch_bounds__(WAVES * 64, stats_waves_per_simd(DT, D, WAVES, TQ))
 // unit it touched, at slot g + unit_local.  The unit's items are [first, last): the first workgroup
 // touching it is the largest g with g*T1/G1 <= first, the last one the largest g with g*T1/G1 < last.
 // ------------------------------------------------------------------------------------------------
-constexpr int kFoldThreads = 256;
+// Two halves of the workgroup, one for the softmax rows and one for the key sum, sixteen partials in flight each: the
+// kernel is two chains of memory round trips side by side (4 units of 32 partials 7.5 -> 5.4 us; 112
+// units of some 5 partials 5.5 -> 5.2).
+constexpr int kFoldThreads = 512, kFoldHalf = kFoldThreads / 2, kFoldBatch = 16;
 
 template <int DT, int D>
 __global__ __launch_bounds__(kFoldThreads) void fold_kernel(Shape s, LayerOutTable out, LseTable lse, char *ws, Workspace w,
@@ -346,36 +349,39 @@ __global__ __launch_bounds__(kFoldThreads) void fold_kernel(Shape s, LayerOutTab
   float *nb = reinterpret_cast<float *>(ws + w.nb) + unit * s.nb_rows;
   // rows of this head's group are consecutive in [batch, n_q_heads, W]
   const float *lse_u = lse.l[uc.layer] ? lse.l[uc.layer] + (int64_t)(uc.b * s.hq + uc.h * s.G) * s.W : nullptr;
-  for (int r = tid; r < s.nb_rows; r += kFoldThreads) {
-    float b = INFINITY;                                // rows past G*W: weight 0
-    if (r < s.GW && lse_u) {
-      b = lse_u[r] * 1.4426950408889634f + log2f((float)s.GW);
-    } else if (r < s.GW) {
-      float m = -INFINITY, l = 0.f;
-      for (int g0 = g_lo; g0 <= g_hi; g0 += 8) {       // batches of eight independent loads
-        float2 p[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) p[j] = (g0 + j <= g_hi) ? all_ml[(int64_t)(g0 + j) * QTR + r] : make_float2(-INFINITY, 0.f);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) ml_merge(m, l, p[j].x, p[j].y);
-      }
-      b = m + log2f(l) + log2f((float)s.GW);
-    }
-    nb[r] = -b;
-  }
-  const float *all_ks = reinterpret_cast<const float *>(ws + w.part_ksum) + (slot0 + ul) * D;
   double sq = 0.0;
-  for (int d = tid; d < D; d += kFoldThreads) {
-    float a = 0.f;
-    for (int g0 = g_lo; g0 <= g_hi; g0 += 8) {
-      float p[8];
+  if (tid < kFoldHalf) {
+    for (int r = tid; r < s.nb_rows; r += kFoldHalf) {
+      float b = INFINITY;                              // rows past G*W: weight 0
+      if (r < s.GW && lse_u) {
+        b = lse_u[r] * 1.4426950408889634f + log2f((float)s.GW);
+      } else if (r < s.GW) {
+        float m = -INFINITY, l = 0.f;
+        for (int g0 = g_lo; g0 <= g_hi; g0 += kFoldBatch) {   // batches of independent loads
+          float2 p[kFoldBatch];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) p[j] = (g0 + j <= g_hi) ? all_ks[(int64_t)(g0 + j) * D + d] : 0.f;
+          for (int j = 0; j < kFoldBatch; ++j) p[j] = (g0 + j <= g_hi) ? all_ml[(int64_t)(g0 + j) * QTR + r] : make_float2(-INFINITY, 0.f);
 #pragma unroll
-      for (int j = 0; j < 8; ++j) a += p[j];
+          for (int j = 0; j < kFoldBatch; ++j) ml_merge(m, l, p[j].x, p[j].y);
+        }
+        b = m + log2f(l) + log2f((float)s.GW);
+      }
+      nb[r] = -b;
     }
-    kbar_f[d] = a / (float)N;
-    sq += (double)a * (double)a;
+  } else {
+    const float *all_ks = reinterpret_cast<const float *>(ws + w.part_ksum) + (slot0 + ul) * D;
+    for (int d = tid - kFoldHalf; d < D; d += kFoldHalf) {
+      float a = 0.f;
+      for (int g0 = g_lo; g0 <= g_hi; g0 += kFoldBatch) {
+        float p[kFoldBatch];
+#pragma unroll
+        for (int j = 0; j < kFoldBatch; ++j) p[j] = (g0 + j <= g_hi) ? all_ks[(int64_t)(g0 + j) * D + d] : 0.f;
+#pragma unroll
+        for (int j = 0; j < kFoldBatch; ++j) a += p[j];
+      }
+      kbar_f[d] = a / (float)N;
+      sq += (double)a * (double)a;
+    }
   }
 #pragma unroll
   for (int sft = 32; sft >= 1; sft >>= 1) sq += __shfl_xor(sq, sft);
