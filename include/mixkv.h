@@ -177,6 +177,8 @@ mixkv_status mixkv_score(const mixkv_params *params, const mixkv_layer_in *in, m
  * n_kv_heads * (B' - budget_floor) slots go to the best remaining candidates of all heads
  * together (ties: smaller head, then smaller position).  Per-head mode: head h of layer l keeps its
  * head_budgets[l][h] - W best candidates.
+ * The workspace is optional in fixed and head-adaptive mode, and so is its size: with mixkv_workspace_size bytes rows
+ * beyond 32 768 candidates and head-adaptive budgets of any size are ranked by many workgroups.
  */
 mixkv_status mixkv_select(const mixkv_params *params, mixkv_layer_out *out, int32_t n_layers,
                           void *workspace, size_t workspace_bytes, void *hip_stream);
