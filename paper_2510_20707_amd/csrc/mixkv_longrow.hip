@@ -29,12 +29,40 @@ __device__ __forceinline__ int slot4(int i) { return i + ((i >> 5) << 2); }
 __host__ __device__ constexpr int slots4(int n) { return n + n / 32 * 4 + 4; }
 
 // Shares of a head's statistics, one per segment (in the rows that held the softmax offsets: the second pass was
-// their last reader).  Sums of intrinsic score and diversity are taken relative to the head's first candidate, so
-// that a range far from zero does not cost them their low bits.
+// their last reader).  Sums of intrinsic score and diversity are taken above the share's own minimum: every term is
+// non-negative, here and where two shares meet, so no outlier costs the sums of the others their low bits.
 struct SegStat {
   float sum_a, sum_v, sum_d, min_v, min_d, max_v, max_d;
-  float ref;                             // even segments: the intrinsic score of candidate 0, odd ones: its diversity
+  float n;                               // candidates in the share
 };
+
+// Two shares as one.  Products and sums are written out (the compiler may not contract them one way here and another
+// there), and a share of no candidates leaves the other one as it is.
+__device__ __forceinline__ SegStat join(const SegStat &x, const SegStat &y) {
+  auto above = [](const SegStat &s, float sum, float lo, float lo_all) { return s.n > 0.f ? fmaf(s.n, lo - lo_all, sum) : 0.f; };
+  SegStat r;
+  r.n = x.n + y.n;
+  r.sum_a = x.sum_a + y.sum_a;
+  r.min_v = fminf(x.min_v, y.min_v); r.max_v = fmaxf(x.max_v, y.max_v);
+  r.min_d = fminf(x.min_d, y.min_d); r.max_d = fmaxf(x.max_d, y.max_d);
+  r.sum_v = above(x, x.sum_v, x.min_v, r.min_v) + above(y, y.sum_v, y.min_v, r.min_v);
+  r.sum_d = above(x, x.sum_d, x.min_d, r.min_d) + above(y, y.sum_d, y.min_d, r.min_d);
+  return r;
+}
+
+// The share that the neighbouring group of 2^LEVEL lanes holds, where all lanes of an aligned group hold the same one.
+template <int LEVEL>
+__device__ __forceinline__ float of_neighbour(float x) {
+  if constexpr (LEVEL == 4) return __shfl_xor(x, 16);
+  constexpr int ctrl = LEVEL == 0 ? 0xB1 : (LEVEL == 1 ? 0x4E : (LEVEL == 2 ? 0x141 : 0x140));   // quad_perm, quad_perm, half mirror, mirror
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), ctrl, 0xf, 0xf, true));
+}
+template <int LEVEL>
+__device__ __forceinline__ SegStat join_neighbour(const SegStat &x) {
+  return join(x, SegStat{of_neighbour<LEVEL>(x.sum_a), of_neighbour<LEVEL>(x.sum_v), of_neighbour<LEVEL>(x.sum_d),
+                         of_neighbour<LEVEL>(x.min_v), of_neighbour<LEVEL>(x.min_d), of_neighbour<LEVEL>(x.max_v),
+                         of_neighbour<LEVEL>(x.max_d), of_neighbour<LEVEL>(x.n)});
+}
 __device__ __forceinline__ SegStat *seg_stats(const Shape &s, char *ws, const Workspace &w, int64_t unit) {
   static_assert(sizeof(SegStat) * kMaxSegs <= 256 * sizeof(float), "a head's shares fit its row of softmax offsets");
   return reinterpret_cast<SegStat *>(reinterpret_cast<float *>(ws + w.nb) + unit * s.nb_rows);
@@ -119,31 +147,33 @@ __global__ __launch_bounds__(THREADS) void segstat_kernel(Shape s, char *ws, Wor
   const int ul = blockIdx.x / nseg, seg = blockIdx.x - ul * nseg, s0 = seg * SEG, tid = threadIdx.x;
   const int64_t unit = unit0 + ul;
   const UnitRows rows(s, ws, w, unit);
-  float4 v0, d0;
-  rows.load_vd(0, v0, d0);
-  const float vref = v0.x, dref = d0.x;
-  float st[7] = {0.f, 0.f, 0.f, INFINITY, INFINITY, -INFINITY, -INFINITY};   // sums a, v, d | min v, d | max v, d
+  float v[EPT], d[EPT], a[EPT];
+  float ext[4] = {INFINITY, INFINITY, -INFINITY, -INFINITY};   // min v, d | max v, d
 #pragma unroll
   for (int g = 0; g < EPT / 4; ++g) {
     const int i = s0 + (g * THREADS + tid) * 4;
     float4 vr, dr;
     rows.load_vd(i, vr, dr);
-    const float v4[4] = {vr.x, vr.y, vr.z, vr.w}, d4[4] = {dr.x, dr.y, dr.z, dr.w};
+    v[4 * g] = vr.x; v[4 * g + 1] = vr.y; v[4 * g + 2] = vr.z; v[4 * g + 3] = vr.w;
+    d[4 * g] = dr.x; d[4 * g + 1] = dr.y; d[4 * g + 2] = dr.z; d[4 * g + 3] = dr.w;
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-      if (i + j < s.Nc) {
-        st[1] += v4[j] - vref; st[2] += d4[j] - dref;
-        st[3] = fminf(st[3], v4[j]); st[4] = fminf(st[4], d4[j]);
-        st[5] = fmaxf(st[5], v4[j]); st[6] = fmaxf(st[6], d4[j]);
+    for (int e = 4 * g; e < 4 * g + 4; ++e)
+      if (i + (e & 3) < s.Nc) {
+        ext[0] = fminf(ext[0], v[e]); ext[1] = fminf(ext[1], d[e]);
+        ext[2] = fmaxf(ext[2], v[e]); ext[3] = fmaxf(ext[3], d[e]);
       }
   }
-  float a[EPT];
   load_pooled<THREADS, EPT>(s, rows.araw, s0, a, a_s);
+  block_reduce_mixed<NW, 0, 2, 2>(ext, sc);
+  float sum[3] = {0.f, 0.f, 0.f};                       // a, v, d
 #pragma unroll
   for (int e = 0; e < EPT; ++e)
-    if (s0 + ((e >> 2) * THREADS + tid) * 4 + (e & 3) < s.Nc) st[0] += a[e];
-  block_reduce_mixed<NW, 3, 2, 2>(st, sc);
-  if (tid == 0) seg_stats(s, ws, w, unit)[seg] = SegStat{st[0], st[1], st[2], st[3], st[4], st[5], st[6], (seg & 1) ? dref : vref};
+    if (s0 + ((e >> 2) * THREADS + tid) * 4 + (e & 3) < s.Nc) {
+      sum[0] += a[e]; sum[1] += v[e] - ext[0]; sum[2] += d[e] - ext[1];
+    }
+  block_reduce_mixed<NW, 3, 0, 0>(sum, sc);
+  if (tid == 0)
+    seg_stats(s, ws, w, unit)[seg] = SegStat{sum[0], sum[1], sum[2], ext[0], ext[1], ext[2], ext[3], (float)min(SEG, s.Nc - s0)};
 }
 
 // num / den to within half a unit in the last place, given rden = 1 / den
@@ -195,23 +225,21 @@ __global__ __launch_bounds__(THREADS) void segmix_kernel(Shape s, LayerInTable i
   }
   load_pooled<THREADS, EPT>(s, rows.araw, s0, a, a_s);
 
-  // ---- the head's statistics: lane l holds segment l's share, every wave folds them alike
+  // ---- the head's statistics: lane l holds segment l's share, every wave folds neighbours, then pairs of them, ...
+  static_assert(kMaxSegs == 32, "five levels");
   const SegStat *shares = seg_stats(s, ws, w, unit);
   SegStat x{0.f, 0.f, 0.f, INFINITY, INFINITY, -INFINITY, -INFINITY, 0.f};
   if (lane < nseg) x = shares[lane];
-  const float sum_a = wave_reduce<WSum>(x.sum_a, 0.f), sum_v = wave_reduce<WSum>(x.sum_v, 0.f), sum_d = wave_reduce<WSum>(x.sum_d, 0.f);
-  const float vmin = wave_reduce<WMin>(x.min_v, INFINITY), dmin = wave_reduce<WMin>(x.min_d, INFINITY);
-  const float vmax = wave_reduce<WMax>(x.max_v, -INFINITY), dmax = wave_reduce<WMax>(x.max_d, -INFINITY);
-  const float vref = read_lane(x.ref, 0), dref = read_lane(x.ref, 1);
+  x = join_neighbour<0>(x); x = join_neighbour<1>(x); x = join_neighbour<2>(x); x = join_neighbour<3>(x); x = join_neighbour<4>(x);
+  const float vmin = read_lane(x.min_v, 0), dmin = read_lane(x.min_d, 0), vmax = read_lane(x.max_v, 0), dmax = read_lane(x.max_d, 0);
   const float inv_n = 1.f / (float)Nc;
   const float r = reinterpret_cast<const float *>(ws + w.rbar)[unit];
   float wi, wd;
   mix_weights(s.mix, r, s.mix == MIXKV_MIX_GIVEN_R ? in.l[layer].r_given[bh] : 0.f, wi, wd);
-  // mean((x - min) / den) = (sum(x - ref) + Nc (ref - min)) / (Nc den)
-  const float mean_ex = sum_a * inv_n;
+  const float mean_ex = read_lane(x.sum_a, 0) * inv_n;
   const float vden = vmax - vmin + s.eps, dden = dmax - dmin + s.eps, rvden = 1.f / vden, rdden = 1.f / dden;
-  const float mean_in = (sum_v * inv_n + (vref - vmin)) / vden;
-  const float mean_dn = (sum_d * inv_n + (dref - dmin)) / dden;
+  const float mean_in = read_lane(x.sum_v, 0) * inv_n / vden;           // mean((x - min) / den)
+  const float mean_dn = read_lane(x.sum_d, 0) * inv_n / dden;
   const float f_in = rows.use_v ? mean_ex / (mean_in + s.eps) : 0.f;    // Sec. 3.2: scale VNorm to mean(s_ex)
   const float mean_imp = rows.use_v ? mean_ex + f_in * mean_in : mean_ex;
   const float f_div = mean_imp / (mean_dn + s.eps);                      // Sec. 3.3: scale diversity to mean(s_imp)

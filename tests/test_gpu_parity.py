@@ -350,6 +350,19 @@ def test_long_rows_pool_across_segments(N, over):
     _run_and_check(wl, n_layers=1, **over)
 
 
+# One value row far longer than the others: the means over the segments must not lose the others' low bits to it (a sum of
+# 33 000 ordinary norms taken from that row's was wrong by 3.6e-5 of the score, beyond the 1e-5 of fp32 inputs).
+@pytest.mark.parametrize("at", [0, 1, 4095, 20000])
+def test_long_rows_with_one_outlying_value_norm(at):
+    wl = WL["c2"].with_(name="long-outlier", dtype="f32", seq_len=33000, batch=1, n_q_heads=1, n_kv_heads=1, window=8, text_suffix_start=32900)
+    lay = synth.make_layer(wl, 0)
+    lay.V[:, :, at, :] *= 300.0
+    _say(f"[case] long row, value row {at} times 300")
+    p, outs = H.run_compress(wl, [lay])
+    st = H.check_layer(wl, lay, p, outs[0])
+    _say(f"       max score err {st['max_err']:.2e}")
+
+
 def test_given_r_needs_the_weights():
     wl = WL["c1"]
     with pytest.raises(B.MixkvError) as e:
