@@ -70,10 +70,10 @@ __device__ __forceinline__ SegStat *seg_stats(const Shape &s, char *ws, const Wo
 
 // Loads the raw attention of the segment [s0, s0 + THREADS * EPT) and its halo into LDS (out-of-range
 // candidates hold the pooling's neutral element) and leaves the pooled values of the thread's candidates in
-// a[]: group g of four belongs to thread g % THREADS, so that all loads are coalesced.  Ends past its reads of LDS
-// only after the caller's next barrier.
-template <int THREADS, int EPT>
-__device__ __forceinline__ void load_pooled(const Shape &s, const float *araw, int s0, float (&a)[EPT], float *a_s) {
+// a[]: group_of(0), group_of(1), ... are the thread's groups of four, consecutive threads holding consecutive groups
+// so that all loads are coalesced.  Ends past its reads of LDS only after the caller's next barrier.
+template <int THREADS, int EPT, class GroupOf>
+__device__ __forceinline__ void load_pooled(const Shape &s, const float *araw, int s0, float (&a)[EPT], float *a_s, GroupOf group_of) {
   const int tid = threadIdx.x, Nc = s.Nc;
   const bool pooled = s.pool != MIXKV_POOL_NONE && s.pool_k > 1, is_max = s.pool == MIXKV_POOL_MAX;
   const float fill = is_max ? -INFINITY : 0.f;          // out-of-range taps: ignored by max, zero for avg
@@ -84,7 +84,7 @@ __device__ __forceinline__ void load_pooled(const Shape &s, const float *araw, i
   }
 #pragma unroll
   for (int g = 0; g < EPT / 4; ++g) {
-    const int li = (g * THREADS + tid) * 4, i = s0 + li;
+    const int li = group_of(g) * 4, i = s0 + li;
     float4 r = make_float4(fill, fill, fill, fill);
     if (i < Nc) {                                       // the rows are padded past the last group
       r = *reinterpret_cast<const float4 *>(araw + i);
@@ -102,7 +102,7 @@ __device__ __forceinline__ void load_pooled(const Shape &s, const float *araw, i
     // sliding window in registers over each group: its own values and the aligned groups on either side
 #pragma unroll
     for (int g = 0; g < EPT / 4; ++g) {
-      const int li = kHalo + (g * THREADS + tid) * 4;
+      const int li = kHalo + group_of(g) * 4;
       const float4 lo = *reinterpret_cast<const float4 *>(&a_s[slot4(li - 4)]);
       const float4 hi = *reinterpret_cast<const float4 *>(&a_s[slot4(li + 4)]);
       const float win[10] = {lo.y, lo.z, lo.w, a[4 * g], a[4 * g + 1], a[4 * g + 2], a[4 * g + 3], hi.x, hi.y, hi.z};
@@ -131,7 +131,7 @@ __device__ __forceinline__ void load_pooled(const Shape &s, const float *araw, i
   } else {
 #pragma unroll
     for (int e = 0; e < EPT; ++e) {
-      const int li = kHalo + ((e >> 2) * THREADS + tid) * 4 + (e & 3);
+      const int li = kHalo + group_of(e >> 2) * 4 + (e & 3);
       float acc = a_s[slot4(li - hk)];
       for (int j = li - hk + 1; j <= li + hk; ++j) acc = is_max ? fmaxf(acc, a_s[slot4(j)]) : acc + a_s[slot4(j)];
       a[e] = is_max ? acc : acc / (float)s.pool_k;
@@ -139,41 +139,62 @@ __device__ __forceinline__ void load_pooled(const Shape &s, const float *araw, i
   }
 }
 
-template <int THREADS, int EPT>
-__global__ __launch_bounds__(THREADS) void segstat_kernel(Shape s, char *ws, Workspace w, int64_t unit0, int nseg) {
-  constexpr int SEG = THREADS * EPT, NW = THREADS / 64;
-  __shared__ __align__(16) float a_s[slots4(SEG + 2 * kHalo)];
-  __shared__ MsScratch sc;
-  const int ul = blockIdx.x / nseg, seg = blockIdx.x - ul * nseg, s0 = seg * SEG, tid = threadIdx.x;
+// The statistics are shares of a wave's 512 candidates, joined along one tree over the row: the eight waves of a block of
+// 4096, neighbouring blocks here if a segment has several, the segments in segmix_kernel.  The tree is the same
+// for every cut, so the bits of the statistics, and with them the scores', depend neither on the budget nor on
+// whether a selection follows.  A block is the work of 512 threads, eight candidates each; a workgroup has one or
+// two such halves, and at four blocks a half takes two.
+constexpr int kStatThreads = 512, kStatEpt = 8, kStatBlock = kStatThreads * kStatEpt, kStatWaves = kStatThreads / 64;
+
+template <int BLOCKS>
+__global__ __launch_bounds__(kStatThreads * (BLOCKS > 1 ? 2 : 1)) void segstat_kernel(Shape s, char *ws, Workspace w, int64_t unit0, int nseg) {
+  static_assert((BLOCKS == 1 || BLOCKS == 2 || BLOCKS == 4) && kStatWaves == 8, "a tree of neighbours, up to five levels");
+  constexpr int HALVES = BLOCKS > 1 ? 2 : 1, THREADS = HALVES * kStatThreads, TURNS = BLOCKS / HALVES, EPT = TURNS * kStatEpt;
+  __shared__ __align__(16) float a_s[slots4(BLOCKS * kStatBlock + 2 * kHalo)];
+  __shared__ SegStat share_s[BLOCKS * kStatWaves];
+  const int ul = blockIdx.x / nseg, seg = blockIdx.x - ul * nseg, s0 = seg * BLOCKS * kStatBlock, tid = threadIdx.x, lane = tid & 63;
+  const int half = tid / kStatThreads, ht = tid % kStatThreads, hw = ht / 64;
   const int64_t unit = unit0 + ul;
   const UnitRows rows(s, ws, w, unit);
+  // group g of the thread: turn g / 2 is block HALVES * (g / 2) + half
+  auto group_of = [&](int g) { return ((HALVES * (g >> 1) + half) * 2 + (g & 1)) * kStatThreads + ht; };
   float v[EPT], d[EPT], a[EPT];
-  float ext[4] = {INFINITY, INFINITY, -INFINITY, -INFINITY};   // min v, d | max v, d
 #pragma unroll
   for (int g = 0; g < EPT / 4; ++g) {
-    const int i = s0 + (g * THREADS + tid) * 4;
     float4 vr, dr;
-    rows.load_vd(i, vr, dr);
+    rows.load_vd(s0 + group_of(g) * 4, vr, dr);
     v[4 * g] = vr.x; v[4 * g + 1] = vr.y; v[4 * g + 2] = vr.z; v[4 * g + 3] = vr.w;
     d[4 * g] = dr.x; d[4 * g + 1] = dr.y; d[4 * g + 2] = dr.z; d[4 * g + 3] = dr.w;
-#pragma unroll
-    for (int e = 4 * g; e < 4 * g + 4; ++e)
-      if (i + (e & 3) < s.Nc) {
-        ext[0] = fminf(ext[0], v[e]); ext[1] = fminf(ext[1], d[e]);
-        ext[2] = fmaxf(ext[2], v[e]); ext[3] = fmaxf(ext[3], d[e]);
-      }
   }
-  load_pooled<THREADS, EPT>(s, rows.araw, s0, a, a_s);
-  block_reduce_mixed<NW, 0, 2, 2>(ext, sc);
-  float sum[3] = {0.f, 0.f, 0.f};                       // a, v, d
+  load_pooled<THREADS, EPT>(s, rows.araw, s0, a, a_s, group_of);
 #pragma unroll
-  for (int e = 0; e < EPT; ++e)
-    if (s0 + ((e >> 2) * THREADS + tid) * 4 + (e & 3) < s.Nc) {
-      sum[0] += a[e]; sum[1] += v[e] - ext[0]; sum[2] += d[e] - ext[1];
-    }
-  block_reduce_mixed<NW, 3, 0, 0>(sum, sc);
-  if (tid == 0)
-    seg_stats(s, ws, w, unit)[seg] = SegStat{sum[0], sum[1], sum[2], ext[0], ext[1], ext[2], ext[3], (float)min(SEG, s.Nc - s0)};
+  for (int t = 0; t < TURNS; ++t) {
+    auto on = [&](int e) { return s0 + group_of(e >> 2) * 4 + (e & 3) < s.Nc; };
+    float min_v = INFINITY, min_d = INFINITY, max_v = -INFINITY, max_d = -INFINITY, sum_a = 0.f, sum_v = 0.f, sum_d = 0.f;
+#pragma unroll
+    for (int e = t * kStatEpt; e < (t + 1) * kStatEpt; ++e)
+      if (on(e)) {
+        min_v = fminf(min_v, v[e]); min_d = fminf(min_d, d[e]);
+        max_v = fmaxf(max_v, v[e]); max_d = fmaxf(max_d, d[e]);
+      }
+    min_v = wave_reduce<WMin>(min_v, INFINITY); min_d = wave_reduce<WMin>(min_d, INFINITY);
+    max_v = wave_reduce<WMax>(max_v, -INFINITY); max_d = wave_reduce<WMax>(max_d, -INFINITY);
+#pragma unroll
+    for (int e = t * kStatEpt; e < (t + 1) * kStatEpt; ++e)
+      if (on(e)) { sum_a += a[e]; sum_v += v[e] - min_v; sum_d += d[e] - min_d; }
+    sum_a = wave_reduce<WSum>(sum_a, 0.f); sum_v = wave_reduce<WSum>(sum_v, 0.f); sum_d = wave_reduce<WSum>(sum_d, 0.f);
+    const int block = HALVES * t + half, left = s.Nc - s0 - block * kStatBlock - hw * 256;   // the wave's first and second 64 groups
+    const int n = min(max(left, 0), 256) + min(max(left - kStatBlock / 2, 0), 256);
+    if (lane == 0) share_s[block * kStatWaves + hw] = SegStat{sum_a, sum_v, sum_d, min_v, min_d, max_v, max_d, (float)n};
+  }
+  __syncthreads();
+  if (tid >= 64) return;
+  SegStat x{0.f, 0.f, 0.f, INFINITY, INFINITY, -INFINITY, -INFINITY, 0.f};
+  if (lane < BLOCKS * kStatWaves) x = share_s[lane];
+  x = join_neighbour<0>(x); x = join_neighbour<1>(x); x = join_neighbour<2>(x);
+  if constexpr (BLOCKS > 1) x = join_neighbour<3>(x);
+  if constexpr (BLOCKS > 2) x = join_neighbour<4>(x);
+  if (lane == 0) seg_stats(s, ws, w, unit)[seg] = x;
 }
 
 // num / den to within half a unit in the last place, given rden = 1 / den
@@ -223,9 +244,11 @@ __global__ __launch_bounds__(THREADS) void segmix_kernel(Shape s, LayerInTable i
     v[4 * g] = vr.x; v[4 * g + 1] = vr.y; v[4 * g + 2] = vr.z; v[4 * g + 3] = vr.w;
     d[4 * g] = dr.x; d[4 * g + 1] = dr.y; d[4 * g + 2] = dr.z; d[4 * g + 3] = dr.w;
   }
-  load_pooled<THREADS, EPT>(s, rows.araw, s0, a, a_s);
+  load_pooled<THREADS, EPT>(s, rows.araw, s0, a, a_s, [&](int g) { return g * THREADS + tid; });
 
   // ---- the head's statistics: lane l holds segment l's share, every wave folds neighbours, then pairs of them, ...
+  // From here on products and sums that the compiler could contract in two ways are written out: all instantiations
+  // give the same bits.
   static_assert(kMaxSegs == 32, "five levels");
   const SegStat *shares = seg_stats(s, ws, w, unit);
   SegStat x{0.f, 0.f, 0.f, INFINITY, INFINITY, -INFINITY, -INFINITY, 0.f};
@@ -241,7 +264,7 @@ __global__ __launch_bounds__(THREADS) void segmix_kernel(Shape s, LayerInTable i
   const float mean_in = read_lane(x.sum_v, 0) * inv_n / vden;           // mean((x - min) / den)
   const float mean_dn = read_lane(x.sum_d, 0) * inv_n / dden;
   const float f_in = rows.use_v ? mean_ex / (mean_in + s.eps) : 0.f;    // Sec. 3.2: scale VNorm to mean(s_ex)
-  const float mean_imp = rows.use_v ? mean_ex + f_in * mean_in : mean_ex;
+  const float mean_imp = rows.use_v ? fmaf(f_in, mean_in, mean_ex) : mean_ex;
   const float f_div = mean_imp / (mean_dn + s.eps);                      // Sec. 3.3: scale diversity to mean(s_imp)
   __syncthreads();                                      // the pooling is done with the raw attention: the scores replace it
 #pragma unroll
@@ -250,8 +273,8 @@ __global__ __launch_bounds__(THREADS) void segmix_kernel(Shape s, LayerInTable i
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int e = 4 * g + j;
-      const float imp = rows.use_v ? a[e] + quotient(v[e] - vmin, vden, rvden) * f_in : a[e];   // Eq. 2
-      c[j] = wi * imp + wd * (quotient(d[e] - dmin, dden, rdden) * f_div);                       // Eq. 5
+      const float imp = rows.use_v ? fmaf(quotient(v[e] - vmin, vden, rvden), f_in, a[e]) : a[e];   // Eq. 2
+      c[j] = fmaf(wi, imp, wd * (quotient(d[e] - dmin, dden, rdden) * f_div));                       // Eq. 5
     }
     *reinterpret_cast<float4 *>(&a_s[slot4((g * THREADS + tid) * 4)]) = make_float4(c[0], c[1], c[2], c[3]);
   }
@@ -361,7 +384,7 @@ static hipError_t launch_segmix_e(const Shape &s, const SegPlan &pl, bool select
                                   char *ws, const Workspace &w, int64_t unit0, int nunits, int cand_m, const int32_t *budgets,
                                   hipStream_t st) {
   const dim3 grid((unsigned)(nunits * pl.nseg)), block(THREADS);
-  hipLaunchKernelGGL((segstat_kernel<THREADS, EPT>), grid, block, 0, st, s, ws, w, unit0, pl.nseg);
+  hipLaunchKernelGGL((segstat_kernel<THREADS * EPT / kStatBlock>), grid, block, 0, st, s, ws, w, unit0, pl.nseg);
   if (select) hipLaunchKernelGGL((segmix_kernel<THREADS, EPT, true>), grid, block, 0, st, s, in, out, ws, w, unit0, pl.nseg, cand_m, budgets);
   else hipLaunchKernelGGL((segmix_kernel<THREADS, EPT, false>), grid, block, 0, st, s, in, out, ws, w, unit0, pl.nseg, 0, nullptr);
   return hipGetLastError();

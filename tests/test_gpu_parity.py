@@ -291,6 +291,37 @@ def test_score_entry_point_matches_compress_scores():
     assert torch.equal(sel.indices, ref[0].indices) and torch.equal(sel.counts, ref[0].counts)
 
 
+# Long rows are cut into segments whose length depends on what is kept; the scores may not depend on the cut.  Budgets
+# that cut 66 001 tokens into segments of 4096, 8192 and 16 384 candidates, and one too large for the lists; 140 001
+# tokens are scored in segments of 8192.
+@pytest.mark.parametrize("N,pool,budgets", [(66001, "max", (64, 1232, 2048, 9032)), (140001, "avg", (64, 1232))])
+def test_scores_of_long_rows_do_not_depend_on_the_budget(N, pool, budgets):
+    wl = WL["c2"].with_(name="long-bits", seq_len=N, n_q_heads=2, n_kv_heads=2, batch=1, text_suffix_start=N - 100, pool=pool)
+    lay = synth.make_layer(wl, 0)
+    dev = "cuda:0"
+    K, V, Q = ([H.to_device(wl, x)] for x in (lay.K, lay.V, lay.Q))
+    p = H.gpu_params(wl)
+    alone = B.alloc_layer_out(p, dev, select=False, gather=False)
+    B.mixkv_score(p, K, V, Q, [alone], B.alloc_workspace(p, 1, dev))
+    for mode in ("fixed", "adaptive"):
+        for budget in budgets:
+            if mode == "adaptive" and budget > N // 20:
+                continue
+            _say(f"[case] {wl.name} N={N} {mode} B={budget}")
+            p = H.gpu_params(wl, budget=budget, budget_mode=mode)
+            out = B.alloc_layer_out(p, dev)
+            ws = B.alloc_workspace(p, 1, dev)
+            B.mixkv_compress(p, K, V, Q, [out], ws)
+            # mixkv_select on the scores taken alone reproduces compress' indices
+            sel = B.alloc_layer_out(p, dev, scores=False, redundancy=False, gather=False)
+            sel.scores = alone.scores
+            B.mixkv_select(p, [sel], ws)
+            torch.cuda.synchronize()
+            assert torch.equal(out.scores.view(torch.int32), alone.scores.view(torch.int32))
+            for name in ("indices", "counts", "offsets"):
+                assert torch.equal(getattr(sel, name), getattr(out, name)), name
+
+
 # ------------------------------------------------------------------ ablation variants (Sec. 4.3, Table 4)
 
 VARIANTS = [dict(intrinsic="knorm"), dict(mix="sum"), dict(mix="div_only"), dict(mix="imp_only"), dict(mix="given_r"),
