@@ -16,6 +16,8 @@
 // At 32 768 tokens (448 heads) the three kernels take 155 us and mixsel_kernel, which holds a whole head, 150.
 //
 // Paper: Sec. 3.2 Eq. 2, Sec. 3.3 Eq. 5, Sec. 3.1 / Algorithm 1 (TopB), as in mixsel_kernel.
+#include <cfloat>
+
 #include "mixkv_topsel.h"
 
 namespace mixkv {
@@ -197,6 +199,9 @@ __global__ __launch_bounds__(kStatThreads * (BLOCKS > 1 ? 2 : 1)) void segstat_k
   if (lane == 0) seg_stats(s, ws, w, unit)[seg] = x;
 }
 
+// 1 / den for quotient().  An eps too small for a float reciprocal leaves a head of equal values (range 0) such a
+// denominator: the quotients are 0 then, not 0 times infinity.
+__device__ __forceinline__ float reciprocal(float den) { return fminf(1.f / den, FLT_MAX); }
 // num / den to within half a unit in the last place, given rden = 1 / den
 __device__ __forceinline__ float quotient(float num, float den, float rden) {
   const float q = num * rden;
@@ -260,7 +265,7 @@ __global__ __launch_bounds__(THREADS) void segmix_kernel(Shape s, LayerInTable i
   float wi, wd;
   mix_weights(s.mix, r, s.mix == MIXKV_MIX_GIVEN_R ? in.l[layer].r_given[bh] : 0.f, wi, wd);
   const float mean_ex = read_lane(x.sum_a, 0) * inv_n;
-  const float vden = vmax - vmin + s.eps, dden = dmax - dmin + s.eps, rvden = 1.f / vden, rdden = 1.f / dden;
+  const float vden = vmax - vmin + s.eps, dden = dmax - dmin + s.eps, rvden = reciprocal(vden), rdden = reciprocal(dden);
   const float mean_in = read_lane(x.sum_v, 0) * inv_n / vden;           // mean((x - min) / den)
   const float mean_dn = read_lane(x.sum_d, 0) * inv_n / dden;
   const float f_in = rows.use_v ? mean_ex / (mean_in + s.eps) : 0.f;    // Sec. 3.2: scale VNorm to mean(s_ex)

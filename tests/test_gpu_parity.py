@@ -394,6 +394,20 @@ def test_long_rows_with_one_outlying_value_norm(at):
     _say(f"       max score err {st['max_err']:.2e}")
 
 
+def test_long_rows_of_equal_keys_and_values_with_an_eps_without_a_reciprocal():
+    # the normalised value norm and diversity are 0 / eps = 0 whatever eps > 0, also where 1 / eps is no float
+    wl = WL["c2"].with_(name="long-equal", seq_len=33000, batch=1, n_q_heads=2, n_kv_heads=1, text_suffix_start=32900)
+    lay = synth.make_layer(wl, 0)
+    lay.K[:] = lay.K[0, 0, 0]
+    lay.V[:] = lay.V[0, 0, 0]
+    _say("[case] long row of equal keys and values, eps 1e-40")
+    _, ref = H.run_compress(wl, [lay], mix="sum")
+    _, out = H.run_compress(wl, [lay], mix="sum", eps=1e-40)
+    assert torch.isfinite(ref[0].scores[:, :, :wl.seq_len - wl.window]).all()
+    assert torch.equal(out[0].scores.view(torch.int32), ref[0].scores.view(torch.int32))
+    assert torch.equal(out[0].indices, ref[0].indices)
+
+
 def test_given_r_needs_the_weights():
     wl = WL["c1"]
     with pytest.raises(B.MixkvError) as e:
