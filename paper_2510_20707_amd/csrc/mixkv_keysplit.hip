@@ -63,6 +63,11 @@ __device__ __forceinline__ void image_of_rows(uint4 *img, const uint4 (&r)[NL], 
   }
 }
 
+// Lanes of a wave exchange a tile through the wave's image: what they stored before is visible to what they read
+// after, and what they read before is not overtaken by what they store after.  The wave's LDS operations execute in
+// order, so this holds the compiler only and costs no instruction.
+__device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local"); }
+
 // ------------------------------------------------------------------------------------------------
 // First pass (see stats_kernel for what it computes): softmax partials, key norms, the sum of normalised keys, value norms.
 // ------------------------------------------------------------------------------------------------
@@ -158,7 +163,9 @@ __global__ __launch_bounds__(kKsThreads, ks_wgs(DT, D)) void ks_stats_kernel(Sha
         const int row = lq * RPL + lrow;
         if (lq < NL && tb + row < N) invnorm[t * 32 + row] = keep;
       }
+      wave_lds_fence();
       image_of_rows<DT, D, NL>(img, kr, lane);
+      wave_lds_fence();
       if (t + W < nt) request(t + W);
 
       // ---- per query tile: scores (keys on the MFMA output rows, query rows on the columns), then the running
@@ -323,7 +330,9 @@ __global__ __launch_bounds__(kKsThreads, ks_wgs(DT, D)) void ks_attn_kernel(Shap
         const int row = lq * RPL + lrow;
         if (lq < NL && tb + row < Nc) kdot[t * 32 + row] = keep;
       }
+      wave_lds_fence();
       image_of_rows<DT, D, NL>(img, kr, lane);
+      wave_lds_fence();
       if (t + W < nt) request(t + W);
 
       // ---- per query tile: scores (query rows on the MFMA output rows, keys on the columns), then the weights
