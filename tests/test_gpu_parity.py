@@ -91,6 +91,53 @@ def test_few_query_rows(dtype, D, N, W, Hq, Hkv, over):
     _run_and_check(wl, n_layers=2, **over)
 
 
+# One and two query tiles of either type, whole tiles and a ragged one, for the two tests below.
+FEW_ROWS = [("bf16", 64, 16, 4, 2), ("bf16", 64, 32, 4, 2), ("bf16", 128, 8, 8, 2), ("f32", 64, 16, 4, 2), ("f32", 64, 32, 4, 2),
+            ("f32", 128, 9, 4, 2), ("f32", 128, 32, 4, 2)]
+
+
+# Logits as in the next test, where the waves of a run hold offsets of their own.  A logit of up to 700 in the log2 domain
+# carries two roundings of half a unit, 2 * 2^-15, so fp32 weights are only good to 6e-5; bf16 inputs have 1e-4 anyway.
+@pytest.mark.parametrize("scale", [30.0, 150.0])
+@pytest.mark.parametrize("dtype,D,W,Hq,Hkv", FEW_ROWS)
+def test_few_query_rows_with_large_logits(dtype, D, W, Hq, Hkv, scale):
+    wl = WL["c2"].with_(name="few-rows-large", dtype=dtype, head_dim=D, seq_len=2048, window=W, n_q_heads=Hq, n_kv_heads=Hkv,
+                        text_suffix_start=1984, softmax_scale=scale)
+    lay = synth.make_layer(wl, 0)
+    _say(f"[case] few rows, large logits {dtype} D={D} W={W} Hq={Hq} scale={scale}")
+    p, outs = H.run_compress(wl, [lay])
+    sc, G = outs[0].scores.cpu().numpy().astype(np.float64), wl.group
+    for h in range(Hkv):
+        want = O.score_unit(lay.K[0, h], lay.V[0, h], lay.Q[0, h * G:(h + 1) * G], H.oracle_params(wl))["s_comp"]
+        err = np.abs(sc[0, h, :wl.seq_len - W] - want) / np.maximum(np.abs(want), np.abs(want).mean())
+        _say(f"       head {h}: max score err {err.max():.2e}")
+        assert err.max() <= 1e-4
+
+
+@pytest.mark.parametrize("dtype,D,W,Hq,Hkv", FEW_ROWS)
+def test_few_query_rows_on_a_strided_cache(dtype, D, W, Hq, Hkv):
+    # tokens outermost, heads inside, both in larger slabs: every stride differs from the dense ones
+    wl = WL["c2"].with_(name="few-rows-strided", dtype=dtype, head_dim=D, seq_len=1001, window=W, n_q_heads=Hq, n_kv_heads=Hkv,
+                        batch=2, text_suffix_start=940)
+    lay = synth.make_layer(wl, 0)
+    dev = "cuda:0"
+    _say(f"[case] few rows, strided {dtype} D={D} W={W} Hq={Hq}")
+    _, ref = H.run_compress(wl, [lay])
+    p = H.gpu_params(wl)
+
+    def strided(x):
+        buf = torch.full((2, wl.seq_len + 3, Hkv + 1, D), float("nan"), dtype=B.TORCH_DTYPE[p.dtype], device=dev)
+        view = buf[:, :wl.seq_len, :Hkv].permute(0, 2, 1, 3)
+        view.copy_(H.to_device(wl, x))
+        return view
+
+    out = B.alloc_layer_out(p, dev)
+    B.mixkv_compress(p, [strided(lay.K)], [strided(lay.V)], [H.to_device(wl, lay.Q)], [out], B.alloc_workspace(p, 1, dev))
+    torch.cuda.synchronize()
+    for name in ("scores", "redundancy", "indices", "counts", "offsets", "K_out", "V_out"):
+        assert torch.equal(getattr(out, name).view(torch.uint8), getattr(ref[0], name).view(torch.uint8)), name
+
+
 @pytest.mark.parametrize("scale", [30.0, 150.0])
 def test_large_logits_move_the_softmax_offset_mid_run(scale):
     # Logits with a standard deviation of 30 and 150: at 150 a row meets keys far more than 88 above
@@ -128,7 +175,7 @@ def test_budget_edges():
     # longer rows: 16 and 32 candidates per thread in the fused mix-and-select kernel
     ("c2", dict(seq_len=12000, batch=1, n_q_heads=4, n_kv_heads=2, text_suffix_start=11900)),
     ("c2", dict(seq_len=20000, batch=1, n_q_heads=4, n_kv_heads=2, text_suffix_start=19900)),
-    # beyond the fused kernel's row length: the stand-alone mix and select kernels
+    # beyond the fused kernel's row length: segments, and the merge of their lists
     ("c2", dict(seq_len=33000, batch=1, n_q_heads=4, n_kv_heads=2, text_suffix_start=32900)),
 ])
 def test_identical_keys_degenerate_head(name, kw):
@@ -233,7 +280,7 @@ def test_adaptive_small_all_units():
     _run_and_check(wl, n_layers=2)
     _run_and_check(wl, n_layers=1, budget_floor=0)
     _run_and_check(wl, n_layers=1, budget_floor=64)     # floor == B': nothing left to pool
-    # a pool too large for per-head candidate lists: the split ranks all candidates of all heads
+    # a pool that may go to one head whole: the lists hold every candidate
     _run_and_check(wl, n_layers=1, budget=400)
 
 
@@ -293,10 +340,12 @@ def test_score_entry_point_matches_compress_scores():
 
 # Long rows are cut into segments whose length depends on what is kept; the scores may not depend on the cut.  Budgets
 # that cut 66 001 tokens into segments of 4096, 8192 and 16 384 candidates, and one too large for the lists; 140 001
-# tokens are scored in segments of 8192.
-@pytest.mark.parametrize("N,pool,budgets", [(66001, "max", (64, 1232, 2048, 9032)), (140001, "avg", (64, 1232))])
-def test_scores_of_long_rows_do_not_depend_on_the_budget(N, pool, budgets):
-    wl = WL["c2"].with_(name="long-bits", seq_len=N, n_q_heads=2, n_kv_heads=2, batch=1, text_suffix_start=N - 100, pool=pool)
+# tokens are scored in segments of 8192, 270 001 in segments of 16 384.
+@pytest.mark.parametrize("N,Hkv,pool,budgets", [(66001, 2, "max", (64, 1232, 2048, 9032)), (140001, 2, "avg", (64, 1232)),
+                                                (270001, 1, "none", (64, 3000))])
+def test_scores_of_long_rows_do_not_depend_on_the_budget(N, Hkv, pool, budgets):
+    wl = WL["c2"].with_(name="long-bits", seq_len=N, n_q_heads=Hkv, n_kv_heads=Hkv, head_dim=64 * Hkv, batch=1,
+                        text_suffix_start=N - 100, pool=pool)
     lay = synth.make_layer(wl, 0)
     dev = "cuda:0"
     K, V, Q = ([H.to_device(wl, x)] for x in (lay.K, lay.V, lay.Q))
@@ -344,7 +393,7 @@ def test_c2_scoring_variants(over):
     ("c1", {}, dict(mix="imp_only", intrinsic="vnorm", pool="avg")),
     ("c2", {}, dict(mix="imp_only", intrinsic="none")),
     ("c2", dict(seq_len=1000, text_suffix_start=940, budget_mode="adaptive", budget_floor=8), dict(mix="imp_only")),
-    # beyond the fused mix kernel's row length: the stand-alone mix kernel
+    # beyond the fused mix kernel's row length: segments
     ("c2", dict(seq_len=33000, batch=1, n_q_heads=2, n_kv_heads=1, text_suffix_start=32900), dict(mix="imp_only", intrinsic="none")),
 ])
 def test_importance_only_without_a_redundancy_output_skips_the_key_statistics(name, kw, over):
@@ -367,7 +416,7 @@ def test_scoring_variants_adaptive_budgets_and_long_fallback():
     wl = WL["c2"].with_(name="adaptive-variants", seq_len=1024, text_suffix_start=960, batch=2, budget=96,
                         budget_mode="adaptive", budget_floor=16, sigma=(0.1, 0.8))
     _run_and_check(wl, layer_ids=[1], mix="given_r", intrinsic="knorm")
-    # sequences too long for the fused mix kernel take the plain one
+    # sequences too long for the fused mix kernel are mixed in segments
     wl = WL["c2"].with_(name="long", seq_len=33000, batch=1, n_q_heads=2, n_kv_heads=1, text_suffix_start=32900)
     _run_and_check(wl, n_layers=1, budget=400, mix="sum", intrinsic="knorm")
 
@@ -379,6 +428,53 @@ def test_scoring_variants_adaptive_budgets_and_long_fallback():
 def test_long_rows_pool_across_segments(N, over):
     wl = WL["c2"].with_(name="long-pool", seq_len=N, batch=2, n_q_heads=2, n_kv_heads=1, text_suffix_start=N - 100)
     _run_and_check(wl, n_layers=1, **over)
+
+
+# Segments of 8192 and 16 384 candidates: the last one shorter than the lists or than the pooling window's reach, window and
+# generic pooling, key-norm scores, head-adaptive and per-head budgets.
+@pytest.mark.parametrize("N,Hkv,over", [
+    (66001, 1, dict(budget=1232)), (66001, 1, dict(budget=2048, pool="avg", pool_kernel=9, intrinsic="knorm")),
+    (140001, 1, dict(pool="max", pool_kernel=31)), (65536 + 32 + 3, 1, dict(budget=3032)), (73728 + 32 + 2, 1, dict(budget=1300)),
+    (66001, 2, dict(budget=700, budget_mode="adaptive", budget_floor=50)), (66001, 2, dict(budget=2048, budget_mode="adaptive", mix="sum")),
+    (66001, 2, dict(budget=1000, budget_mode="per_head", head_budgets=np.array([[1900, 64]], dtype=np.int32)))])
+def test_long_rows_in_wide_segments(N, Hkv, over):
+    wl = WL["c2"].with_(name="long-wide", seq_len=N, n_q_heads=Hkv, n_kv_heads=Hkv, text_suffix_start=N - 100, sigma=(0.1, 0.8))
+    _run_and_check(wl, n_layers=1, **over)
+
+
+# Budgets beyond what the merge holds: the row is mixed in segments, its scores go to the workspace, and the selection
+# kernels rank the whole row.
+@pytest.mark.parametrize("Hkv,over", [(1, dict(budget=30000)), (2, dict(budget=16000, budget_mode="adaptive", budget_floor=100)),
+                                      (2, dict(budget=16000, budget_mode="per_head", head_budgets=np.array([[31000, 64]], dtype=np.int32)))])
+def test_long_rows_with_budgets_beyond_the_merge(Hkv, over):
+    wl = WL["c2"].with_(name="long-budget", seq_len=33000, n_q_heads=Hkv, n_kv_heads=Hkv, text_suffix_start=32900, sigma=(0.1, 0.8))
+    lay = synth.make_layer(wl, 0)
+    hb = over.get("head_budgets")
+    kw = {k: v for k, v in over.items() if k != "head_budgets"}
+    _say(f"[case] {wl.name} Hkv={Hkv} {over}, no scores asked for")
+    p, outs = H.run_compress(wl, [lay], want_scores=False, head_budgets=hb, **kw)
+    st = H.check_layer(wl, lay, p, outs[0], head_budgets=None if hb is None else hb[0], **kw)
+    assert st["checked"] == Hkv
+
+
+# Rows that no cut into 32 segments reaches: the one-workgroup mix and selection kernels.
+def test_rows_beyond_any_cut_take_the_plain_mix_and_selection():
+    N = 524288 + 32 + 9
+    wl = WL["c2"].with_(name="longest", seq_len=N, head_dim=64, n_q_heads=1, n_kv_heads=1, text_suffix_start=N - 100)
+    lay = synth.make_layer(wl, 0)
+    for over in (dict(), dict(intrinsic="knorm", mix="sum", pool="avg", pool_kernel=9, budget=700),
+                 dict(mix="imp_only", pool="none", budget_mode="adaptive", budget_floor=5)):
+        want_scores = over.get("mix") != "imp_only"            # without: the scores go to the workspace, the key statistics are skipped
+        _say(f"[case] {wl.name} N={N} {over}")
+        p, outs = H.run_compress(wl, [lay], want_scores=want_scores, want_redundancy=want_scores, **over)
+        st = H.check_layer(wl, lay, p, outs[0], **over)
+        _say(f"       max score err {st['max_err']:.2e}, identical index sets {st['exact']}")
+        assert st["checked"] == 1
+        if want_scores:
+            alone = B.alloc_layer_out(p, "cuda:0", select=False, gather=False)
+            B.mixkv_score(p, [H.to_device(wl, lay.K)], [H.to_device(wl, lay.V)], [H.to_device(wl, lay.Q)], [alone], B.alloc_workspace(p, 1, "cuda:0"))
+            torch.cuda.synchronize()
+            assert torch.equal(alone.scores.view(torch.int32), outs[0].scores.view(torch.int32))
 
 
 # One value row far longer than the others: the means over the segments must not lose the others' low bits to it (a sum of
@@ -509,7 +605,7 @@ def test_given_lse_must_cover_every_layer_of_a_call():
 
 
 def test_very_long_video_cache_128k_tokens():
-    # 256 frames of 510 tokens: beyond the fused mix kernel (plain mix, select and gather kernels),
+    # 256 frames of 510 tokens: beyond the fused mix kernel (mixed in segments, their lists merged, rows gathered),
     # 1024 chunks per head in the streaming kernels; oracle on one head
     wl = WL["c5"].with_(name="video-128k", batch=1, seq_len=64 + 256 * 510 + 64, text_suffix_start=64 + 256 * 510,
                         n_frames=256, budget_mode="fixed", budget=256)
