@@ -133,15 +133,21 @@ typedef struct {
  * Bytes of device workspace mixkv_score / mixkv_compress need for `n_layers`
  * layers of this shape.  mixkv_select needs none and accepts NULL, except in
  * per-head budget mode, where it stages the budget table there and needs
- * n_layers * n_kv_heads * 4 bytes.  In head-adaptive mode mixkv_select uses a
- * workspace of n_layers * batch * n_kv_heads * 8192 bytes if it is given one
- * (two 1024-entry candidate lists per head) and a head's candidates fit them,
- * M = floor + n_kv_heads * (budget - window - floor) <= 1024 and n_kv_heads * M
- * <= 4096: every head is then ranked by a
- * workgroup of its own and a small kernel splits the pool, about ten times
- * faster on long caches than without, where one workgroup per batch item ranks
- * the scores of all heads; the results are the same.  This function's figure
- * is always enough for mixkv_select.
+ * n_layers * n_kv_heads * 4 bytes.  With more it ranks in more workgroups, with
+ * the same results; whatever it is given is scratch that the call may write, in
+ * every budget mode:
+ *   n_layers * batch * n_kv_heads * 8192 bytes (two 1024-entry candidate lists
+ *     per head): in head-adaptive mode, with up to 32 768 candidates and
+ *     M = min(floor + n_kv_heads * (budget - window - floor), Nc) <= 1024, every
+ *     head is ranked by a workgroup of its own and a small kernel splits the pool;
+ *   this function's figure: the same for any M, and beyond 32 768 candidates (up
+ *     to 524 288), in every mode, a head's row is cut into segments with a
+ *     workgroup each, as long as the segments' lists (of up to M entries, or in
+ *     fixed and per-head mode as many as the largest budget keeps beside the
+ *     window) have at most 28 672 entries per head.
+ * In all other cases one workgroup ranks the whole rows of a head (fixed and
+ * per-head mode) or of all heads of a batch item (head-adaptive mode), several
+ * to some tens of times slower on long rows.
  * Host only; touches no GPU (head_budgets is not read).  The workspace needs no
  * initialisation and 256-byte alignment.
  */
@@ -177,8 +183,8 @@ mixkv_status mixkv_score(const mixkv_params *params, const mixkv_layer_in *in, m
  * n_kv_heads * (B' - budget_floor) slots go to the best remaining candidates of all heads
  * together (ties: smaller head, then smaller position).  Per-head mode: head h of layer l keeps its
  * head_budgets[l][h] - W best candidates.
- * The workspace is optional in fixed and head-adaptive mode, and so is its size: with mixkv_workspace_size bytes rows
- * beyond 32 768 candidates and head-adaptive budgets of any size are ranked by many workgroups.
+ * The workspace is optional in fixed and head-adaptive mode, and so is its size (mixkv_workspace_size says what each
+ * size brings); like every workspace it belongs to the call until the call's work is done.
  */
 mixkv_status mixkv_select(const mixkv_params *params, mixkv_layer_out *out, int32_t n_layers,
                           void *workspace, size_t workspace_bytes, void *hip_stream);
