@@ -64,7 +64,7 @@ struct Workspace {
   size_t araw;           // float  [units][Npad]             window/group mean attention before pooling
   size_t sdiv;           // float  [units][Npad]             K_i . Kbar (the mix kernel applies -1/|K_i|)
   size_t cand_idx;       // int32  [units][kMaxCandPerHead]  adaptive mode, selection alone: every head's best
-  size_t cand_key;       // uint32 [units][kMaxCandPerHead]  candidates, ascending, and their order-preserving keys
+  size_t cand_key;       // uint32 [units][kMaxCandPerHead]  candidates, ascending, and their order keys (unused in the full layout)
   size_t scores;         // float  [units][N]                used when the caller passes no scores buffer
   size_t total;
 };

@@ -11,7 +11,7 @@
 //
 // Bound: HBM (four rows of floats per key, read by the statistics and again by the mix; the diversity and the
 // intrinsic score stay in registers from then on).  One 130 688-token prompt of 28 layers and 4 KV heads (234 MB of
-// rows, budget 128, head-adaptive): statistics 51 us (4.6 TB/s), mix and lists 83, merge 33, split 9.  One workgroup
+// rows, budget 128, head-adaptive): statistics 51 us (4.6 TB/s), mix and lists 80, merge 31, split 9.  One workgroup
 // per head for the mix and one per layer for the selection left most of the chip idle: 784 + 2 583 us.
 // At 32 768 tokens (448 heads) the three kernels take 155 us and mixsel_kernel, which holds a whole head, 150.
 //
@@ -145,7 +145,8 @@ __device__ __forceinline__ void load_pooled(const Shape &s, const float *araw, i
 // 4096, neighbouring blocks here if a segment has several, the segments in segmix_kernel.  The tree is the same
 // for every cut, so the bits of the statistics, and with them the scores', depend neither on the budget nor on
 // whether a selection follows.  A block is the work of 512 threads, eight candidates each; a workgroup has one or
-// two such halves, and at four blocks a half takes two.
+// two such halves, and at four blocks a half takes two.  Against one reduction over whatever the workgroup holds:
+// statistics and mix 125 -> 126 us (one block, 112 heads of 130 688), 137 -> 139 (two, 140 001), 173 -> 182 (four, 131 000).
 constexpr int kStatThreads = 512, kStatEpt = 8, kStatBlock = kStatThreads * kStatEpt, kStatWaves = kStatThreads / 64;
 
 template <int BLOCKS>
