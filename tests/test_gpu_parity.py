@@ -284,6 +284,15 @@ def test_adaptive_small_all_units():
     _run_and_check(wl, n_layers=1, budget=400)
 
 
+# Lists as long as the pool, kept in the per-key rows the mix has read: 8, 16 and 32 candidates per thread, split from
+# registers (up to 16 384 entries per batch item) and from memory.
+@pytest.mark.parametrize("N,Hkv,budget,floor", [(7000, 4, 900, 200), (12000, 4, 900, 0), (12000, 2, 5000, 37), (30000, 2, 3000, 0), (30000, 2, 6000, 500)])
+def test_adaptive_budgets_with_long_lists(N, Hkv, budget, floor):
+    wl = WL["c2"].with_(name="adaptive-lists", seq_len=N, text_suffix_start=N - 100, n_q_heads=Hkv, n_kv_heads=Hkv, budget=budget,
+                        budget_mode="adaptive", budget_floor=floor, sigma=(0.1, 0.8))
+    _run_and_check(wl, n_layers=1)
+
+
 def test_more_layers_than_one_launch_group():
     wl = WL["c1"].with_(n_layers=35)
     _run_and_check(wl, n_layers=35)
@@ -691,3 +700,43 @@ def test_a_call_captured_in_a_graph_replays_to_the_eager_results():
         for o, w in zip(outs, want):
             for g, x in zip(fields(o), w):
                 assert torch.equal(g, x), f"replay {rep} differs from the eager call"
+
+
+def test_long_rows_few_query_rows_and_lists_replay_from_a_graph():
+    """The same for the kernels of long rows (segments, merge, split), of few query rows and of a selection on a full-size
+    workspace, captured one after the other in one graph."""
+    wl = WL["c2"].with_(name="graph-long", seq_len=33100, n_q_heads=2, n_kv_heads=2, text_suffix_start=33000, window=8)
+    dev = "cuda:0"
+    lay = synth.make_layer(wl, 0)
+    p = H.gpu_params(wl, budget=200, budget_mode="adaptive", budget_floor=20)
+    out, sel = B.alloc_layer_out(p, dev), B.alloc_layer_out(p, dev, scores=False, redundancy=False, gather=False)
+    sel.scores = out.scores
+    ws = B.alloc_workspace(p, 1, dev)
+    call = B.PreparedCall(p, [H.to_device(wl, lay.K)], [H.to_device(wl, lay.V)], [H.to_device(wl, lay.Q)], [out], ws)
+    _say(f"[case] graph capture {wl.name} N={wl.seq_len}")
+
+    def both(stream):
+        call.compress(stream)
+        B.mixkv_select(p, [sel], ws, stream)
+
+    fields = (out.scores, out.redundancy, out.indices, out.counts, out.offsets, out.K_out, out.V_out, sel.indices, sel.counts, sel.offsets)
+    both(None)
+    torch.cuda.synchronize()
+    want = [t.clone() for t in fields]
+    assert torch.equal(sel.indices, out.indices)
+    side = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        both(side)                                         # warm-up on the capture stream
+        side.synchronize()
+        with torch.cuda.graph(graph, stream=side):
+            both(torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    for rep in range(3):
+        for t in fields:
+            t.zero_()                                      # eager work between the replays
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for g, x in zip(fields, want):
+            assert torch.equal(g, x), f"replay {rep} differs from the eager call"

@@ -117,3 +117,25 @@ def test_heat_map_tile_edges(dtype, D, N, block):
     wl = WL["c2"].with_(name="map-edges", dtype=dtype, head_dim=D, seq_len=N, window=8, budget=16, n_q_heads=3, n_kv_heads=3,
                         text_prefix=4, text_suffix_start=N - 4)
     _check(wl, [synth.make_layer(wl, 0)], "K", block)
+
+
+def test_outputs_are_optional_layer_by_layer():
+    # the means and the heat-map come from one launch: each must be what it is with both asked for
+    wl = WL["c2"].with_(name="sim-optional", seq_len=650, n_layers=3, text_suffix_start=600, n_q_heads=3, n_kv_heads=3)
+    p = H.gpu_params(wl)
+    Xs = [H.to_device(wl, synth.make_layer(wl, l).K) for l in range(3)]
+    print("[case] similarity with optional outputs", flush=True)
+    red, maps = B.mixkv_similarity(p, Xs, 10)
+    only_red, none = B.mixkv_similarity(p, Xs, 10, want_map=False)
+    ws = torch.empty(B.mixkv_similarity_workspace_size(p, 3, 10), dtype=torch.uint8, device="cuda:0")
+    only_maps = [torch.full_like(m, float("nan")) for m in maps]
+    B.PreparedSimilarity(p, Xs, None, only_maps, 10, ws).run()
+    torch.cuda.synchronize()
+    some_red, some_maps = [torch.zeros_like(red[0]), None, torch.zeros_like(red[0])], [None, torch.zeros_like(maps[0]), torch.zeros_like(maps[0])]
+    B.PreparedSimilarity(p, Xs, some_red, some_maps, 10, ws).run()
+    torch.cuda.synchronize()
+    assert none is None
+    for l in range(3):
+        assert torch.equal(only_red[l], red[l]) and torch.equal(only_maps[l], maps[l])
+        assert some_red[l] is None or torch.equal(some_red[l], red[l])
+        assert some_maps[l] is None or torch.equal(some_maps[l], maps[l])
