@@ -42,7 +42,7 @@ __device__ __forceinline__ float inv_norm_a(float ss) {
 // 64 / PPR rows.  Each lane keeps the running sum of its piece of the normalised rows; at the end
 // the lanes holding the same piece are folded and the first PPR lanes store S_a.  diag[a] gets
 // sum_i |Xh_i|^2 (the number of non-zero rows up to rounding), the trace part of the matrix.
-template <int DT, int D>
+template <int DT, int D, bool ONCE>
 __global__ __launch_bounds__(256) void blocksum_kernel(AShape a, RowsInTable in, float *S, float *diag, int nunits) {
   constexpr int EB = DT == MIXKV_BF16 ? 2 : 4, E = 16 / EB, PPR = D * EB / 16, RPL = 64 / PPR, U = 8;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -65,7 +65,8 @@ __global__ __launch_bounds__(256) void blocksum_kernel(AShape a, RowsInTable in,
     for (int u = 0; u < U; ++u) {
       const int row = r + u * RPL + lr;
       q[u] = make_uint4(0u, 0u, 0u, 0u);
-      if (row < rend) q[u] = *reinterpret_cast<const uint4 *>(base + (int64_t)row * L.sn * EB + piece * 16);
+      const char *p = base + (int64_t)row * L.sn * EB + piece * 16;
+      if (row < rend) q[u] = ONCE ? load_piece<true>(p) : load_piece<false>(p);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -290,13 +291,15 @@ mixkv_status mixkv_similarity(const mixkv_params *params, const mixkv_rows_in *i
     const int64_t tiles = any_map ? (a.nb + kMapTile - 1) / kMapTile : 0;
     const dim3 grid_a((unsigned)(nunits * ((a.nb + 3) / 4))), grid_b((unsigned)(nunits + (nunits * tiles * tiles + 7) / 8 * 8));
     const bool bf = params->dtype == MIXKV_BF16;
+    const bool once = read_once((int64_t)nunits * a.N * a.D * eb);
+    auto sums = [&](auto kern) { hipLaunchKernelGGL(kern, grid_a, dim3(256), 0, stream, a, ti, Sg, dg, nunits); };
     if (a.D == 128) {
-      if (bf) hipLaunchKernelGGL((blocksum_kernel<MIXKV_BF16, 128>), grid_a, dim3(256), 0, stream, a, ti, Sg, dg, nunits);
-      else hipLaunchKernelGGL((blocksum_kernel<MIXKV_F32, 128>), grid_a, dim3(256), 0, stream, a, ti, Sg, dg, nunits);
+      if (bf) once ? sums(blocksum_kernel<MIXKV_BF16, 128, true>) : sums(blocksum_kernel<MIXKV_BF16, 128, false>);
+      else once ? sums(blocksum_kernel<MIXKV_F32, 128, true>) : sums(blocksum_kernel<MIXKV_F32, 128, false>);
       hipLaunchKernelGGL(blockgram_kernel<128>, grid_b, dim3(kMapThreads), 0, stream, a, to, Sg, dg, nunits);
     } else {
-      if (bf) hipLaunchKernelGGL((blocksum_kernel<MIXKV_BF16, 64>), grid_a, dim3(256), 0, stream, a, ti, Sg, dg, nunits);
-      else hipLaunchKernelGGL((blocksum_kernel<MIXKV_F32, 64>), grid_a, dim3(256), 0, stream, a, ti, Sg, dg, nunits);
+      if (bf) once ? sums(blocksum_kernel<MIXKV_BF16, 64, true>) : sums(blocksum_kernel<MIXKV_BF16, 64, false>);
+      else once ? sums(blocksum_kernel<MIXKV_F32, 64, true>) : sums(blocksum_kernel<MIXKV_F32, 64, false>);
       hipLaunchKernelGGL(blockgram_kernel<64>, grid_b, dim3(kMapThreads), 0, stream, a, to, Sg, dg, nunits);
     }
     if (hipGetLastError() != hipSuccess) return MIXKV_ERR_HIP;

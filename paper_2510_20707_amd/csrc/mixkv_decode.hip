@@ -113,8 +113,8 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(DShape s, DecodeTab
       if (ok[u]) {
         const char *kp, *vp;
         row_ptrs(row, kp, vp);
-        kq[u] = *reinterpret_cast<const uint4 *>(kp + piece * 16);
-        vq[u] = *reinterpret_cast<const uint4 *>(vp + piece * 16);
+        kq[u] = load_piece<true>(kp + piece * 16);
+        vq[u] = load_piece<true>(vp + piece * 16);
       }
     }
 #pragma unroll
@@ -262,8 +262,8 @@ __global__ __launch_bounds__(D * 2, 2) void decode_mfma_kernel(DShape s, DecodeT
       const int row = min(tb + trow, n - 1);                       // rows past the range repeat its last row
       const int64_t at = (int64_t)row * RB + (lq ^ tile_swz<DT, D>(trow)) * 16;
       const char *kp = (row < cnt ? Kc : Kt) + at, *vp = (row < cnt ? Vc : Vt) + at;
-      __builtin_amdgcn_global_load_lds((glb_void_t *)kp, (lds_void_t *)(uintptr_t)(kring_a + off + j * 1024), 16, 0, 0);
-      __builtin_amdgcn_global_load_lds((glb_void_t *)vp, (lds_void_t *)(uintptr_t)(vring_a + off + j * 1024), 16, 0, 0);
+      load_to_lds<true>(kp, kring_a + off + j * 1024);    // non-temporal: a step reads every row once (143 MB: 43.0 -> 38.8 us a step)
+      load_to_lds<true>(vp, vring_a + off + j * 1024);
     }
   };
 #pragma unroll

@@ -14,6 +14,14 @@ constexpr int kMaxCandPerHead = 1024;   // head-adaptive budgets: list length of
 constexpr int kMaxSegs = 32;            // segments a long row is cut into at most
 constexpr int kMaxStreamGrid = 1024;    // upper bound on the workgroups of a streaming kernel launch
 
+// Loads of cache rows carry the non-temporal bit where a launch streams more than the 256 MB Infinity Cache would keep of
+// it for the next reader.  A plain read of 0.5 to 4 GB then runs at 7.0 to 7.4 TB/s, without the bit at 6.2.  Whole calls,
+// without -> with, by the bytes of K and V: 67 MB 60.8 -> 63.8 us, 134 MB 80.9 -> 83.1, 168 MB 101 -> 104, 197 MB (f32) 79.4 ->
+// 77.2, 235 MB 130 -> 126, 336 MB 166 -> 157, 2.1 GB 730 -> 686; block sums of 117 MB of keys 28.3 -> 29.7, of 235 MB 58.7 -> 54.2.
+// A template parameter, not a branch: the branch in the tile loops cost 2 to 5 %.
+constexpr int64_t kCachedBytes = 180 * 1000 * 1000;
+inline int32_t read_once(int64_t bytes) { return bytes >= kCachedBytes; }
+
 // Per-layer device pointers handed to the kernels by value.
 struct LayerIn {
   const void *K, *V, *Q;
@@ -46,6 +54,7 @@ struct Shape {
   int32_t pool, pool_k, causal, intrinsic, mix, adaptive, per_head, floor_;
   int32_t kstats;        // 1 / |K_i|, the mean normalised key and r are needed (else nothing reads them: the
                          // importance-only mix without the key-norm intrinsic score and without a redundancy output)
+  int32_t once;          // the launch streams more than the caches keep (read_once): non-temporal loads
   float scale_log2e;     // softmax_scale * log2(e)
   float eps;
 };

@@ -34,23 +34,22 @@ __host__ __device__ constexpr int ks_wgs(int dtype, int D) {
 // The 32-row tile that starts at `tile` (wave-uniform) in row layout: load j holds rows j * RPL + lane / PPR, piece
 // lane % PPR.  A whole tile is a uniform address per load plus one lane offset; rows past the last one (row
 // `rows` - 1) repeat it.
-template <int DT, int D, int NL>
+template <int DT, int D, bool ONCE, int NL>
 __device__ __forceinline__ void load_rows(uint4 (&r)[NL], const char *tile, int64_t row_bytes, int rows, int lane) {
   constexpr int PPR = D * Tr<DT>::EB / 16, RPL = 64 / PPR;
   const int lrow = lane / PPR, lq = lane % PPR;
   if (rows >= 32) {
     const uint32_t off = (uint32_t)lrow * (uint32_t)row_bytes + (uint32_t)lq * 16;
 #pragma unroll
-    for (int j = 0; j < NL; ++j) r[j] = *reinterpret_cast<const uint4 *>(tile + (int64_t)(j * RPL) * row_bytes + off);
+    for (int j = 0; j < NL; ++j) r[j] = load_piece<ONCE>(tile + (int64_t)(j * RPL) * row_bytes + off);
   } else {
 #pragma unroll
     for (int j = 0; j < NL; ++j) {
       const int row = min(j * RPL + lrow, rows - 1);
-      r[j] = *reinterpret_cast<const uint4 *>(tile + row * row_bytes + lq * 16);
+      r[j] = load_piece<ONCE>(tile + row * row_bytes + lq * 16);
     }
   }
 }
-
 // Row-layout registers into the wave's tile image (the rotation of read_key_frag).
 template <int DT, int D, int NL>
 __device__ __forceinline__ void image_of_rows(uint4 *img, const uint4 (&r)[NL], int lane) {
@@ -71,7 +70,7 @@ __device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOM
 // ------------------------------------------------------------------------------------------------
 // First pass (see stats_kernel for what it computes): softmax partials, key norms, the sum of normalised keys, value norms.
 // ------------------------------------------------------------------------------------------------
-template <int DT, int D, int TQ>
+template <int DT, int D, int TQ, bool ONCE>
 __global__ __launch_bounds__(kKsThreads, ks_wgs(DT, D)) void ks_stats_kernel(Shape s, LayerInTable in, char *ws, Workspace w, int64_t unit0,
                                                                 int nunits, int64_t slot0) {
   constexpr int EB = Tr<DT>::EB, EPC = Tr<DT>::EPC, NCHK = D / (2 * EPC), PPR = D * EB / 16, RPL = 64 / PPR, TILE = 32 * PPR;
@@ -108,8 +107,8 @@ __global__ __launch_bounds__(kKsThreads, ks_wgs(DT, D)) void ks_stats_kernel(Sha
 
     uint4 kr[NL], vr[NL];
     auto request = [&](int t) {
-      load_rows<DT, D, NL>(kr, Kr + (int64_t)t * 32 * row_bytes, row_bytes, N - key0 - t * 32, lane);
-      if (use_v) load_rows<DT, D, NL>(vr, Vr + (int64_t)t * 32 * row_bytes, row_bytes, N - key0 - t * 32, lane);
+      load_rows<DT, D, ONCE, NL>(kr, Kr + (int64_t)t * 32 * row_bytes, row_bytes, N - key0 - t * 32, lane);
+      if (use_v) load_rows<DT, D, ONCE, NL>(vr, Vr + (int64_t)t * 32 * row_bytes, row_bytes, N - key0 - t * 32, lane);
     };
     if (wave < nt) request(wave);
     Frag qf[TQ][NCHK];
@@ -247,7 +246,7 @@ __global__ __launch_bounds__(kKsThreads, ks_wgs(DT, D)) void ks_stats_kernel(Sha
 // ------------------------------------------------------------------------------------------------
 // Second pass (see attn_kernel): mean attention weight per key and K_i . Kbar.
 // ------------------------------------------------------------------------------------------------
-template <int DT, int D, int TQ>
+template <int DT, int D, int TQ, bool ONCE>
 __global__ __launch_bounds__(kKsThreads, ks_wgs(DT, D)) void ks_attn_kernel(Shape s, LayerInTable in, char *ws, Workspace w, int64_t unit0,
                                                                int nunits) {
   constexpr int EB = Tr<DT>::EB, EPC = Tr<DT>::EPC, NCHK = D / (2 * EPC), PPR = D * EB / 16, RPL = 64 / PPR, TILE = 32 * PPR;
@@ -283,7 +282,7 @@ __global__ __launch_bounds__(kKsThreads, ks_wgs(DT, D)) void ks_attn_kernel(Shap
     const uint4 *kbarp = reinterpret_cast<const uint4 *>(ws + w.kbarp) + unit * (NCHK * 4);
 
     uint4 kr[NL];
-    auto request = [&](int t) { load_rows<DT, D, NL>(kr, Kr + (int64_t)t * 32 * row_bytes, row_bytes, N - key0 - t * 32, lane); };
+    auto request = [&](int t) { load_rows<DT, D, ONCE, NL>(kr, Kr + (int64_t)t * 32 * row_bytes, row_bytes, N - key0 - t * 32, lane); };
     if (wave < nt) request(wave);
     // piece lq of the mean key (bf16: head and remainder rows)
     float kbar[EPC];
@@ -384,11 +383,12 @@ int keysplit_grid(const Shape &s, int dtype, int nunits, int num_cus) {
 }
 
 template <class F>
-static void with_types(int dtype, int D, int QT, F f) {
+static void with_types(int dtype, int D, int QT, bool once, F f) {
   auto tq = [&](auto dt, auto d) {
-    if constexpr (dt() == MIXKV_BF16 && d() == 128) f(dt, d, std::integral_constant<int, 1>{});
-    else if (QT <= 1) f(dt, d, std::integral_constant<int, 1>{});
-    else f(dt, d, std::integral_constant<int, 2>{});
+    auto go = [&](auto t) { once ? f(dt, d, t, std::true_type{}) : f(dt, d, t, std::false_type{}); };
+    if constexpr (dt() == MIXKV_BF16 && d() == 128) go(std::integral_constant<int, 1>{});
+    else if (QT <= 1) go(std::integral_constant<int, 1>{});
+    else go(std::integral_constant<int, 2>{});
   };
   auto dd = [&](auto dt) {
     if (D == 128) tq(dt, std::integral_constant<int, 128>{});
@@ -400,16 +400,16 @@ static void with_types(int dtype, int D, int QT, F f) {
 
 hipError_t launch_ks_stats(const Shape &s, int dtype, const LayerInTable &in, char *ws, const Workspace &w, int64_t unit0, int nunits,
                            int grid, int64_t slot0, hipStream_t st) {
-  with_types(dtype, s.D, s.QT, [&](auto dt, auto d, auto tq) {
-    hipLaunchKernelGGL((ks_stats_kernel<dt(), d(), tq()>), dim3(grid), dim3(kKsThreads), 0, st, s, in, ws, w, unit0, nunits, slot0);
+  with_types(dtype, s.D, s.QT, s.once, [&](auto dt, auto d, auto tq, auto once) {
+    hipLaunchKernelGGL((ks_stats_kernel<dt(), d(), tq(), once()>), dim3(grid), dim3(kKsThreads), 0, st, s, in, ws, w, unit0, nunits, slot0);
   });
   return hipGetLastError();
 }
 
 hipError_t launch_ks_attn(const Shape &s, int dtype, const LayerInTable &in, char *ws, const Workspace &w, int64_t unit0, int nunits,
                           int grid, hipStream_t st) {
-  with_types(dtype, s.D, s.QT, [&](auto dt, auto d, auto tq) {
-    hipLaunchKernelGGL((ks_attn_kernel<dt(), d(), tq()>), dim3(grid), dim3(kKsThreads), 0, st, s, in, ws, w, unit0, nunits);
+  with_types(dtype, s.D, s.QT, s.once, [&](auto dt, auto d, auto tq, auto once) {
+    hipLaunchKernelGGL((ks_attn_kernel<dt(), d(), tq(), once()>), dim3(grid), dim3(kKsThreads), 0, st, s, in, ws, w, unit0, nunits);
   });
   return hipGetLastError();
 }

@@ -123,8 +123,26 @@ __device__ __forceinline__ UnitCoord unit_coord(const Shape &s, int ul) {
   return c;
 }
 
+// A 16-byte piece of a cache row to registers; ONCE: non-temporal.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+template <bool ONCE>
+__device__ __forceinline__ uint4 load_piece(const void *p) {
+  if constexpr (ONCE) {
+    const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
+    return make_uint4(v.x, v.y, v.z, v.w);
+  } else {
+    return *reinterpret_cast<const uint4 *>(p);
+  }
+}
+
 typedef __attribute__((address_space(3))) void lds_void_t;
 typedef __attribute__((address_space(1))) const void glb_void_t;
+
+// 64 lanes x 16 bytes from `src` (per lane) to LDS address `dst` (wave-uniform), directly; ONCE: non-temporal.
+template <bool ONCE>
+__device__ __forceinline__ void load_to_lds(const char *src, uint32_t dst) {
+  __builtin_amdgcn_global_load_lds((glb_void_t *)src, (lds_void_t *)(uintptr_t)dst, 16, 0, ONCE ? 2 : 0);
+}
 
 // Key tiles per chunk.  A chunk is the unit of the work split between workgroups and of the
 // column-sum hand-over in attn_kernel; wide f32 tiles get one tile per chunk.
@@ -164,7 +182,7 @@ __device__ __forceinline__ int tile_swz(int r) {
 // `tile` points at row tb of the tensor (the callers keep it as a running scalar pointer, so the
 // common path is that pointer plus loop-invariant scalar and lane offsets and needs no vector
 // arithmetic).  fetch_tile_clamped is the last tile of a sequence, kept out of line.
-template <int DT, int D, int WAVES>
+template <int DT, int D, int WAVES, bool ONCE>
 __device__ __attribute__((noinline)) void fetch_tile_clamped(const char *tile, int64_t row_bytes, int tb, int N, uint32_t img,
                                                              int wave, int lane) {
   constexpr int PPR = D * Tr<DT>::EB / 16, LOADS = 32 * PPR / 64, RPL = 64 / PPR;
@@ -175,11 +193,11 @@ __device__ __attribute__((noinline)) void fetch_tile_clamped(const char *tile, i
     const int row = j * RPL + lrow;
     const int krow = min(row, N - 1 - tb);                     // rows past the last one repeat it
     const char *src = tile + (int64_t)krow * row_bytes + (lq ^ tile_swz<DT, D>(row)) * 16;
-    __builtin_amdgcn_global_load_lds((glb_void_t *)src, (lds_void_t *)(uintptr_t)(img + j * 1024), 16, 0, 0);
+    load_to_lds<ONCE>(src, img + j * 1024);
   }
 }
 
-template <int DT, int D, int WAVES>
+template <int DT, int D, int WAVES, bool ONCE>
 __device__ __forceinline__ void fetch_tile(const char *tile, int64_t row_bytes, int tb, int N, uint32_t img, int wave,
                                            int lane) {
   constexpr int PPR = D * Tr<DT>::EB / 16, LOADS = 32 * PPR / 64;      // loads per tile
@@ -193,10 +211,10 @@ __device__ __forceinline__ void fetch_tile(const char *tile, int64_t row_bytes, 
       const int j = (jj * WAVES + wave) % LOADS;
       const char *base = tile + (int64_t)(j * RPL) * row_bytes;                  // wave-uniform
       const uint32_t off = (uint32_t)lrow * rb + (uint32_t)((lq ^ tile_swz<DT, D>(j * RPL + lrow)) * 16);   // loop-invariant
-      __builtin_amdgcn_global_load_lds((glb_void_t *)(base + off), (lds_void_t *)(uintptr_t)(img + j * 1024), 16, 0, 0);
+      load_to_lds<ONCE>(base + off, img + j * 1024);
     }
   } else {
-    fetch_tile_clamped<DT, D, WAVES>(tile, row_bytes, tb, N, img, wave, lane);
+    fetch_tile_clamped<DT, D, WAVES, ONCE>(tile, row_bytes, tb, N, img, wave, lane);
   }
 }
 

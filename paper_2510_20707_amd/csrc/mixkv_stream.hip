@@ -43,7 +43,7 @@ __host__ __device__ constexpr int stats_waves_per_simd(int dtype, int D, int wav
   return waves / 4 * wgs;
 }
 
-template <int DT, int D, int WAVES, int TQ, bool GIVEN_LSE = false>
+template <int DT, int D, int WAVES, int TQ, bool ONCE, bool GIVEN_LSE>
 __global__ __launch_bounds__(WAVES * 64, stats_waves_per_simd(DT, D, WAVES, TQ)) void stats_kernel(
     Shape s, LayerInTable in, char *ws, Workspace w, int64_t unit0, int nunits, int64_t slot0) {
   constexpr int EB = Tr<DT>::EB, EPC = Tr<DT>::EPC, NCHK = D / (2 * EPC), PPR = D * EB / 16;
@@ -91,8 +91,8 @@ __global__ __launch_bounds__(WAVES * 64, stats_waves_per_simd(DT, D, WAVES, TQ))
     auto request = [&](int tr) {
       const int tbr = key0 + tr * 32;
       const uint32_t off = (uint32_t)(tr & (kRing - 1)) * (TILE * 16);
-      fetch_tile<DT, D, WAVES>(Kb + tbr * row_bytes, row_bytes, tbr, N, kring_a + off, wave, lane);
-      if (use_v) fetch_tile<DT, D, WAVES>(Vb + tbr * row_bytes, row_bytes, tbr, N, vring_a + off, wave, lane);
+      fetch_tile<DT, D, WAVES, ONCE>(Kb + tbr * row_bytes, row_bytes, tbr, N, kring_a + off, wave, lane);
+      if (use_v) fetch_tile<DT, D, WAVES, ONCE>(Vb + tbr * row_bytes, row_bytes, tbr, N, vring_a + off, wave, lane);
     };
     // first rows of the tile the next step of the loop requests (tile t + kLead at step t)
     const char *Kreq = Kb + (key0 + kLead * 32) * row_bytes, *Vreq = Vb + (key0 + kLead * 32) * row_bytes;
@@ -139,8 +139,8 @@ __global__ __launch_bounds__(WAVES * 64, stats_waves_per_simd(DT, D, WAVES, TQ))
       if (t + kLead < nt) {                            // tile t + kLead goes into the image tile t - 1 has left
         constexpr uint32_t off = (uint32_t)((SLOT + kLead) & (kRing - 1)) * (TILE * 16);
         const int tbr = key0 + (t + kLead) * 32;
-        fetch_tile<DT, D, WAVES>(Kreq, row_bytes, tbr, N, kring_a + off, wave, lane);
-        if (use_v) fetch_tile<DT, D, WAVES>(Vreq, row_bytes, tbr, N, vring_a + off, wave, lane);
+        fetch_tile<DT, D, WAVES, ONCE>(Kreq, row_bytes, tbr, N, kring_a + off, wave, lane);
+        if (use_v) fetch_tile<DT, D, WAVES, ONCE>(Vreq, row_bytes, tbr, N, vring_a + off, wave, lane);
       }
       Kreq += tile_bytes;
       Vreq += tile_bytes;
@@ -440,7 +440,7 @@ __host__ __device__ constexpr int attn_waves_per_simd(int dtype, int D, int wave
   return (dtype == MIXKV_F32 && D == 128 && waves == 4 && tq == 2) ? 1 : 2;
 }
 
-template <int DT, int D, int WAVES, int TQ, bool SPARE>
+template <int DT, int D, int WAVES, int TQ, bool SPARE, bool ONCE>
 __global__ __launch_bounds__(WAVES * 64, attn_waves_per_simd(DT, D, WAVES, TQ)) void attn_kernel(Shape s, LayerInTable in, LayerOutTable out, char *ws,
                                                             Workspace w, int64_t unit0, int nunits) {
   constexpr int EB = Tr<DT>::EB, EPC = Tr<DT>::EPC, NCHK = D / (2 * EPC), PPR = D * EB / 16;
@@ -485,7 +485,7 @@ __global__ __launch_bounds__(WAVES * 64, attn_waves_per_simd(DT, D, WAVES, TQ)) 
 
     const int64_t tile_bytes = 32 * row_bytes;
     auto request = [&](int tr) {
-      fetch_tile<DT, D, WAVES>(Kb + (key0 + tr * 32) * row_bytes, row_bytes, key0 + tr * 32, N,
+      fetch_tile<DT, D, WAVES, ONCE>(Kb + (key0 + tr * 32) * row_bytes, row_bytes, key0 + tr * 32, N,
                                kring_a + (uint32_t)(tr & (kRing - 1)) * (TILE * 16), wave, lane);
     };
     // first row of the tile the next step of the loop requests (tile t + 1 + kLead at step t)
@@ -597,7 +597,7 @@ __global__ __launch_bounds__(WAVES * 64, attn_waves_per_simd(DT, D, WAVES, TQ)) 
       wait_tile<KL>(t + 1, nt);
       lds_barrier();                                   // every wave has read the fragments of tile t: its image is free
       if (t + 1 + kLead < nt)                          // tile t + kRing goes into the image of tile t
-        fetch_tile<DT, D, WAVES>(Kreq, row_bytes, key0 + (t + 1 + kLead) * 32, N, kring_a + (uint32_t)SLOT * (TILE * 16), wave,
+        fetch_tile<DT, D, WAVES, ONCE>(Kreq, row_bytes, key0 + (t + 1 + kLead) * 32, N, kring_a + (uint32_t)SLOT * (TILE * 16), wave,
                                  lane);
       Kreq += tile_bytes;
       const int k = SLOT % KT, g = t / KT;             // tile within its chunk, chunk within the run
@@ -739,7 +739,7 @@ int stream_grid(const Shape &s, int nunits, int num_cus) {
 template <int DT, int D, int WAVES, int TQ, bool GIVEN_LSE = false>
 static hipError_t launch_stats_c(const Shape &s, const LayerInTable &in, char *ws, const Workspace &w, int64_t unit0,
                                  int nunits, int grid, int64_t slot0, hipStream_t st) {
-  auto kern = stats_kernel<DT, D, WAVES, TQ, GIVEN_LSE>;
+  auto kern = s.once ? stats_kernel<DT, D, WAVES, TQ, true, GIVEN_LSE> : stats_kernel<DT, D, WAVES, TQ, false, GIVEN_LSE>;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(WAVES * 64), 0, st, s, in, ws, w, unit0, nunits, slot0);
   return hipGetLastError();
 }
@@ -750,10 +750,10 @@ static hipError_t launch_attn_c(const Shape &s, const LayerInTable &in, const La
                                 hipStream_t st) {
   // with a spare query tile in the padded block the mean key rides in its first two rows
   if (s.QT < WAVES * TQ) {
-    auto kern = attn_kernel<DT, D, WAVES, TQ, true>;
+    auto kern = s.once ? attn_kernel<DT, D, WAVES, TQ, true, true> : attn_kernel<DT, D, WAVES, TQ, true, false>;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(WAVES * 64), 0, st, s, in, out, ws, w, unit0, nunits);
   } else {
-    auto kern = attn_kernel<DT, D, WAVES, TQ, false>;
+    auto kern = s.once ? attn_kernel<DT, D, WAVES, TQ, false, true> : attn_kernel<DT, D, WAVES, TQ, false, false>;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(WAVES * 64), 0, st, s, in, out, ws, w, unit0, nunits);
   }
   return hipGetLastError();
