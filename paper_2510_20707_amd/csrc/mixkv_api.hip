@@ -66,7 +66,6 @@ mixkv_status make_shape(const mixkv_params *p, Shape *s) {
   s->per_head = p->budget_mode == MIXKV_BUDGET_PER_HEAD;
   s->scale_log2e = (float)((double)p->softmax_scale * 1.4426950408889634);
   s->eps = p->eps;
-  s->once = 0;                                      // run() sets it for every launch group
   s->kstats = 1;                                    // run() clears it when nothing reads the key statistics
   return MIXKV_OK;
 }
@@ -280,7 +279,6 @@ static mixkv_status run(const mixkv_params *params, const mixkv_layer_in *in, mi
       to.l[l] = LayerOut{scores, lo.redundancy, lo.indices, lo.counts, lo.offsets, lo.K_out, lo.V_out};
     }
     const int nunits = nl * s.units_per_layer;
-    s.once = read_once((int64_t)nunits * s.N * s.D * eb * (s.intrinsic == MIXKV_INTRINSIC_VNORM ? 2 : 1));
     const int32_t *budgets_l0 = budgets_dev ? budgets_dev + (size_t)l0 * s.hkv : nullptr;
     if (result == MIXKV_OK && (stages & kScore)) {
       const int64_t slot0 = (int64_t)(l0 / kLayersPerLaunch) * (kMaxStreamGrid + kLayersPerLaunch * s.units_per_layer);
@@ -294,6 +292,8 @@ static mixkv_status run(const mixkv_params *params, const mixkv_layer_in *in, mi
           ok(timed(1, [&] {
             hipError_t e = launch_fold(s, params->dtype, to, tl, ws, w, unit0, nunits, ks_stats ? ks_grid : grid, s.nchunks, slot0, stream);
             if (e != hipSuccess) return e;
+            if (!keysplit && keystat_supported(s, params->dtype, nunits, num_cus))
+              return launch_kst_attn(s, ti, ws, w, unit0, nunits, num_cus, stream);
             return keysplit ? launch_ks_attn(s, params->dtype, ti, ws, w, unit0, nunits, ks_grid, stream)
                             : launch_attn(s, params->dtype, ti, to, tl, ws, w, unit0, nunits, grid, slot0, stream);
           })) &&

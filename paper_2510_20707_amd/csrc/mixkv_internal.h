@@ -20,7 +20,7 @@ constexpr int kMaxStreamGrid = 1024;    // upper bound on the workgroups of a st
 // 77.2, 235 MB 130 -> 126, 336 MB 166 -> 157, 2.1 GB 730 -> 686; block sums of 117 MB of keys 28.3 -> 29.7, of 235 MB 58.7 -> 54.2.
 // A template parameter, not a branch: the branch in the tile loops cost 2 to 5 %.
 constexpr int64_t kCachedBytes = 180 * 1000 * 1000;
-inline int32_t read_once(int64_t bytes) { return bytes >= kCachedBytes; }
+inline bool read_once(int64_t bytes) { return bytes >= kCachedBytes; }
 
 // Per-layer device pointers handed to the kernels by value.
 struct LayerIn {
@@ -54,10 +54,14 @@ struct Shape {
   int32_t pool, pool_k, causal, intrinsic, mix, adaptive, per_head, floor_;
   int32_t kstats;        // 1 / |K_i|, the mean normalised key and r are needed (else nothing reads them: the
                          // importance-only mix without the key-norm intrinsic score and without a redundancy output)
-  int32_t once;          // the launch streams more than the caches keep (read_once): non-temporal loads
   float scale_log2e;     // softmax_scale * log2(e)
   float eps;
 };
+
+// read_once for the two passes over `nunits` heads.
+inline bool pass_once(const Shape &s, int dtype, int nunits) {
+  return read_once((int64_t)nunits * s.N * s.D * (dtype == MIXKV_BF16 ? 2 : 4) * (s.intrinsic == MIXKV_INTRINSIC_VNORM ? 2 : 1));
+}
 
 // Workspace carve-up (byte offsets from a 256-byte aligned base).  Sizes are per call (all units).
 struct Workspace {
@@ -117,6 +121,10 @@ hipError_t launch_ks_stats(const Shape &s, int dtype, const LayerInTable &in, ch
                            int grid, int64_t slot0, hipStream_t st);
 hipError_t launch_ks_attn(const Shape &s, int dtype, const LayerInTable &in, char *ws, const Workspace &w, int64_t unit0, int nunits,
                           int grid, hipStream_t st);
+// The second pass of long bf16 launches (mixkv_keystat.hip).
+bool keystat_supported(const Shape &s, int dtype, int nunits, int num_cus);
+hipError_t launch_kst_attn(const Shape &s, const LayerInTable &in, char *ws, const Workspace &w, int64_t unit0, int nunits, int num_cus,
+                           hipStream_t st);
 hipError_t launch_mix(const Shape &s, const LayerInTable &in, const LayerOutTable &out, char *ws, const Workspace &w,
                       int64_t unit0, int nunits, hipStream_t st);
 // Weights of s_imp and of the scaled diversity in s_comp (Sec. 3.3, Eq. 5; Table 4's variants);

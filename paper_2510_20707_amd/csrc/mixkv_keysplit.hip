@@ -400,7 +400,7 @@ static void with_types(int dtype, int D, int QT, bool once, F f) {
 
 hipError_t launch_ks_stats(const Shape &s, int dtype, const LayerInTable &in, char *ws, const Workspace &w, int64_t unit0, int nunits,
                            int grid, int64_t slot0, hipStream_t st) {
-  with_types(dtype, s.D, s.QT, s.once, [&](auto dt, auto d, auto tq, auto once) {
+  with_types(dtype, s.D, s.QT, pass_once(s, dtype, nunits), [&](auto dt, auto d, auto tq, auto once) {
     hipLaunchKernelGGL((ks_stats_kernel<dt(), d(), tq(), once()>), dim3(grid), dim3(kKsThreads), 0, st, s, in, ws, w, unit0, nunits, slot0);
   });
   return hipGetLastError();
@@ -408,7 +408,7 @@ hipError_t launch_ks_stats(const Shape &s, int dtype, const LayerInTable &in, ch
 
 hipError_t launch_ks_attn(const Shape &s, int dtype, const LayerInTable &in, char *ws, const Workspace &w, int64_t unit0, int nunits,
                           int grid, hipStream_t st) {
-  with_types(dtype, s.D, s.QT, s.once, [&](auto dt, auto d, auto tq, auto once) {
+  with_types(dtype, s.D, s.QT, pass_once(s, dtype, nunits), [&](auto dt, auto d, auto tq, auto once) {
     hipLaunchKernelGGL((ks_attn_kernel<dt(), d(), tq(), once()>), dim3(grid), dim3(kKsThreads), 0, st, s, in, ws, w, unit0, nunits);
   });
   return hipGetLastError();

@@ -1,0 +1,219 @@
+// The second pass over long bf16 caches with the keys in registers and the window queries in LDS.
+//
+// attn_kernel keeps the queries in registers and walks a key tile with all waves of a workgroup, a barrier per tile and two matrix
+// instructions per fragment read from LDS.  Here a wave takes 64 keys of its own into registers, and every fragment of a query tile that
+// it reads from LDS serves both of its key tiles; column sums are complete inside the wave, and nothing crosses waves until the run ends.
+// Any number of query tiles, a loop, shares one kernel.
+//   * The keys come through a private 32-row LDS image per wave (direct-to-LDS loads, whole rows): one of the block's two tiles waits in
+//     registers, the other is asked for as soon as its predecessor has been read, half a block ahead.  Straight from memory in fragment form
+//     (32-byte pieces) the pass reads 4.3 TB/s, through the image 4.9.
+//   * Blocks are walked from a run's last to its first: the first pass read those last, and the caches may still hold them (1 % of a call).
+//   * K_i . Kbar: 16x16x32 matrix instructions on the same key fragments (half the cost of a 32-row tile): a fragment's lanes 0-15 and
+//     16-31 are two groups of keys, told apart by the contraction group, so the mean key's rows are zero for the other group's.
+// Bound: the card's power.  Matrix instructions alone run at 1.8 GHz here, with the weights' arithmetic at 1.9 to 2.0 and with the key
+// stream at 1.5 to 1.7 of 2.4 GHz; a chain of eight and its 48 vector instructions take 207 to 224 ns per SIMD in isolation, 250 here.
+// attn_kernel -> this, us, alone on the chip, 7 query tiles and 224 heads of 32768 keys 535 -> 505, 4 tiles and 256 heads of 16384 keys
+// 248 -> 214, 2 tiles and 224 heads of 8192 keys 120 -> 90.
+// Not better: three waves per SIMD, blocks dealt by a counter (the younger wave of a SIMD ends later, but the time is the same), four key
+// tiles a wave (no registers left for the next).
+#include "mixkv_stream.h"
+
+namespace mixkv {
+
+constexpr int kKstWaves = 8, kKstThreads = kKstWaves * 64;
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// Wait for everything this wave has in flight towards its image; nothing that reads the image moves up past it.
+__device__ __forceinline__ void image_landed() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+// The image's reads have reached registers: it may be requested anew.
+__device__ __forceinline__ void image_read() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+template <int D, int QTMAX, bool ONCE>
+__global__ __launch_bounds__(kKstThreads, 2) void kst_attn_kernel(Shape s, LayerInTable in, char *ws, Workspace w, int64_t unit0,
+                                                                  int nunits, int nblk) {
+  constexpr int DT = MIXKV_BF16, EB = 2, NCHK = D / 16, PPR = D / 8, TILE = 32 * PPR, BK = 64;
+  __shared__ uint4 q_s[QTMAX * TILE];                  // query tiles, bank-rotated rows
+  __shared__ uint4 img_s[kKstWaves * TILE];            // one key tile per wave on its way to registers
+  __shared__ float nb_s[QTMAX * 32];                   // exponent offsets -b_r
+  __shared__ int lim_s[QTMAX * 32];                    // last key each query row attends to
+  __shared__ uint4 kb_s[NCHK * 4];                     // mean key: bf16 head and remainder
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int N = s.N, Nc = s.Nc, Npad = s.Npad, QT = s.QT;
+  const float c2 = s.scale_log2e;
+  const int free_limit = s.causal ? Nc : N - 1;
+  const uint4 *img = img_s + wave * TILE;
+  const uint32_t img_a = lds_base_of(img_s) + (uint32_t)wave * (TILE * 16), q_a = lds_base_of(q_s);
+  for (int r = tid; r < QTMAX * 32; r += kKstThreads) lim_s[r] = s.causal ? Nc + r % s.W : N - 1;
+  const int64_t T = (int64_t)nunits * nblk;
+  int64_t item = wg_first_item(blockIdx.x, gridDim.x, T);
+  const int64_t item_end = wg_first_item(blockIdx.x + 1, gridDim.x, T);
+
+  while (item < item_end) {
+    const int ul = (int)(item / nblk), b0 = (int)(item - (int64_t)ul * nblk);
+    const int nb = (int)min((int64_t)(nblk - b0), item_end - item);   // blocks of the run
+    const int64_t unit = unit0 + ul;
+    const UnitCoord uc = unit_coord(s, ul);
+    const LayerIn L = in.l[uc.layer];
+    const int64_t row_bytes = L.sn * EB;
+    const char *Kb = reinterpret_cast<const char *>(L.K) + ((int64_t)uc.b * L.sb + (int64_t)uc.h * L.sh) * EB;
+    const char *Qb = reinterpret_cast<const char *>(L.Q) + ((int64_t)(uc.b * s.hq + uc.h * s.G) * s.W * D) * EB;
+    float *araw = reinterpret_cast<float *>(ws + w.araw) + unit * s.Npad;
+    float *kdot = reinterpret_cast<float *>(ws + w.sdiv) + unit * s.Npad;
+    const float *nbg = reinterpret_cast<const float *>(ws + w.nb) + unit * s.nb_rows;
+    const uint4 *kbarp = reinterpret_cast<const uint4 *>(ws + w.kbarp) + unit * (NCHK * 4);
+
+    // Request the key tile of rows [row0, row0 + 32) into the wave's image (rows past the last one repeat it).
+    auto request = [&](int row0) {
+      const int r0 = min(row0, N - 1);
+      fetch_tile<DT, D, 1, ONCE>(Kb + r0 * row_bytes, row_bytes, r0, N, img_a, 0, lane);
+    };
+    auto take = [&](Frag (&k)[NCHK]) {
+#pragma unroll
+      for (int c = 0; c < NCHK; ++c) k[c].q = read_key_frag<DT, D>(img, 0, c, l32, half);
+    };
+    const int b9 = b0 + nb - 1;
+    const int row_first = (b9 - min(wave, nb - 1)) * BK;
+    lds_barrier();                                     // the previous run is done with LDS
+    request(row_first);
+    for (int q = wave; q < QT; q += kKstWaves)
+      fetch_tile<DT, D, 1, false>(Qb + (int64_t)q * 32 * D * EB, D * EB, q * 32, s.GW, q_a + q * (TILE * 16), 0, lane);
+    for (int r = tid; r < QT * 32; r += kKstThreads) nb_s[r] = nbg[r];
+    for (int p = tid; p < NCHK * 4; p += kKstThreads) kb_s[p] = kbarp[p];
+    image_landed();
+    lds_barrier();
+    // The results of a block are stored at the start of the wave's next one, in front of its requests: the waits for the
+    // image then find them long finished.
+    int tbp = Npad;                                    // first key of the block whose results are held (none yet)
+    float csp = 0.f, kdp[2];
+    auto store = [&] {
+      if (tbp + lane < Nc) araw[tbp + lane] = csp;
+      if (half == 0 && tbp + l32 < Nc) kdot[tbp + l32] = kdp[0];
+      if (half == 0 && tbp + 32 + l32 < Nc) kdot[tbp + 32 + l32] = kdp[1];
+    };
+    Frag kn[NCHK], kf[2][NCHK];
+    take(kn);
+    image_read();
+    request(row_first + 32);
+
+    for (int blk = wave; blk < nb; blk += kKstWaves) {
+      const int tb = (b9 - blk) * BK;
+      const int nxt = (b9 - min(blk + kKstWaves, nb - 1)) * BK;
+#pragma unroll
+      for (int c = 0; c < NCHK; ++c) kf[0][c] = kn[c];
+      image_landed();
+      take(kf[1]);
+      image_read();
+      store();
+      request(nxt);
+      const bool masked = tb + BK - 1 > free_limit;
+
+      // ---- K_i . Kbar: rows 0, 1 (head, remainder) belong to keys 0-15 of a tile, rows 4, 5 to keys 16-31
+      float kd[2];
+      {
+        f32x4 kacc[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) kacc[t][i] = 0.f;
+        const int m = lane & 15, kg = lane >> 4;         // row and contraction group of the 16x16x32 operand
+        const bool mine = (m >> 2) == (kg & 1) && (m & 2) == 0 && m < 8;
+#pragma unroll
+        for (int c = 0; c < NCHK; ++c) {
+          Frag a;
+          a.q = kb_s[(c * 2 + (kg >> 1)) * 2 + (m & 1)];
+          if (!mine) a.q = make_uint4(0, 0, 0, 0);
+#pragma unroll
+          for (int t = 0; t < 2; ++t) kacc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.h, kf[t][c].h, kacc[t], 0, 0, 0);
+        }
+#pragma unroll
+        for (int t = 0; t < 2; ++t) kd[t] = kacc[t][0] + kacc[t][1];
+      }
+
+      // ---- weights of one query tile on both key tiles
+      float cs[2] = {0.f, 0.f};
+      auto tile = [&](int q) {
+        Frag qf[NCHK];
+#pragma unroll
+        for (int c = 0; c < NCHK; ++c) qf[c].q = read_key_frag<DT, D>(q_s, q, c, l32, half);
+        f32x16 acc[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) acc[t][i] = 0.f;
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int c = 0; c < NCHK; ++c) acc[t] = mma<DT>(qf[c], kf[t][c], acc[t]);
+        float nbv[16];
+#pragma unroll
+        for (int k4 = 0; k4 < 4; ++k4) {
+          const float4 v = *reinterpret_cast<const float4 *>(nb_s + q * 32 + 8 * k4 + 4 * half);
+          nbv[4 * k4 + 0] = v.x; nbv[4 * k4 + 1] = v.y; nbv[4 * k4 + 2] = v.z; nbv[4 * k4 + 3] = v.w;
+        }
+        if (masked) {
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            const int lim = lim_s[q * 32 + 8 * (i >> 2) + 4 * half + (i & 3)];
+#pragma unroll
+            for (int t = 0; t < 2; ++t) acc[t][i] = (tb + t * 32 + l32 <= lim) ? acc[t][i] : -INFINITY;
+          }
+        }
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          float c4[4];
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            const float wgt = fast_exp2(fmaf(acc[t][i], c2, nbv[i]));
+            c4[i & 3] = i < 4 ? wgt : c4[i & 3] + wgt;
+          }
+          cs[t] += (c4[0] + c4[1]) + (c4[2] + c4[3]);
+        }
+      };
+      const int qm = QT / 2;
+      for (int q = 0; q < qm; ++q) tile(q);
+      image_landed();
+      take(kn);
+      image_read();
+      request(nxt + 32);
+      for (int q = qm; q < QT; ++q) tile(q);
+#pragma unroll
+      for (int t = 0; t < 2; ++t) cs[t] += __shfl_xor(cs[t], 32);
+      // lanes 0..31 hold K_i . Kbar of their tile row l32 (see `mine`); the upper half keeps the second tile's column sums
+      csp = half ? cs[1] : cs[0];
+      kdp[0] = kd[0];
+      kdp[1] = kd[1];
+      tbp = tb;
+    }
+    store();
+    image_landed();                                    // requests past the run's last block are unused, but must not land later
+    item += nb;
+  }
+}
+
+// From sixteen 128-key chunks per compute unit on (64 KB of queries are staged per workgroup and run): 7 query tiles, 8192 keys per
+// head, old -> this, us: 3.5 chunks per unit 9.4 -> 11.9, 14 chunks 45 -> 48, 28 chunks 80 -> 73; 4 query tiles: 8 chunks 21.4 -> 21.9, 16
+// chunks 36.7 -> 35.7, 32 chunks 67 -> 64.
+// A wave takes whole 64-key blocks: not where the last round of them would leave more than a tenth of the time idle (112 heads of 7013 keys,
+// 6.02 blocks a wave: 170 us a call with attn_kernel, 172 with this).
+bool keystat_supported(const Shape &s, int dtype, int nunits, int num_cus) {
+  if (dtype != MIXKV_BF16 || s.QT > (s.D == 128 ? 8 : 16) || (int64_t)nunits * s.nchunks < 16 * (int64_t)num_cus) return false;
+  const int64_t blocks = (int64_t)nunits * ((s.N + 63) / 64), waves = (int64_t)num_cus * kKstWaves, rounds = (blocks + waves - 1) / waves;
+  return 10 * rounds * waves <= 11 * blocks;
+}
+
+hipError_t launch_kst_attn(const Shape &s, const LayerInTable &in, char *ws, const Workspace &w, int64_t unit0, int nunits, int num_cus,
+                           hipStream_t st) {
+  const int nblk = (s.N + 63) / 64;
+  const int64_t T = (int64_t)nunits * nblk, cap = (int64_t)num_cus;
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)(T < cap ? T : cap)), dim3(kKstThreads), 0, st, s, in, ws, w, unit0, nunits, nblk);
+    return hipGetLastError();
+  };
+  const bool once = pass_once(s, MIXKV_BF16, nunits);
+  if (s.D == 128) return once ? go(kst_attn_kernel<128, 8, true>) : go(kst_attn_kernel<128, 8, false>);
+  return once ? go(kst_attn_kernel<64, 16, true>) : go(kst_attn_kernel<64, 16, false>);
+}
+
+}  // namespace mixkv

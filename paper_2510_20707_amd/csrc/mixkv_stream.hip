@@ -739,7 +739,7 @@ int stream_grid(const Shape &s, int nunits, int num_cus) {
 template <int DT, int D, int WAVES, int TQ, bool GIVEN_LSE = false>
 static hipError_t launch_stats_c(const Shape &s, const LayerInTable &in, char *ws, const Workspace &w, int64_t unit0,
                                  int nunits, int grid, int64_t slot0, hipStream_t st) {
-  auto kern = s.once ? stats_kernel<DT, D, WAVES, TQ, true, GIVEN_LSE> : stats_kernel<DT, D, WAVES, TQ, false, GIVEN_LSE>;
+  auto kern = pass_once(s, DT, nunits) ? stats_kernel<DT, D, WAVES, TQ, true, GIVEN_LSE> : stats_kernel<DT, D, WAVES, TQ, false, GIVEN_LSE>;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(WAVES * 64), 0, st, s, in, ws, w, unit0, nunits, slot0);
   return hipGetLastError();
 }
@@ -750,10 +750,10 @@ static hipError_t launch_attn_c(const Shape &s, const LayerInTable &in, const La
                                 hipStream_t st) {
   // with a spare query tile in the padded block the mean key rides in its first two rows
   if (s.QT < WAVES * TQ) {
-    auto kern = s.once ? attn_kernel<DT, D, WAVES, TQ, true, true> : attn_kernel<DT, D, WAVES, TQ, true, false>;
+    auto kern = pass_once(s, DT, nunits) ? attn_kernel<DT, D, WAVES, TQ, true, true> : attn_kernel<DT, D, WAVES, TQ, true, false>;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(WAVES * 64), 0, st, s, in, out, ws, w, unit0, nunits);
   } else {
-    auto kern = s.once ? attn_kernel<DT, D, WAVES, TQ, false, true> : attn_kernel<DT, D, WAVES, TQ, false, false>;
+    auto kern = pass_once(s, DT, nunits) ? attn_kernel<DT, D, WAVES, TQ, false, true> : attn_kernel<DT, D, WAVES, TQ, false, false>;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(WAVES * 64), 0, st, s, in, out, ws, w, unit0, nunits);
   }
   return hipGetLastError();
