@@ -285,12 +285,17 @@ static mixkv_status run(const mixkv_params *params, const mixkv_layer_in *in, mi
       const bool given_lse = in[0].window_lse != nullptr, keysplit = keysplit_supported(s, params->dtype);
       const int grid = stream_grid(s, nunits, num_cus), ks_grid = keysplit_grid(s, params->dtype, nunits, num_cus);
       const bool ks_stats = keysplit && !given_lse;
+      int64_t max_stride_n = 0;
+      for (int l = 0; l < nl; ++l) max_stride_n = in[l0 + l].kv_stride_n > max_stride_n ? in[l0 + l].kv_stride_n : max_stride_n;
+      const bool q_stats = !keysplit && !given_lse && qstats_supported(s, params->dtype, nunits, num_cus, max_stride_n);
+      const int stats_grid = q_stats ? qstats_grid(s, nunits, num_cus) : ks_stats ? ks_grid : grid;
       ok(timed(0, [&] {
+        if (q_stats) return launch_qstats(s, ti, ws, w, unit0, nunits, stats_grid, slot0, stream);
         return ks_stats ? launch_ks_stats(s, params->dtype, ti, ws, w, unit0, nunits, ks_grid, slot0, stream)
                         : launch_stats(s, params->dtype, ti, ws, w, unit0, nunits, grid, slot0, given_lse, stream);
       })) &&
           ok(timed(1, [&] {
-            hipError_t e = launch_fold(s, params->dtype, to, tl, ws, w, unit0, nunits, ks_stats ? ks_grid : grid, s.nchunks, slot0, stream);
+            hipError_t e = launch_fold(s, params->dtype, to, tl, ws, w, unit0, nunits, stats_grid, s.nchunks, slot0, stream);
             if (e != hipSuccess) return e;
             if (!keysplit && keystat_supported(s, params->dtype, nunits, num_cus))
               return launch_kst_attn(s, ti, ws, w, unit0, nunits, num_cus, stream);

@@ -121,6 +121,11 @@ hipError_t launch_ks_stats(const Shape &s, int dtype, const LayerInTable &in, ch
                            int grid, int64_t slot0, hipStream_t st);
 hipError_t launch_ks_attn(const Shape &s, int dtype, const LayerInTable &in, char *ws, const Workspace &w, int64_t unit0, int nunits,
                           int grid, hipStream_t st);
+// The first pass of long bf16 launches (mixkv_qstats.hip); `max_stride_n`: largest row stride of the launch, in elements.
+bool qstats_supported(const Shape &s, int dtype, int nunits, int num_cus, int64_t max_stride_n);
+int qstats_grid(const Shape &s, int nunits, int num_cus);
+hipError_t launch_qstats(const Shape &s, const LayerInTable &in, char *ws, const Workspace &w, int64_t unit0, int nunits, int grid,
+                         int64_t slot0, hipStream_t st);
 // The second pass of long bf16 launches (mixkv_keystat.hip).
 bool keystat_supported(const Shape &s, int dtype, int nunits, int num_cus);
 hipError_t launch_kst_attn(const Shape &s, const LayerInTable &in, char *ws, const Workspace &w, int64_t unit0, int nunits, int num_cus,
