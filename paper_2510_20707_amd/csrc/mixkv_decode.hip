@@ -342,7 +342,7 @@ __global__ __launch_bounds__(D * 2, 2) void decode_mfma_kernel(DShape s, DecodeT
       }
     }
     float lnew = l + ((sum[0] + sum[1]) + (sum[2] + sum[3]));
-    if (__builtin_amdgcn_ballot_w64(!(lnew < 1e30f)) != 0) {
+    if (__builtin_amdgcn_ballot_w64(!(lnew < kSumLimit)) != 0) {
       float tmax = fmaxf(acc[0], acc[1]);
 #pragma unroll
       for (int i = 2; i < 16; i += 2) tmax = fmaxf(fmaxf(tmax, acc[i]), acc[i + 1]);

@@ -198,7 +198,7 @@ __global__ __launch_bounds__(kKsThreads, ks_wgs(DT, D)) void ks_stats_kernel(Sha
           sum[i & 3] = i < 4 ? term : sum[i & 3] + term;
         }
         float lnew = l[q] + ((sum[0] + sum[1]) + (sum[2] + sum[3]));
-        if (__builtin_amdgcn_ballot_w64(!(lnew < INFINITY)) != 0) {
+        if (__builtin_amdgcn_ballot_w64(!(lnew < kSumLimit)) != 0) {
           float tmax = fmaxf(acc[0], acc[1]);
 #pragma unroll
           for (int i = 2; i < 16; i += 2) tmax = fmaxf(fmaxf(tmax, acc[i]), acc[i + 1]);

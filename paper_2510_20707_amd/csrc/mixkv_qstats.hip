@@ -260,7 +260,7 @@ __global__ __launch_bounds__(kQsThreads, 2) void qs_stats_kernel(Shape s, LayerI
           sum[e & 3] = e < 4 ? term : sum[e & 3] + term;
         }
         float lnew = l[q] + ((sum[0] + sum[1]) + (sum[2] + sum[3]));
-        if (__builtin_amdgcn_ballot_w64(!(lnew < INFINITY)) != 0) {
+        if (__builtin_amdgcn_ballot_w64(!(lnew < kSumLimit)) != 0) {
           float tmax = fmaxf(acc[0], acc[1]);
 #pragma unroll
           for (int e = 2; e < 16; e += 2) tmax = fmaxf(fmaxf(tmax, acc[e]), acc[e + 1]);

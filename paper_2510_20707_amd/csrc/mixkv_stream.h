@@ -97,6 +97,11 @@ __device__ __forceinline__ float inv_norm(float ss) {
   return ss > 0.f ? fminf(y, 1e30f) : 0.f;
 }
 
+// A running sum of softmax terms that reaches this moves its row's offset.  Not the largest float: where the offset rises by more than 126 the
+// factor 2^(old - new) is flushed to zero, which drops a sum of up to 2^100 at 2^-26 of the new one, but would drop a sum of 2^127 that
+// is as large as the new one.
+constexpr float kSumLimit = 1e30f;
+
 // Merge two running (max, sum) pairs of a softmax row (log2 domain).  A pair that has seen no
 // key is (-inf, 0).
 __device__ __forceinline__ void ml_merge(float &m, float &l, float m2, float l2) {

@@ -244,10 +244,10 @@ __global__ __launch_bounds__(WAVES * 64, stats_waves_per_simd(DT, D, WAVES, TQ))
         if (nq == 0) break;                               // wave-uniform: this wave has no query tile
         // The offset m of a row only has to keep the terms inside the range of a float: exp2 of
         // (logit - m) may be far above 1.  So the terms are formed with the offset as it stands,
-        // and only if a row's sum comes out infinite or undefined (a term or the sum overflowed, or the
+        // and only if a row's sum comes out beyond kSumLimit or undefined (a term or the sum overflowed, or the
         // row has no offset yet: m = -inf gives inf or NaN for every key) does the wave take the tile's
         // maximum, move the offset there, rescale the sum and form the terms again.  After a
-        // row's first tile that takes a logit 88 above everything the row has seen before.
+        // row's first tile that takes a logit 69 above the offset.
         float sum[4];                                     // four chains: the adds do not wait on each other
         {
           const float nmu = -m[q];
@@ -258,7 +258,7 @@ __global__ __launch_bounds__(WAVES * 64, stats_waves_per_simd(DT, D, WAVES, TQ))
           }
         }
         float lnew = l[q] + ((sum[0] + sum[1]) + (sum[2] + sum[3]));
-        if (__builtin_amdgcn_ballot_w64(!(lnew < INFINITY)) != 0) {
+        if (__builtin_amdgcn_ballot_w64(!(lnew < kSumLimit)) != 0) {
           float tmax = fmaxf(acc[q][0], acc[q][1]);
 #pragma unroll
           for (int i = 2; i < 16; i += 2) tmax = fmaxf(fmaxf(tmax, acc[q][i]), acc[q][i + 1]);

@@ -1,0 +1,28 @@
+"""Which kernels a call's streaming passes go to: the library's own dispatch rules, asked on the host (no GPU).  They are
+C++ functions inside libmixkv.so; the shape they take is filled in by the library and never looked into here."""
+import ctypes as C
+
+from paper_2510_20707_amd import binding as B
+
+
+def _function(name, *argtypes):
+    f = getattr(B.lib(), name)
+    f.argtypes, f.restype = argtypes, C.c_int
+    return lambda *a: f(*a) & 0xff                   # a C++ bool is the low byte
+
+
+def passes(p: B.MixkvParams, n_layers: int, num_cus: int = 256, stride_n: int = 0):
+    """(first pass, second pass) of a launch of `n_layers` layers without given softmax normalisers."""
+    assert n_layers <= 32                            # one launch group
+    shape = C.create_string_buffer(1024)             # larger than mixkv::Shape
+    make = getattr(B.lib(), "_ZN5mixkv10make_shapeEPK12mixkv_paramsPNS_5ShapeE")
+    make.argtypes, make.restype = [C.POINTER(B.MixkvParams), C.c_void_p], C.c_int
+    assert make(C.byref(p), shape) == B.MIXKV_OK
+    units = n_layers * p.batch * p.n_kv_heads
+    keysplit = _function("_ZN5mixkv18keysplit_supportedERKNS_5ShapeEi", C.c_void_p, C.c_int)
+    qstats = _function("_ZN5mixkv16qstats_supportedERKNS_5ShapeEiiil", C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_int64)
+    keystat = _function("_ZN5mixkv17keystat_supportedERKNS_5ShapeEiii", C.c_void_p, C.c_int, C.c_int, C.c_int)
+    if keysplit(shape, p.dtype):
+        return "ks_stats", "ks_attn"
+    return ("qs_stats" if qstats(shape, p.dtype, units, num_cus, stride_n or p.head_dim) else "stats",
+            "kst_attn" if keystat(shape, p.dtype, units, num_cus) else "attn")
