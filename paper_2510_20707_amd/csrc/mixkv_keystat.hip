@@ -197,9 +197,24 @@ __global__ __launch_bounds__(kKstThreads, 2) void kst_attn_kernel(Shape s, Layer
 // chunks 36.7 -> 35.7, 32 chunks 67 -> 64.
 // A wave takes whole 64-key blocks: not where the last round of them would leave more than a tenth of the time idle (112 heads of 7013 keys,
 // 6.02 blocks a wave: 170 us a call with attn_kernel, 172 with this).
+// A run ends with its head, so that short heads pay the staging and a last round of the eight waves again and again: time of a call with
+// attn_kernel over that with this, 16 to 56 chunks per compute unit, by keys per head:
+//   128 elements   512          1024         1536         2048         4096         8192
+//     8 tiles      0.99-1.04    1.02-1.07    1.05-1.09    1.04-1.11    1.08-1.11    1.09-1.10
+//     7            0.89-0.93    0.92-0.97    0.95-0.99    0.95-0.99    0.98-1.01    1.00-1.01
+//     4 to 6       0.91-0.97    0.92-1.01    0.98-1.04    0.98-1.05    1.00-1.08    1.01-1.09
+//     2, 3         0.92-0.98    0.92-1.01    0.96-1.02    0.97-1.04    0.96-1.02    0.97-1.02 (below 24 chunks 0.96-0.98)
+//   64 elements
+//     9 to 16      1.04-1.17    1.05-1.20    1.08-1.22    1.07-1.22    1.09-1.23    1.08-1.23 (384 keys 0.91-1.00)
+//     3 to 8       0.93-0.98    0.97-1.03    1.00-1.05    0.99-1.07    1.02-1.09    1.03-1.10
+// (attn_kernel computes whole slots of 4, 8 or 16 query tiles, and the mean key costs it extra where none is spare: 4, 8, 16.)
 bool keystat_supported(const Shape &s, int dtype, int nunits, int num_cus) {
-  if (dtype != MIXKV_BF16 || s.QT > (s.D == 128 ? 8 : 16) || (int64_t)nunits * s.nchunks < 16 * (int64_t)num_cus) return false;
-  const int64_t blocks = (int64_t)nunits * ((s.N + 63) / 64), waves = (int64_t)num_cus * kKstWaves, rounds = (blocks + waves - 1) / waves;
+  if (dtype != MIXKV_BF16 || s.QT > (s.D == 128 ? 8 : 16)) return false;
+  const int head = (s.N + 63) / 64;                    // blocks of a head
+  const bool few = s.D == 128 && s.QT <= 3;
+  const int least = s.D == 64 ? (s.QT > 8 ? 8 : 24) : (few || s.QT == 7) ? 64 : s.QT == 8 ? 16 : 24;
+  if (head < least || (int64_t)nunits * s.nchunks < (few ? 24 : 16) * (int64_t)num_cus) return false;
+  const int64_t blocks = (int64_t)nunits * head, waves = (int64_t)num_cus * kKstWaves, rounds = (blocks + waves - 1) / waves;
   return 10 * rounds * waves <= 11 * blocks;
 }
 

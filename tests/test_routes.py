@@ -1,0 +1,37 @@
+"""Which kernels long bf16 launches take (no GPU): a launch of many short heads is long as a whole, but its workgroups walk one head at a
+time, and the second pass with the keys in registers is the slower one there (figures at its rule)."""
+import pytest
+
+from paper_2510_20707_amd import binding as B
+from tests import routes
+
+UNITS = 1024
+
+
+def _second(tiles, d, n, units=UNITS):
+    p = B.make_params("bf16", units // 8, 4 * tiles, 4, d, n, 32, 64)
+    return routes.passes(p, 2)[1]
+
+
+@pytest.mark.parametrize("tiles,d,least", [(2, 128, 4096), (3, 128, 4096), (4, 128, 1536), (5, 128, 1536), (6, 128, 1536), (7, 128, 4096),
+                                           (8, 128, 1024), (3, 64, 1536), (8, 64, 1536), (9, 64, 512), (16, 64, 512)])
+def test_heads_too_short_for_keys_in_registers(tiles, d, least):
+    # every launch here is beyond 16 chunks per compute unit, and no wave of it idle if blocks were dealt over the whole launch
+    for n in (320, 384, 512, 640, 768, 1024, 1536, 2048, 3072, 4096, 8192):
+        units = UNITS * max(1, 1024 // n)
+        assert _second(tiles, d, n, units) == ("kst_attn" if n >= least else "attn"), n
+
+
+def test_few_tiles_need_longer_launches():
+    # 4096 keys per head, 16 and 24 chunks of 128 keys per compute unit
+    assert _second(3, 128, 4096, 128) == "attn" and _second(3, 128, 4096, 192) == "kst_attn"
+    assert _second(4, 128, 4096, 128) == "kst_attn"
+
+
+def test_only_shapes_the_kernels_are_written_for():
+    assert _second(9, 128, 8192) == "attn"
+    for dtype, hq, d, want in (("f32", 28, 128, ("stats", "attn")), ("bf16", 4, 128, ("ks_stats", "ks_attn")), ("bf16", 36, 128, ("stats", "attn"))):
+        assert routes.passes(B.make_params(dtype, 16, hq, 4, d, 8192, 32, 64), 8) == want
+    p = B.make_params("bf16", 16, 28, 4, 128, 8192, 32, 64)
+    assert routes.passes(p, 8) == ("qs_stats", "kst_attn")
+    assert routes.passes(p, 8, stride_n=1 << 25)[0] == "stats"          # the first pass forms 32-bit offsets inside a tile
