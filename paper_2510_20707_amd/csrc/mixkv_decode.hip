@@ -52,8 +52,8 @@ __device__ __forceinline__ uint16_t bf16_rne(float f) {
   return (uint16_t)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
 }
 
-// GT: query heads carried per workgroup (1, 2, 4 or 8; heads past G are idle).
-template <int DT, int D, int GT>
+// GT: query heads carried per workgroup (1, 2, 4 or 8; heads past G are idle); ONCE: see decode_reads_once.
+template <int DT, int D, int GT, bool ONCE>
 __global__ __launch_bounds__(kDecThreads) void decode_kernel(DShape s, DecodeTable tab, float *part) {
   constexpr int EB = DT == MIXKV_BF16 ? 2 : 4, E = 16 / EB, PPR = D * EB / 16, RPL = 64 / PPR;
   __shared__ float sm[kDecWaves][GT], sl[kDecWaves][GT], so[kDecWaves][GT][D];
@@ -113,8 +113,8 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(DShape s, DecodeTab
       if (ok[u]) {
         const char *kp, *vp;
         row_ptrs(row, kp, vp);
-        kq[u] = load_piece<true>(kp + piece * 16);
-        vq[u] = load_piece<true>(vp + piece * 16);
+        kq[u] = load_piece<ONCE>(kp + piece * 16);
+        vq[u] = load_piece<ONCE>(vp + piece * 16);
       }
     }
 #pragma unroll
@@ -215,7 +215,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(DShape s, DecodeTab
 //     per fragment), its output lane (g, half) holds head g's sixteen elements of the slice.
 // Partials and outputs have the layout of decode_kernel.
 // ------------------------------------------------------------------------------------------------
-template <int D>
+template <int D, bool ONCE>
 __global__ __launch_bounds__(D * 2, 2) void decode_mfma_kernel(DShape s, DecodeTable tab, float *part) {
   constexpr int DT = MIXKV_BF16, EB = 2, PPR = D * EB / 16, TILE = 32 * PPR, WAVES = D / 32, RPL = 64 / PPR;
   constexpr int NCHK = D / 16;                            // MFMAs per score tile
@@ -262,8 +262,8 @@ __global__ __launch_bounds__(D * 2, 2) void decode_mfma_kernel(DShape s, DecodeT
       const int row = min(tb + trow, n - 1);                       // rows past the range repeat its last row
       const int64_t at = (int64_t)row * RB + (lq ^ tile_swz<DT, D>(trow)) * 16;
       const char *kp = (row < cnt ? Kc : Kt) + at, *vp = (row < cnt ? Vc : Vt) + at;
-      load_to_lds<true>(kp, kring_a + off + j * 1024);    // non-temporal: a step reads every row once (143 MB: 43.0 -> 38.8 us a step)
-      load_to_lds<true>(vp, vring_a + off + j * 1024);
+      load_to_lds<ONCE>(kp, kring_a + off + j * 1024);
+      load_to_lds<ONCE>(vp, vring_a + off + j * 1024);
     }
   };
 #pragma unroll
@@ -444,10 +444,24 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(DShape s, DecodeTable
   else reinterpret_cast<float *>(tab.l[layer].out)[at] = res;
 }
 
+constexpr int kDecMfmaHeads = 32;    // query heads of one group a matrix-core workgroup serves: the columns of a tile
+
+// Row loads carry the non-temporal bit where a head's rows are read by one workgroup.  Where its query heads take several, the
+// later ones find the rows in the caches if the first has left them there.  Plain -> non-temporal, us a step, caches in turn (600 MB of
+// them; between two steps of a program lie its weights):
+//   one workgroup, bf16: 9 MB 8.9 -> 8.7, 31 MB 13.7 -> 13.1, 62 MB 17.5 -> 16.2, 125 MB 33.0 -> 31.0, 239 MB 49.8 -> 44.7, 478 MB 93.5 -> 84.7
+//     (up to 8 MB the same within 1 %); fp32: 72 MB 22.0 -> 20.6, 250 MB 57.6 -> 51.4
+//   several: 80 query heads per KV head, 119 MB 74.0 -> 79.3, 31 MB 30.8 -> 32.0, 2 MB 9.3 -> 9.7; 40 heads 119 MB 49.2 -> 48.5, 31 MB 21.0 ->
+//     21.2, 2 MB 8.8 -> 9.0; fp32, 24 heads, 119 MB 152 -> 155; 16 heads, 239 MB 203 -> 207
+// The same cache again and again, nothing in between: the non-temporal step is 2 to 4 % slower from 100 to 270 MB, else the same.
+bool decode_reads_once(int heads_per_group, int dtype) { return heads_per_group <= (dtype == MIXKV_BF16 ? kDecMfmaHeads : kDecHeads); }
+
 template <int DT, int D, int GT>
 static void launch_decode_gt(const DShape &s, const DecodeTable &t, int nunits, float *part, hipStream_t st) {
   const dim3 grid((unsigned)(nunits * s.gchunks * s.nsplit)), block(kDecThreads);
-  hipLaunchKernelGGL((decode_kernel<DT, D, GT>), grid, block, 0, st, s, t, part);
+  const bool once = GT < kDecHeads || decode_reads_once(s.G, DT);      // fewer heads than a workgroup carries: one chunk
+  auto kern = once ? decode_kernel<DT, D, GT, true> : decode_kernel<DT, D, GT, GT < kDecHeads>;
+  hipLaunchKernelGGL(kern, grid, block, 0, st, s, t, part);
   if (s.nsplit > 1)
     hipLaunchKernelGGL((decode_merge_kernel<DT, D>), dim3((unsigned)(nunits * s.gchunks), (unsigned)((s.gt * D + 255) / 256)), dim3(256), 0, st, s, t,
                        part);
@@ -466,13 +480,13 @@ static void launch_decode_g(const DShape &s, const DecodeTable &t, int nunits, i
 template <int D>
 static void launch_decode_mfma(const DShape &s, const DecodeTable &t, int nunits, float *part, hipStream_t st) {
   const dim3 grid((unsigned)(nunits * s.gchunks * s.nsplit)), block(D * 2);
-  hipLaunchKernelGGL((decode_mfma_kernel<D>), grid, block, 0, st, s, t, part);
+  auto kern = decode_reads_once(s.G, MIXKV_BF16) ? decode_mfma_kernel<D, true> : decode_mfma_kernel<D, false>;
+  hipLaunchKernelGGL(kern, grid, block, 0, st, s, t, part);
   if (s.nsplit > 1)
     hipLaunchKernelGGL((decode_merge_kernel<MIXKV_BF16, D>), dim3((unsigned)(nunits * s.gchunks), (unsigned)((s.gt * D + 255) / 256)), dim3(256),
                        0, st, s, t, part);
 }
 
-constexpr int kDecMfmaHeads = 32;    // query heads of one group a matrix-core workgroup serves: the columns of a tile
 constexpr int kDecTargetWgs = 512;   // two resident workgroups on each of 256 compute units
 
 // Query heads served per workgroup (hpw), their stride in the partials (gt), chunks of query heads

@@ -26,3 +26,8 @@ def passes(p: B.MixkvParams, n_layers: int, num_cus: int = 256, stride_n: int = 
         return "ks_stats", "ks_attn"
     return ("qs_stats" if qstats(shape, p.dtype, units, num_cus, stride_n or p.head_dim) else "stats",
             "kst_attn" if keystat(shape, p.dtype, units, num_cus) else "attn")
+
+
+def decode_reads_once(heads_per_group: int, dtype: str):
+    """Whether a decoding step's row loads are non-temporal."""
+    return bool(_function("_ZN5mixkv17decode_reads_onceEii", C.c_int, C.c_int)(heads_per_group, B.DTYPE[dtype]))

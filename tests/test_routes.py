@@ -35,3 +35,10 @@ def test_only_shapes_the_kernels_are_written_for():
     p = B.make_params("bf16", 16, 28, 4, 128, 8192, 32, 64)
     assert routes.passes(p, 8) == ("qs_stats", "kst_attn")
     assert routes.passes(p, 8, stride_n=1 << 25)[0] == "stats"          # the first pass forms 32-bit offsets inside a tile
+
+
+@pytest.mark.parametrize("dtype,most", [("bf16", 32), ("f32", 8)])
+def test_decode_rows_read_by_several_workgroups_stay_cached(dtype, most):
+    # up to `most` query heads per KV head one workgroup serves them all and the rows are read once
+    for g in (1, 7, most, most + 1, 2 * most, 2 * most + 1, 256):
+        assert routes.decode_reads_once(g, dtype) == (g <= most), g
