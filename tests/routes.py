@@ -11,8 +11,8 @@ def _function(name, *argtypes):
     return lambda *a: f(*a) & 0xff                   # a C++ bool is the low byte
 
 
-def passes(p: B.MixkvParams, n_layers: int, num_cus: int = 256, stride_n: int = 0):
-    """(first pass, second pass) of a launch of `n_layers` layers without given softmax normalisers."""
+def passes(p: B.MixkvParams, n_layers: int, num_cus: int = 256, stride_n: int = 0, given_lse: bool = False):
+    """(first pass, second pass) of a launch of `n_layers` layers (given softmax normalisers: the first pass only streams)."""
     assert n_layers <= 32                            # one launch group
     shape = C.create_string_buffer(1024)             # larger than mixkv::Shape
     make = getattr(B.lib(), "_ZN5mixkv10make_shapeEPK12mixkv_paramsPNS_5ShapeE")
@@ -23,8 +23,8 @@ def passes(p: B.MixkvParams, n_layers: int, num_cus: int = 256, stride_n: int = 
     qstats = _function("_ZN5mixkv16qstats_supportedERKNS_5ShapeEiiil", C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_int64)
     keystat = _function("_ZN5mixkv17keystat_supportedERKNS_5ShapeEiii", C.c_void_p, C.c_int, C.c_int, C.c_int)
     if keysplit(shape, p.dtype):
-        return "ks_stats", "ks_attn"
-    return ("qs_stats" if qstats(shape, p.dtype, units, num_cus, stride_n or p.head_dim) else "stats",
+        return "stats" if given_lse else "ks_stats", "ks_attn"
+    return ("qs_stats" if not given_lse and qstats(shape, p.dtype, units, num_cus, stride_n or p.head_dim) else "stats",
             "kst_attn" if keystat(shape, p.dtype, units, num_cus) else "attn")
 
 
