@@ -207,13 +207,20 @@ __global__ __launch_bounds__(kKstThreads, 2) void kst_attn_kernel(Shape s, Layer
 //   64 elements
 //     9 to 16      1.04-1.17    1.05-1.20    1.08-1.22    1.07-1.22    1.09-1.23    1.08-1.23 (384 keys 0.91-1.00)
 //     3 to 8       0.93-0.98    0.97-1.03    1.00-1.05    0.99-1.07    1.02-1.09    1.03-1.10
+// Between those lengths the last round counts (blocks of 64 keys a head; 18, 28, 40, 60 chunks per compute unit):
+//   64 elements, 16 tiles: 8 blocks 1.02 1.06 1.07 1.08; 9 0.92 0.93 0.97 0.97; 10 0.96 0.97 1.00 1.01; 11 1.01 1.00 1.01 1.03; 17 1.04 1.02 1.05 1.06
+//     13 tiles: 9 blocks 0.95 0.97 0.99 1.00; 10 0.98 1.00 1.03 1.03; 12 tiles: 9 blocks 0.97 0.98 1.01 1.03; 9 tiles: 9 blocks 1.04 1.06 1.09 1.10
+//   128 elements, 6 tiles: 25 blocks 0.97 0.96 1.00 1.00; 28 0.99 0.99 1.02 1.03; 30 0.94 0.97 1.02 1.00; 31 1.03 1.01 1.04 1.03
+//     4 and 5 tiles: 24 to 28 blocks 0.98-1.06
 // (attn_kernel computes whole slots of 4, 8 or 16 query tiles, and the mean key costs it extra where none is spare: 4, 8, 16.)
 bool keystat_supported(const Shape &s, int dtype, int nunits, int num_cus) {
   if (dtype != MIXKV_BF16 || s.QT > (s.D == 128 ? 8 : 16)) return false;
   const int head = (s.N + 63) / 64;                    // blocks of a head
   const bool few = s.D == 128 && s.QT <= 3;
   const int least = s.D == 64 ? (s.QT > 8 ? 8 : 24) : (few || s.QT == 7) ? 64 : s.QT == 8 ? 16 : 24;
-  if (head < least || (int64_t)nunits * s.nchunks < (few ? 24 : 16) * (int64_t)num_cus) return false;
+  const bool idle_round = s.D == 64 && ((head == 9 && s.QT > 12) || (head == 10 && s.QT > 14));
+  const int chunks = few ? 24 : (s.D == 128 && s.QT == 6 && head < 31) ? 32 : 16;    // per compute unit
+  if (head < least || idle_round || (int64_t)nunits * s.nchunks < chunks * (int64_t)num_cus) return false;
   const int64_t blocks = (int64_t)nunits * head, waves = (int64_t)num_cus * kKstWaves, rounds = (blocks + waves - 1) / waves;
   return 10 * rounds * waves <= 11 * blocks;
 }

@@ -14,18 +14,23 @@ def _second(tiles, d, n, units=UNITS):
 
 
 @pytest.mark.parametrize("tiles,d,least", [(2, 128, 4096), (3, 128, 4096), (4, 128, 1536), (5, 128, 1536), (6, 128, 1536), (7, 128, 4096),
-                                           (8, 128, 1024), (3, 64, 1536), (8, 64, 1536), (9, 64, 512), (16, 64, 512)])
+                                           (8, 128, 1024), (3, 64, 1536), (8, 64, 1536), (9, 64, 512), (13, 64, 512), (16, 64, 512)])
 def test_heads_too_short_for_keys_in_registers(tiles, d, least):
     # every launch here is beyond 16 chunks per compute unit, and no wave of it idle if blocks were dealt over the whole launch
-    for n in (320, 384, 512, 640, 768, 1024, 1536, 2048, 3072, 4096, 8192):
-        units = UNITS * max(1, 1024 // n)
-        assert _second(tiles, d, n, units) == ("kst_attn" if n >= least else "attn"), n
+    for n in (320, 384, 512, 550, 640, 704, 768, 1024, 1536, 2048, 3072, 4096, 8192):
+        units = UNITS * max(2, 1024 // n)
+        # a second round of the eight waves with one or two 64-key blocks
+        idle = d == 64 and (tiles > 12 and n == 550 or tiles > 14 and n == 640)
+        assert _second(tiles, d, n, units) == ("kst_attn" if n >= least and not idle else "attn"), n
 
 
 def test_few_tiles_need_longer_launches():
     # 4096 keys per head, 16 and 24 chunks of 128 keys per compute unit
     assert _second(3, 128, 4096, 128) == "attn" and _second(3, 128, 4096, 192) == "kst_attn"
     assert _second(4, 128, 4096, 128) == "kst_attn"
+    # 6 tiles, 30 blocks of 64 keys per head: from 32 chunks on; 31 blocks: from 16 on
+    assert _second(6, 128, 1900, 512) == "attn" and _second(6, 128, 1900, 1024) == "kst_attn"
+    assert _second(6, 128, 1970, 512) == "kst_attn"
 
 
 def test_only_shapes_the_kernels_are_written_for():
