@@ -14,11 +14,14 @@ constexpr int kMaxCandPerHead = 1024;   // head-adaptive budgets: list length of
 constexpr int kMaxSegs = 32;            // segments a long row is cut into at most
 constexpr int kMaxStreamGrid = 1024;    // upper bound on the workgroups of a streaming kernel launch
 
-// Loads of cache rows carry the non-temporal bit where a launch streams more than the 256 MB Infinity Cache would keep of
-// it for the next reader.  A plain read of 0.5 to 4 GB then runs at 7.0 to 7.4 TB/s, without the bit at 6.2.  Whole calls,
-// without -> with, by the bytes of K and V: 67 MB 60.8 -> 63.8 us, 134 MB 80.9 -> 83.1, 168 MB 101 -> 104, 197 MB (f32) 79.4 ->
-// 77.2, 235 MB 130 -> 126, 336 MB 166 -> 157, 2.1 GB 730 -> 686; block sums of 117 MB of keys 28.3 -> 29.7, of 235 MB 58.7 -> 54.2.
+// Loads of cache rows carry the non-temporal bit where a launch streams more than the Infinity Cache would keep of it for the next
+// reader.  A plain read of 0.5 to 4 GB then runs at 7.0 to 7.4 TB/s, without the bit at 6.2.  Whole calls, without -> with, by the bytes of K
+// and V: 67 MB 60.8 -> 63.8 us, 134 MB 80.9 -> 83.1, 168 MB 101 -> 104, 197 MB (f32) 79.4 -> 77.2, 235 MB 130 -> 126, 336 MB 166 ->
+// 157, 2.1 GB 730 -> 686; block sums of 117 MB of keys 28.3 -> 29.7, of 235 MB 58.7 -> 54.2.  Time without over time with, one to twelve query
+// tiles, caches in turn: 182 MB 0.99-1.08, 260 MB 1.00-1.12, 400 MB 0.98-1.12; the same cache again and again (a cache is compressed
+// once): 182 MB 0.87-0.99, 260 MB 0.84-1.00, 400 MB 0.97-1.03.
 // A template parameter, not a branch: the branch in the tile loops cost 2 to 5 %.
+constexpr int64_t kInfinityCache = 256 * 1000 * 1000;
 constexpr int64_t kCachedBytes = 180 * 1000 * 1000;
 inline bool read_once(int64_t bytes) { return bytes >= kCachedBytes; }
 

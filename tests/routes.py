@@ -11,13 +11,18 @@ def _function(name, *argtypes):
     return lambda *a: f(*a) & 0xff                   # a C++ bool is the low byte
 
 
-def passes(p: B.MixkvParams, n_layers: int, num_cus: int = 256, stride_n: int = 0, given_lse: bool = False):
-    """(first pass, second pass) of a launch of `n_layers` layers (given softmax normalisers: the first pass only streams)."""
-    assert n_layers <= 32                            # one launch group
+def _shape(p):
     shape = C.create_string_buffer(1024)             # larger than mixkv::Shape
     make = getattr(B.lib(), "_ZN5mixkv10make_shapeEPK12mixkv_paramsPNS_5ShapeE")
     make.argtypes, make.restype = [C.POINTER(B.MixkvParams), C.c_void_p], C.c_int
     assert make(C.byref(p), shape) == B.MIXKV_OK
+    return shape
+
+
+def passes(p: B.MixkvParams, n_layers: int, num_cus: int = 256, stride_n: int = 0, given_lse: bool = False):
+    """(first pass, second pass) of a launch of `n_layers` layers (given softmax normalisers: the first pass only streams)."""
+    assert n_layers <= 32                            # one launch group
+    shape = _shape(p)
     units = n_layers * p.batch * p.n_kv_heads
     keysplit = _function("_ZN5mixkv18keysplit_supportedERKNS_5ShapeEi", C.c_void_p, C.c_int)
     qstats = _function("_ZN5mixkv16qstats_supportedERKNS_5ShapeEiiil", C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_int64)
@@ -31,3 +36,8 @@ def passes(p: B.MixkvParams, n_layers: int, num_cus: int = 256, stride_n: int = 
 def decode_reads_once(heads_per_group: int, dtype: str):
     """Whether a decoding step's row loads are non-temporal."""
     return bool(_function("_ZN5mixkv17decode_reads_onceEii", C.c_int, C.c_int)(heads_per_group, B.DTYPE[dtype]))
+
+
+def few_rows_read_once(p: B.MixkvParams, n_layers: int):
+    """Whether the two passes for few query rows load keys and values non-temporally."""
+    return bool(_function("_ZN5mixkv13keysplit_onceERKNS_5ShapeEii", C.c_void_p, C.c_int, C.c_int)(_shape(p), p.dtype, n_layers * p.batch * p.n_kv_heads))

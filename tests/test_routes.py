@@ -47,3 +47,16 @@ def test_decode_rows_read_by_several_workgroups_stay_cached(dtype, most):
     # up to `most` query heads per KV head one workgroup serves them all and the rows are read once
     for g in (1, 7, most, most + 1, 2 * most, 2 * most + 1, 256):
         assert routes.decode_reads_once(g, dtype) == (g <= most), g
+
+
+@pytest.mark.parametrize("dtype,d,alone", [("bf16", 64, 256), ("f32", 64, 256), ("f32", 128, 256), ("bf16", 128, 180)])
+def test_keys_that_the_second_pass_reads_again_stay_cached(dtype, d, alone):
+    # one query tile, eight layers; keys and values from 180 MB on, keys alone from `alone` MB on
+    row = d * (2 if dtype == "bf16" else 4)
+    for mb in (170, 190, 220, 250, 260, 300):
+        units = round(mb * 1e6 / (1000 * row * 8))
+        make = lambda n, intrinsic: B.make_params(dtype, units, 1, 1, d, n, 32, 64, intrinsic=intrinsic)  # noqa: E731
+        assert routes.few_rows_read_once(make(1000, "knorm"), 8) == (mb > alone), mb
+        assert routes.few_rows_read_once(make(500, "vnorm"), 8) == (mb > 180), mb
+    units = round(200e6 / (400 * row * 8))               # short heads
+    assert not routes.few_rows_read_once(B.make_params(dtype, units, 1, 1, d, 400, 32, 64, intrinsic="none"), 8)
