@@ -66,7 +66,7 @@ __global__ __launch_bounds__(256) void blocksum_kernel(AShape a, RowsInTable in,
       const int row = r + u * RPL + lr;
       q[u] = make_uint4(0u, 0u, 0u, 0u);
       const char *p = base + (int64_t)row * L.sn * EB + piece * 16;
-      if (row < rend) q[u] = ONCE ? load_piece<true>(p) : load_piece<false>(p);
+      if (row < rend) q[u] = load_piece<ONCE>(p);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {

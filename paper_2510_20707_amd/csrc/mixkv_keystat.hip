@@ -10,8 +10,8 @@
 //   * Blocks are walked from a run's last to its first: the first pass read those last, and the caches may still hold them (1 % of a call).
 //   * K_i . Kbar: 16x16x32 matrix instructions on the same key fragments (half the cost of a 32-row tile): a fragment's lanes 0-15 and
 //     16-31 are two groups of keys, told apart by the contraction group, so the mean key's rows are zero for the other group's.
-// Bound: the card's power.  Matrix instructions alone run at 1.8 GHz here, with the weights' arithmetic at 1.9 to 2.0 and with the key
-// stream at 1.5 to 1.7 of 2.4 GHz; a chain of eight and its 48 vector instructions take 207 to 224 ns per SIMD in isolation, 250 here.
+// Bound: issue, at the clock that the card's power leaves.  448 heads of 32768 keys, 7 query tiles: 1.61 GHz (a copy runs at 2.40); of the
+// SIMDs' clocks the matrix units are busy in 46 %, the vector units in 60 %, one or the other in 90 %; 3.8 GB from memory at 3.4 TB/s.
 // attn_kernel -> this, us, alone on the chip, 7 query tiles and 224 heads of 32768 keys 535 -> 505, 4 tiles and 256 heads of 16384 keys
 // 248 -> 214, 2 tiles and 224 heads of 8192 keys 120 -> 90.
 // Not better: three waves per SIMD, blocks dealt by a counter (the younger wave of a SIMD ends later, but the time is the same), four key

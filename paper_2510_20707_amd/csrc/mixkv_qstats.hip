@@ -1,13 +1,15 @@
 // The first pass over long bf16 caches with five to eight query tiles: two waves hold all window queries in registers.
 //
 // stats_kernel gives each of eight waves one query tile, so every wave reads the whole key tile from LDS: 64 of the 96 KB of LDS traffic per tile,
-// about as much energy as the matrix instructions, and the card runs both passes at its power limit (1.5 to 1.9 of 2.4 GHz).  Here a wave
+// and the card runs both passes below its clock (1.6 to 1.8 of 2.4 GHz here).  Here a wave
 // holds three or four tiles (96 to 128 registers), a fragment read serves as many matrix instructions, and the norms come from registers:
 //   * 1 / |K_i| from the score fragments (a lane has half a row), on the wave with fewer query tiles or on both in turn;
 //   * the sum of normalised keys on the matrix cores: 1 / |K_i| as three bf16 addends (exact: 24 bits) times the keys, read transposed
 //     from the tile image (ds_read_b64_tr_b16), eight small instructions and no vector work where stats_kernel takes 16 per 16 bytes;
 //   * value rows through a private image per wave, four lanes to a row.
 // A tile step: the key tile was asked for two steps ahead, the value rows one; requests, waits and LDS accesses are written out (see lds_read8).
+// Bound: 448 heads of 32768 keys, 7 tiles: 1.81 GHz; the matrix units busy in 31 % of the SIMDs' clocks, the vector units in 52 %, one or the
+// other in 75 %; 7.6 GB at 4.9 TB/s; bank conflicts in 30 % of the LDS cycles.
 // 244 registers, 34 KB of LDS: four workgroups per compute unit.  First pass of 224 heads of 32768 keys, 7 tiles: 820 -> 740 us (stats_kernel
 // with non-temporal loads 794 to 828); without its requests 506 to 590, without its arithmetic 757 with plain loads.
 #include "mixkv_stream.h"
@@ -332,10 +334,17 @@ __global__ __launch_bounds__(kQsThreads, 2) void qs_stats_kernel(Shape s, LayerI
 }
 
 // bf16 rows of 128 elements, 5 to 8 query tiles, from 32 chunks of 128 keys per compute unit on, row strides whose 32-row offsets fit 32
-// bits.  stats_kernel -> this, whole calls: 448 heads of 32768 keys (7 tiles, 448 chunks per unit) 2697 -> 2645 us, 112 heads of
-// 130688 2740 -> 2659; this pass alone, 224 heads of 8192 keys (5 tiles, 56 chunks) 215 to 230 -> 185 to 188, 112 heads of 8192 (7
-// tiles, 28 chunks) the same call time, 14 chunks 62 to 72 -> 75 (a workgroup's queries go to registers once per run).  With up to
-// four tiles one wave would hold all of them: 256 heads of 16384 keys 662 -> 669 us a call.
+// bits.  stats_kernel -> this, whole calls: 448 heads of 32768 keys (7 tiles, 448 chunks per unit) 2705 -> 2612 us, 112 heads of
+// 130688 2674 -> 2585; this pass alone, 224 heads of 8192 keys (5 tiles, 56 chunks) 215 to 230 -> 185 to 188; 112 and 128 heads of 8192 (7
+// tiles, 28 and 32 chunks) the same call time, 14 chunks 62 to 72 -> 75 (a workgroup's queries go to registers once per run).
+// Short heads, which end a run each, do not move the line: stats_kernel loads its queries as often.  Time of a call with stats_kernel over that
+// with this, 32, 48 and 96 chunks per unit:
+//   keys per head  256        384        512        768        1024       2048       4096       8192
+//     5 tiles      1.04-1.08  1.04-1.05  1.05-1.09  1.02-1.05  0.99-1.03  0.99-1.00  1.00-1.05  0.98-1.02
+//     6            1.04-1.09  1.02-1.04  1.06-1.07  1.05-1.08  1.04-1.09  1.01-1.04  1.01-1.03  1.00-1.03
+//     7            1.04-1.07  1.01-1.06  1.05-1.06  1.02-1.06  1.04-1.07  1.02-1.04  1.03-1.04  1.01-1.03
+//     8            1.05-1.07  1.01-1.05  1.06-1.07  1.02-1.05  1.04       1.02-1.04  1.02-1.03  1.00-1.04
+// With up to four tiles one wave would hold all of them: 256 heads of 16384 keys 662 -> 669 us a call.
 bool qstats_supported(const Shape &s, int dtype, int nunits, int num_cus, int64_t max_stride_n) {
   return dtype == MIXKV_BF16 && s.D == 128 && s.QT >= 5 && s.QT <= 8 && (int64_t)nunits * s.nchunks >= 32 * (int64_t)num_cus &&
          max_stride_n < (int64_t)1 << 25;

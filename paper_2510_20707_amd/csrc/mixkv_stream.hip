@@ -802,8 +802,8 @@ hipError_t launch_stats(const Shape &s, int dtype, const LayerInTable &in, char 
   return launch_stats_t<MIXKV_F32, 64>(s, in, ws, w, unit0, nunits, grid, slot0, given_lse, st);
 }
 
-// `grid` must be the grid stats_kernel ran with: both kernels split the same items the same way,
-// and attn_kernel uses it to find the partials of its units.
+// `grid` workgroups split the chunks of all units among themselves; the first pass may have been cut differently (what it left per head comes
+// from fold_kernel).
 hipError_t launch_attn(const Shape &s, int dtype, const LayerInTable &in, const LayerOutTable &out, const LseTable &lse,
                        char *ws, const Workspace &w, int64_t unit0, int nunits, int grid, int64_t slot0, hipStream_t st) {
   if (dtype == MIXKV_BF16) {

@@ -71,6 +71,7 @@ RUNS = {  # query heads per KV head (one KV head), window, head dim, batch, laye
     "8 tiles, no causal mask": (dict(ROOMY, g=8, bt=89, n=1500), "qs_stats", "kst_attn", dict(causal_window=False)),
     "7 tiles, heads of 289 keys": (dict(ROOMY, g=7, bt=344, n=289), "qs_stats", "attn", dict(odd_rows=True)),
     "8 tiles, heads of 200 keys, key norms": (dict(ROOMY, g=8, bt=520, n=200), "qs_stats", "attn", dict(intrinsic="knorm")),
+    "8 tiles, heads of 130 keys alone, cacheable loads": (dict(ROOMY, g=8, bt=520, n=130), "qs_stats", "attn", dict(intrinsic="none")),
     "5 tiles, a second launch group of two layers": (dict(ROOMY, bt=13, L=34, n=2600), "qs_stats", "kst_attn", {}),
     "5 tiles, given normalisers": (ROOMY, "stats", "kst_attn", dict(lse=True)),
     "4 tiles, keys alone, cacheable loads": (dict(ROOMY, g=4, bt=31), "stats", "kst_attn", dict(intrinsic="none", mix="imp_only", redundancy=False)),
