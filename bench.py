@@ -41,9 +41,9 @@ MFMA_BF16_PEAK = 2.5e15
 # taken on: the record carries a hash of their sources, and the bench line reports the figure only for
 # the profiled command (default workload, budget and variant, three copies) and unchanged sources.
 PROFILED_TRAFFIC = {
-    "sources": ["mixkv_stream.hip", "mixkv_stream.h"],
-    "sources_sha256": "0aed24e39e2132a59ae53ba95b5d474fb825e816d0d147d83b7546f353440a0c",
-    "kernels": {"stats": ("stats_kernel<bf16,128,8,1>", 513.6e6), "attn": ("attn_kernel<bf16,128,4,2,spare>", 278.3e6)},
+    "sources": ["mixkv_stream.hip", "mixkv_stream.h", "mixkv_keystat.hip"],
+    "sources_sha256": "5ebdc3684ab45f76f61609ecb56fbca850fc8d0279a1c0c6c7076637d31cc217",
+    "kernels": {"stats": ("stats_kernel<bf16,128,8,1>", 513.8e6), "attn": ("kst_attn_kernel<128,8>", 276.0e6)},
 }
 
 
