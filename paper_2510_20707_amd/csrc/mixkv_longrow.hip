@@ -11,9 +11,10 @@
 //
 // Bound: HBM (four rows of floats per key, read by the statistics and again by the mix; the diversity and the
 // intrinsic score stay in registers from then on).  One 130 688-token prompt of 28 layers and 4 KV heads (234 MB of
-// rows, budget 128, head-adaptive): statistics 51 us (4.6 TB/s), mix and lists 80, merge 31, split 9.  One workgroup
+// rows, budget 128, head-adaptive): statistics 38 us (6.2 TB/s), mix and lists 76, merge 23, split 8.6 (44, 82, 31 and 8.8 before
+// the loads of a thread were in flight together and the search took six barriers).  One workgroup
 // per head for the mix and one per layer for the selection left most of the chip idle: 784 + 2 583 us.
-// At 32 768 tokens (448 heads) the three kernels take 155 us and mixsel_kernel, which holds a whole head, 150.
+// At 32 768 tokens (448 heads) mixsel_kernel, which holds a whole head, takes 103 us, and the three kernels took no less than it.
 //
 // Paper: Sec. 3.2 Eq. 2, Sec. 3.3 Eq. 5, Sec. 3.1 / Algorithm 1 (TopB), as in mixsel_kernel.
 #include <cfloat>
@@ -24,11 +25,6 @@ namespace mixkv {
 
 constexpr int kHalo = 32;                // candidates on either side of a segment that the pooling window may reach
 constexpr int kMaxMerge = 1024 * 28;     // list entries mergetop_kernel can hold (LDS)
-
-// LDS slot of a float: four pad words per 32 keep every aligned group of four together and spread the groups of
-// owners a power of two apart over the banks.
-__device__ __forceinline__ int slot4(int i) { return i + ((i >> 5) << 2); }
-__host__ __device__ constexpr int slots4(int n) { return n + n / 32 * 4 + 4; }
 
 // Shares of a head's statistics, one per segment (in the rows that held the softmax offsets: the second pass was
 // their last reader).  Sums of intrinsic score and diversity are taken above the share's own minimum: every term is
@@ -70,15 +66,35 @@ __device__ __forceinline__ SegStat *seg_stats(const Shape &s, char *ws, const Wo
   return reinterpret_cast<SegStat *>(reinterpret_cast<float *>(ws + w.nb) + unit * s.nb_rows);
 }
 
+// Intrinsic score and diversity of the thread's groups of four, all loads in flight together.
+template <int EPT, class GroupOf>
+__device__ __forceinline__ void load_rows(const UnitRows &rows, int s0, float (&v)[EPT], float (&d)[EPT], GroupOf group_of) {
+  constexpr int G = EPT / 4;
+  int at[G];
+  float4 vr[G], dr[G];
+#pragma unroll
+  for (int g = 0; g < G; ++g) at[g] = rows.inside(s0 + group_of(g) * 4);
+  rows.load_vd<G>(at, vr, dr);
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    v[4 * g] = vr[g].x; v[4 * g + 1] = vr[g].y; v[4 * g + 2] = vr[g].z; v[4 * g + 3] = vr[g].w;
+    d[4 * g] = dr[g].x; d[4 * g + 1] = dr[g].y; d[4 * g + 2] = dr[g].z; d[4 * g + 3] = dr[g].w;
+  }
+}
+
 // Loads the raw attention of the segment [s0, s0 + THREADS * EPT) and its halo into LDS (out-of-range
 // candidates hold the pooling's neutral element) and leaves the pooled values of the thread's candidates in
 // a[]: group_of(0), group_of(1), ... are the thread's groups of four, consecutive threads holding consecutive groups
 // so that all loads are coalesced.  Ends past its reads of LDS only after the caller's next barrier.
 template <int THREADS, int EPT, class GroupOf>
-__device__ __forceinline__ void load_pooled(const Shape &s, const float *araw, int s0, float (&a)[EPT], float *a_s, GroupOf group_of) {
+__device__ __forceinline__ void load_pooled(const Shape &s, const UnitRows &rows, int s0, float (&a)[EPT], float *a_s, GroupOf group_of) {
+  const float *araw = rows.araw;
   const int tid = threadIdx.x, Nc = s.Nc;
   const bool pooled = s.pool != MIXKV_POOL_NONE && s.pool_k > 1, is_max = s.pool == MIXKV_POOL_MAX;
   const float fill = is_max ? -INFINITY : 0.f;          // out-of-range taps: ignored by max, zero for avg
+  float4 raw[EPT / 4];                                  // the rows are padded past the last group
+#pragma unroll
+  for (int g = 0; g < EPT / 4; ++g) raw[g] = *reinterpret_cast<const float4 *>(araw + rows.inside(s0 + group_of(g) * 4));
   if (tid < 2 * kHalo) {
     const int i = tid < kHalo ? s0 - kHalo + tid : s0 + THREADS * EPT + tid - kHalo;
     const int li = tid < kHalo ? tid : THREADS * EPT + tid;
@@ -87,13 +103,11 @@ __device__ __forceinline__ void load_pooled(const Shape &s, const float *araw, i
 #pragma unroll
   for (int g = 0; g < EPT / 4; ++g) {
     const int li = group_of(g) * 4, i = s0 + li;
-    float4 r = make_float4(fill, fill, fill, fill);
-    if (i < Nc) {                                       // the rows are padded past the last group
-      r = *reinterpret_cast<const float4 *>(araw + i);
-      if (i + 1 >= Nc) r.y = fill;
-      if (i + 2 >= Nc) r.z = fill;
-      if (i + 3 >= Nc) r.w = fill;
-    }
+    float4 r = raw[g];
+    if (i >= Nc) r.x = fill;
+    if (i + 1 >= Nc) r.y = fill;
+    if (i + 2 >= Nc) r.z = fill;
+    if (i + 3 >= Nc) r.w = fill;
     a[4 * g] = r.x; a[4 * g + 1] = r.y; a[4 * g + 2] = r.z; a[4 * g + 3] = r.w;
     *reinterpret_cast<float4 *>(&a_s[slot4(kHalo + li)]) = r;
   }
@@ -162,14 +176,8 @@ __global__ __launch_bounds__(kStatThreads * (BLOCKS > 1 ? 2 : 1)) void segstat_k
   // group g of the thread: turn g / 2 is block HALVES * (g / 2) + half
   auto group_of = [&](int g) { return ((HALVES * (g >> 1) + half) * 2 + (g & 1)) * kStatThreads + ht; };
   float v[EPT], d[EPT], a[EPT];
-#pragma unroll
-  for (int g = 0; g < EPT / 4; ++g) {
-    float4 vr, dr;
-    rows.load_vd(s0 + group_of(g) * 4, vr, dr);
-    v[4 * g] = vr.x; v[4 * g + 1] = vr.y; v[4 * g + 2] = vr.z; v[4 * g + 3] = vr.w;
-    d[4 * g] = dr.x; d[4 * g + 1] = dr.y; d[4 * g + 2] = dr.z; d[4 * g + 3] = dr.w;
-  }
-  load_pooled<THREADS, EPT>(s, rows.araw, s0, a, a_s, group_of);
+  load_rows<EPT>(rows, s0, v, d, group_of);
+  load_pooled<THREADS, EPT>(s, rows, s0, a, a_s, group_of);
 #pragma unroll
   for (int t = 0; t < TURNS; ++t) {
     auto on = [&](int e) { return s0 + group_of(e >> 2) * 4 + (e & 3) < s.Nc; };
@@ -215,18 +223,13 @@ __device__ __forceinline__ int head_keep(const Shape &s, const int32_t *budgets,
   return cand_m > 0 ? cand_m : (budgets ? budgets[layer * s.hkv + h] : s.B) - s.W;
 }
 
-// The segment's best min(keep, len) candidates, out of the scores in a_s (slot4(0) is candidate s0).
+// The segment's best min(keep, len) candidates, out of the order keys in k_s (slot4(0) is candidate s0).
 template <int THREADS, int EPT>
-__device__ __forceinline__ void segment_list(const float *a_s, int s0, int len, int keep, int32_t *idx, uint32_t *ckey,
-                                             MsScratch &sc) {
+__device__ __forceinline__ void segment_list(const uint32_t *k_s, int s0, int len, int keep, int32_t *idx, uint32_t *ckey, MsScratch &sc) {
   const int base = threadIdx.x * EPT;
-  float a[EPT];
-#pragma unroll
-  for (int e = 0; e < EPT; e += 4) {
-    const float4 v = *reinterpret_cast<const float4 *>(&a_s[slot4(base + e)]);
-    a[e] = v.x; a[e + 1] = v.y; a[e + 2] = v.z; a[e + 3] = v.w;
-  }
-  top_select<THREADS, EPT>(a, len - base, s0 + base, min(keep, len), idx, ckey, 0, sc);
+  uint32_t key[EPT];
+  read_keys<EPT>(k_s, base, len, key);
+  top_select_keys<THREADS, EPT>(key, min(keep, len), idx, ckey, 0, sc, [&](int e) { return s0 + base + e; });
 }
 
 template <int THREADS, int EPT, bool SELECT>
@@ -240,17 +243,11 @@ __global__ __launch_bounds__(THREADS) void segmix_kernel(Shape s, LayerInTable i
   const int layer = ul / s.units_per_layer, bh = ul - layer * s.units_per_layer, Nc = s.Nc;
   const LayerOut O = out.l[layer];
   const UnitRows rows(s, ws, w, unit);
-  if (tid == 0) { sc.ur[0] = 0xffffffffu; sc.ur[1] = 0u; }   // for the key range, read after later barriers
 
   float v[EPT], d[EPT], a[EPT];
-#pragma unroll
-  for (int g = 0; g < EPT / 4; ++g) {
-    float4 vr, dr;
-    rows.load_vd(s0 + (g * THREADS + tid) * 4, vr, dr);
-    v[4 * g] = vr.x; v[4 * g + 1] = vr.y; v[4 * g + 2] = vr.z; v[4 * g + 3] = vr.w;
-    d[4 * g] = dr.x; d[4 * g + 1] = dr.y; d[4 * g + 2] = dr.z; d[4 * g + 3] = dr.w;
-  }
-  load_pooled<THREADS, EPT>(s, rows.araw, s0, a, a_s, [&](int g) { return g * THREADS + tid; });
+  auto group_of = [&](int g) { return g * THREADS + tid; };
+  load_rows<EPT>(rows, s0, v, d, group_of);
+  load_pooled<THREADS, EPT>(s, rows, s0, a, a_s, group_of);
 
   // ---- the head's statistics: lane l holds segment l's share, every wave folds neighbours, then pairs of them, ...
   // From here on products and sums that the compiler could contract in two ways are written out: all instantiations
@@ -272,36 +269,36 @@ __global__ __launch_bounds__(THREADS) void segmix_kernel(Shape s, LayerInTable i
   const float f_in = rows.use_v ? mean_ex / (mean_in + s.eps) : 0.f;    // Sec. 3.2: scale VNorm to mean(s_ex)
   const float mean_imp = rows.use_v ? fmaf(f_in, mean_in, mean_ex) : mean_ex;
   const float f_div = mean_imp / (mean_dn + s.eps);                      // Sec. 3.3: scale diversity to mean(s_imp)
-  __syncthreads();                                      // the pooling is done with the raw attention: the scores replace it
+  const int len = min(SEG, Nc - s0);
+  float *scores = O.scores ? O.scores + (int64_t)bh * s.N + s0 : nullptr;
+  uint32_t *k_s = reinterpret_cast<uint32_t *>(a_s);
+  uint32_t largest = 0;
+  if constexpr (SELECT) __syncthreads();                // the pooling is done with the raw attention: the order keys replace it
 #pragma unroll
   for (int g = 0; g < EPT / 4; ++g) {
-    float c[4];
+    const int li = group_of(g) * 4;
+    uint32_t k4[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int e = 4 * g + j;
       const float imp = rows.use_v ? fmaf(quotient(v[e] - vmin, vden, rvden), f_in, a[e]) : a[e];   // Eq. 2
-      c[j] = fmaf(wi, imp, wd * (quotient(d[e] - dmin, dden, rdden) * f_div));                       // Eq. 5
+      const float c = fmaf(wi, imp, wd * (quotient(d[e] - dmin, dden, rdden) * f_div));              // Eq. 5
+      if (scores && li + j < len) scores[li + j] = c;
+      k4[j] = li + j < len ? order_key_u(c) : 0u;
+      largest = max(largest, k4[j]);
     }
-    *reinterpret_cast<float4 *>(&a_s[slot4((g * THREADS + tid) * 4)]) = make_float4(c[0], c[1], c[2], c[3]);
+    if constexpr (SELECT) *reinterpret_cast<uint4 *>(&k_s[slot4(li)]) = make_uint4(k4[0], k4[1], k4[2], k4[3]);
   }
-  __syncthreads();
-  const int len = min(SEG, Nc - s0);
-  if (O.scores) {
-    float *scores = O.scores + (int64_t)bh * s.N;
-#pragma unroll
-    for (int k = 0; k < EPT; ++k) {
-      const int li = k * THREADS + tid;
-      if (li < len) scores[s0 + li] = a_s[slot4(li)];
-    }
-    if (seg == nseg - 1)
-      for (int i = Nc + tid; i < s.N; i += THREADS) scores[i] = INFINITY;
-  }
+  if (scores && seg == nseg - 1)
+    for (int i = len + tid; i < s.N - s0; i += THREADS) scores[i] = INFINITY;
+  if constexpr (SELECT) thresholds_begin<THREADS>(largest, sc);
+  if constexpr (SELECT) __syncthreads();
   if constexpr (SELECT) {
     // the list takes the place of the segment's own share of two rows that have been read
     const int keep = head_keep(s, budgets, layer, bh % s.hkv, cand_m);
     int32_t *idx = reinterpret_cast<int32_t *>(ws + w.sdiv) + unit * s.Npad + s0;
     uint32_t *ckey = reinterpret_cast<uint32_t *>(ws + w.invnorm) + unit * s.Npad + s0;
-    if (keep > 0) segment_list<THREADS, EPT>(a_s, s0, len, keep, idx, ckey, sc);
+    if (keep > 0) segment_list<THREADS, EPT>(k_s, s0, len, keep, idx, ckey, sc);
   }
 }
 
@@ -309,23 +306,28 @@ template <int THREADS, int EPT>
 __global__ __launch_bounds__(THREADS) void segtop_kernel(Shape s, LayerOutTable out, char *ws, Workspace w, int64_t unit0,
                                                          int nseg, int cand_m, const int32_t *budgets) {
   constexpr int SEG = THREADS * EPT;
-  __shared__ __align__(16) float a_s[slots4(SEG)];
+  __shared__ __align__(16) uint32_t k_s[slots4(SEG)];
   __shared__ MsScratch sc;
   const int ul = blockIdx.x / nseg, seg = blockIdx.x - ul * nseg, s0 = seg * SEG, tid = threadIdx.x;
   const int64_t unit = unit0 + ul;
   const int layer = ul / s.units_per_layer, bh = ul - layer * s.units_per_layer, len = min(SEG, s.Nc - s0);
   const float *scores = out.l[layer].scores + (int64_t)bh * s.N + s0;
-  if (tid == 0) { sc.ur[0] = 0xffffffffu; sc.ur[1] = 0u; }
+  float a[EPT];
+#pragma unroll
+  for (int k = 0; k < EPT; ++k) a[k] = scores[min(k * THREADS + tid, len - 1)];     // all in flight together
+  uint32_t largest = 0;
 #pragma unroll
   for (int k = 0; k < EPT; ++k) {
-    const int li = k * THREADS + tid;
-    a_s[slot4(li)] = li < len ? scores[li] : 0.f;
+    const uint32_t key = order_key_u(a[k]);
+    largest = max(largest, key);                        // past the segment its last score again
+    k_s[slot4(k * THREADS + tid)] = key;
   }
+  thresholds_begin<THREADS>(largest, sc);
   __syncthreads();
   const int keep = head_keep(s, budgets, layer, bh % s.hkv, cand_m);
   int32_t *idx = reinterpret_cast<int32_t *>(ws + w.sdiv) + unit * s.Npad + s0;
   uint32_t *ckey = reinterpret_cast<uint32_t *>(ws + w.invnorm) + unit * s.Npad + s0;
-  if (keep > 0) segment_list<THREADS, EPT>(a_s, s0, len, keep, idx, ckey, sc);
+  if (keep > 0) segment_list<THREADS, EPT>(k_s, s0, len, keep, idx, ckey, sc);
 }
 
 // One workgroup per head: its rows (fixed and per-head mode) or its candidates for the head-adaptive split, out
@@ -333,35 +335,41 @@ __global__ __launch_bounds__(THREADS) void segtop_kernel(Shape s, LayerOutTable 
 template <int THREADS, int EPT>
 __global__ __launch_bounds__(THREADS) void mergetop_kernel(Shape s, LayerOutTable out, char *ws, Workspace w, CandLists cl,
                                                            int64_t unit0, int seg, int nseg, int cand_m, const int32_t *budgets) {
-  extern __shared__ __align__(16) float a_s[];
+  extern __shared__ __align__(16) uint32_t k_s[];
   __shared__ MsScratch sc;
-  uint32_t *k_s = reinterpret_cast<uint32_t *>(a_s);
   const int ul = blockIdx.x, tid = threadIdx.x;
   const int64_t unit = unit0 + ul;
   const int layer = ul / s.units_per_layer, bh = ul - layer * s.units_per_layer, h = bh % s.hkv, b = bh / s.hkv;
   const LayerOut O = out.l[layer];
   const int32_t *lidx = reinterpret_cast<const int32_t *>(ws + w.sdiv) + unit * s.Npad;
   const uint32_t *lkey = reinterpret_cast<const uint32_t *>(ws + w.invnorm) + unit * s.Npad;
-  if (tid == 0) { sc.ur[0] = 0xffffffffu; sc.ur[1] = 0u; }
   const int keep = head_keep(s, budgets, layer, h, cand_m), per = min(keep, seg);   // entries per list, the last one's may be fewer
   const int n = per > 0 ? (nseg - 1) * per + min(per, s.Nc - (nseg - 1) * seg) : 0;
   auto at = [&](int e) { const int g = e / per; return g * seg + (e - g * per); };
-  for (int e = tid; e < n; e += THREADS) k_s[slot4(e)] = lkey[at(e)];
-  __syncthreads();
   const int base = tid * EPT;
-  uint32_t key[EPT];
+  uint32_t key[EPT], largest = 0;
+  if (n > 0) {
 #pragma unroll
-  for (int e = 0; e < EPT; ++e) key[e] = base + e < n ? k_s[slot4(base + e)] : 0u;
+    for (int k = 0; k < EPT; ++k) key[k] = lkey[at(min(k * THREADS + tid, n - 1))];  // all in flight together
+#pragma unroll
+    for (int k = 0; k < EPT; ++k) {
+      largest = max(largest, key[k]);                   // past the lists the last entry again
+      if (k * THREADS + tid < n) k_s[slot4(k * THREADS + tid)] = key[k];
+    }
+  }
+  thresholds_begin<THREADS>(largest, sc);
+  __syncthreads();
+  read_keys<EPT>(k_s, base, n, key);
   auto pos = [&](int e) { return lidx[at(base + e)]; };
   if (cand_m > 0) {
-    top_select_keys<THREADS, EPT>(key, n - base, cand_m, reinterpret_cast<int32_t *>(ws + cl.idx) + unit * cl.stride,
+    top_select_keys<THREADS, EPT>(key, cand_m, reinterpret_cast<int32_t *>(ws + cl.idx) + unit * cl.stride,
                                   reinterpret_cast<uint32_t *>(ws + cl.key) + unit * cl.stride, s.floor_, sc, pos);
     return;
   }
   int Bh, row0;
   head_rows(s, budgets, layer, h, Bh, row0);
   int32_t *idx = O.indices + (int64_t)b * s.hkv * s.B + row0;
-  if (keep > 0) top_select_keys<THREADS, EPT>(key, n - base, keep, idx, nullptr, 0, sc, pos);
+  if (keep > 0) top_select_keys<THREADS, EPT>(key, keep, idx, nullptr, 0, sc, pos);
   finish_head(s, O, b, h, Bh, row0, idx, THREADS);
 }
 

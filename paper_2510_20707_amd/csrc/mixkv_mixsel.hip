@@ -4,11 +4,15 @@
 // Loading, pooling, statistics and mixing deal the candidates to the threads in groups of four,
 // round-robin, so that every load is coalesced; the pooled attention needs neighbours, so the raw
 // attention row is staged once in LDS.  For the selection thread t owns the EPT consecutive
-// candidates [t*EPT, (t+1)*EPT) (the mixed scores change hands through the same LDS row), so the
-// kept indices come out in ascending order from a plain prefix sum.  The selection is a
-// most-significant-digit radix select on order-preserving integer keys kept in registers; it
-// starts at the first bit in which the keys of the head differ at all, which keeps the first
-// histogram from collapsing into one bin.
+// candidates [t*EPT, (t+1)*EPT) (the order keys of the mixed scores change hands through the same LDS row), so the
+// kept indices come out in ascending order from a plain prefix sum.  The selection is a threshold search by histograms
+// on order-preserving integer keys kept in registers (radix_thresholds).
+//
+// Bound: the instructions of a workgroup's 4 to 16 waves and the length of their chain (112 workgroups use less than half of the
+// chip); past 16 384 candidates the loads of four rows too.  All of a thread's loads in flight together, keys formed as
+// they are dealt, whole groups through LDS, one search of six barriers for both thresholds, us a launch before and now:
+// 2 heads of 504 11.6 -> 8.9, 4 of 4064 13.4 -> 11.1, 112 of 8160 18.5 -> 16.3, 256 of 16 128 49.7 -> 43.3, 448 of 32 736
+// 137 -> 103 (head-adaptive lists).
 //
 // Paper: Sec. 3.2 Eq. 2 (importance = attention + scaled value norm), Sec. 3.3 (min-max and mean
 // matching of the diversity, Eq. 5 mix), Sec. 3.1 / Algorithm 1 (TopB with B' = B - W); Sec. 4.3 /
@@ -22,15 +26,16 @@ __global__ __launch_bounds__(THREADS) void mixsel_kernel(Shape s, LayerOutTable 
                                                            int64_t unit0, LayerInTable in, int gather_eb, int cand_m,
                                                            CandLists cl, const int32_t *budgets) {
   constexpr int NW = THREADS / 64;
-  extern __shared__ float a_s[];                        // [Nc] raw window attention of this head
+  extern __shared__ __align__(16) float a_s[];          // raw window attention of this head, later its order keys
   __shared__ MsScratch sc;
-  const int tid = threadIdx.x, ul = blockIdx.x;
+  const int ul = blockIdx.x;
+  int tid = threadIdx.x;
   const int64_t unit = unit0 + ul;
   const int layer = ul / s.units_per_layer, bh = ul - layer * s.units_per_layer;
   const LayerOut O = out.l[layer];
   const UnitRows rows(s, ws, w, unit);
   const float r = reinterpret_cast<const float *>(ws + w.rbar)[unit];
-  const int Nc = s.Nc, N = s.N, base = tid * EPT;
+  const int Nc = s.Nc, N = s.N, base = threadIdx.x * EPT;
   const bool use_v = rows.use_v;
   const float inv_n = 1.f / (float)Nc;
   float wi, wd;
@@ -45,61 +50,66 @@ __global__ __launch_bounds__(THREADS) void mixsel_kernel(Shape s, LayerOutTable 
   // Runs of EPT consecutive candidates per thread would touch one cache line per lane and load, but the selection needs
   // consecutive runs (ascending output from one prefix sum): s_comp reaches their owners through LDS.
   auto cidx = [&](int e) { return (((e >> 2) * THREADS + tid) << 2) + (e & 3); };
-  const int nvalid = Nc - base;             // consecutive ownership: candidates of this thread inside the row
   // up to 16 candidates per thread the other two fit beside it
   constexpr bool KEEP = EPT <= 16;
   float a[EPT], vk[KEEP ? EPT : 1], dk[KEEP ? EPT : 1];
   float st[7] = {0.f, 0.f, 0.f, INFINITY, INFINITY, -INFINITY, -INFINITY};   // sums a, v, d | min v, d | max v, d
-  auto load_vd = [&](int i, float4 &vr, float4 &dr) { rows.load_vd(i, vr, dr); };
-  // The raw attention row goes to LDS with one pad word per 32 so that the accesses of
-  // consecutive-range owners (a thread stride of EPT words) spread over the banks.
-  auto slot = [](int i) { return i + (i >> 5); };
-  if (tid == 0) { sc.ur[0] = 0xffffffffu; sc.ur[1] = 0u; }   // for the key range, read after later barriers
+  constexpr int GB = EPT <= 16 ? EPT / 4 : 2;           // groups whose loads are in flight together
+  // The raw attention row goes to LDS four words up, between the pooling's neutral element on either side.
+  const bool pooled = s.pool != MIXKV_POOL_NONE && s.pool_k > 1, is_max = s.pool == MIXKV_POOL_MAX;
+  const float fill = is_max ? -INFINITY : 0.f;          // out-of-range taps: ignored by max, zero for avg
+  if (threadIdx.x < 2) {
+    const int at = threadIdx.x == 0 ? 0 : 4 + ((Nc + 3) & ~3);
+    *reinterpret_cast<float4 *>(&a_s[slot4(at)]) = make_float4(fill, fill, fill, fill);
+  }
 #pragma unroll
-  for (int e4 = 0; e4 < EPT; e4 += 4) {
-    const int i = cidx(e4);
-    float4 ar = make_float4(0.f, 0.f, 0.f, 0.f), vr, dr;
-    if (i < Nc) ar = *reinterpret_cast<const float4 *>(rows.araw + i);
-    load_vd(i, vr, dr);
-    const float a4[4] = {ar.x, ar.y, ar.z, ar.w};
-    const float v4[4] = {vr.x, vr.y, vr.z, vr.w}, d4[4] = {dr.x, dr.y, dr.z, dr.w};
+  for (int g0 = 0; g0 < EPT / 4; g0 += GB) {
+    if constexpr (!KEEP) __builtin_amdgcn_sched_barrier(0);      // the next batch's loads would not fit the registers
+    int at[GB];
+    float4 ar[GB], vr[GB], dr[GB];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      a[e4 + j] = a4[j];
-      if constexpr (KEEP) { vk[e4 + j] = v4[j]; dk[e4 + j] = d4[j]; }
-      if (i + j < Nc) {
-        a_s[slot(i + j)] = a4[j];
-        st[1] += v4[j]; st[2] += d4[j];
-        st[3] = fminf(st[3], v4[j]); st[4] = fminf(st[4], d4[j]);
-        st[5] = fmaxf(st[5], v4[j]); st[6] = fmaxf(st[6], d4[j]);
+    for (int g = 0; g < GB; ++g) {
+      at[g] = rows.inside(cidx(4 * (g0 + g)));
+      ar[g] = *reinterpret_cast<const float4 *>(rows.araw + at[g]);
+    }
+    rows.load_vd<GB>(at, vr, dr);
+#pragma unroll
+    for (int g = 0; g < GB; ++g) {
+      const int e4 = 4 * (g0 + g), i = cidx(e4);
+      const float a4[4] = {ar[g].x, ar[g].y, ar[g].z, ar[g].w};
+      const float v4[4] = {vr[g].x, vr[g].y, vr[g].z, vr[g].w}, d4[4] = {dr[g].x, dr[g].y, dr[g].z, dr[g].w};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        a[e4 + j] = a4[j];
+        if constexpr (KEEP) { vk[e4 + j] = v4[j]; dk[e4 + j] = d4[j]; }
+        if (i + j < Nc) {
+          st[1] += v4[j]; st[2] += d4[j];
+          st[3] = fminf(st[3], v4[j]); st[4] = fminf(st[4], d4[j]);
+          st[5] = fmaxf(st[5], v4[j]); st[6] = fmaxf(st[6], d4[j]);
+        }
       }
+      if (i < Nc)
+        *reinterpret_cast<float4 *>(&a_s[slot4(4 + i)]) =
+            make_float4(a4[0], i + 1 < Nc ? a4[1] : fill, i + 2 < Nc ? a4[2] : fill, i + 3 < Nc ? a4[3] : fill);
     }
   }
   __syncthreads();
+  if constexpr (!KEEP) asm("" : "+v"(tid));             // positions and LDS slots are formed again, not held in registers
 
   // ---- pooled attention (candidates only) and the first round of statistics
-  if (s.pool != MIXKV_POOL_NONE && s.pool_k > 1) {
+  if (pooled) {
     const int hk = s.pool_k >> 1;
-    const bool is_max = s.pool == MIXKV_POOL_MAX;
-    const float fill = is_max ? -INFINITY : 0.f;        // out-of-range taps: ignored by max, zero for avg
     if (hk <= 3) {
-      // sliding window in registers over each group of four: its own values plus three neighbours
-      // on either side
-      constexpr int RUN = 4;
+      // sliding window in registers over each group of four: its own values and the groups on either side
 #pragma unroll
-      for (int e0 = 0; e0 < EPT; e0 += RUN) {
-        const int i0 = cidx(e0);
-        float win[RUN + 6];
+      for (int e0 = 0; e0 < EPT; e0 += 4) {
+        const int at = 4 + rows.inside(cidx(e0));
+        const float4 lo = *reinterpret_cast<const float4 *>(&a_s[slot4(at - 4)]);
+        const float4 own = *reinterpret_cast<const float4 *>(&a_s[slot4(at)]);
+        const float4 hi = *reinterpret_cast<const float4 *>(&a_s[slot4(at + 4)]);
+        const float win[10] = {lo.y, lo.z, lo.w, own.x, own.y, own.z, own.w, hi.x, hi.y, hi.z};
 #pragma unroll
-        for (int j = 0; j < 3; ++j) {
-          const int il = i0 - 3 + j, ir = i0 + RUN + j;
-          win[j] = (il >= 0 && il < Nc) ? a_s[slot(il)] : fill;
-          win[RUN + 3 + j] = (ir < Nc) ? a_s[slot(ir)] : fill;
-        }
-#pragma unroll
-        for (int e = 0; e < RUN; ++e) win[3 + e] = (i0 + e < Nc) ? a[e0 + e] : fill;
-#pragma unroll
-        for (int e = 0; e < RUN; ++e) {
+        for (int e = 0; e < 4; ++e) {
           float acc = win[3 + e];
           if (is_max) {
             if (hk >= 1) acc = fmaxf(acc, fmaxf(win[2 + e], win[4 + e]));
@@ -126,11 +136,11 @@ __global__ __launch_bounds__(THREADS) void mixsel_kernel(Shape s, LayerOutTable 
         const int i = cidx(e);
         if (i < Nc) {
           const int lo = max(0, i - hk), hi = min(Nc - 1, i + hk);
-          float acc = a_s[slot(lo)];
+          float acc = a_s[slot4(4 + lo)];
           if (is_max) {
-            for (int j = lo + 1; j <= hi; ++j) acc = fmaxf(acc, a_s[slot(j)]);
+            for (int j = lo + 1; j <= hi; ++j) acc = fmaxf(acc, a_s[slot4(4 + j)]);
           } else {
-            for (int j = lo + 1; j <= hi; ++j) acc += a_s[slot(j)];
+            for (int j = lo + 1; j <= hi; ++j) acc += a_s[slot4(4 + j)];
             acc = acc / (float)s.pool_k;
           }
           a[e] = acc;
@@ -157,37 +167,51 @@ __global__ __launch_bounds__(THREADS) void mixsel_kernel(Shape s, LayerOutTable 
     const float imp = use_v ? ai + (vi - vmin) * rvden * f_in : ai;       // Eq. 2
     return wi * imp + wd * ((di - dmin) * rdden * f_div);                 // Eq. 5
   };
-  // every thread is past the reduction's barriers, so the pooling has read all it needs of the raw
-  // row: s_comp replaces it in LDS and comes back dealt in consecutive runs of EPT
+  // Every thread is past the reduction's barriers, so the pooling has read all it needs of the raw row: the order keys
+  // of s_comp replace it in LDS and come back dealt in consecutive runs of EPT.
+  uint32_t *k_s = reinterpret_cast<uint32_t *>(a_s);
+  float *scores = O.scores ? O.scores + (int64_t)bh * N : nullptr;
+  uint32_t largest = 0;
 #pragma unroll
-  for (int e4 = 0; e4 < EPT; e4 += 4) {
-    const int i = cidx(e4);
-    float v4[4], d4[4];
-    if constexpr (KEEP) {
+  for (int g0 = 0; g0 < EPT / 4; g0 += GB) {
+    float4 vr[GB], dr[GB];
+    if constexpr (!KEEP) {
+      __builtin_amdgcn_sched_barrier(0);
+      int at[GB];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) { v4[j] = vk[e4 + j]; d4[j] = dk[e4 + j]; }
-    } else {
-      float4 vr, dr;
-      load_vd(i, vr, dr);
-      v4[0] = vr.x; v4[1] = vr.y; v4[2] = vr.z; v4[3] = vr.w;
-      d4[0] = dr.x; d4[1] = dr.y; d4[2] = dr.z; d4[3] = dr.w;
+      for (int g = 0; g < GB; ++g) at[g] = rows.inside(cidx(4 * (g0 + g)));
+      rows.load_vd<GB>(at, vr, dr);
     }
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-      if (i + j < Nc) a_s[slot(i + j)] = s_comp(a[e4 + j], v4[j], d4[j]);
+    for (int g = 0; g < GB; ++g) {
+      const int e4 = 4 * (g0 + g), i = cidx(e4);
+      float v4[4], d4[4];
+      if constexpr (KEEP) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { v4[j] = vk[e4 + j]; d4[j] = dk[e4 + j]; }
+      } else {
+        v4[0] = vr[g].x; v4[1] = vr[g].y; v4[2] = vr[g].z; v4[3] = vr[g].w;
+        d4[0] = dr[g].x; d4[1] = dr[g].y; d4[2] = dr[g].z; d4[3] = dr[g].w;
+      }
+      uint32_t k4[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float c = s_comp(a[e4 + j], v4[j], d4[j]);
+        if (scores && i + j < Nc) scores[i + j] = c;
+        k4[j] = i + j < Nc ? order_key_u(c) : 0u;
+        largest = max(largest, k4[j]);
+      }
+      if constexpr (SELECT)
+        if (i < Nc) *reinterpret_cast<uint4 *>(&k_s[slot4(i)]) = make_uint4(k4[0], k4[1], k4[2], k4[3]);
+    }
   }
-  __syncthreads();
-#pragma unroll
-  for (int e = 0; e < EPT; ++e) a[e] = e < nvalid ? a_s[slot(base + e)] : 0.f;
-
-  if (O.scores) {
-    float *scores = O.scores + (int64_t)bh * N;
-#pragma unroll
-    for (int e = 0; e < EPT; ++e)
-      if (e < nvalid) scores[base + e] = a[e];
+  if (scores)
     for (int i = Nc + tid; i < N; i += THREADS) scores[i] = INFINITY;
-  }
   if constexpr (!SELECT) return;
+  thresholds_begin<THREADS>(largest, sc);
+  __syncthreads();
+  uint32_t key[EPT];
+  read_keys<EPT>(k_s, base, Nc, key);
 
   // ---- TopB': the B' candidates with the largest s_comp, ties to the smaller index.  In fixed
   // budget mode B' = B - W and the indices are the head's final ones; with a budget table (per-head
@@ -202,7 +226,7 @@ __global__ __launch_bounds__(THREADS) void mixsel_kernel(Shape s, LayerOutTable 
   int32_t *idx = cand ? reinterpret_cast<int32_t *>(ws + cl.idx) + unit * cl.stride : O.indices + out_row0;
   uint32_t *ckey = reinterpret_cast<uint32_t *>(ws + cl.key) + unit * cl.stride;
   const int Bp = cand ? cand_m : Bh - s.W;
-  if (Bp > 0) top_select<THREADS, EPT>(a, nvalid, base, Bp, idx, cand ? ckey : nullptr, s.floor_, sc);
+  if (Bp > 0) top_select_keys<THREADS, EPT>(key, Bp, idx, cand ? ckey : nullptr, s.floor_, sc, [&](int e) { return base + e; });
   if (cand) return;
   finish_head(s, O, b, h, Bh, row0, idx, THREADS);
   // ---- gather of the kept rows (Sec. 3.1, the compacted cache), if asked for: gather_eb is the
@@ -230,27 +254,35 @@ __global__ __launch_bounds__(THREADS) void mixsel_kernel(Shape s, LayerOutTable 
 
 // topsel_kernel: the selection half alone, on scores that are already in memory (the caller's, for
 // mixkv_select).  One workgroup per unit reads the Nc candidate scores of its head once (coalesced,
-// through the padded LDS row to their consecutive-range owners) and selects from registers as
+// their order keys through the padded LDS row to their consecutive-range owners) and selects from registers as
 // above: the head's final rows in fixed and per-head mode, or with cand_m > 0 its best cand_m
-// candidates with their keys for the head-adaptive split (Sec. 3.1 / Algorithm 1, TopB).
+// candidates with their keys for the head-adaptive split (Sec. 3.1 / Algorithm 1, TopB).  112 heads of 8160, 1536 candidates
+// and a floor each: 14.9 -> 9.0 us with the search of mixkv_topsel.h as it is now.
 template <int THREADS, int EPT>
 __global__ __launch_bounds__(THREADS) void topsel_kernel(Shape s, LayerOutTable out, char *ws, CandLists cl, int64_t unit0,
                                                            int cand_m, const int32_t *budgets) {
-  extern __shared__ float a_s[];                        // [Nc] padded: the head's scores
+  extern __shared__ __align__(16) float a_s[];          // the head's order keys
   __shared__ MsScratch sc;
   const int tid = threadIdx.x, ul = blockIdx.x;
   const int64_t unit = unit0 + ul;
   const int layer = ul / s.units_per_layer, bh = ul - layer * s.units_per_layer;
   const LayerOut O = out.l[layer];
   const float *scores = O.scores + (int64_t)bh * s.N;
-  const int Nc = s.Nc, base = tid * EPT, nvalid = Nc - base;
-  auto slot = [](int i) { return i + (i >> 5); };
-  if (tid == 0) { sc.ur[0] = 0xffffffffu; sc.ur[1] = 0u; }
-  for (int i = tid; i < Nc; i += THREADS) a_s[slot(i)] = scores[i];
-  __syncthreads();
-  float a[EPT];
+  const int Nc = s.Nc, base = tid * EPT;
+  uint32_t *k_s = reinterpret_cast<uint32_t *>(a_s);
+  float c[EPT];
 #pragma unroll
-  for (int e = 0; e < EPT; ++e) a[e] = e < nvalid ? a_s[slot(base + e)] : 0.f;
+  for (int e = 0; e < EPT; ++e) c[e] = scores[min(e * THREADS + tid, Nc - 1)];      // all in flight together
+  uint32_t largest = 0, key[EPT];
+#pragma unroll
+  for (int e = 0; e < EPT; ++e) {
+    key[e] = order_key_u(c[e]);
+    largest = max(largest, key[e]);                     // past the row the last score again
+    if (e * THREADS + tid < Nc) k_s[slot4(e * THREADS + tid)] = key[e];
+  }
+  thresholds_begin<THREADS>(largest, sc);
+  __syncthreads();
+  read_keys<EPT>(k_s, base, Nc, key);
   const bool cand = cand_m > 0;
   const int h = bh % s.hkv, b = bh / s.hkv;
   int Bh, row0;
@@ -259,7 +291,7 @@ __global__ __launch_bounds__(THREADS) void topsel_kernel(Shape s, LayerOutTable 
                       : O.indices + (int64_t)b * s.hkv * s.B + row0;
   uint32_t *ckey = cand ? reinterpret_cast<uint32_t *>(ws + cl.key) + unit * cl.stride : nullptr;
   const int Bp = cand ? cand_m : Bh - s.W;
-  if (Bp > 0) top_select<THREADS, EPT>(a, nvalid, base, Bp, idx, ckey, s.floor_, sc);
+  if (Bp > 0) top_select_keys<THREADS, EPT>(key, Bp, idx, ckey, s.floor_, sc, [&](int e) { return base + e; });
   if (!cand) finish_head(s, O, b, h, Bh, row0, idx, THREADS);
 }
 
@@ -269,8 +301,9 @@ __global__ __launch_bounds__(THREADS) void topsel_kernel(Shape s, LayerOutTable 
 // best remaining candidates of all heads together, ties to the smaller head, then the smaller
 // position.  A head can keep at most f + H * (B' - f) <= M candidates, so the lists hold every
 // candidate that can be kept and the result is the same as ranking all scores.  Thread t owns EPT
-// consecutive entries of the H lists laid end to end: that order is the tie order, and the kept
-// entries of a head come out in ascending position from one prefix sum.
+// consecutive entries of the H lists laid end to end, each rounded up to whole threads: that order is the tie order,
+// the kept entries of a head come out in ascending position from one prefix sum, and a thread's entries are one
+// aligned run of one list.
 template <int THREADS, int EPT>
 __global__ __launch_bounds__(THREADS) void candsplit_kernel(Shape s, LayerOutTable out, char *ws, CandLists cl, int64_t unit0,
                                                               int M) {
@@ -279,81 +312,81 @@ __global__ __launch_bounds__(THREADS) void candsplit_kernel(Shape s, LayerOutTab
   __shared__ int hstart[65];                           // kept entries before each head's list; [H]: all
   const int tid = threadIdx.x, lb = blockIdx.x, layer = lb / s.batch, b = lb - layer * s.batch;
   const LayerOut O = out.l[layer];
-  const int Nc = s.Nc, H = s.hkv, n = H * M, rest = H * (s.Bp - s.floor_);
+  const int Nc = s.Nc, H = s.hkv, rest = H * (s.Bp - s.floor_);
   const int64_t unit = unit0 + (int64_t)lb * H;        // first head of this (layer, batch item)
-  const uint32_t *cidx = reinterpret_cast<const uint32_t *>(ws + cl.idx) + unit * cl.stride;
-  const uint32_t *ckey = reinterpret_cast<const uint32_t *>(ws + cl.key) + unit * cl.stride;
   int32_t *idx = O.indices + (int64_t)b * H * s.B;
-  if (tid == 0) { sc.ur[0] = 0xffffffffu; sc.ur[1] = 0u; }
+  const int tph = (M + EPT - 1) / EPT;                 // threads to a list
+  const int h = tid / tph, i0 = (tid - h * tph) * EPT, left = h < H ? M - i0 : 0;    // entries from the thread's first one on
+  // Whole runs: what lies behind a list's last entry (inside its row of the workspace) is not looked at.
+  const int64_t at = (unit + min(h, H - 1)) * cl.stride + i0;
+  const uint4 *krun = reinterpret_cast<const uint4 *>(reinterpret_cast<const uint32_t *>(ws + cl.key) + at);
+  const uint4 *prun = reinterpret_cast<const uint4 *>(reinterpret_cast<const uint32_t *>(ws + cl.idx) + at);
   uint32_t key[EPT], pw[EPT];
-  int head[EPT];
-  uint32_t inmask = 0, vmask = 0;                       // entries inside the lists; of those, outside the floors
-  uint32_t kmin = 0xffffffffu, kmax = 0;
+#pragma unroll
+  for (int g = 0; g < EPT / 4; ++g) {
+    const uint4 kq = krun[g], pq = prun[g];
+    key[4 * g] = kq.x; key[4 * g + 1] = kq.y; key[4 * g + 2] = kq.z; key[4 * g + 3] = kq.w;
+    pw[4 * g] = pq.x; pw[4 * g + 1] = pq.y; pw[4 * g + 2] = pq.z; pw[4 * g + 3] = pq.w;
+  }
+  // the search sees the entries outside the floors (key 0: not this one)
+  uint32_t floors = 0, largest = 0;                     // entries that are kept as they are
 #pragma unroll
   for (int j = 0; j < EPT; ++j) {
-    const int e = tid * EPT + j;
-    head[j] = j == 0 ? e / M : head[j - 1] + (e >= (head[j - 1] + 1) * M ? 1 : 0);
-    key[j] = 0; pw[j] = 0;
-    if (e < n) {
-      const int64_t at = head[j] * cl.stride + (e - head[j] * M);
-      key[j] = ckey[at];
-      pw[j] = cidx[at];
-      inmask |= 1u << j;
-      if (!(pw[j] & kFloorFlag)) { vmask |= 1u << j; kmin = min(kmin, key[j]); kmax = max(kmax, key[j]); }
-    }
+    const bool flag = (pw[j] & kFloorFlag) != 0;
+    floors |= j < left && flag ? 1u << j : 0u;
+    key[j] = j < left && !flag && rest > 0 ? key[j] : 0u;
+    largest = max(largest, key[j]);
   }
+  thresholds_begin<THREADS>(largest, sc);
   __syncthreads();
-  uint32_t tau = 0xffffffffu;
-  int k = 0;
-  if (rest > 0) {
-    block_minmax_u32(kmin, kmax, sc);
-    tau = radix_threshold<THREADS, EPT>(key, vmask, kmin, kmax, rest, sc, k);
+  const int want[1] = {rest};
+  uint32_t tau[1] = {0xffffffffu};
+  int k[1] = {0};
+  if (rest > 0) radix_thresholds<THREADS, EPT, 1>(key, want, sc, tau, k);
+  // kept for sure (low half) and equal to the threshold (high half) share a word
+  int packed = __popc(floors), total;
+#pragma unroll
+  for (int j = 0; j < EPT; ++j) packed += key[j] > tau[0] ? 1 : 0;
+  if (k[0] > 0) {
+#pragma unroll
+    for (int j = 0; j < EPT; ++j) packed += key[j] == tau[0] ? 1 << 16 : 0;
   }
-  int ngt = 0, neq = 0;
+  packed = block_scan_excl<NW>(packed, sc, &total);
+  int seen = (int)((uint32_t)packed >> 16);
+  int pos = (packed & 0xffff) + min(seen, k[0]);       // kept entries before this thread's
+  const int kept = (total & 0xffff) + min((int)((uint32_t)total >> 16), k[0]);
+  if (i0 == 0 && h < H) hstart[h] = pos;
+  pos += h * s.W;
 #pragma unroll
   for (int j = 0; j < EPT; ++j) {
-    const bool v = ((vmask >> j) & 1u) != 0 && rest > 0;
-    ngt += (((inmask & ~vmask) >> j) & 1u) + ((v && key[j] > tau) ? 1 : 0);    // floor entries are kept as they are
-    neq += (v && key[j] == tau) ? 1 : 0;
-  }
-  int total;
-  const int packed = block_scan_excl<NW>(ngt | (neq << 16), sc, &total);
-  int seen = packed >> 16;
-  int pos = (packed & 0xffff) + min(seen, k);          // kept entries before this thread's
-  const int kept = (total & 0xffff) + min(total >> 16, k);
-  bool keep[EPT];
-#pragma unroll
-  for (int j = 0; j < EPT; ++j) {
-    const bool v = ((vmask >> j) & 1u) != 0 && rest > 0;
-    keep[j] = (((inmask & ~vmask) >> j) & 1u) != 0 || (v && key[j] > tau);
-    if (v && key[j] == tau) keep[j] = seen++ < k;
-    if (((inmask >> j) & 1u) && tid * EPT + j == head[j] * M) hstart[head[j]] = pos;   // first entry of a list
-    if (keep[j]) idx[pos + head[j] * s.W] = (int32_t)(pw[j] & ~kFloorFlag);
-    pos += keep[j] ? 1 : 0;
+    bool keep = ((floors >> j) & 1u) != 0 || key[j] > tau[0];
+    if (k[0] > 0 && key[j] == tau[0]) keep = seen++ < k[0];
+    if (keep) idx[pos++] = (int32_t)(pw[j] & ~kFloorFlag);
   }
   if (tid == 0) hstart[H] = kept;
   __syncthreads();
   // per head: count, offset, and the window behind the kept candidates
-  for (int h = tid >> 6; h < H; h += NW) {
-    const int lane = tid & 63, first = hstart[h] + h * s.W, cnt = hstart[h + 1] - hstart[h];
+  for (int hh = tid >> 6; hh < H; hh += NW) {
+    const int lane = tid & 63, first = hstart[hh] + hh * s.W, cnt = hstart[hh + 1] - hstart[hh];
     for (int wv = lane; wv < s.W; wv += 64) idx[first + cnt + wv] = Nc + wv;
     if (lane == 0) {
-      O.counts[b * H + h] = cnt + s.W;
-      O.offsets[b * (H + 1) + h] = first;
-      if (h == H - 1) O.offsets[b * (H + 1) + H] = first + cnt + s.W;
+      O.counts[b * H + hh] = cnt + s.W;
+      O.offsets[b * (H + 1) + hh] = first;
+      if (hh == H - 1) O.offsets[b * (H + 1) + H] = first + cnt + s.W;
     }
   }
 }
 
 // Largest sequence the fused kernel handles: 32 candidates per thread, and the raw attention row
 // must fit in LDS next to the scratch.
-bool mixsel_supported(const Shape &s) { return s.Nc <= kMsMaxThreads * 32 && (size_t)(s.Nc + s.Nc / 32 + 1) * 4 <= (size_t)kMsMaxLds; }
+static size_t mixsel_lds(const Shape &s) { return (size_t)slots4(s.Nc + 12) * 4; }      // the row, four words up, with fill on either side
+bool mixsel_supported(const Shape &s) { return s.Nc <= kMsMaxThreads * 32 && mixsel_lds(s) <= (size_t)kMsMaxLds; }
 
 template <int THREADS, int EPT>
 static hipError_t launch_mixsel_e(const Shape &s, bool select, const LayerOutTable &out, char *ws, const Workspace &w,
                                   int64_t unit0, int nunits, const LayerInTable &in, int gather_eb, int cand_m,
                                   const CandLists &cl, const int32_t *budgets, hipStream_t st) {
-  const size_t lds = (size_t)(s.Nc + s.Nc / 32 + 1) * 4;
+  const size_t lds = mixsel_lds(s);
   // The kernels may use more dynamic LDS than the default limit.  The limit is a property of the
   // kernel, shared by every stream and thread, so it is raised once, to the most mixsel_supported
   // admits, once per device, and never touched again (a per-launch value could be lowered by another
@@ -376,13 +409,15 @@ static hipError_t launch_mixsel_e(const Shape &s, bool select, const LayerOutTab
 
 // Mix (and, with `select`, selection: the final fixed-budget one, or with cand_m > 0 every head's
 // best cand_m candidates for the head-adaptive split; with `gather_eb` > 0 also the gather of the
-// kept rows, gather_eb being the element size) for `nunits` units starting at unit0.  Few waves per
-// workgroup keep the many block-wide steps cheap; long heads get more threads.
+// kept rows, gather_eb being the element size) for `nunits` units starting at unit0.  Threads and candidates per thread by
+// what takes the time, a wave's instructions (504 candidates: 256 threads of 4 8.9 us, of 8 10.5; 4064: 512 of 8 and 1024 of 4
+// the same 11.1, 256 of 16 13.9; 8160 on 112 heads: 1024 of 8 16.3, 512 of 16 17.9; 16 352 on 256 heads: 1024 of 16 44, 512 of 32 52).
 hipError_t launch_mixsel(const Shape &s, bool select, const LayerOutTable &out, char *ws, const Workspace &w,
                          int64_t unit0, int nunits, const LayerInTable &in, int gather_eb, int cand_m,
                          const CandLists &cl, const int32_t *budgets, hipStream_t st) {
   const int nc = s.Nc;
-  if (nc <= 256 * 8) return launch_mixsel_e<256, 8>(s, select, out, ws, w, unit0, nunits, in, gather_eb, cand_m, cl, budgets, st);
+  if (nc <= 256 * 4) return launch_mixsel_e<256, 4>(s, select, out, ws, w, unit0, nunits, in, gather_eb, cand_m, cl, budgets, st);
+  if (nc <= 512 * 4) return launch_mixsel_e<512, 4>(s, select, out, ws, w, unit0, nunits, in, gather_eb, cand_m, cl, budgets, st);
   if (nc <= 512 * 8) return launch_mixsel_e<512, 8>(s, select, out, ws, w, unit0, nunits, in, gather_eb, cand_m, cl, budgets, st);
   if (nc <= 1024 * 8) return launch_mixsel_e<1024, 8>(s, select, out, ws, w, unit0, nunits, in, gather_eb, cand_m, cl, budgets, st);
   if (nc <= 1024 * 16) return launch_mixsel_e<1024, 16>(s, select, out, ws, w, unit0, nunits, in, gather_eb, cand_m, cl, budgets, st);
@@ -392,7 +427,7 @@ hipError_t launch_mixsel(const Shape &s, bool select, const LayerOutTable &out, 
 template <int THREADS, int EPT>
 static hipError_t launch_topsel_e(const Shape &s, const LayerOutTable &out, char *ws, const CandLists &cl, int64_t unit0,
                                   int nunits, int cand_m, const int32_t *budgets, hipStream_t st) {
-  const size_t lds = (size_t)(s.Nc + s.Nc / 32 + 1) * 4;
+  const size_t lds = mixsel_lds(s);
   auto kern = topsel_kernel<THREADS, EPT>;
   static LdsLimitOnce once;
   const hipError_t attr = once.raise(reinterpret_cast<const void *>(kern));
@@ -406,7 +441,8 @@ static hipError_t launch_topsel_e(const Shape &s, const LayerOutTable &out, char
 hipError_t launch_topsel(const Shape &s, const LayerOutTable &out, char *ws, const CandLists &cl, int64_t unit0, int nunits,
                          int cand_m, const int32_t *budgets, hipStream_t st) {
   const int nc = s.Nc;
-  if (nc <= 256 * 8) return launch_topsel_e<256, 8>(s, out, ws, cl, unit0, nunits, cand_m, budgets, st);
+  if (nc <= 256 * 4) return launch_topsel_e<256, 4>(s, out, ws, cl, unit0, nunits, cand_m, budgets, st);
+  if (nc <= 512 * 4) return launch_topsel_e<512, 4>(s, out, ws, cl, unit0, nunits, cand_m, budgets, st);
   if (nc <= 512 * 8) return launch_topsel_e<512, 8>(s, out, ws, cl, unit0, nunits, cand_m, budgets, st);
   if (nc <= 1024 * 8) return launch_topsel_e<1024, 8>(s, out, ws, cl, unit0, nunits, cand_m, budgets, st);
   if (nc <= 1024 * 16) return launch_topsel_e<1024, 16>(s, out, ws, cl, unit0, nunits, cand_m, budgets, st);
@@ -414,7 +450,9 @@ hipError_t launch_topsel(const Shape &s, const LayerOutTable &out, char *ws, con
 }
 
 // The head-adaptive split of `nlayers` layers' candidate lists of M entries per head: one workgroup per (layer, batch
-// item) with all entries in registers, or, past 16 of them per thread, streamed from memory.
+// item) with all entries in registers, or, past 32 of them per thread, streamed from memory.  As many threads as there
+// are groups of four entries, up to 1024: a wave's instructions are what takes the time (4 lists of 1536 entries: 1024 threads
+// of 8 7.4 us, 512 of 16 8.6; with lists that shared a thread and branches on every entry 13.2).
 template <int THREADS, int EPT>
 static hipError_t launch_candsplit_e(const Shape &s, const LayerOutTable &out, char *ws, const CandLists &cl, int64_t unit0,
                                      int grid, int cand_m, hipStream_t st) {
@@ -423,13 +461,14 @@ static hipError_t launch_candsplit_e(const Shape &s, const LayerOutTable &out, c
 }
 hipError_t launch_select_candidates(const Shape &s, const LayerOutTable &out, char *ws, const CandLists &cl, int64_t unit0,
                                     int nlayers, int cand_m, hipStream_t st) {
-  const int64_t n = (int64_t)cand_m * s.hkv;
   const int grid = nlayers * s.batch;
-  if (n <= 256 * 4) return launch_candsplit_e<256, 4>(s, out, ws, cl, unit0, grid, cand_m, st);
-  if (n <= 512 * 4) return launch_candsplit_e<512, 4>(s, out, ws, cl, unit0, grid, cand_m, st);
-  if (n <= 1024 * 4) return launch_candsplit_e<1024, 4>(s, out, ws, cl, unit0, grid, cand_m, st);
-  if (n <= 1024 * 8) return launch_candsplit_e<1024, 8>(s, out, ws, cl, unit0, grid, cand_m, st);
-  if (n <= 1024 * 16) return launch_candsplit_e<1024, 16>(s, out, ws, cl, unit0, grid, cand_m, st);
+  auto fits = [&](int threads, int ept) { return (int64_t)((cand_m + ept - 1) / ept) * s.hkv <= threads; };
+  if (fits(256, 4)) return launch_candsplit_e<256, 4>(s, out, ws, cl, unit0, grid, cand_m, st);
+  if (fits(512, 4)) return launch_candsplit_e<512, 4>(s, out, ws, cl, unit0, grid, cand_m, st);
+  if (fits(1024, 4)) return launch_candsplit_e<1024, 4>(s, out, ws, cl, unit0, grid, cand_m, st);
+  if (fits(1024, 8)) return launch_candsplit_e<1024, 8>(s, out, ws, cl, unit0, grid, cand_m, st);
+  if (fits(1024, 16)) return launch_candsplit_e<1024, 16>(s, out, ws, cl, unit0, grid, cand_m, st);
+  if (fits(1024, 32)) return launch_candsplit_e<1024, 32>(s, out, ws, cl, unit0, grid, cand_m, st);
   return launch_split_stream(s, out, ws, cl, unit0, nlayers, cand_m, st);
 }
 

@@ -10,17 +10,23 @@
 namespace mixkv {
 
 constexpr int kMsMaxThreads = 1024, kMsMaxWaves = kMsMaxThreads / 64;
-constexpr int kDigit = 11, kBins = 1 << kDigit;     // radix-select digit
+constexpr int kDigit = 11, kBins = 1 << kDigit;     // a histogram of the threshold search
+constexpr int kSurvivors = 128;                      // keys of a boundary bin that are ranked by counting
 
 struct MsScratch {
   float f[kMsMaxWaves][8];
-  float fr[8];
-  uint32_t ur[2];
-  int i[kMsMaxWaves + 1];
+  uint32_t wmax[kMsMaxWaves];            // every wave's largest key
+  int i[kMsMaxWaves], i2[kMsMaxWaves];
   int hist[kBins];
-  int hist0[kBins];                      // the first round's histogram of a head, for a second threshold on the same keys
-  int bin, krem, cut;
+  struct { int bin, k, count; } cut[2];  // per threshold: its bin, the keys still needed of that bin, the keys in it
+  int nsurv[2], krem[2];
+  uint32_t tau[2], surv[2][kSurvivors];
 };
+
+// LDS slot of a word: four pad words per 32 keep every aligned group of four together and spread the groups of
+// owners a power of two apart over the banks.
+__device__ __forceinline__ int slot4(int i) { return i + ((i >> 5) << 2); }
+__host__ __device__ constexpr int slots4(int n) { return n + n / 32 * 4 + 4; }
 
 // Block-wide reduction of NS sums, NMIN minima and NMAX maxima at once; every thread gets the
 // results back in place.  Fixed order: lanes in lane order inside a wave, then waves in wave order.
@@ -48,192 +54,263 @@ __device__ __forceinline__ void block_reduce_mixed(float (&v)[NS + NMIN + NMAX],
   }
 }
 
-// Block-wide minimum and maximum of unsigned keys through two LDS atomics per wave (integer
-// min / max do not depend on the order).  sc.ur must hold {0xffffffff, 0} from before an earlier
-// barrier of the kernel.
-__device__ __forceinline__ void block_minmax_u32(uint32_t &lo, uint32_t &hi, MsScratch &sc) {
-  const int lane = threadIdx.x & 63;
-  lo = wave_reduce<WMin>(lo, 0xffffffffu);
-  hi = wave_reduce<WMax>(hi, 0u);
-  if (lane == 0) { atomicMin(&sc.ur[0], lo); atomicMax(&sc.ur[1], hi); }
-  __syncthreads();
-  lo = sc.ur[0];
-  hi = sc.ur[1];
-}
-
-// Exclusive prefix sum of one int per thread (thread order); *total receives the block sum.
 __device__ __forceinline__ int read_lane_dyn(int x, int lane_uniform) {
   return __builtin_amdgcn_readlane(x, __builtin_amdgcn_readfirstlane(lane_uniform));
 }
 
+// Exclusive prefix sums of one int per wave's thread, given every wave's total in tot[]; *total receives the block sum.
 template <int NW>
-__device__ __forceinline__ int block_scan_excl(int v, MsScratch &sc, int *total) {
+__device__ __forceinline__ int waves_before(const int *tot, int *total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int wtot;
-  const int inc = wave_scan_incl_add(v, &wtot);
-  __syncthreads();
-  if (lane == 0) sc.i[wave] = wtot;
-  __syncthreads();
-  const int x = (lane & 15) < NW ? sc.i[lane & 15] : 0;
+  const int x = (lane & 15) < NW ? tot[lane & 15] : 0;
   const int y = row_scan_incl<WSum>(x, 0);              // inclusive over the waves, in every row of lanes
   *total = read_lane(y, 15);
-  const int before = wave == 0 ? 0 : read_lane_dyn(y, wave - 1);
-  return before + inc - v;
+  return wave == 0 ? 0 : read_lane_dyn(y, wave - 1);
 }
 
+// Exclusive prefix sum of one int per thread (thread order) behind one barrier; *total receives the block sum.  A barrier
+// must lie between this and the last reads of sc.i.
+template <int NW>
+__device__ __forceinline__ int block_scan_excl(int v, MsScratch &sc, int *total) {
+  int wtot;
+  const int inc = wave_scan_incl_add(v, &wtot);
+  if ((threadIdx.x & 63) == 0) sc.i[threadIdx.x >> 6] = wtot;
+  __syncthreads();
+  return waves_before<NW>(sc.i, total) + inc - v;
+}
+
+// The same for two ints; *total receives the block sum of the first.  A barrier must lie between this and the last reads of sc.i and sc.i2.
+template <int NW>
+__device__ __forceinline__ void block_scan_excl(int &v, int &v2, MsScratch &sc, int *total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int wtot, wtot2, total2;
+  const int inc = wave_scan_incl_add(v, &wtot), inc2 = wave_scan_incl_add(v2, &wtot2);
+  if (lane == 0) { sc.i[wave] = wtot; sc.i2[wave] = wtot2; }
+  __syncthreads();
+  v = waves_before<NW>(sc.i, total) + inc - v;
+  v2 = waves_before<NW>(sc.i2, &total2) + inc2 - v2;
+}
+
+// Order-preserving map float -> uint32 >= 1 (larger float <=> larger key); 0 is left for "no candidate".
 __device__ __forceinline__ uint32_t order_key_u(float x) {
   uint32_t u = __float_as_uint(x);
   if (u == 0x80000000u) u = 0;                          // -0 and +0 are the same score
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+  return max(u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u), 1u);
 }
 
-// One count into a shared histogram bin per lane, with the lanes that share the wave's most common
-// bin (as seen from its first active lane) merged into a single atomic.
-__device__ __forceinline__ void hist_add(int *hist, int bin, bool on) {
-  const unsigned long long act = __ballot(on);
-  if (act == 0) return;
-  const int first = __ffsll((long long)act) - 1;                  // wave-uniform
-  const int b0 = __builtin_amdgcn_readlane(bin, first);
-  const unsigned long long same = __ballot(on && bin == b0);
-  const int lane = threadIdx.x & 63;
-  if (lane == first) atomicAdd(&hist[b0], __popcll(same));
-  if (on && bin != b0) atomicAdd(&hist[bin], 1);
+// One count into a shared histogram bin per lane (all lanes take part), with the lanes that share lane 0's bin merged into
+// a single atomic: scores of one head often agree in their leading bits, and 64 atomics on one LDS word would run one
+// after the other.
+__device__ __forceinline__ void hist_add(int *hist, int bin) {
+  const int b0 = __builtin_amdgcn_readfirstlane(bin);
+  const bool same = bin == b0, lead = (threadIdx.x & 63) == 0;
+  const int n = __popcll(__ballot(same));
+  if (!same || lead) atomicAdd(&hist[bin], lead ? n : 1);
 }
 
-// Threshold of the k largest of a workgroup's keys (1 <= k <= number of valid keys): every thread holds
-// EPT keys, those with their bit set in `vmask` valid, and [kmin, kmax] is the range of all valid keys.  Most-significant-digit radix select from the first
-// bit in which the keys differ.  Returns tau, the k-th largest key, and in krem how many of the
-// keys equal to tau still belong to the k (0: all of them).  Ends behind a barrier: may be called again.
-// The first round counts every valid key and does not depend on k: FIRST = 1 keeps its histogram
-// aside, FIRST = 2 takes it from there (a second threshold on the same keys), 0 does neither.
-template <int THREADS, int EPT, int FIRST = 0>
-__device__ __forceinline__ uint32_t radix_threshold(const uint32_t (&key)[EPT], uint32_t vmask, uint32_t kmin, uint32_t kmax,
-                                                    int k, MsScratch &sc, int &krem) {
-  constexpr int NW = THREADS / 64;
+// The bins of sc.hist in which the first k[q] counts end (q < NK; none for k[q] < 1), to sc.cut[Q0 + q].  Ends behind a
+// barrier.
+template <int THREADS, int NK, int Q0 = 0>
+__device__ __forceinline__ void find_bins(const int (&k)[NK], MsScratch &sc) {
+  constexpr int NW = THREADS / 64, BPT = kBins / THREADS;
   const int tid = threadIdx.x;
-  // bits at and above `undecided` are common to all keys; digits of up to kDigit bits from there down
-  int undecided = kmin == kmax ? 0 : 32 - __clz((int)(kmin ^ kmax));
-  uint32_t prefix = undecided >= 32 ? 0u : (kmax >> undecided) << undecided;
-  bool all_equal = false, first = true;
-  while (undecided > 0) {
-    const int wbits = min(kDigit, undecided), shift = undecided - wbits;
-    const uint32_t himask = undecided >= 32 ? 0u : ~0u << undecided;
-    const bool saved = FIRST == 2 && first;             // this round's histogram is already in hist0
-    int *hist = saved ? sc.hist0 : sc.hist;
-    if (!saved) {
-      for (int i = tid; i < kBins; i += THREADS) sc.hist[i] = 0;
-      __syncthreads();
+  int c[BPT], cnt = 0;
 #pragma unroll
-      for (int e = 0; e < EPT; ++e) {
-        const bool on = ((vmask >> e) & 1u) != 0 && (key[e] & himask) == (prefix & himask);
-        hist_add(sc.hist, (int)((key[e] >> shift) & ((1u << wbits) - 1u)), on);
-      }
-      __syncthreads();
-    }
-    // walk the bins from the top: thread t sums bins [kBins - (t+1)*BPT, kBins - t*BPT)
-    constexpr int BPT = (kBins + THREADS - 1) / THREADS;
-    int cnt = 0;
+  for (int j = 0; j < BPT; ++j) { c[j] = sc.hist[tid * BPT + j]; cnt += c[j]; }
+  int wtot, total;
+  const int inc = wave_scan_incl_add(cnt, &wtot);
+  if ((tid & 63) == 0) sc.i[tid >> 6] = wtot;
+  __syncthreads();
+  const int excl = waves_before<NW>(sc.i, &total) + inc - cnt;
 #pragma unroll
-    for (int j = 0; j < BPT; ++j) {
-      const int bi = kBins - 1 - (tid * BPT + j);
-      const int c = bi >= 0 ? hist[bi] : 0;
-      if (FIRST == 1 && first && bi >= 0) sc.hist0[bi] = c;
-      cnt += c;
-    }
-    first = false;
-    int total;
-    const int excl = block_scan_excl<NW>(cnt, sc, &total);
-    if (excl < k && k <= excl + cnt) {
+  for (int q = 0; q < NK; ++q)
+    if (excl < k[q] && k[q] <= excl + cnt) {
       int run = excl;
 #pragma unroll
       for (int j = 0; j < BPT; ++j) {
-        const int bi = kBins - 1 - (tid * BPT + j);
-        const int c = bi >= 0 ? hist[bi] : 0;
-        if (run < k && k <= run + c) { sc.bin = bi; sc.krem = k - run; sc.cut = c; }
-        run += c;
+        if (run < k[q] && k[q] <= run + c[j]) sc.cut[Q0 + q] = {tid * BPT + j, k[q] - run, c[j]};
+        run += c[j];
       }
     }
-    __syncthreads();
-    prefix |= (uint32_t)sc.bin << shift;
-    k = sc.krem;
-    undecided = shift;
-    const bool whole_bin = sc.cut == k && shift > 0 && prefix != 0;
-    __syncthreads();
-    // Every key of the bin is needed: the kept set is "all keys at or above the bin", whatever
-    // the lower digits are, so the remaining rounds can be skipped.
-    if (whole_bin) { prefix -= 1; all_equal = true; break; }
+  __syncthreads();
+}
+
+// Sum over aligned groups of L = 1, 2, 4 or 8 lanes, in every lane.
+template <int L>
+__device__ __forceinline__ int group_sum(int x) {
+  if (L >= 2) x += __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xf, 0xf, true);      // quad_perm [1,0,3,2]
+  if (L >= 4) x += __builtin_amdgcn_update_dpp(0, x, 0x4E, 0xf, 0xf, true);      // quad_perm [2,3,0,1]
+  if (L >= 8) x += __builtin_amdgcn_update_dpp(0, x, 0x141, 0xf, 0xf, true);     // row_half_mirror
+  return x;
+}
+
+// What the threshold search needs from before a barrier: every wave's largest key and an empty histogram.
+template <int THREADS>
+__device__ __forceinline__ void thresholds_begin(uint32_t largest_of_thread, MsScratch &sc) {
+  const int tid = threadIdx.x;
+#pragma unroll
+  for (int i = 0; i < kBins / THREADS; ++i) sc.hist[i * THREADS + tid] = 0;
+  if (tid < 2) sc.nsurv[tid] = 0;
+  const uint32_t m = wave_reduce<WMax>(largest_of_thread, 0u);
+  if ((tid & 63) == 0) sc.wmax[tid >> 6] = m;
+}
+
+// Thresholds of the want[q] largest of a workgroup's keys (q < NK; want[q] < 1: not asked for, else at most the number of
+// keys): every thread holds EPT keys, 0 where there is none.  The want[q] largest are the keys above tau[q] and, if
+// krem[q] > 0, the first krem[q] (by position) of those equal to it.  thresholds_begin and a barrier come before.
+// The first histogram takes the distance of a key to the largest one in steps of 2^17 (a float's upper six mantissa bits), up
+// to 32 powers of two below it; the keys of a threshold's bin, if they are no more than kSurvivors and not all needed,
+// are listed and ranked by counting, a few lanes to a key; fuller bins and what lies further below are divided by more
+// histograms.
+// Bound: instruction issue (16 waves on one compute unit) and, with few waves, the length of the chain.  A search from the
+// first bit in which the keys differ (their range first, a histogram per eleven bits and threshold, masks of valid keys)
+// took 3 to 6 us more; keys at odds with the fixed steps (all of a head within a few 2^17) take one histogram more here.
+constexpr int kFirstShift = 17;
+template <int THREADS, int EPT, int NK>
+__device__ __forceinline__ void radix_thresholds(const uint32_t (&key)[EPT], const int (&want)[NK], MsScratch &sc, uint32_t (&tau)[NK],
+                                                 int (&krem)[NK]) {
+  constexpr int NW = THREADS / 64, L = THREADS / kSurvivors;        // L lanes to a listed key
+  static_assert(kBins % THREADS == 0 && THREADS % kSurvivors == 0, "whole bins and lanes per thread");
+  const int tid = threadIdx.x, lane = tid & 63;
+  const uint32_t kmax = read_lane(row_scan_incl<WMax>((lane & 15) < NW ? sc.wmax[lane & 15] : 0u, 0u), 15);
+#pragma unroll
+  for (int e = 0; e < EPT; ++e) hist_add(sc.hist, (int)min((kmax - key[e]) >> kFirstShift, (uint32_t)kBins - 1));
+  __syncthreads();
+  find_bins<THREADS, NK>(want, sc);
+  uint32_t hi[NK], width[NK];                            // a threshold's bin: the keys from hi - width to hi
+  int count[NK];
+  bool ranked[NK], any = false;
+#pragma unroll
+  for (int q = 0; q < NK; ++q) {
+    ranked[q] = false;
+    tau[q] = 0xffffffffu;
+    krem[q] = 0;
+    if (want[q] < 1) continue;
+    const int bin = sc.cut[q].bin;
+    hi[q] = kmax - ((uint32_t)bin << kFirstShift);
+    width[q] = min(hi[q] - 1, bin == kBins - 1 ? 0xffffffffu : (1u << kFirstShift) - 1);     // keys are at least 1
+    krem[q] = sc.cut[q].k;
+    count[q] = sc.cut[q].count;
+    if (bin == kBins - 1) count[q] = 0x7fffffff;         // as wide as it gets, and "no key" is counted here: look again
+    while (width[q] > 0 && count[q] > kSurvivors && count[q] != krem[q]) {        // uniform over the workgroup
+      const int shift = max(0, 32 - __clz((int)width[q]) - kDigit);
+#pragma unroll
+      for (int i = 0; i < kBins / THREADS; ++i) sc.hist[i * THREADS + tid] = 0;
+      __syncthreads();
+#pragma unroll
+      for (int e = 0; e < EPT; ++e)
+        if (hi[q] - key[e] <= width[q]) atomicAdd(&sc.hist[(hi[q] - key[e]) >> shift], 1);
+      __syncthreads();
+      const int k1[1] = {krem[q]};
+      if (q == 0) find_bins<THREADS, 1, 0>(k1, sc); else find_bins<THREADS, 1, NK - 1>(k1, sc);
+      const uint32_t step = (uint32_t)sc.cut[q].bin << shift;
+      hi[q] -= step;
+      width[q] = min(width[q] - step, (1u << shift) - 1);
+      krem[q] = sc.cut[q].k;
+      count[q] = sc.cut[q].count;
+    }
+    if (count[q] == krem[q]) {                           // the whole bin is needed
+      tau[q] = hi[q] - width[q] - 1;
+      krem[q] = 0;
+      continue;
+    }
+    tau[q] = hi[q];
+    if (width[q] == 0) continue;                         // the bin is one key
+    ranked[q] = any = true;
+#pragma unroll
+    for (int e = 0; e < EPT; ++e)
+      if (hi[q] - key[e] <= width[q]) {
+        const int at = atomicAdd(&sc.nsurv[q], 1);
+        if (at < kSurvivors) sc.surv[q][at] = key[e];
+      }
   }
-  krem = all_equal ? 0 : k;
-  return prefix;
+  if (!any) return;
+  __syncthreads();
+  const int mine = tid / L, part = tid % L;
+#pragma unroll
+  for (int q = 0; q < NK; ++q)
+    if (ranked[q] && mine < sc.nsurv[q]) {
+      const int n = sc.nsurv[q];
+      const uint32_t x = sc.surv[q][mine];
+      int above = 0, equal = 0;
+      for (int j = part; j < n; j += L) {
+        const uint32_t y = sc.surv[q][j];
+        above += y > x ? 1 : 0;
+        equal += y == x ? 1 : 0;
+      }
+      above = group_sum<L>(above);
+      equal = group_sum<L>(equal);
+      if (above < krem[q] && krem[q] <= above + equal) {                          // equal keys write the same
+        const bool all = krem[q] == above + equal;
+        sc.tau[q] = all ? x - 1 : x;
+        sc.krem[q] = all ? 0 : krem[q] - above;
+      }
+    }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < NK; ++q)
+    if (ranked[q]) { tau[q] = sc.tau[q]; krem[q] = sc.krem[q]; }
 }
 
 // The Bp >= 1 largest of a workgroup's keys, ties to the smaller position: every thread holds EPT consecutive
-// keys of which the first `nvalid` exist, in ascending order of position over the threads (Sec. 3.1 /
+// keys, 0 where there is none, in ascending order of position over the threads (Sec. 3.1 /
 // Algorithm 1, TopB).  pos(e) is the position of the thread's key e; it is asked for kept keys only.  The
 // kept positions go to idx[0, Bp) in ascending order.  With ckey not null the list is a head's candidates for
 // the head-adaptive split: the order keys go beside the positions, and the head's `floor` <= Bp best carry
-// kFloorFlag in their position word.  sc.ur must hold {0xffffffff, 0} from before an earlier barrier.
+// kFloorFlag in their position word.  thresholds_begin and a barrier come before.
 template <int THREADS, int EPT, class Pos>
-__device__ __forceinline__ void top_select_keys(const uint32_t (&key)[EPT], int nvalid, int Bp, int32_t *idx, uint32_t *ckey,
-                                                int floor, MsScratch &sc, Pos pos_of) {
-  constexpr int NW = THREADS / 64;
-  uint32_t kmin = 0xffffffffu, kmax = 0;
-#pragma unroll
-  for (int e = 0; e < EPT; ++e)
-    if (e < nvalid) { kmin = min(kmin, key[e]); kmax = max(kmax, key[e]); }
-  block_minmax_u32(kmin, kmax, sc);
-  const uint32_t vmask = nvalid >= EPT ? (EPT >= 32 ? 0xffffffffu : (1u << (EPT & 31)) - 1u)
-                                       : (nvalid <= 0 ? 0u : (1u << nvalid) - 1u);
-  int k;                             // of the keys equal to tau, the first k (by position) are kept
+__device__ __forceinline__ void top_select_keys(const uint32_t (&key)[EPT], int Bp, int32_t *idx, uint32_t *ckey, int floor, MsScratch &sc,
+                                                Pos pos_of) {
   const bool flags = ckey != nullptr && floor > 0;
-  int kf = 0;
-  uint32_t tau, tauf = 0xffffffffu;
-  if (flags) {
-    tau = radix_threshold<THREADS, EPT, 1>(key, vmask, kmin, kmax, Bp, sc, k);
-    tauf = radix_threshold<THREADS, EPT, 2>(key, vmask, kmin, kmax, floor, sc, kf);
-  } else {
-    tau = radix_threshold<THREADS, EPT>(key, vmask, kmin, kmax, Bp, sc, k);
-  }
-  // one scan carries both counts: keys above tau (low half) and keys equal to tau (high half)
-  int ngt = 0, neq = 0, neqf = 0;
-#pragma unroll
-  for (int e = 0; e < EPT; ++e) {
-    const bool in = e < nvalid;
-    ngt += (in && key[e] > tau) ? 1 : 0;
-    neq += (in && key[e] == tau) ? 1 : 0;
-    neqf += (in && key[e] == tauf) ? 1 : 0;
-  }
+  const int want[2] = {Bp, flags ? floor : 0};
+  uint32_t tau[2];
+  int k[2];
+  radix_thresholds<THREADS, EPT, 2>(key, want, sc, tau, k);
+  auto put = [&](int e, int pos, bool in_floor) {
+    if (pos >= Bp) return;
+    idx[pos] = (int32_t)((uint32_t)pos_of(e) | (in_floor ? kFloorFlag : 0u));
+    if (ckey) ckey[pos] = key[e];
+  };
   int total;
-  const int packed = block_scan_excl<NW>(ngt | (neq << 16), sc, &total);
-  int seen = packed >> 16;                          // equal keys at smaller indices
-  int pos = (packed & 0xffff) + min(seen, k);       // kept entries at smaller indices
-  int seenf = flags ? block_scan_excl<NW>(neqf, sc, &total) : 0;
+  if (k[0] == 0 && k[1] == 0) {                         // no key equal to a threshold is left out
+    int pos = 0;
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) pos += key[e] > tau[0] ? 1 : 0;
+    pos = block_scan_excl<THREADS / 64>(pos, sc, &total);
+#pragma unroll
+    for (int e = 0; e < EPT; ++e)
+      if (key[e] > tau[0]) put(e, pos++, key[e] > tau[1]);
+    return;
+  }
+  // keys above tau (low half) and keys equal to tau (high half) share a word
+  int packed = 0, seenf = 0;
 #pragma unroll
   for (int e = 0; e < EPT; ++e) {
-    if (e < nvalid) {
-      bool sel = key[e] > tau;
-      if (key[e] == tau) sel = seen++ < k;
-      bool inf = flags && key[e] > tauf;
-      if (flags && key[e] == tauf) inf = seenf++ < kf;
-      if (sel) {
-        if (pos < Bp) {
-          idx[pos] = (int32_t)((uint32_t)pos_of(e) | (inf ? kFloorFlag : 0u));
-          if (ckey) ckey[pos] = key[e];
-        }
-        ++pos;
-      }
-    }
+    packed += (key[e] > tau[0] ? 1 : 0) + (key[e] == tau[0] ? 1 << 16 : 0);
+    seenf += key[e] == tau[1] ? 1 : 0;
+  }
+  block_scan_excl<THREADS / 64>(packed, seenf, sc, &total);
+  int seen = packed >> 16;                          // equal keys at smaller indices
+  int pos = (packed & 0xffff) + min(seen, k[0]);    // kept entries at smaller indices
+#pragma unroll
+  for (int e = 0; e < EPT; ++e) {
+    bool sel = key[e] > tau[0], inf = key[e] > tau[1];
+    if (key[e] == tau[0]) sel = seen++ < k[0];
+    if (key[e] == tau[1]) inf = seenf++ < k[1];
+    if (sel) put(e, pos++, inf);
   }
 }
 
-// top_select_keys on the scores a[] of the EPT consecutive candidates base .. base + nvalid - 1.
-template <int THREADS, int EPT>
-__device__ __forceinline__ void top_select(const float (&a)[EPT], int nvalid, int base, int Bp, int32_t *idx,
-                                           uint32_t *ckey, int floor, MsScratch &sc) {
-  uint32_t key[EPT];
+// The EPT consecutive order keys from `base` on out of the LDS row k_s of n keys (whole groups of four were written), 0 past it.
+template <int EPT>
+__device__ __forceinline__ void read_keys(const uint32_t *k_s, int base, int n, uint32_t (&key)[EPT]) {
 #pragma unroll
-  for (int e = 0; e < EPT; ++e) key[e] = order_key_u(a[e]);
-  top_select_keys<THREADS, EPT>(key, nvalid, Bp, idx, ckey, floor, sc, [&](int e) { return base + e; });
+  for (int e = 0; e < EPT; e += 4) {
+    const uint4 v = base + e < n ? *reinterpret_cast<const uint4 *>(&k_s[slot4(base + e)]) : make_uint4(0u, 0u, 0u, 0u);
+    key[e] = v.x; key[e + 1] = v.y; key[e + 2] = v.z; key[e + 3] = v.w;
+#pragma unroll
+    for (int j = 1; j < 4; ++j) key[e + j] = base + e + j < n ? key[e + j] : 0u;
+  }
 }
 
 // Rows head h of a layer keeps and its first row inside the batch item: B each, or the layer's
@@ -274,28 +351,40 @@ struct UnitRows {
         kdot(reinterpret_cast<const float *>(ws + w.sdiv) + unit * s.Npad),
         invn(reinterpret_cast<const float *>(ws + w.invnorm) + unit * s.Npad), Nc(s.Nc), kstats(s.kstats != 0),
         use_v(s.intrinsic != MIXKV_INTRINSIC_NONE), knorm(s.intrinsic == MIXKV_INTRINSIC_KNORM) {}
-  // intrinsic score and diversity of the four candidates from i on (i a multiple of four; zeros past the row)
-  __device__ __forceinline__ void load_vd(int i, float4 &vr, float4 &dr) const {
-    float4 kr = make_float4(0.f, 0.f, 0.f, 0.f), nr = kr;
-    vr = kr;
-    if (i < Nc) {
-      if (kstats) {                          // else nobody wrote them: the diversity is 0 and carries weight 0
-        kr = *reinterpret_cast<const float4 *>(kdot + i);
-        nr = *reinterpret_cast<const float4 *>(invn + i);
-      }
-      if (knorm) vr = make_float4(neg_key_norm(nr.x), neg_key_norm(nr.y), neg_key_norm(nr.z), neg_key_norm(nr.w));
-      else if (use_v) vr = *reinterpret_cast<const float4 *>(vnorm + i);
+  // A group of four candidates to read for the group from i on: a group past the row re-reads the row's last one (its
+  // values are not used), so that no load waits behind a branch on the one before.
+  __device__ __forceinline__ int inside(int i) const { return min(i, (Nc - 1) & ~3); }
+  // Intrinsic score and diversity of G groups of four candidates, group g from i[g] on (a multiple of four, inside()
+  // the row): all loads are in flight together.
+  template <int G>
+  __device__ __forceinline__ void load_vd(const int (&i)[G], float4 (&vr)[G], float4 (&dr)[G]) const {
+    float4 nr[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) vr[g] = dr[g] = nr[g] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (kstats) {                            // else nobody wrote them: the diversity is 0 and carries weight 0
+#pragma unroll
+      for (int g = 0; g < G; ++g) dr[g] = *reinterpret_cast<const float4 *>(kdot + i[g]);
+#pragma unroll
+      for (int g = 0; g < G; ++g) nr[g] = *reinterpret_cast<const float4 *>(invn + i[g]);
     }
-    // s_div: a product rounded on its own.  The minimum is taken from the first reading and must
-    // cancel exactly against the second, so the compiler may not fuse the product into the
-    // subtraction that follows there (it may by default); the empty statements hide where it came from.
-    dr = make_float4(-kr.x * nr.x, -kr.y * nr.y, -kr.z * nr.z, -kr.w * nr.w);
-    asm("" : "+v"(dr.x), "+v"(dr.y), "+v"(dr.z), "+v"(dr.w));
+    if (use_v && !knorm) {
+#pragma unroll
+      for (int g = 0; g < G; ++g) vr[g] = *reinterpret_cast<const float4 *>(vnorm + i[g]);
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      if (knorm) vr[g] = make_float4(neg_key_norm(nr[g].x), neg_key_norm(nr[g].y), neg_key_norm(nr[g].z), neg_key_norm(nr[g].w));
+      // s_div: a product rounded on its own.  The minimum is taken from the first reading and must
+      // cancel exactly against the second, so the compiler may not fuse the product into the
+      // subtraction that follows there (it may by default); the empty statements hide where it came from.
+      dr[g] = make_float4(-dr[g].x * nr[g].x, -dr[g].y * nr[g].y, -dr[g].z * nr[g].z, -dr[g].w * nr[g].w);
+      asm("" : "+v"(dr[g].x), "+v"(dr[g].y), "+v"(dr[g].z), "+v"(dr[g].w));
+    }
   }
 };
 
 // Most dynamic LDS any of these kernels asks for, next to their scratch.
-constexpr int kMsMaxLds = 140 * 1024;
+constexpr int kMsMaxLds = 146 * 1024;
 
 // Raises a kernel's dynamic-LDS limit to kMsMaxLds the first time it is launched on a device.
 struct LdsLimitOnce {
