@@ -99,6 +99,16 @@ void carve_workspace(const Shape &s, int64_t units, Workspace *w, bool select_on
 
 static bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
+// Whether the kept rows of `nunits` heads are copied by a kernel of their own behind the fused mix and selection.  One workgroup moves
+// some 40 KB a microsecond (reads and writes), the launch of its own costs 4 to 5 us and then moves 5 MB a microsecond with the
+// whole chip: so the launch pays where moved / 40 > 4500 + nunits * moved / 5000 (bytes, ns).  Calls, copied inside -> apart,
+// bf16, D = 128: 4 heads of 256 rows 44.4 -> 44.3 us, of 400 41.4 -> 38.8; 8 of 2048 63.9 -> 44.2; 28 of 1024 98.4 -> 91.3; 56 of 1500 158 ->
+// 142; 112 of 2048 259 -> 235 (240 with the copy inside as it is now).
+static bool gather_apart(const Shape &s, int eb, int max_head_rows, int64_t nunits) {
+  const int64_t moved = (int64_t)max_head_rows * s.D * eb * 4;
+  return moved * (125 - nunits) > (int64_t)4500 * 5000;
+}
+
 enum Stage { kScore = 1, kSelect = 2, kGather = 4 };
 
 // Compute units of the current device (0 on failure); asked of the runtime once per device.
@@ -249,7 +259,8 @@ static mixkv_status run(const mixkv_params *params, const mixkv_layer_in *in, mi
   const bool long_select = cut_sel.seg > 0 && (!s.adaptive || cand_m > 0);
   const bool fused = (stages & kScore) && short_row;
   const bool fused_select = fused && do_select && !s.adaptive;
-  const bool fused_gather = fused_select && (stages & kGather);   // the selecting workgroup also copies its rows
+  // the selecting workgroup also copies its rows, unless they are many and the workgroups few
+  const bool fused_gather = fused_select && (stages & kGather) && !gather_apart(s, eb, max_head_rows, (n_layers < kLayersPerLaunch ? n_layers : kLayersPerLaunch) * s.units_per_layer);
   const bool topsel = select_only && short_row && (!s.adaptive || cand_m > 0);
   StageTimer timed;
   timed.stream = stream;

@@ -509,14 +509,19 @@ __global__ __launch_bounds__(256) void gather_kernel(Shape s, int eb, LayerInTab
   const int ppr = s.D * eb / 16, rows_per_block = blockDim.x / ppr;
   const int p = blockIdx.x * rows_per_block + threadIdx.x / ppr, piece = threadIdx.x % ppr;
   const int H = s.hkv, total = H * s.B;
-  if (p >= total) return;
   int h;
   if (s.adaptive || s.per_head) {
+    // lane j holds where head j + 1 (of 64 at a time) begins: one round trip, not one per head
     const int32_t *offs = O.offsets + b * (H + 1);
-    if (p >= offs[H]) return;                          // per-head budgets may leave the tail unused
+    const int end = min(offs[H], total);
     h = 0;
-    while (h + 1 < H && p >= offs[h + 1]) ++h;
+    for (int h0 = 0; h0 + 1 < H; h0 += 64) {
+      const int next = offs[min(h0 + (int)(threadIdx.x & 63) + 1, H)], n = min(64, H - 1 - h0);
+      for (int j = 0; j < n; ++j) h += p >= __builtin_amdgcn_readlane(next, j) ? 1 : 0;
+    }
+    if (p >= end) return;                              // per-head budgets may leave the tail unused
   } else {
+    if (p >= total) return;
     h = p / s.B;
   }
   const int64_t prow = (int64_t)b * total + p;

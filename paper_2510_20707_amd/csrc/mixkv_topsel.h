@@ -257,10 +257,11 @@ __device__ __forceinline__ void radix_thresholds(const uint32_t (&key)[EPT], con
 // Algorithm 1, TopB).  pos(e) is the position of the thread's key e; it is asked for kept keys only.  The
 // kept positions go to idx[0, Bp) in ascending order.  With ckey not null the list is a head's candidates for
 // the head-adaptive split: the order keys go beside the positions, and the head's `floor` <= Bp best carry
-// kFloorFlag in their position word.  thresholds_begin and a barrier come before.
+// kFloorFlag in their position word.  `kept`, if not null, is an LDS array that receives the positions too; it may be where
+// the keys came from.  thresholds_begin and a barrier come before.
 template <int THREADS, int EPT, class Pos>
 __device__ __forceinline__ void top_select_keys(const uint32_t (&key)[EPT], int Bp, int32_t *idx, uint32_t *ckey, int floor, MsScratch &sc,
-                                                Pos pos_of) {
+                                                Pos pos_of, int32_t *kept = nullptr) {
   const bool flags = ckey != nullptr && floor > 0;
   const int want[2] = {Bp, flags ? floor : 0};
   uint32_t tau[2];
@@ -268,8 +269,10 @@ __device__ __forceinline__ void top_select_keys(const uint32_t (&key)[EPT], int 
   radix_thresholds<THREADS, EPT, 2>(key, want, sc, tau, k);
   auto put = [&](int e, int pos, bool in_floor) {
     if (pos >= Bp) return;
-    idx[pos] = (int32_t)((uint32_t)pos_of(e) | (in_floor ? kFloorFlag : 0u));
+    const int32_t word = (int32_t)((uint32_t)pos_of(e) | (in_floor ? kFloorFlag : 0u));
+    idx[pos] = word;
     if (ckey) ckey[pos] = key[e];
+    if (kept) kept[pos] = word;
   };
   int total;
   if (k[0] == 0 && k[1] == 0) {                         // no key equal to a threshold is left out

@@ -1,0 +1,36 @@
+"""The kept rows of a fused selection, copied by the selecting workgroup or by a kernel behind it (many rows, few heads):
+bit for bit the source rows, on either side of that rule, with row counts around the pieces a workgroup has in flight,
+the window alone, everything kept, unequal budgets per head and more heads than a wave has lanes."""
+import numpy as np
+import pytest
+
+from paper_2510_20707_amd import synth
+from tests import harness as H
+
+pytestmark = pytest.mark.gpu
+WL = synth.WORKLOADS
+
+
+@pytest.mark.parametrize("dtype,D,N,W,Hkv,B", [
+    ("bf16", 128, 700, 8, 2, 8), ("bf16", 128, 700, 8, 2, 64), ("bf16", 64, 700, 8, 2, 129), ("f32", 128, 700, 8, 2, 33),     # inside
+    ("bf16", 128, 900, 8, 2, 900), ("f32", 64, 3000, 16, 1, 2900), ("bf16", 64, 9000, 8, 1, 1031), ("f32", 128, 2500, 8, 3, 511)])   # apart
+def test_gathered_rows_of_equal_budgets(dtype, D, N, W, Hkv, B):
+    print(f"[case] gather {dtype} D={D} N={N} W={W} Hkv={Hkv} B={B}", flush=True)
+    wl = WL["c2"].with_(name="gather", dtype=dtype, head_dim=D, seq_len=N, window=W, n_q_heads=Hkv, n_kv_heads=Hkv, budget=B,
+                        text_suffix_start=N - 50)
+    lay = synth.make_layer(wl, 0)
+    p, outs = H.run_compress(wl, [lay])
+    H.check_layer(wl, lay, p, outs[0])
+
+
+@pytest.mark.parametrize("Hkv,B,top", [(3, 40, 90), (3, 900, 1900), (66, 30, 400), (66, 30, 60)])
+def test_gathered_rows_of_unequal_budgets(Hkv, B, top):
+    N, W = 2000, 8
+    print(f"[case] gather per head Hkv={Hkv} B={B} top={top}", flush=True)
+    wl = WL["c2"].with_(name="gather-table", head_dim=64, seq_len=N, window=W, n_q_heads=Hkv, n_kv_heads=Hkv, budget=B,
+                        text_suffix_start=N - 50)
+    hb = np.full((1, Hkv), W, dtype=np.int32)
+    hb[0, 1], hb[0, -1] = top, W + 3
+    lay = synth.make_layer(wl, 0)
+    p, outs = H.run_compress(wl, [lay], head_budgets=hb, budget_mode="per_head")
+    H.check_layer(wl, lay, p, outs[0], head_budgets=hb[0], budget_mode="per_head", units=[(0, 0), (0, 1)])
