@@ -7,10 +7,13 @@
 // split over several workgroups per head (contiguous row ranges); each leaves its running softmax
 // in the workspace and decode_merge_kernel folds them in order.
 //
-// bf16 caches go through the matrix cores (decode_mfma_kernel): the rows travel global -> LDS in
-// 32-row tiles, the scores of a tile against all query heads of the group are one chain of MFMAs
+// bf16 caches go through the matrix cores (decode_wave_kernel up to 16 query heads per KV head, decode_mfma_kernel beyond): the
+// scores of a 32-row tile against all query heads of the group are one chain of MFMAs
 // with the keys on the output rows, and the weighted values a second product with the weights as
 // they stand in the accumulators.  fp32 caches take the vector path (decode_kernel).
+#include <algorithm>
+#include <cmath>
+
 #include "mixkv_stream.h"
 
 namespace mixkv {
@@ -196,7 +199,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(DShape s, DecodeTab
 }
 
 // ------------------------------------------------------------------------------------------------
-// decode_mfma_kernel (bf16): one workgroup of D/32 waves per (layer, batch item, KV head, chunk of
+// decode_mfma_kernel (bf16, more than 16 query heads per KV head): one workgroup of D/32 waves per (layer, batch item, KV head, chunk of
 // up to 32 query heads, row range).
 //   * Tiles of 32 rows of K and of V go global -> LDS through the ring of mixkv_stream.h (direct
 //     loads, requested kLead tiles ahead, bank-rotated images); the compacted rows and the appended
@@ -403,6 +406,211 @@ __global__ __launch_bounds__(D * 2, 2) void decode_mfma_kernel(DShape s, DecodeT
   for (int i = 0; i < 16; ++i) out[8 * (i >> 2) + 4 * half + (i & 3)] = bf16_rne(tot > 0.f ? o[i] / tot : 0.f);
 }
 
+// ------------------------------------------------------------------------------------------------
+// decode_wave_kernel (bf16, up to 16 query heads per KV head): a workgroup of four waves per (layer, batch item, KV
+// head, row range), every wave on 32-row tiles of its own.
+//   * Wave w takes the tiles w, w + 4, ...: rows global -> registers (whole rows, coalesced, a tile ahead) -> a private LDS image,
+//     first the keys, then, once their fragments have been read, the values: no barrier before the end.
+//   * Scores: keys on the output rows of two 16 x 16 x 32 products, query heads on the columns: lane (g = lane % 16, quad) holds
+//     the scores of head g on rows 16 r + 4 quad + i at register 4 r + i.  That order is the contraction index of the second product, so
+//     the weights, split into a bf16 head and a bf16 remainder, feed it as they stand, and the values come transposed out of
+//     the image (ds_read_b64_tr_b16: 16 lanes read four rows of 16 elements and receive a column each).
+//   * Offsets as in decode_mfma_kernel; the four lanes of a head share one.  The waves meet once, in wave order, at the end.
+// Bound: HBM for long caches, one chain of memory round trips for short ones.  decode_mfma_kernel has all its waves form
+// every score tile and meet at a barrier per tile, and half of its 32 columns are empty up to 16 heads.  us a step, decode_mfma_kernel ->
+// here, with the merge: 4 heads of 81 rows 6.3 -> 5.1, 112 of 81 7.2 -> 5.8, 256 of 1089 31.8 -> 25.3 (5.6 TB/s), of unequal length 36.7 ->
+// 29.5, 384 of 2148 81.9 -> 68 (6.2 TB/s), 112 of 2065 rows of 64 elements 22.4 -> 15.3.  175 registers for rows of 128 elements: two
+// workgroups per compute unit (three spill, and were 5 % slower).
+// ------------------------------------------------------------------------------------------------
+constexpr int kDecWaveHeads = 16, kDecWaveThreads = 256;
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((__vector_size__(16)));
+
+// Rotation of the 16-byte pieces of a row in a value image: a transposed read takes two pieces of four neighbouring rows.
+template <int D>
+__device__ __forceinline__ int value_swz(int r) { return D == 128 ? (2 * r) & 15 : r & 6; }
+
+template <int D, bool ONCE>
+__global__ __launch_bounds__(kDecWaveThreads, 2) void decode_wave_kernel(DShape s, DecodeTable tab, float *part) {
+  constexpr int DT = MIXKV_BF16, RB = D * 2, PPR = RB / 16, TILE = 32 * PPR, NL = TILE / 64, RPL = 64 / PPR, NC = D / 32, NS = D / 16, W = 4;
+  __shared__ uint4 img_s[W * TILE];
+  __shared__ float m_s[W][kDecWaveHeads], l_s[W][kDecWaveHeads];
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, quad = lane >> 4, lrow = lane / PPR, lq = lane % PPR;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  uint4 *img = img_s + wave * TILE;
+  const int sp = blockIdx.x % s.nsplit, ul = blockIdx.x / s.nsplit;   // row split, unit
+  const int layer = ul / s.units_per_layer, bh = ul - layer * s.units_per_layer;
+  const int b = bh / s.hkv, h = bh - b * s.hkv, ng = s.G;
+  const DecodeLayer L = tab.l[layer];
+  const float c2 = s.scale_log2e;
+
+  // rows of this head: `cnt` compacted ones, then `tail_len` appended ones
+  const int cap = s.packed ? s.hkv * s.B : s.B;                   // rows the head's slot can hold at most
+  int row0 = s.packed ? (L.offsets ? L.offsets[b * (s.hkv + 1) + h] : 0) : 0;
+  int cnt = L.counts[bh];
+  // the query heads in fragment form: lane (g, quad) holds pieces quad, quad + 4, ... of head g's row
+  u32x4 qf[NC];
+  {
+    const char *qrow = reinterpret_cast<const char *>(L.Q) + (int64_t)(b * s.hq + h * s.G + (l16 < ng ? l16 : 0)) * RB + quad * 16;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) qf[c] = *reinterpret_cast<const u32x4 *>(qrow + c * 64);
+  }
+  row0 = min(max(row0, 0), cap);
+  cnt = min(max(cnt, 0), cap - row0);                             // the clamps only guard the loads
+  const int n_all = cnt + s.tail_len;
+  const int r_begin = (int)((int64_t)n_all * sp / s.nsplit), n = (int)((int64_t)n_all * (sp + 1) / s.nsplit);   // rows [r_begin, n)
+  const int nt = (n - r_begin + 31) / 32;                         // tiles of the range
+  const int64_t slot_rows = s.packed ? (int64_t)b * s.hkv * s.B + row0 : (int64_t)bh * s.B;
+  const char *Kc = reinterpret_cast<const char *>(L.Kc) + slot_rows * RB;
+  const char *Vc = reinterpret_cast<const char *>(L.Vc) + slot_rows * RB;
+  const char *Kt = reinterpret_cast<const char *>(L.Kt) + ((int64_t)bh * s.tail_cap - cnt) * RB;   // row r >= cnt at Kt + r * RB
+  const char *Vt = reinterpret_cast<const char *>(L.Vt) + ((int64_t)bh * s.tail_cap - cnt) * RB;
+
+  // the tile that starts at row tb: load j holds rows tb + j RPL + lane / PPR; rows past the range repeat its last one
+  auto load_tile = [&](u32x4 (&r)[NL], const char *compact, const char *tail, int tb) {
+    if (tb + 32 <= min(cnt, n)) {
+      const char *tile = compact + (int64_t)tb * RB;
+      const uint32_t off = (uint32_t)(lane * 16);
+#pragma unroll
+      for (int j = 0; j < NL; ++j) r[j] = load_vec<ONCE>(tile + j * 1024 + off);
+    } else {
+#pragma unroll
+      for (int j = 0; j < NL; ++j) {
+        const int row = min(tb + j * RPL + lrow, n - 1);
+        r[j] = load_vec<ONCE>((row < cnt ? compact : tail) + (int64_t)row * RB + lq * 16);
+      }
+    }
+  };
+  u32x4 kr[NL], vr[NL];
+  if (wave < nt) {
+    load_tile(kr, Kc, Kt, r_begin + wave * 32);
+    load_tile(vr, Vc, Vt, r_begin + wave * 32);
+  }
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+    if (l16 >= ng) qf[c] = u32x4{0u, 0u, 0u, 0u};                  // heads past the group are zero columns
+
+  float m = -INFINITY, l = 0.f;      // head g's offset and this lane's share of the sum of weights
+  f32x4 o[NS];                       // head g's elements 16 s + 4 quad + i, times 2^-m
+#pragma unroll
+  for (int i = 0; i < NS; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const uint32_t img_a = (uint32_t)(uintptr_t)(lds_void_t *)img;
+
+  for (int t = wave; t < nt; t += W) {
+    const int tb = r_begin + t * 32;
+    // ---- keys: image, fragments, scores; the next tile's keys are on their way from then on
+#pragma unroll
+    for (int j = 0; j < NL; ++j) {
+      const int row = j * RPL + lrow;
+      reinterpret_cast<u32x4 *>(img)[row * PPR + (lq ^ tile_swz<DT, D>(row))] = kr[j];
+    }
+    if (t + W < nt) load_tile(kr, Kc, Kt, tb + W * 32);
+    wave_lds_fence();
+    f32x4 acc[2];
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      acc[r] = f32x4{0.f, 0.f, 0.f, 0.f};
+      const int row = 16 * r + l16;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        const u32x4 kf = reinterpret_cast<const u32x4 *>(img)[row * PPR + ((4 * c + quad) ^ tile_swz<DT, D>(row))];
+        acc[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf), __builtin_bit_cast(bf16x8, qf[c]), acc[r], 0, 0, 0);
+      }
+    }
+    wave_lds_fence();
+    // ---- values into the image the keys have left
+#pragma unroll
+    for (int j = 0; j < NL; ++j) {
+      const int row = j * RPL + lrow;
+      reinterpret_cast<u32x4 *>(img)[row * PPR + (lq ^ value_swz<D>(row))] = vr[j];
+    }
+    if (t + W < nt) load_tile(vr, Vc, Vt, tb + W * 32);
+    wave_lds_fence();
+
+    float x[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const float a = i < 4 ? acc[0][i & 3] : acc[1][i & 3];
+      x[i] = tb + 16 * (i >> 2) + 4 * quad + (i & 3) < n ? a : -INFINITY;
+    }
+    // ---- weights (see decode_mfma_kernel)
+    float p[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) p[i] = fast_exp2(fmaf(x[i], c2, -m));
+    float lnew = l + (((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7])));
+    if (__builtin_amdgcn_ballot_w64(!(lnew < kSumLimit)) != 0) {
+      float tmax = fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), fmaxf(fmaxf(x[4], x[5]), fmaxf(x[6], x[7])));
+      tmax = fmaxf(tmax, __shfl_xor(tmax, 16));
+      tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
+      const float mn = fmaxf(m, tmax * c2);              // c2 > 0: scaling commutes with max
+      const float mu = (mn == -INFINITY) ? 0.f : mn;
+      const float f = fast_exp2(m - mu);                 // 0 while there is no offset yet
+#pragma unroll
+      for (int i = 0; i < 8; ++i) p[i] = fast_exp2(fmaf(x[i], c2, -mu));
+      lnew = l * f + (((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7])));
+#pragma unroll
+      for (int i = 0; i < NS; ++i) o[i] *= f;
+      m = mn;
+    }
+    l = lnew;
+    bf16x8 ph, pl;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const __bf16 hi = (__bf16)p[j];
+      ph[j] = hi;
+      pl[j] = (__bf16)(p[j] - (float)hi);
+    }
+    // ---- weighted values: block s of 16 elements, rows 4 quad + i and 16 + 4 quad + i
+    const uint32_t r0 = 4 * quad + (l16 >> 2);
+#pragma unroll
+    for (int sl = 0; sl < NS; ++sl) {
+      uint32_t at[2];
+#pragma unroll
+      for (int r = 0; r < 2; ++r)
+        at[r] = img_a + (r0 + 16 * r) * RB + ((2 * sl + ((l16 & 3) >> 1)) ^ value_swz<D>(r0 + 16 * r)) * 16 + (l16 & 1) * 8;
+      const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(uintptr_t)at[0]);
+      const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(uintptr_t)at[1]);
+      const s16x8 vv = __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7);
+      o[sl] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vv), ph, o[sl], 0, 0, 0);
+      o[sl] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vv), pl, o[sl], 0, 0, 0);
+    }
+    wave_lds_fence();
+  }
+
+  // ---- the waves' shares: sums and offsets, and the weighted values in the waves' own images (head g's element d in piece
+  // (d / 4) ^ g of row g)
+  l += __shfl_xor(l, 16);
+  l += __shfl_xor(l, 32);
+  if (quad == 0) { m_s[wave][l16] = m; l_s[wave][l16] = l; }
+  float *o_w = reinterpret_cast<float *>(img);
+#pragma unroll
+  for (int sl = 0; sl < NS; ++sl)
+    *reinterpret_cast<f32x4 *>(o_w + l16 * D + ((4 * sl + quad) ^ l16) * 4) = o[sl];
+  __syncthreads();
+  const float *o_all = reinterpret_cast<const float *>(img_s);
+  for (int idx = tid; idx < ng * D; idx += kDecWaveThreads) {
+    const int g = idx / D, d = idx - g * D, at = g * D + ((d >> 2) ^ g) * 4 + (d & 3);
+    float mn = m_s[0][g];
+#pragma unroll
+    for (int w = 1; w < W; ++w) mn = fmaxf(mn, m_s[w][g]);
+    const float mu = mn == -INFINITY ? 0.f : mn;
+    float acc = 0.f, tot = 0.f;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {                          // waves in order
+      const float f = fast_exp2(m_s[w][g] - mu);
+      acc = fmaf(o_all[w * kDecWaveHeads * D + at], f, acc);
+      tot = fmaf(l_s[w][g], f, tot);
+    }
+    if (s.nsplit > 1) {                                    // partial: weighted values, then (offset, sum)
+      float *dst = part + ((int64_t)blockIdx.x * s.gt + g) * (D + 2);
+      dst[d] = acc;
+      if (d == 0) { dst[D] = mn; dst[D + 1] = tot; }
+      continue;
+    }
+    reinterpret_cast<uint16_t *>(L.out)[(int64_t)(b * s.hq + h * s.G + g) * D + d] = bf16_rne(tot > 0.f ? acc / tot : 0.f);
+  }
+}
+
 // Folds the nsplit <= 16 partial results of one (unit, query-head chunk) in split order and writes the
 // output rows: one thread per output element (blockIdx.y walks the chunk's elements 256 at a time), every
 // split's three values requested before the first is used.
@@ -480,8 +688,12 @@ static void launch_decode_g(const DShape &s, const DecodeTable &t, int nunits, i
 template <int D>
 static void launch_decode_mfma(const DShape &s, const DecodeTable &t, int nunits, float *part, hipStream_t st) {
   const dim3 grid((unsigned)(nunits * s.gchunks * s.nsplit)), block(D * 2);
-  auto kern = decode_reads_once(s.G, MIXKV_BF16) ? decode_mfma_kernel<D, true> : decode_mfma_kernel<D, false>;
-  hipLaunchKernelGGL(kern, grid, block, 0, st, s, t, part);
+  if (s.G <= kDecWaveHeads) {
+    hipLaunchKernelGGL((decode_wave_kernel<D, true>), grid, dim3(kDecWaveThreads), 0, st, s, t, part);
+  } else {
+    auto kern = decode_reads_once(s.G, MIXKV_BF16) ? decode_mfma_kernel<D, true> : decode_mfma_kernel<D, false>;
+    hipLaunchKernelGGL(kern, grid, block, 0, st, s, t, part);
+  }
   if (s.nsplit > 1)
     hipLaunchKernelGGL((decode_merge_kernel<MIXKV_BF16, D>), dim3((unsigned)(nunits * s.gchunks), (unsigned)((s.gt * D + 255) / 256)), dim3(256),
                        0, st, s, t, part);
@@ -491,11 +703,12 @@ constexpr int kDecTargetWgs = 512;   // two resident workgroups on each of 256 c
 
 // Query heads served per workgroup (hpw), their stride in the partials (gt), chunks of query heads
 // per group and row splits per head for a shape.  Host only; depends on nothing but the arguments.
+// *least: the splits whose workspace a caller has to bring at least (a call with room for no more uses them).
 static void decode_config(const Shape &sh, int dtype, int n_layers, int tail_len, int *hpw, int *gt, int *gchunks,
-                          int *nsplit) {
+                          int *nsplit, int *least) {
   const int rows = sh.B + tail_len;                     // per head, on average in the packed layouts
   if (dtype == MIXKV_BF16) {
-    // Matrix-core path.  A workgroup's fixed cost (dependent loads of counts, queries and the first
+    // Matrix-core paths.  decode_mfma_kernel: a workgroup's fixed cost (dependent loads of counts, queries and the first
     // tiles) is a few microseconds, so rows are split only as far as it takes to put two workgroups
     // on every compute unit, and never below 256 rows a piece (short caches: no merge launch).
     *hpw = kDecMfmaHeads;
@@ -505,7 +718,20 @@ static void decode_config(const Shape &sh, int dtype, int n_layers, int tail_len
     int ns = (int)(kDecTargetWgs / (wgs < 1 ? 1 : wgs));
     const int by_rows = rows / 256;
     if (ns > by_rows) ns = by_rows;
-    *nsplit = ns < 1 ? 1 : (ns > kDecMaxSplit ? kDecMaxSplit : ns);
+    *least = *nsplit = ns < 1 ? 1 : (ns > kDecMaxSplit ? kDecMaxSplit : ns);
+    if (sh.G > kDecWaveHeads) return;
+    // decode_wave_kernel: a row takes a workgroup 10 ns by itself (64 elements: 7) and all of them together what 6.5 TB/s allow;
+    // the measured times follow the root of the sum of squares of the two to a few per cent.  Splitting divides the first by the
+    // number of pieces, of at least 128 rows (a tile per wave) and no more than fill the chip twice, and costs the merge, 3.5 us.
+    // us, unsplit -> in 2, 4, 8 pieces, D = 128: 4 heads of 512 rows 8.3 -> 9.0, 8.0; 4 of 2048 24.6 -> 17.5, 12.3, 9.8; 112 of 512 10.5 ->
+    // 11.3, 11.8; 112 of 1024 16.6 -> 16.0, 16.7, 19.2; 112 of 2048 33.1 -> 26.3, 25.5, 27.9; 224 of 1024 21.5 -> 26.1, 28.6, 30.9; 256 of
+    // some 1089 29.5 -> 31.5, 31.8, 35.5; D = 64: 112 of 1024 13.1 -> 12.3, 11.1, 11.6; 224 of 1024 15.6 -> 15.4, 16.5, 18.1.
+    const float own = sh.D == 128 ? 0.010f : 0.007f, shared = (float)wgs * sh.D * 4 / 6.5e6f;
+    auto us = [&](int pieces) { return rows * std::sqrt(own / pieces * (own / pieces) + shared * shared) + (pieces > 1 ? 3.5f : 0.f); };
+    const int most = *least == 1 ? 1 : (int)std::min<int64_t>(std::min(rows / 128, kDecMaxSplit), kDecTargetWgs / wgs);
+    *nsplit = 1;
+    for (int pieces = 2; pieces <= most; ++pieces)
+      if (us(pieces) < us(*nsplit)) *nsplit = pieces;
     return;
   }
   *hpw = kDecHeads;
@@ -513,7 +739,7 @@ static void decode_config(const Shape &sh, int dtype, int n_layers, int tail_len
   while (*gt < sh.G && *gt < kDecHeads) *gt <<= 1;
   *gchunks = (sh.G + kDecHeads - 1) / kDecHeads;
   int ns = (rows + 383) / 384;
-  *nsplit = ns < 1 ? 1 : (ns > kDecMaxSplit ? kDecMaxSplit : ns);
+  *least = *nsplit = ns < 1 ? 1 : (ns > kDecMaxSplit ? kDecMaxSplit : ns);
 }
 static size_t decode_part_bytes(const Shape &sh, int n_layers, int gt, int gchunks, int nsplit) {
   if (nsplit == 1) return 0;
@@ -529,9 +755,9 @@ extern "C" mixkv_status mixkv_decode_workspace_size(const mixkv_params *params, 
   mixkv_status st = make_shape(params, &sh);
   if (st != MIXKV_OK) return st;
   if (!bytes || n_layers < 1 || n_layers > MIXKV_MAX_LAYERS || tail_len < 0) return MIXKV_ERR_INVALID_ARG;
-  int hpw, gt, gchunks, nsplit;
-  decode_config(sh, params->dtype, n_layers, tail_len, &hpw, &gt, &gchunks, &nsplit);
-  *bytes = (decode_part_bytes(sh, n_layers, gt, gchunks, nsplit) + 255) / 256 * 256;
+  int hpw, gt, gchunks, nsplit, least;
+  decode_config(sh, params->dtype, n_layers, tail_len, &hpw, &gt, &gchunks, &nsplit, &least);
+  *bytes = (decode_part_bytes(sh, n_layers, gt, gchunks, std::max(nsplit, least)) + 255) / 256 * 256;
   return MIXKV_OK;
 }
 
@@ -544,13 +770,14 @@ extern "C" mixkv_status mixkv_decode_attention(const mixkv_params *params, const
   if (st != MIXKV_OK) return st;
   if (!layers || n_layers < 1 || n_layers > MIXKV_MAX_LAYERS) return MIXKV_ERR_INVALID_ARG;
   if (tail_len < 0 || tail_capacity < tail_len) return MIXKV_ERR_INVALID_ARG;
-  int hpw, gt, gchunks, nsplit;
-  decode_config(sh, params->dtype, n_layers, tail_len, &hpw, &gt, &gchunks, &nsplit);
-  const size_t need = decode_part_bytes(sh, n_layers, gt, gchunks, nsplit);
+  int hpw, gt, gchunks, nsplit, least;
+  decode_config(sh, params->dtype, n_layers, tail_len, &hpw, &gt, &gchunks, &nsplit, &least);
+  const size_t need = decode_part_bytes(sh, n_layers, gt, gchunks, least);
   if (need > 0) {
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u)) return MIXKV_ERR_INVALID_ARG;
     if (workspace_bytes < need) return MIXKV_ERR_WORKSPACE_TOO_SMALL;
   }
+  if (decode_part_bytes(sh, n_layers, gt, gchunks, nsplit) > workspace_bytes) nsplit = least;
   const bool packed = params->budget_mode != MIXKV_BUDGET_FIXED;
   auto bad16 = [](const void *p) { return !p || (reinterpret_cast<uintptr_t>(p) & 15u); };
   for (int l = 0; l < n_layers; ++l) {

@@ -68,11 +68,6 @@ __device__ __forceinline__ void image_of_rows(uint4 *img, const uint4 (&r)[NL], 
   }
 }
 
-// Lanes of a wave exchange a tile through the wave's image: what they stored before is visible to what they read
-// after, and what they read before is not overtaken by what they store after.  The wave's LDS operations execute in
-// order, so this holds the compiler only and costs no instruction.
-__device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local"); }
-
 // ------------------------------------------------------------------------------------------------
 // First pass (see stats_kernel for what it computes): softmax partials, key norms, the sum of normalised keys, value norms.
 // ------------------------------------------------------------------------------------------------

@@ -140,7 +140,20 @@ __device__ __forceinline__ uint4 load_piece(const void *p) {
   }
 }
 
+// The same as a vector value: arrays of these stay in registers where arrays of HIP's own uint4 may not.
+template <bool ONCE>
+__device__ __forceinline__ u32x4 load_vec(const void *p) {
+  return ONCE ? __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p)) : *reinterpret_cast<const u32x4 *>(p);
+}
+
+// Lanes of a wave exchange a tile through the wave's image: what they stored before is visible to what they read
+// after, and what they read before is not overtaken by what they store after.  The wave's LDS operations execute in
+// order, so this holds the compiler only and costs no instruction.
+__device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local"); }
+
 typedef __attribute__((address_space(3))) void lds_void_t;
+typedef short s16x4 __attribute__((__vector_size__(8)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 typedef __attribute__((address_space(1))) const void glb_void_t;
 
 // 64 lanes x 16 bytes from `src` (per lane) to LDS address `dst` (wave-uniform), directly; ONCE: non-temporal.

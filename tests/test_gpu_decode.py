@@ -206,3 +206,30 @@ def test_append_then_decode_token_by_token(name, over):
                 for g in range(Hq):
                     err = np.abs(got[b, g] - want[g]).max() / np.abs(want[g]).max()
                     assert err <= TOL[wl.dtype], f"step {t} layer {li} b{b} g{g}: error {err:.2e}"
+
+
+# Up to 16 query heads per KV head every wave takes 32-row tiles of its own: rows at and around one tile, one tile per wave
+# and the next round of tiles, tails that begin inside a tile, one to 16 heads, and more heads than that (the other kernel)
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("B,tail_len,G", [(31, 0, 1), (32, 1, 16), (33, 31, 7), (97, 30, 4), (128, 0, 5), (129, 1, 15), (250, 9, 2), (255, 2, 17)])
+def test_bf16_tiles_dealt_to_the_waves(D, B, tail_len, G):
+    wl = WL["c2"].with_(name="wave-dec", head_dim=D, seq_len=400, window=5, n_q_heads=2 * G, n_kv_heads=2, budget=B, batch=1,
+                        text_prefix=16, text_suffix_start=360)
+    _decode_and_check(wl, [0], tail_len, tail_len + 3)
+
+
+def test_bf16_split_on_less_than_the_largest_workspace():
+    """A workspace sized for fewer row ranges than the library would use is used with fewer; the result is the same to
+    the rounding of the merged partials."""
+    wl = WL["c2"]
+    p, caches = H.run_compress(wl, [synth.make_layer(wl, 0)], budget=1024)
+    q = (torch.randn((wl.batch, wl.n_q_heads, wl.head_dim), device="cuda:0") * 0.3).to(torch.bfloat16)
+    G, units = wl.group, wl.batch * wl.n_kv_heads
+    least = units * 4 * G * (wl.head_dim + 2) * 4                # 1024 rows in four ranges
+    assert B.mixkv_decode_workspace_size(p, 1, 0) > least
+    outs = [B.mixkv_decode_attention(p, caches, None, [q], 0, workspace=w)[0].float()
+            for w in ("alloc", torch.empty(least, dtype=torch.uint8, device="cuda:0"))]
+    with pytest.raises(B.MixkvError) as e:
+        B.mixkv_decode_attention(p, caches, None, [q], 0, workspace=torch.empty(least - 4, dtype=torch.uint8, device="cuda:0"))
+    assert e.value.status == B.MIXKV_ERR_WORKSPACE_TOO_SMALL
+    assert (outs[0] - outs[1]).abs().max() <= 2.0 ** -7 * outs[0].abs().max()      # one bf16 rounding either side
