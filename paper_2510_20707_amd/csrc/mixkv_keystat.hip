@@ -10,10 +10,17 @@
 //   * Blocks are walked from a run's last to its first: the first pass read those last, and the caches may still hold them (1 % of a call).
 //   * K_i . Kbar: 16x16x32 matrix instructions on the same key fragments (half the cost of a 32-row tile): a fragment's lanes 0-15 and
 //     16-31 are two groups of keys, told apart by the contraction group, so the mean key's rows are zero for the other group's.
-// Bound: issue, at the clock that the card's power leaves.  448 heads of 32768 keys, 7 query tiles: 1.61 GHz (a copy runs at 2.40); of the
-// SIMDs' clocks the matrix units are busy in 46 %, the vector units in 60 %, one or the other in 90 %; 3.8 GB from memory at 3.4 TB/s.
-// attn_kernel -> this, us, alone on the chip, 7 query tiles and 224 heads of 32768 keys 535 -> 505, 4 tiles and 256 heads of 16384 keys
-// 248 -> 214, 2 tiles and 224 heads of 8192 keys 120 -> 90.
+//   * Keys on the output rows: a lane follows one query row, whose offset is one register (with queries on the rows it took four LDS reads per
+//     query tile, a third of all), and adds up its 32 keys over the tiles; 32 registers of 32 lanes meet once per block.
+//   * The matrix instructions run half a tile ahead of the weights, an eighth (D = 64: a quarter) of them beside each: fma, exp2 and add of a
+//     half tile are issued while the next half's scores are formed.
+//   * Query rows lie a piece apart in LDS, so that a tile's fragments are one address and immediates.
+// 448 heads of 32768 keys, 7 query tiles, us: queries on the rows, matrix and vector work taking turns 993; keys on the rows 973;
+// half a tile ahead 909 (2649 -> 2595 the call: the card holds its power, and the first pass then runs 1 % slower).  28 chunks of
+// 128 keys per compute unit: 8 tiles 88.8 -> 79.4, 7 82.0 -> 78.1, 4 58.7 -> 55.9, 3 54.9 -> 55.2; 64-element heads, 16 tiles 97.5 -> 89.0, 4
+// 40.2 -> 37.9.
+// attn_kernel -> the first of these, us, alone on the chip, 7 query tiles and 224 heads of 32768 keys 535 -> 505, 4 tiles and 256 heads of
+// 16384 keys 248 -> 214, 2 tiles and 224 heads of 8192 keys 120 -> 90.
 // Not better: three waves per SIMD, blocks dealt by a counter (the younger wave of a SIMD ends later, but the time is the same), four key
 // tiles a wave (no registers left for the next).
 #include "mixkv_stream.h"
@@ -29,26 +36,59 @@ __device__ __forceinline__ void image_landed() { asm volatile("s_waitcnt vmcnt(0
 // The image's reads have reached registers: it may be requested anew.
 __device__ __forceinline__ void image_read() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
+// Sum over 32 lanes of each of 32 registers: lane l (of each half of the wave) gets register l's.  Every step adds the two lanes of a pair
+// and keeps half of the registers in either lane.
+__device__ __forceinline__ float sum_over_lanes(float (&v)[32], int lane) {
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[j]), __float_as_uint(v[j + 16]), false, false);
+    v[j] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  }
+  auto step = [&](auto ctrl_c, auto half_c) {
+    constexpr int CTRL = decltype(ctrl_c)::value, H = decltype(half_c)::value;
+    const bool upper = (lane & H) != 0;
+#pragma unroll
+    for (int j = 0; j < H; ++j) {
+      const float a = v[j] + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v[j]), CTRL, 0xf, 0xf, true));
+      const float b = v[j + H] + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v[j + H]), CTRL, 0xf, 0xf, true));
+      v[j] = upper ? b : a;
+    }
+  };
+  step(std::integral_constant<int, 0x140>{}, std::integral_constant<int, 8>{});   // row_mirror
+  step(std::integral_constant<int, 0x141>{}, std::integral_constant<int, 4>{});   // row_half_mirror
+  step(std::integral_constant<int, 0x4E>{}, std::integral_constant<int, 2>{});    // quad_perm [2,3,0,1]
+  step(std::integral_constant<int, 0xB1>{}, std::integral_constant<int, 1>{});    // quad_perm [1,0,3,2]
+  return v[0];
+}
+
 template <int D, int QTMAX, bool ONCE>
 __global__ __launch_bounds__(kKstThreads, 2) void kst_attn_kernel(Shape s, LayerInTable in, char *ws, Workspace w, int64_t unit0,
                                                                   int nunits, int nblk) {
   constexpr int DT = MIXKV_BF16, EB = 2, NCHK = D / 16, PPR = D / 8, TILE = 32 * PPR, BK = 64;
-  __shared__ uint4 q_s[QTMAX * TILE];                  // query tiles, bank-rotated rows
+  constexpr int PITCH = PPR + 1;                       // query rows in LDS, in 16-byte pieces: a piece apart, so that rows meet in no bank
+  __shared__ uint4 q_s[QTMAX * 32 * PITCH];            // window queries
   __shared__ uint4 img_s[kKstWaves * TILE];            // one key tile per wave on its way to registers
   __shared__ float nb_s[QTMAX * 32];                   // exponent offsets -b_r
   __shared__ int lim_s[QTMAX * 32];                    // last key each query row attends to
-  __shared__ uint4 kb_s[NCHK * 4];                     // mean key: bf16 head and remainder
+  __shared__ uint4 kb_s[NCHK * 8];                     // mean key: bf16 head and remainder; then zeros
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int N = s.N, Nc = s.Nc, Npad = s.Npad, QT = s.QT;
   const float c2 = s.scale_log2e;
   const int free_limit = s.causal ? Nc : N - 1;
   const uint4 *img = img_s + wave * TILE;
-  const uint32_t img_a = lds_base_of(img_s) + (uint32_t)wave * (TILE * 16), q_a = lds_base_of(q_s);
+  const uint32_t img_a = lds_base_of(img_s) + (uint32_t)wave * (TILE * 16);
   for (int r = tid; r < QTMAX * 32; r += kKstThreads) lim_s[r] = s.causal ? Nc + r % s.W : N - 1;
+  for (int p = tid; p < NCHK * 4; p += kKstThreads) kb_s[NCHK * 4 + p] = make_uint4(0, 0, 0, 0);
   const int64_t T = (int64_t)nunits * nblk;
   int64_t item = wg_first_item(blockIdx.x, gridDim.x, T);
   const int64_t item_end = wg_first_item(blockIdx.x + 1, gridDim.x, T);
+  // K_i . Kbar: row and contraction group of the 16x16x32 operand; lanes of another row or group read the zeros
+  const int km = lane & 15, kg = lane >> 4;
+  const bool kb_mine = (km >> 2) == (kg & 1) && (km & 2) == 0 && km < 8;
+  const uint4 *kb_row = kb_s + (kb_mine ? (kg >> 1) * 2 + (km & 1) : NCHK * 4);
+  const uint4 *q_row = q_s + l32 * PITCH + half;
+  const int koff = (l32 >> 4) * 32 + 8 * ((l32 >> 2) & 3) + 4 * half + (l32 & 3);   // key of the block whose sum this lane ends with
 
   while (item < item_end) {
     const int ul = (int)(item / nblk), b0 = (int)(item - (int64_t)ul * nblk);
@@ -76,11 +116,24 @@ __global__ __launch_bounds__(kKstThreads, 2) void kst_attn_kernel(Shape s, Layer
     const int b9 = b0 + nb - 1;
     const int row_first = (b9 - min(wave, nb - 1)) * BK;
     lds_barrier();                                     // the previous run is done with LDS
-    request(row_first);
-    for (int q = wave; q < QT; q += kKstWaves)
-      fetch_tile<DT, D, 1, false>(Qb + (int64_t)q * 32 * D * EB, D * EB, q * 32, s.GW, q_a + q * (TILE * 16), 0, lane);
+    // the queries (rows past the last one repeat it: their offsets make their weights 0)
+    constexpr int QL = QTMAX * TILE / kKstThreads;
+    u32x4 qv[QL];
+    int qtid = tid;
+    asm volatile("" : "+v"(qtid));                     // the pieces' addresses are formed here, once per run, and hold no registers elsewhere
+#pragma unroll
+    for (int j = 0; j < QL; ++j) {
+      const int p = j * kKstThreads + qtid;
+      qv[j] = load_vec<false>(Qb + (int64_t)min(p / PPR, s.GW - 1) * (D * EB) + (p % PPR) * 16);
+    }
+#pragma unroll
+    for (int j = 0; j < QL; ++j) {
+      const int p = j * kKstThreads + qtid;
+      *reinterpret_cast<u32x4 *>(q_s + (p / PPR) * PITCH + p % PPR) = qv[j];
+    }
     for (int r = tid; r < QT * 32; r += kKstThreads) nb_s[r] = nbg[r];
     for (int p = tid; p < NCHK * 4; p += kKstThreads) kb_s[p] = kbarp[p];
+    request(row_first);
     image_landed();
     lds_barrier();
     // The results of a block are stored at the start of the wave's next one, in front of its requests: the waits for the
@@ -88,14 +141,26 @@ __global__ __launch_bounds__(kKstThreads, 2) void kst_attn_kernel(Shape s, Layer
     int tbp = Npad;                                    // first key of the block whose results are held (none yet)
     float csp = 0.f, kdp[2];
     auto store = [&] {
-      if (tbp + lane < Nc) araw[tbp + lane] = csp;
+      if (tbp + koff < Nc) araw[tbp + koff] = csp;
       if (half == 0 && tbp + l32 < Nc) kdot[tbp + l32] = kdp[0];
       if (half == 0 && tbp + 32 + l32 < Nc) kdot[tbp + 32 + l32] = kdp[1];
     };
-    Frag kn[NCHK], kf[2][NCHK];
+    Frag kn[NCHK], kf[2][NCHK], qf[NCHK];
     take(kn);
     image_read();
     request(row_first + 32);
+    const int qm = QT / 2;
+    constexpr int EPS = 16 / NCHK;                     // weights beside one matrix instruction
+    f32x16 acc[2];
+    auto q_frag = [&](int q, int c) { return q_row[q * (32 * PITCH) + c * 2]; };
+    // The chain of matrix instructions runs one half tile (32 keys x 32 queries) ahead of the weights.
+#pragma unroll
+    for (int c = 0; c < NCHK; ++c) qf[c].q = q_frag(0, c);
+    float nbq = nb_s[l32], nbn = 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[0][i] = 0.f;
+#pragma unroll
+    for (int c = 0; c < NCHK; ++c) acc[0] = mma<DT>(kn[c], qf[c], acc[0]);
 
     for (int blk = wave; blk < nb; blk += kKstWaves) {
       const int tb = (b9 - blk) * BK;
@@ -110,80 +175,101 @@ __global__ __launch_bounds__(kKstThreads, 2) void kst_attn_kernel(Shape s, Layer
       const bool masked = tb + BK - 1 > free_limit;
 
       // ---- K_i . Kbar: rows 0, 1 (head, remainder) belong to keys 0-15 of a tile, rows 4, 5 to keys 16-31
-      float kd[2];
       {
         f32x4 kacc[2];
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
           for (int i = 0; i < 4; ++i) kacc[t][i] = 0.f;
-        const int m = lane & 15, kg = lane >> 4;         // row and contraction group of the 16x16x32 operand
-        const bool mine = (m >> 2) == (kg & 1) && (m & 2) == 0 && m < 8;
 #pragma unroll
         for (int c = 0; c < NCHK; ++c) {
           Frag a;
-          a.q = kb_s[(c * 2 + (kg >> 1)) * 2 + (m & 1)];
-          if (!mine) a.q = make_uint4(0, 0, 0, 0);
+          a.q = kb_row[c * 4];
 #pragma unroll
           for (int t = 0; t < 2; ++t) kacc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.h, kf[t][c].h, kacc[t], 0, 0, 0);
         }
 #pragma unroll
-        for (int t = 0; t < 2; ++t) kd[t] = kacc[t][0] + kacc[t][1];
+        for (int t = 0; t < 2; ++t) kdp[t] = kacc[t][0] + kacc[t][1];
       }
 
-      // ---- weights of one query tile on both key tiles
-      float cs[2] = {0.f, 0.f};
-      auto tile = [&](int q) {
-        Frag qf[NCHK];
+      float cs[32];
 #pragma unroll
-        for (int c = 0; c < NCHK; ++c) qf[c].q = read_key_frag<DT, D>(q_s, q, c, l32, half);
-        f32x16 acc[2];
+      for (int i = 0; i < 32; ++i) cs[i] = 0.f;
+      // Keys on the output rows: a lane follows one query row and adds up each of its 32 keys over the query tiles.  Weights of the tile on
+      // the first 32 keys, one slice beside each matrix instruction of the second 32; tile qn's fragments follow the old ones.
+      auto first = [&](int qn) {
+        __builtin_amdgcn_sched_barrier(0);
+        nbn = nb_s[qn * 32 + l32];
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
+        for (int c = 0; c < NCHK; ++c) {
+          if (c == 0) {
 #pragma unroll
-          for (int i = 0; i < 16; ++i) acc[t][i] = 0.f;
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-          for (int c = 0; c < NCHK; ++c) acc[t] = mma<DT>(qf[c], kf[t][c], acc[t]);
-        float nbv[16];
-#pragma unroll
-        for (int k4 = 0; k4 < 4; ++k4) {
-          const float4 v = *reinterpret_cast<const float4 *>(nb_s + q * 32 + 8 * k4 + 4 * half);
-          nbv[4 * k4 + 0] = v.x; nbv[4 * k4 + 1] = v.y; nbv[4 * k4 + 2] = v.z; nbv[4 * k4 + 3] = v.w;
-        }
-        if (masked) {
-#pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const int lim = lim_s[q * 32 + 8 * (i >> 2) + 4 * half + (i & 3)];
-#pragma unroll
-            for (int t = 0; t < 2; ++t) acc[t][i] = (tb + t * 32 + l32 <= lim) ? acc[t][i] : -INFINITY;
+            for (int i = 0; i < 16; ++i) acc[1][i] = 0.f;
           }
-        }
+          acc[1] = mma<DT>(kf[1][c], qf[c], acc[1]);
+          qf[c].q = q_frag(qn, c);
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          float c4[4];
-#pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const float wgt = fast_exp2(fmaf(acc[t][i], c2, nbv[i]));
-            c4[i & 3] = i < 4 ? wgt : c4[i & 3] + wgt;
-          }
-          cs[t] += (c4[0] + c4[1]) + (c4[2] + c4[3]);
+          for (int i = c * EPS; i < (c + 1) * EPS; ++i) cs[i] += fast_exp2(fmaf(acc[0][i], c2, nbq));
+          __builtin_amdgcn_sched_barrier(0);
         }
       };
-      const int qm = QT / 2;
-      for (int q = 0; q < qm; ++q) tile(q);
-      image_landed();
-      take(kn);
-      image_read();
-      request(nxt + 32);
-      for (int q = qm; q < QT; ++q) tile(q);
+      // Weights of the second 32 keys beside the next tile's first (of these keys, or the wave's next block).
+      auto second = [&](const Frag (&k)[NCHK]) {
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int t = 0; t < 2; ++t) cs[t] += __shfl_xor(cs[t], 32);
-      // lanes 0..31 hold K_i . Kbar of their tile row l32 (see `mine`); the upper half keeps the second tile's column sums
-      csp = half ? cs[1] : cs[0];
-      kdp[0] = kd[0];
-      kdp[1] = kd[1];
+        for (int c = 0; c < NCHK; ++c) {
+          if (c == 0) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[0][i] = 0.f;
+          }
+          acc[0] = mma<DT>(k[c], qf[c], acc[0]);
+#pragma unroll
+          for (int i = c * EPS; i < (c + 1) * EPS; ++i) cs[16 + i] += fast_exp2(fmaf(acc[1][i], c2, nbq));
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        nbq = nbn;
+      };
+      if (!masked) {
+        for (int q = 0; q < qm; ++q) { first(q + 1); second(kf[0]); }
+        image_landed();
+        take(kn);
+        image_read();
+        request(nxt + 32);
+        for (int q = qm; q < QT - 1; ++q) { first(q + 1); second(kf[0]); }
+        first(0);
+        second(kn);
+      } else {
+        // a block that reaches into the window or past the last key: no overlap, the next block's first scores at the end
+        image_landed();
+        take(kn);
+        image_read();
+        request(nxt + 32);
+        for (int q = 0; q < QT; ++q) {
+          const float nbm = nb_s[q * 32 + l32];
+          const int lim = lim_s[q * 32 + l32] - tb - 4 * half;
+#pragma unroll
+          for (int c = 0; c < NCHK; ++c) qf[c].q = q_frag(q, c);
+#pragma unroll
+          for (int t = 0; t < 2; ++t) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[0][i] = 0.f;
+#pragma unroll
+            for (int c = 0; c < NCHK; ++c) acc[0] = mma<DT>(kf[t][c], qf[c], acc[0]);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+              const float x = (t * 32 + 8 * (i >> 2) + (i & 3) <= lim) ? acc[0][i] : -INFINITY;
+              cs[t * 16 + i] += fast_exp2(fmaf(x, c2, nbm));
+            }
+          }
+        }
+#pragma unroll
+        for (int c = 0; c < NCHK; ++c) qf[c].q = q_frag(0, c);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[0][i] = 0.f;
+#pragma unroll
+        for (int c = 0; c < NCHK; ++c) acc[0] = mma<DT>(kn[c], qf[c], acc[0]);
+      }
+      csp = sum_over_lanes(cs, lane);
       tbp = tb;
     }
     store();
