@@ -142,9 +142,9 @@ typedef struct {
  *     head is ranked by a workgroup of its own and a small kernel splits the pool;
  *   this function's figure: the same for any M, and beyond 32 768 candidates (up
  *     to 524 288), in every mode, a head's row is cut into segments with a
- *     workgroup each, as long as the segments' lists (of up to M entries, or in
+ *     workgroup each, as long as a segment's list (of up to M entries, or in
  *     fixed and per-head mode as many as the largest budget keeps beside the
- *     window) have at most 28 672 entries per head.
+ *     window) has at most 16 384 entries, or all of a head's together 32 768.
  * In all other cases one workgroup ranks the whole rows of a head (fixed and
  * per-head mode) or of all heads of a batch item (head-adaptive mode), several
  * to some tens of times slower on long rows.

@@ -251,10 +251,11 @@ static mixkv_status run(const mixkv_params *params, const mixkv_layer_in *in, mi
   // kernels that rank whole rows: rows or budgets too long for the lists, or no workspace to hold them).
   const bool do_select = (stages & kSelect) != 0, short_row = mixsel_supported(s);
   const int best = do_select && s.adaptive ? adaptive_candidates(s) : 0;
-  const CandLists lists = rows_fit ? CandLists{w_full.araw, w_full.vnorm, s.Npad} : CandLists{w.cand_idx, w.cand_key, kMaxCandPerHead};
   const bool lists_hold = rows_fit || (lists_fit && best <= kMaxCandPerHead);
-  const SegPlan cut_sel = (!short_row && rows_fit && do_select) ? plan_segments(s, s.adaptive ? best : max_head_rows - s.W) : SegPlan{0, 0, 0};
-  const SegPlan cut_mix = cut_sel.seg > 0 ? cut_sel : ((!short_row && (stages & kScore)) ? plan_segments(s, 0) : SegPlan{0, 0, 0});
+  const int keep = s.adaptive ? best : max_head_rows - s.W;      // the longest list a segment hands on
+  const SegPlan cut_sel = (!short_row && rows_fit && do_select) ? plan_segments(s, keep) : SegPlan{0, 0, 0, 0};
+  const SegPlan cut_mix = cut_sel.seg > 0 ? cut_sel : ((!short_row && (stages & kScore)) ? plan_segments(s, 0) : SegPlan{0, 0, 0, 0});
+  const CandLists lists = rows_fit ? merged_lists(cut_sel, s, w_full) : CandLists{w.cand_idx, w.cand_key, kMaxCandPerHead};
   const int cand_m = lists_hold && (short_row || cut_sel.seg > 0) ? best : 0;
   const bool long_select = cut_sel.seg > 0 && (!s.adaptive || cand_m > 0);
   const bool fused = (stages & kScore) && short_row;
@@ -329,7 +330,7 @@ static mixkv_status run(const mixkv_params *params, const mixkv_layer_in *in, mi
           const hipError_t e = launch_segtop(s, cut_sel, to, ws, w_full, unit0, nunits, cand_m, budgets_l0, stream);
           if (e != hipSuccess) return e;
         }
-        const hipError_t e = launch_mergetop(s, cut_sel, to, ws, w_full, lists, unit0, nunits, cand_m, budgets_l0, stream);
+        const hipError_t e = launch_mergetop(s, cut_sel, keep, to, ws, w_full, lists, unit0, nunits, cand_m, budgets_l0, stream);
         return e != hipSuccess || cand_m == 0 ? e : launch_select_candidates(s, to, ws, lists, unit0, nl, cand_m, stream);
       }));
     else if (result == MIXKV_OK && do_select && cand_m > 0)

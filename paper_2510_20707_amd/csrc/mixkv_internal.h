@@ -96,8 +96,9 @@ struct CandLists {
 constexpr uint32_t kFloorFlag = 0x80000000u;
 
 // How a long row is cut over several workgroups: nseg segments of seg candidates, whose lists have `merge` entries
-// together (seg 0: the row cannot be cut).
-struct SegPlan { int seg, nseg, merge; };
+// together (seg 0: the row cannot be cut); with `rounds` > 0 lists are merged in groups that many times first, and the
+// last merge has up to `merge` entries.
+struct SegPlan { int seg, nseg, merge, rounds; };
 
 mixkv_status make_shape(const mixkv_params *p, Shape *s);
 void carve_workspace(const Shape &s, int64_t units, Workspace *w, bool select_only = false);
@@ -162,12 +163,13 @@ hipError_t launch_split_stream(const Shape &s, const LayerOutTable &out, char *w
 // Long rows (mixkv_longrow.hip): the cut for up to `keep` kept candidates per head, the mix (and with `select` the
 // segments' lists), the lists from scores in memory, and their merge.
 SegPlan plan_segments(const Shape &s, int keep);
+CandLists merged_lists(const SegPlan &pl, const Shape &s, const Workspace &w);   // where the heads' lists are after the merge
 hipError_t launch_segmix(const Shape &s, const SegPlan &pl, bool select, const LayerInTable &in, const LayerOutTable &out, char *ws,
                          const Workspace &w, int64_t unit0, int nunits, int cand_m, const int32_t *budgets, hipStream_t st);
 hipError_t launch_segtop(const Shape &s, const SegPlan &pl, const LayerOutTable &out, char *ws, const Workspace &w, int64_t unit0,
                          int nunits, int cand_m, const int32_t *budgets, hipStream_t st);
-hipError_t launch_mergetop(const Shape &s, const SegPlan &pl, const LayerOutTable &out, char *ws, const Workspace &w, const CandLists &cl,
-                           int64_t unit0, int nunits, int cand_m, const int32_t *budgets, hipStream_t st);
+hipError_t launch_mergetop(const Shape &s, const SegPlan &pl, int keep, const LayerOutTable &out, char *ws, const Workspace &w,
+                           const CandLists &cl, int64_t unit0, int nunits, int cand_m, const int32_t *budgets, hipStream_t st);
 hipError_t launch_gather(const Shape &s, int dtype, const LayerInTable &in, const LayerOutTable &out, int nlayers,
                          hipStream_t st);
 

@@ -5,7 +5,8 @@
 //   segmix_kernel    folds the shares, forms the segment's mixed scores and, if a selection follows, hands the
 //                    segment's best `keep` candidates on as a list (ascending positions, with their order keys);
 //   segtop_kernel    the same lists from scores that are already in memory (mixkv_select);
-//   mergetop_kernel  one workgroup per head selects from the head's lists laid end to end.
+//   mergetop_kernel  one workgroup per head selects from the head's lists laid end to end; lists too long for one
+//                    workgroup are merged in groups first, each group's best `keep` being the next round's list.
 // A head that keeps `keep` candidates keeps none that is not among the `keep` best of its own segment, and the
 // lists hold equal scores in ascending position, so the result is the one a ranking of the whole row gives.
 //
@@ -18,13 +19,15 @@
 //
 // Paper: Sec. 3.2 Eq. 2, Sec. 3.3 Eq. 5, Sec. 3.1 / Algorithm 1 (TopB), as in mixsel_kernel.
 #include <cfloat>
+#include <type_traits>
+#include <utility>
 
 #include "mixkv_topsel.h"
 
 namespace mixkv {
 
 constexpr int kHalo = 32;                // candidates on either side of a segment that the pooling window may reach
-constexpr int kMaxMerge = 1024 * 28;     // list entries mergetop_kernel can hold (LDS)
+constexpr int kMaxMerge = 1024 * 32;     // list entries mergetop_kernel can hold (registers and LDS)
 
 // Shares of a head's statistics, one per segment (in the rows that held the softmax offsets: the second pass was
 // their last reader).  Sums of intrinsic score and diversity are taken above the share's own minimum: every term is
@@ -331,20 +334,23 @@ __global__ __launch_bounds__(THREADS) void segtop_kernel(Shape s, LayerOutTable 
 }
 
 // One workgroup per head: its rows (fixed and per-head mode) or its candidates for the head-adaptive split, out
-// of its segments' lists.  `seg` is the segment length the lists were made with.
-template <int THREADS, int EPT>
-__global__ __launch_bounds__(THREADS) void mergetop_kernel(Shape s, LayerOutTable out, char *ws, Workspace w, CandLists cl,
-                                                           int64_t unit0, int seg, int nseg, int cand_m, const int32_t *budgets) {
+// of its lists: nseg of them in `from`, each with the best of `seg` candidates.  PART: one workgroup per `group`
+// lists, which leaves the best of them as one list in `to`, at the group's first candidate.
+template <int THREADS, int EPT, bool PART>
+__global__ __launch_bounds__(THREADS) void mergetop_kernel(Shape s, LayerOutTable out, char *ws, CandLists from, CandLists to,
+                                                           int64_t unit0, int seg, int nseg, int group, int cand_m, const int32_t *budgets) {
   extern __shared__ __align__(16) uint32_t k_s[];
   __shared__ MsScratch sc;
-  const int ul = blockIdx.x, tid = threadIdx.x;
+  const int ngroups = PART ? (nseg + group - 1) / group : 1;
+  const int ul = PART ? blockIdx.x / ngroups : blockIdx.x, first = PART ? (blockIdx.x - ul * ngroups) * group : 0, tid = threadIdx.x;
   const int64_t unit = unit0 + ul;
   const int layer = ul / s.units_per_layer, bh = ul - layer * s.units_per_layer, h = bh % s.hkv, b = bh / s.hkv;
   const LayerOut O = out.l[layer];
-  const int32_t *lidx = reinterpret_cast<const int32_t *>(ws + w.sdiv) + unit * s.Npad;
-  const uint32_t *lkey = reinterpret_cast<const uint32_t *>(ws + w.invnorm) + unit * s.Npad;
-  const int keep = head_keep(s, budgets, layer, h, cand_m), per = min(keep, seg);   // entries per list, the last one's may be fewer
-  const int n = per > 0 ? (nseg - 1) * per + min(per, s.Nc - (nseg - 1) * seg) : 0;
+  const int32_t *lidx = reinterpret_cast<const int32_t *>(ws + from.idx) + unit * from.stride + first * seg;
+  const uint32_t *lkey = reinterpret_cast<const uint32_t *>(ws + from.key) + unit * from.stride + first * seg;
+  const int keep = head_keep(s, budgets, layer, h, cand_m), per = min(keep, seg);   // entries per list, the row's last one may have fewer
+  const int lists = PART ? min(group, nseg - first) : nseg;
+  const int n = per > 0 ? (lists - 1) * per + min(per, s.Nc - (first + lists - 1) * seg) : 0;
   auto at = [&](int e) { const int g = e / per; return g * seg + (e - g * per); };
   const int base = tid * EPT;
   uint32_t key[EPT], largest = 0;
@@ -361,9 +367,11 @@ __global__ __launch_bounds__(THREADS) void mergetop_kernel(Shape s, LayerOutTabl
   __syncthreads();
   read_keys<EPT>(k_s, base, n, key);
   auto pos = [&](int e) { return lidx[at(base + e)]; };
-  if (cand_m > 0) {
-    top_select_keys<THREADS, EPT>(key, cand_m, reinterpret_cast<int32_t *>(ws + cl.idx) + unit * cl.stride,
-                                  reinterpret_cast<uint32_t *>(ws + cl.key) + unit * cl.stride, s.floor_, sc, pos);
+  if (PART || cand_m > 0) {
+    int32_t *idx = reinterpret_cast<int32_t *>(ws + to.idx) + unit * to.stride + first * seg;
+    uint32_t *ckey = reinterpret_cast<uint32_t *>(ws + to.key) + unit * to.stride + first * seg;
+    if (!PART) top_select_keys<THREADS, EPT>(key, cand_m, idx, ckey, s.floor_, sc, pos);
+    else if (n > 0) top_select_keys<THREADS, EPT>(key, min(keep, n), idx, ckey, 0, sc, pos);
     return;
   }
   int Bh, row0;
@@ -376,21 +384,50 @@ __global__ __launch_bounds__(THREADS) void mergetop_kernel(Shape s, LayerOutTabl
 // ------------------------------------------------------------------------------------------------
 // launchers
 // ------------------------------------------------------------------------------------------------
+// Entries of the lists of up to `keep` candidates that nseg segments of `seg` candidates leave of a row.
+static int64_t list_entries(const Shape &s, int keep, int64_t seg, int nseg) {
+  const int64_t per = keep < seg ? keep : seg, last = s.Nc - (nseg - 1) * seg;
+  return (nseg - 1) * per + (per < last ? per : last);
+}
+
+// Lists per workgroup of a round that leaves fewer lists, as even as they come: `keep` <= kMaxMerge / 2 entries each.
+static int round_group(int keep, int nseg) {
+  const int most = kMaxMerge / keep, groups = (nseg + most - 1) / most;
+  return (nseg + groups - 1) / groups;
+}
+
 // The cut of a row of Nc candidates of which up to `keep` survive per head (0: no selection): the smallest
 // segments that give at most kMaxSegs of them, as long as the merge has no more than 16 384 entries to look at
-// (beyond that its one workgroup per head is the longer half); failing that the largest that fit it.
+// (beyond that its one workgroup per head is the longer half); failing that the largest that fit it.  Longer lists, of up
+// to half of what a workgroup holds, are merged in rounds.  Beyond that one workgroup ranks whole rows
+// (select_adaptive_kernel: all heads' rows of a batch item), which took these, too: selection alone, head-adaptive, us before ->
+// after: 130 688 tokens, 4 heads, budget 1200 1856 -> 86, 28 layers of them 2399 -> 146, budget 960 (one merge of 29 696 entries) 2396 -> 100;
+// 8 heads, budget 600 3671 -> 174; 14 layers of 131 072 tokens, 8 heads, budget 2048 4603 -> 884; 60 000 tokens, 8 heads, budget 2048
+// 1691 -> 376.
 SegPlan plan_segments(const Shape &s, int keep) {
-  SegPlan best{0, 0, 0};
+  SegPlan best{0, 0, 0, 0};
   for (int seg : {4096, 8192, 16384}) {
     const int nseg = (s.Nc + seg - 1) / seg;
     if (nseg < 2 || nseg > kMaxSegs) continue;
-    const int per = keep < seg ? keep : seg, last = s.Nc - (nseg - 1) * seg;
-    const int64_t n = (int64_t)(nseg - 1) * per + (per < last ? per : last);
+    const int64_t n = list_entries(s, keep, seg, nseg);
     if (n > kMaxMerge) continue;
-    best = SegPlan{seg, nseg, (int)n};
+    best = SegPlan{seg, nseg, (int)n, 0};
     if (n <= 16384) break;
   }
+  const int seg = 16384, nseg = (s.Nc + seg - 1) / seg;
+  if (best.seg == 0 && keep <= seg && nseg >= 2 && nseg <= kMaxSegs) {
+    best = SegPlan{seg, nseg, kMaxMerge, 0};
+    for (int64_t len = seg, left = nseg; list_entries(s, keep, len, (int)left) > kMaxMerge; ++best.rounds) {
+      const int group = round_group(keep, (int)left);
+      left = (left + group - 1) / group;
+      len *= group;
+    }
+  }
   return best;
+}
+
+CandLists merged_lists(const SegPlan &pl, const Shape &s, const Workspace &w) {
+  return pl.rounds % 2 ? CandLists{w.sdiv, w.invnorm, s.Npad} : CandLists{w.araw, w.vnorm, s.Npad};
 }
 
 template <int THREADS, int EPT>
@@ -420,24 +457,40 @@ hipError_t launch_segtop(const Shape &s, const SegPlan &pl, const LayerOutTable 
   return hipGetLastError();
 }
 
-template <int THREADS, int EPT>
-static hipError_t launch_mergetop_e(const Shape &s, const SegPlan &pl, const LayerOutTable &out, char *ws, const Workspace &w,
-                                    const CandLists &cl, int64_t unit0, int nunits, int cand_m, const int32_t *budgets, hipStream_t st) {
-  auto kern = mergetop_kernel<THREADS, EPT>;
+// Rounds of merges, the lists going to and fro between the two pairs of rows, and the last merge.
+template <int THREADS, int EPT, bool PART>
+static hipError_t launch_mergetop_e(const Shape &s, int entries, const LayerOutTable &out, char *ws, const CandLists &from, const CandLists &to,
+                                    int64_t unit0, int nunits, int seg, int nseg, int group, int cand_m, const int32_t *budgets, hipStream_t st) {
+  auto kern = mergetop_kernel<THREADS, EPT, PART>;
   static LdsLimitOnce once;
   const hipError_t attr = once.raise(reinterpret_cast<const void *>(kern));
   if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL(kern, dim3(nunits), dim3(THREADS), (size_t)slots4(pl.merge) * 4, st, s, out, ws, w,
-                     cl, unit0, pl.seg, pl.nseg, cand_m, budgets);
+  hipLaunchKernelGGL(kern, dim3(nunits * (PART ? (nseg + group - 1) / group : 1)), dim3(THREADS), (size_t)slots4(entries) * 4, st, s, out, ws,
+                     from, to, unit0, seg, nseg, group, cand_m, budgets);
   return hipGetLastError();
 }
 
-hipError_t launch_mergetop(const Shape &s, const SegPlan &pl, const LayerOutTable &out, char *ws, const Workspace &w, const CandLists &cl,
-                           int64_t unit0, int nunits, int cand_m, const int32_t *budgets, hipStream_t st) {
-  if (pl.merge <= 512 * 8) return launch_mergetop_e<512, 8>(s, pl, out, ws, w, cl, unit0, nunits, cand_m, budgets, st);
-  if (pl.merge <= 1024 * 8) return launch_mergetop_e<1024, 8>(s, pl, out, ws, w, cl, unit0, nunits, cand_m, budgets, st);
-  if (pl.merge <= 1024 * 16) return launch_mergetop_e<1024, 16>(s, pl, out, ws, w, cl, unit0, nunits, cand_m, budgets, st);
-  return launch_mergetop_e<1024, 32>(s, pl, out, ws, w, cl, unit0, nunits, cand_m, budgets, st);
+hipError_t launch_mergetop(const Shape &s, const SegPlan &pl, int keep, const LayerOutTable &out, char *ws, const Workspace &w,
+                           const CandLists &cl, int64_t unit0, int nunits, int cand_m, const int32_t *budgets, hipStream_t st) {
+  CandLists from{w.sdiv, w.invnorm, s.Npad}, to{w.araw, w.vnorm, s.Npad};
+  int seg = pl.seg, nseg = pl.nseg;
+  for (int r = 0; r < pl.rounds; ++r) {
+    const int group = round_group(keep, nseg);
+    const hipError_t e = launch_mergetop_e<1024, 32, true>(s, group * keep, out, ws, from, to, unit0, nunits, seg, nseg, group, cand_m, budgets, st);
+    if (e != hipSuccess) return e;
+    nseg = (nseg + group - 1) / group;
+    seg *= group;
+    std::swap(from, to);
+  }
+  auto merge = [&](auto threads, auto ept) {
+    return launch_mergetop_e<decltype(threads)::value, decltype(ept)::value, false>(s, pl.merge, out, ws, from, cl, unit0, nunits, seg, nseg, nseg,
+                                                                                    cand_m, budgets, st);
+  };
+  using std::integral_constant;
+  if (pl.merge <= 512 * 8) return merge(integral_constant<int, 512>{}, integral_constant<int, 8>{});
+  if (pl.merge <= 1024 * 8) return merge(integral_constant<int, 1024>{}, integral_constant<int, 8>{});
+  if (pl.merge <= 1024 * 16) return merge(integral_constant<int, 1024>{}, integral_constant<int, 16>{});
+  return merge(integral_constant<int, 1024>{}, integral_constant<int, 32>{});
 }
 
 }  // namespace mixkv

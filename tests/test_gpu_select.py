@@ -218,3 +218,15 @@ def test_selection_on_a_full_workspace_is_bit_exact(kind, mode, N, W, Bud, Hkv, 
         for h in range(Hkv):
             want = O.select_unit(s[b, h, :N - W].astype(np.float64), int(bp[h]), N, W)
             np.testing.assert_array_equal(idx[b, off[b, h]:off[b, h + 1]], want)
+
+
+# Lists that one workgroup cannot merge go through rounds of partial merges: one to four rounds, groups and segments that do
+# not divide evenly, a last segment of one candidate, heads that keep nothing beside the window, the longest list a round
+# takes and the most entries that one merge takes.
+@pytest.mark.parametrize("kind", ["normal", "ties", "constant"])
+@pytest.mark.parametrize("mode,N,W,Bud,Hkv,floor", [
+    ("adaptive", 130688, 32, 1200, 4, 16), ("adaptive", 131072, 8, 2048, 8, 0), ("adaptive", 130688, 32, 960, 4, 0),
+    ("fixed", 3 * 16384 + 1 + 32, 32, 16384 + 32, 1, 0), ("fixed", 300007, 32, 9000, 1, 0), ("fixed", 524288 + 32, 32, 16416, 1, 0),
+    ("per_head", 90001, 32, 6000, 3, 0)])
+def test_long_lists_merged_in_rounds_are_bit_exact(kind, mode, N, W, Bud, Hkv, floor):
+    test_selection_on_a_full_workspace_is_bit_exact(kind, mode, N, W, Bud, Hkv, floor)
