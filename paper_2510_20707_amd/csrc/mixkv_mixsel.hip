@@ -320,7 +320,8 @@ __global__ __launch_bounds__(THREADS) void topsel_kernel(Shape s, LayerOutTable 
 // candidate that can be kept and the result is the same as ranking all scores.  Thread t owns EPT
 // consecutive entries of the H lists laid end to end, each rounded up to whole threads: that order is the tie order,
 // the kept entries of a head come out in ascending position from one prefix sum, and a thread's entries are one
-// aligned run of one list.
+// aligned run of one list.  Up to 32 entries per thread stay in registers with their positions; of 64 the keys alone, the
+// positions of kept entries being read again.
 template <int THREADS, int EPT>
 __global__ __launch_bounds__(THREADS) void candsplit_kernel(Shape s, LayerOutTable out, char *ws, CandLists cl, int64_t unit0,
                                                               int M) {
@@ -338,21 +339,32 @@ __global__ __launch_bounds__(THREADS) void candsplit_kernel(Shape s, LayerOutTab
   const int64_t at = (unit + min(h, H - 1)) * cl.stride + i0;
   const uint4 *krun = reinterpret_cast<const uint4 *>(reinterpret_cast<const uint32_t *>(ws + cl.key) + at);
   const uint4 *prun = reinterpret_cast<const uint4 *>(reinterpret_cast<const uint32_t *>(ws + cl.idx) + at);
-  uint32_t key[EPT], pw[EPT];
-#pragma unroll
-  for (int g = 0; g < EPT / 4; ++g) {
-    const uint4 kq = krun[g], pq = prun[g];
-    key[4 * g] = kq.x; key[4 * g + 1] = kq.y; key[4 * g + 2] = kq.z; key[4 * g + 3] = kq.w;
-    pw[4 * g] = pq.x; pw[4 * g + 1] = pq.y; pw[4 * g + 2] = pq.z; pw[4 * g + 3] = pq.w;
-  }
+  constexpr bool HOLD = EPT <= 32;
+  constexpr int STEP = HOLD ? EPT : 16;                 // entries loaded together
+  uint32_t key[EPT], pw[HOLD ? EPT : 1];
   // the search sees the entries outside the floors (key 0: not this one)
-  uint32_t floors = 0, largest = 0;                     // entries that are kept as they are
+  uint32_t floors[EPT / STEP], largest = 0;             // entries that are kept as they are
 #pragma unroll
-  for (int j = 0; j < EPT; ++j) {
-    const bool flag = (pw[j] & kFloorFlag) != 0;
-    floors |= j < left && flag ? 1u << j : 0u;
-    key[j] = j < left && !flag && rest > 0 ? key[j] : 0u;
-    largest = max(largest, key[j]);
+  for (int j0 = 0; j0 < EPT; j0 += STEP) {
+    uint32_t p[STEP];
+#pragma unroll
+    for (int g = 0; g < STEP / 4; ++g) {
+      // behind a list that ends earlier its last group of four again, which is inside the workspace
+      const int gi = HOLD ? g : min(j0 / 4 + g, max(left - 1, 0) / 4);
+      const uint4 kq = krun[gi], pq = prun[gi];
+      key[j0 + 4 * g] = kq.x; key[j0 + 4 * g + 1] = kq.y; key[j0 + 4 * g + 2] = kq.z; key[j0 + 4 * g + 3] = kq.w;
+      p[4 * g] = pq.x; p[4 * g + 1] = pq.y; p[4 * g + 2] = pq.z; p[4 * g + 3] = pq.w;
+    }
+    floors[j0 / STEP] = 0;
+#pragma unroll
+    for (int j = 0; j < STEP; ++j) {
+      const bool flag = (p[j] & kFloorFlag) != 0;
+      floors[j0 / STEP] |= j0 + j < left && flag ? 1u << j : 0u;
+      key[j0 + j] = j0 + j < left && !flag && rest > 0 ? key[j0 + j] : 0u;
+      largest = max(largest, key[j0 + j]);
+      if constexpr (HOLD) pw[j] = p[j];
+    }
+    if constexpr (!HOLD) __builtin_amdgcn_sched_barrier(0);
   }
   thresholds_begin<THREADS>(largest, sc);
   __syncthreads();
@@ -361,7 +373,9 @@ __global__ __launch_bounds__(THREADS) void candsplit_kernel(Shape s, LayerOutTab
   int k[1] = {0};
   if (rest > 0) radix_thresholds<THREADS, EPT, 1>(key, want, sc, tau, k);
   // kept for sure (low half) and equal to the threshold (high half) share a word
-  int packed = __popc(floors), total;
+  int packed = 0, total;
+#pragma unroll
+  for (int j = 0; j < EPT / STEP; ++j) packed += __popc(floors[j]);
 #pragma unroll
   for (int j = 0; j < EPT; ++j) packed += key[j] > tau[0] ? 1 : 0;
   if (k[0] > 0) {
@@ -376,9 +390,9 @@ __global__ __launch_bounds__(THREADS) void candsplit_kernel(Shape s, LayerOutTab
   pos += h * s.W;
 #pragma unroll
   for (int j = 0; j < EPT; ++j) {
-    bool keep = ((floors >> j) & 1u) != 0 || key[j] > tau[0];
+    bool keep = ((floors[j / STEP] >> (j % STEP)) & 1u) != 0 || key[j] > tau[0];
     if (k[0] > 0 && key[j] == tau[0]) keep = seen++ < k[0];
-    if (keep) idx[pos++] = (int32_t)(pw[j] & ~kFloorFlag);
+    if (keep) idx[pos++] = (int32_t)((HOLD ? pw[HOLD ? j : 0] : reinterpret_cast<const uint32_t *>(prun)[j]) & ~kFloorFlag);
   }
   if (tid == 0) hstart[H] = kept;
   __syncthreads();
@@ -467,9 +481,10 @@ hipError_t launch_topsel(const Shape &s, const LayerOutTable &out, char *ws, con
 }
 
 // The head-adaptive split of `nlayers` layers' candidate lists of M entries per head: one workgroup per (layer, batch
-// item) with all entries in registers, or, past 32 of them per thread, streamed from memory.  As many threads as there
+// item) with all entries in registers, or, past 64 of them per thread, streamed from memory.  As many threads as there
 // are groups of four entries, up to 1024: a wave's instructions are what takes the time (4 lists of 1536 entries: 1024 threads
-// of 8 7.4 us, 512 of 16 8.6; with lists that shared a thread and branches on every entry 13.2).
+// of 8 7.4 us, 512 of 16 8.6; with lists that shared a thread and branches on every entry 13.2).  64 of them against the stream, the
+// selection's whole call: 8 lists of 5344 entries 126 -> 58 us, of 7744 161 -> 68, 28 layers of those 176 -> 88.
 template <int THREADS, int EPT>
 static hipError_t launch_candsplit_e(const Shape &s, const LayerOutTable &out, char *ws, const CandLists &cl, int64_t unit0,
                                      int grid, int cand_m, hipStream_t st) {
@@ -486,6 +501,8 @@ hipError_t launch_select_candidates(const Shape &s, const LayerOutTable &out, ch
   if (fits(1024, 8)) return launch_candsplit_e<1024, 8>(s, out, ws, cl, unit0, grid, cand_m, st);
   if (fits(1024, 16)) return launch_candsplit_e<1024, 16>(s, out, ws, cl, unit0, grid, cand_m, st);
   if (fits(1024, 32)) return launch_candsplit_e<1024, 32>(s, out, ws, cl, unit0, grid, cand_m, st);
+  // (kept entries and entries equal to the threshold are counted in 16 bits each)
+  if (fits(1024, 64) && (int64_t)cand_m * s.hkv < 1 << 16) return launch_candsplit_e<1024, 64>(s, out, ws, cl, unit0, grid, cand_m, st);
   return launch_split_stream(s, out, ws, cl, unit0, nlayers, cand_m, st);
 }
 

@@ -230,3 +230,12 @@ def test_selection_on_a_full_workspace_is_bit_exact(kind, mode, N, W, Bud, Hkv, 
     ("per_head", 90001, 32, 6000, 3, 0)])
 def test_long_lists_merged_in_rounds_are_bit_exact(kind, mode, N, W, Bud, Hkv, floor):
     test_selection_on_a_full_workspace_is_bit_exact(kind, mode, N, W, Bud, Hkv, floor)
+
+
+# Head-adaptive pools of more than 32 and up to 64 entries per thread of the split's one workgroup: lists that end inside a thread's run, the most
+# entries that its 16-bit counts admit, one past them, and floors that take everything.
+@pytest.mark.parametrize("kind", ["normal", "ties", "constant"])
+@pytest.mark.parametrize("N,W,Bud,Hkv,floor", [(9001, 32, 650, 8, 3), (20000, 8, 2631, 5, 2), (20000, 8, 2632, 5, 3), (20000, 32, 12032, 4, 12000),
+                                               (4100, 4, 600, 9, 17)])
+def test_split_of_long_pools_is_bit_exact(kind, N, W, Bud, Hkv, floor):
+    test_selection_on_a_full_workspace_is_bit_exact(kind, "adaptive", N, W, Bud, Hkv, floor)
