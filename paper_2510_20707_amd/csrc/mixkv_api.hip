@@ -236,10 +236,11 @@ static mixkv_status run(const mixkv_params *params, const mixkv_layer_in *in, mi
   char *ws = reinterpret_cast<char *>(workspace);
   int num_cus = 0;
   if ((stages & kScore) && (num_cus = compute_units()) < 1) return MIXKV_ERR_HIP;
-  const int32_t *budgets_dev = nullptr;
+  int32_t *budgets_dev = nullptr;
+  const bool fold_budgets = stage_budgets && (stages & kScore) && (n_layers < kLayersPerLaunch ? n_layers : kLayersPerLaunch) * s.hkv <= kFoldBudgets;
   if (stage_budgets) {
     int32_t *dst = reinterpret_cast<int32_t *>(ws + w.budgets);
-    if (upload_ints(params->head_budgets, n_layers * s.hkv, dst, stream) != hipSuccess) return MIXKV_ERR_HIP;
+    if (!fold_budgets && upload_ints(params->head_budgets, n_layers * s.hkv, dst, stream) != hipSuccess) return MIXKV_ERR_HIP;
     budgets_dev = dst;
   }
   // How the rows are mixed and selected.
@@ -297,6 +298,13 @@ static mixkv_status run(const mixkv_params *params, const mixkv_layer_in *in, mi
       const bool given_lse = in[0].window_lse != nullptr, keysplit = keysplit_supported(s, params->dtype);
       const int grid = stream_grid(s, nunits, num_cus), ks_grid = keysplit_grid(s, params->dtype, nunits, num_cus);
       const bool ks_stats = keysplit && !given_lse;
+      BudgetRows rows;
+      if (fold_budgets) {
+        std::memset(&rows, 0, sizeof(rows));
+        rows.dst = budgets_dev + (size_t)l0 * s.hkv;
+        rows.n = nl * s.hkv;
+        std::memcpy(rows.v, params->head_budgets + (size_t)l0 * s.hkv, (size_t)rows.n * sizeof(int32_t));
+      }
       int64_t max_stride_n = 0;
       for (int l = 0; l < nl; ++l) max_stride_n = in[l0 + l].kv_stride_n > max_stride_n ? in[l0 + l].kv_stride_n : max_stride_n;
       const bool q_stats = !keysplit && !given_lse && qstats_supported(s, params->dtype, nunits, num_cus, max_stride_n);
@@ -307,7 +315,7 @@ static mixkv_status run(const mixkv_params *params, const mixkv_layer_in *in, mi
                         : launch_stats(s, params->dtype, ti, ws, w, unit0, nunits, grid, slot0, given_lse, stream);
       })) &&
           ok(timed(1, [&] {
-            hipError_t e = launch_fold(s, params->dtype, to, tl, ws, w, unit0, nunits, stats_grid, s.nchunks, slot0, stream);
+            hipError_t e = launch_fold(s, params->dtype, to, tl, ws, w, unit0, nunits, stats_grid, s.nchunks, slot0, fold_budgets ? &rows : nullptr, stream);
             if (e != hipSuccess) return e;
             if (!keysplit && keystat_supported(s, params->dtype, nunits, num_cus))
               return launch_kst_attn(s, ti, ws, w, unit0, nunits, num_cus, stream);

@@ -112,10 +112,16 @@ int stream_grid(const Shape &s, int nunits, int num_cus);
 // statistics only; `lse` then holds them per layer (all null otherwise).
 hipError_t launch_stats(const Shape &s, int dtype, const LayerInTable &in, char *ws, const Workspace &w, int64_t unit0,
                         int nunits, int grid, int64_t slot0, bool given_lse, hipStream_t st);
+// A launch's rows of the budget table (per-head mode), which fold_kernel writes to the workspace: its other arguments leave room for 256
+// entries in 4 KB (28 layers of 4 heads, 32 of 8).  More of them, and calls without the scoring passes, go through upload_ints, a
+// launch of its own.  Calls with that launch -> without: one layer of 4096 tokens 40.8 -> 38.1 us, 28 of 512 48.8 -> 47.4, 8 of 2000
+// tokens and 8 heads 54.0 -> 52.8.
+constexpr int kFoldBudgets = 256;
+struct BudgetRows { int32_t *dst; int32_t n; int32_t v[kFoldBudgets]; };
 // Folds the first pass's per-run partials per unit (exponent offsets, mean key, redundancy).  `grid`
 // and `items_per_unit` describe the work split of the first-pass kernel that wrote them.
 hipError_t launch_fold(const Shape &s, int dtype, const LayerOutTable &out, const LseTable &lse, char *ws, const Workspace &w,
-                       int64_t unit0, int nunits, int grid, int items_per_unit, int64_t slot0, hipStream_t st);
+                       int64_t unit0, int nunits, int grid, int items_per_unit, int64_t slot0, const BudgetRows *budgets, hipStream_t st);
 hipError_t launch_attn(const Shape &s, int dtype, const LayerInTable &in, const LayerOutTable &out, const LseTable &lse,
                        char *ws, const Workspace &w, int64_t unit0, int nunits, int grid, int64_t slot0, hipStream_t st);
 // The two passes for few query rows (mixkv_keysplit.hip); `grid` from keysplit_grid.

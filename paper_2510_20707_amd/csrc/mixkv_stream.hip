@@ -322,7 +322,8 @@ __global__ __launch_bounds__(WAVES * 64, stats_waves_per_simd(DT, D, WAVES, TQ))
 //     with the caller's log-sum-exp of the row, b_r = lse_r * log2(e) + log2(G*W) instead;
 //   * the mean normalised key as two rows of 16-byte pieces: row 0 its bf16 head, row 1 the bf16
 //     remainder (zero for f32), piece (c, half) of row r at index (c * 2 + half) * 2 + r;
-//   * the redundancy r (paper Sec. 3.3, Eq. 3-4).
+//   * the redundancy r (paper Sec. 3.3, Eq. 3-4);
+//   * in per-head budget mode the launch's rows of the budget table, on their way to the selection.
 // Workgroup g of the stats grid owned the items [g*T1/G1, (g+1)*T1/G1) and wrote one partial per
 // unit it touched, at slot g + unit_local.  The unit's items are [first, last): the first workgroup
 // touching it is the largest g with g*T1/G1 <= first, the last one the largest g with g*T1/G1 < last.
@@ -332,13 +333,17 @@ __global__ __launch_bounds__(WAVES * 64, stats_waves_per_simd(DT, D, WAVES, TQ))
 // units of some 5 partials 5.5 -> 5.2).
 constexpr int kFoldThreads = 512, kFoldHalf = kFoldThreads / 2, kFoldBatch = 16;
 
-template <int DT, int D>
+struct NoBudgets {};
+template <int DT, int D, class Budgets>
 __global__ __launch_bounds__(kFoldThreads) void fold_kernel(Shape s, LayerOutTable out, LseTable lse, char *ws, Workspace w,
-                                                            int64_t unit0, int nunits, int G1, int ipu, int64_t slot0) {
+                                                            int64_t unit0, int nunits, int G1, int ipu, int64_t slot0, Budgets budgets) {
   constexpr int EPC = Tr<DT>::EPC, NCHK = D / (2 * EPC), NW = kFoldThreads / 64;
   __shared__ float kbar_f[D];
   __shared__ double red_s[NW];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, ul = blockIdx.x;
+  static_assert(kFoldBudgets <= kFoldThreads, "an entry per thread");
+  if constexpr (std::is_same_v<Budgets, BudgetRows>)
+    if (ul == 0 && tid < budgets.n) budgets.dst[tid] = budgets.v[tid];
   const int64_t unit = unit0 + ul;
   const UnitCoord uc = unit_coord(s, ul);
   const int N = s.N, QTR = s.QT * 32;
@@ -783,13 +788,18 @@ static hipError_t launch_attn_t(const Shape &s, const LayerInTable &in, const La
 
 // `grid` workgroups of the first pass split `items_per_unit` items per unit among themselves.
 hipError_t launch_fold(const Shape &s, int dtype, const LayerOutTable &out, const LseTable &lse, char *ws, const Workspace &w,
-                       int64_t unit0, int nunits, int grid, int items_per_unit, int64_t slot0, hipStream_t st) {
-  auto go = [&](auto kern) {
-    hipLaunchKernelGGL(kern, dim3(nunits), dim3(kFoldThreads), 0, st, s, out, lse, ws, w, unit0, nunits, grid, items_per_unit, slot0);
-    return hipGetLastError();
+                       int64_t unit0, int nunits, int grid, int items_per_unit, int64_t slot0, const BudgetRows *budgets, hipStream_t st) {
+  auto go = [&](auto b) {
+    auto with = [&](auto kern) {
+      hipLaunchKernelGGL(kern, dim3(nunits), dim3(kFoldThreads), 0, st, s, out, lse, ws, w, unit0, nunits, grid, items_per_unit, slot0, b);
+      return hipGetLastError();
+    };
+    using Rows = decltype(b);
+    if (dtype == MIXKV_BF16) return s.D == 128 ? with(fold_kernel<MIXKV_BF16, 128, Rows>) : with(fold_kernel<MIXKV_BF16, 64, Rows>);
+    return s.D == 128 ? with(fold_kernel<MIXKV_F32, 128, Rows>) : with(fold_kernel<MIXKV_F32, 64, Rows>);
   };
-  if (dtype == MIXKV_BF16) return s.D == 128 ? go(fold_kernel<MIXKV_BF16, 128>) : go(fold_kernel<MIXKV_BF16, 64>);
-  return s.D == 128 ? go(fold_kernel<MIXKV_F32, 128>) : go(fold_kernel<MIXKV_F32, 64>);
+  // without a table the arguments stay a kilobyte shorter
+  return budgets ? go(*budgets) : go(NoBudgets{});
 }
 
 hipError_t launch_stats(const Shape &s, int dtype, const LayerInTable &in, char *ws, const Workspace &w, int64_t unit0,

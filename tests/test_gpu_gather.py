@@ -3,7 +3,9 @@ bit for bit the source rows, on either side of that rule, with row counts around
 the window alone, everything kept, unequal budgets per head and more heads than a wave has lanes."""
 import numpy as np
 import pytest
+import torch
 
+from paper_2510_20707_amd import binding as B
 from paper_2510_20707_amd import synth
 from tests import harness as H
 
@@ -34,3 +36,31 @@ def test_gathered_rows_of_unequal_budgets(Hkv, B, top):
     lay = synth.make_layer(wl, 0)
     p, outs = H.run_compress(wl, [lay], head_budgets=hb, budget_mode="per_head")
     H.check_layer(wl, lay, p, outs[0], head_budgets=hb[0], budget_mode="per_head", units=[(0, 0), (0, 1)])
+
+
+# The budget table travels with the fold's arguments up to 256 entries per launch, else in a launch of its own: on either side of that,
+# over more layers than one launch takes, the rows are those that the selection alone keeps of the same scores.
+@pytest.mark.parametrize("L,Hkv", [(1, 3), (32, 8), (33, 8), (35, 7), (29, 9), (4, 65)])
+def test_budget_tables_on_either_side_of_the_fold(L, Hkv):
+    N, W, D, Bud = 200, 8, 64, 40
+    print(f"[case] budget table L={L} Hkv={Hkv}", flush=True)
+    rng = np.random.default_rng([11, L, Hkv])
+    hb = rng.integers(W, 2 * Bud - W, size=(L, Hkv)).astype(np.int32)
+    hb[hb.sum(1) > Hkv * Bud] = Bud
+    p = B.make_params("f32", 1, Hkv, Hkv, D, N, W, Bud, budget_mode="per_head", head_budgets=hb)
+    g = torch.Generator(device="cuda:0").manual_seed(5)
+    K, V = (torch.randn((1, Hkv, N, D), generator=g, device="cuda:0") for _ in range(2))
+    Q = torch.randn((1, Hkv, W, D), generator=g, device="cuda:0") / D ** 0.5
+    outs, alone = ([B.alloc_layer_out(p, "cuda:0", scores=True) for _ in range(L)] for _ in range(2))
+    ws = B.alloc_workspace(p, L, "cuda:0")
+    ws.fill_(0xff)                                       # no table is there yet
+    B.mixkv_compress(p, [K] * L, [V] * L, [Q] * L, outs, ws)
+    for a, o in zip(alone, outs):
+        a.scores.copy_(o.scores)
+    B.mixkv_select(p, alone, B.alloc_workspace(p, L, "cuda:0"))
+    torch.cuda.synchronize()
+    for l in range(L):
+        assert outs[l].counts.cpu().numpy().ravel().tolist() == hb[l].tolist()
+        kept = int(hb[l].sum())
+        assert torch.equal(outs[l].indices.view(-1)[:kept], alone[l].indices.view(-1)[:kept])
+        assert torch.equal(outs[l].offsets, alone[l].offsets)
