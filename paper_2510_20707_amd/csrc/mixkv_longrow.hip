@@ -275,7 +275,7 @@ __global__ __launch_bounds__(THREADS) void segmix_kernel(Shape s, LayerInTable i
   const int len = min(SEG, Nc - s0);
   float *scores = O.scores ? O.scores + (int64_t)bh * s.N + s0 : nullptr;
   uint32_t *k_s = reinterpret_cast<uint32_t *>(a_s);
-  uint32_t largest = 0;
+  KeyRange range;
   if constexpr (SELECT) __syncthreads();                // the pooling is done with the raw attention: the order keys replace it
 #pragma unroll
   for (int g = 0; g < EPT / 4; ++g) {
@@ -288,13 +288,13 @@ __global__ __launch_bounds__(THREADS) void segmix_kernel(Shape s, LayerInTable i
       const float c = fmaf(wi, imp, wd * (quotient(d[e] - dmin, dden, rdden) * f_div));              // Eq. 5
       if (scores && li + j < len) scores[li + j] = c;
       k4[j] = li + j < len ? order_key_u(c) : 0u;
-      largest = max(largest, k4[j]);
+      range.add_or_none(k4[j], li + j < len);
     }
     if constexpr (SELECT) *reinterpret_cast<uint4 *>(&k_s[slot4(li)]) = make_uint4(k4[0], k4[1], k4[2], k4[3]);
   }
   if (scores && seg == nseg - 1)
     for (int i = len + tid; i < s.N - s0; i += THREADS) scores[i] = INFINITY;
-  if constexpr (SELECT) thresholds_begin<THREADS>(largest, sc);
+  if constexpr (SELECT) thresholds_begin<THREADS>(range, sc);
   if constexpr (SELECT) __syncthreads();
   if constexpr (SELECT) {
     // the list takes the place of the segment's own share of two rows that have been read
@@ -318,14 +318,14 @@ __global__ __launch_bounds__(THREADS) void segtop_kernel(Shape s, LayerOutTable 
   float a[EPT];
 #pragma unroll
   for (int k = 0; k < EPT; ++k) a[k] = scores[min(k * THREADS + tid, len - 1)];     // all in flight together
-  uint32_t largest = 0;
+  KeyRange range;
 #pragma unroll
   for (int k = 0; k < EPT; ++k) {
     const uint32_t key = order_key_u(a[k]);
-    largest = max(largest, key);                        // past the segment its last score again
+    range.add(key);                                     // past the segment its last score again
     k_s[slot4(k * THREADS + tid)] = key;
   }
-  thresholds_begin<THREADS>(largest, sc);
+  thresholds_begin<THREADS>(range, sc);
   __syncthreads();
   const int keep = head_keep(s, budgets, layer, bh % s.hkv, cand_m);
   int32_t *idx = reinterpret_cast<int32_t *>(ws + w.sdiv) + unit * s.Npad + s0;
@@ -353,17 +353,18 @@ __global__ __launch_bounds__(THREADS) void mergetop_kernel(Shape s, LayerOutTabl
   const int n = per > 0 ? (lists - 1) * per + min(per, s.Nc - (first + lists - 1) * seg) : 0;
   auto at = [&](int e) { const int g = e / per; return g * seg + (e - g * per); };
   const int base = tid * EPT;
-  uint32_t key[EPT], largest = 0;
+  uint32_t key[EPT];
+  KeyRange range;
   if (n > 0) {
 #pragma unroll
     for (int k = 0; k < EPT; ++k) key[k] = lkey[at(min(k * THREADS + tid, n - 1))];  // all in flight together
 #pragma unroll
     for (int k = 0; k < EPT; ++k) {
-      largest = max(largest, key[k]);                   // past the lists the last entry again
+      range.add(key[k]);                                // past the lists the last entry again
       if (k * THREADS + tid < n) k_s[slot4(k * THREADS + tid)] = key[k];
     }
   }
-  thresholds_begin<THREADS>(largest, sc);
+  thresholds_begin<THREADS>(range, sc);
   __syncthreads();
   read_keys<EPT>(k_s, base, n, key);
   auto pos = [&](int e) { return lidx[at(base + e)]; };

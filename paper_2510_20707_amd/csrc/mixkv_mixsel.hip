@@ -174,7 +174,7 @@ __global__ __launch_bounds__(THREADS) void mixsel_kernel(Shape s, LayerOutTable 
   // of s_comp replace it in LDS and come back dealt in consecutive runs of EPT.
   uint32_t *k_s = reinterpret_cast<uint32_t *>(a_s);
   float *scores = O.scores ? O.scores + (int64_t)bh * N : nullptr;
-  uint32_t largest = 0;
+  KeyRange range;
 #pragma unroll
   for (int g0 = 0; g0 < EPT / 4; g0 += GB) {
     float4 vr[GB], dr[GB];
@@ -202,7 +202,7 @@ __global__ __launch_bounds__(THREADS) void mixsel_kernel(Shape s, LayerOutTable 
         const float c = s_comp(a[e4 + j], v4[j], d4[j]);
         if (scores && i + j < Nc) scores[i + j] = c;
         k4[j] = i + j < Nc ? order_key_u(c) : 0u;
-        largest = max(largest, k4[j]);
+        range.add_or_none(k4[j], i + j < Nc);
       }
       if constexpr (SELECT)
         if (i < Nc) *reinterpret_cast<uint4 *>(&k_s[slot4(i)]) = make_uint4(k4[0], k4[1], k4[2], k4[3]);
@@ -211,7 +211,7 @@ __global__ __launch_bounds__(THREADS) void mixsel_kernel(Shape s, LayerOutTable 
   if (scores)
     for (int i = Nc + tid; i < N; i += THREADS) scores[i] = INFINITY;
   if constexpr (!SELECT) return;
-  thresholds_begin<THREADS>(largest, sc);
+  thresholds_begin<THREADS>(range, sc);
   __syncthreads();
   uint32_t key[EPT];
   read_keys<EPT>(k_s, base, Nc, key);
@@ -290,14 +290,15 @@ __global__ __launch_bounds__(THREADS) void topsel_kernel(Shape s, LayerOutTable 
   float c[EPT];
 #pragma unroll
   for (int e = 0; e < EPT; ++e) c[e] = scores[min(e * THREADS + tid, Nc - 1)];      // all in flight together
-  uint32_t largest = 0, key[EPT];
+  uint32_t key[EPT];
+  KeyRange range;
 #pragma unroll
   for (int e = 0; e < EPT; ++e) {
     key[e] = order_key_u(c[e]);
-    largest = max(largest, key[e]);                     // past the row the last score again
+    range.add(key[e]);                                  // past the row the last score again
     if (e * THREADS + tid < Nc) k_s[slot4(e * THREADS + tid)] = key[e];
   }
-  thresholds_begin<THREADS>(largest, sc);
+  thresholds_begin<THREADS>(range, sc);
   __syncthreads();
   read_keys<EPT>(k_s, base, Nc, key);
   const bool cand = cand_m > 0;
@@ -343,7 +344,8 @@ __global__ __launch_bounds__(THREADS) void candsplit_kernel(Shape s, LayerOutTab
   constexpr int STEP = HOLD ? EPT : 16;                 // entries loaded together
   uint32_t key[EPT], pw[HOLD ? EPT : 1];
   // the search sees the entries outside the floors (key 0: not this one)
-  uint32_t floors[EPT / STEP], largest = 0;             // entries that are kept as they are
+  KeyRange range;
+  uint32_t floors[EPT / STEP];             // entries that are kept as they are
 #pragma unroll
   for (int j0 = 0; j0 < EPT; j0 += STEP) {
     uint32_t p[STEP];
@@ -360,13 +362,14 @@ __global__ __launch_bounds__(THREADS) void candsplit_kernel(Shape s, LayerOutTab
     for (int j = 0; j < STEP; ++j) {
       const bool flag = (p[j] & kFloorFlag) != 0;
       floors[j0 / STEP] |= j0 + j < left && flag ? 1u << j : 0u;
-      key[j0 + j] = j0 + j < left && !flag && rest > 0 ? key[j0 + j] : 0u;
-      largest = max(largest, key[j0 + j]);
+      const bool there = j0 + j < left && !flag && rest > 0;
+      key[j0 + j] = there ? key[j0 + j] : 0u;
+      range.add_or_none(key[j0 + j], there);
       if constexpr (HOLD) pw[j] = p[j];
     }
     if constexpr (!HOLD) __builtin_amdgcn_sched_barrier(0);
   }
-  thresholds_begin<THREADS>(largest, sc);
+  thresholds_begin<THREADS>(range, sc);
   __syncthreads();
   const int want[1] = {rest};
   uint32_t tau[1] = {0xffffffffu};

@@ -15,7 +15,8 @@ constexpr int kSurvivors = 128;                      // keys of a boundary bin t
 
 struct MsScratch {
   float f[kMsMaxWaves][8];
-  uint32_t wmax[kMsMaxWaves];            // every wave's largest key
+  uint2 wrange[kMsMaxWaves];             // every wave's KeyRange
+  uint2 bin_range[2][kMsMaxWaves];       // per threshold: every wave's greatest and least distance inside its bin
   int i[kMsMaxWaves], i2[kMsMaxWaves];
   int hist[kBins];
   struct { int bin, k, count; } cut[2];  // per threshold: its bin, the keys still needed of that bin, the keys in it
@@ -108,6 +109,22 @@ __device__ __forceinline__ void hist_add(int *hist, int bin) {
   if (!same || lead) atomicAdd(&hist[bin], lead ? n : 1);
 }
 
+// The same for the lanes with `in` set, merged on the bin of the first of them.
+__device__ __forceinline__ void hist_add(int *hist, int bin, bool in) {
+  const int first = max(__ffsll((long long)__ballot(in)) - 1, 0);         // wave-uniform
+  const bool same = in && bin == __builtin_amdgcn_readlane(bin, first), lead = (int)(threadIdx.x & 63) == first;
+  const int n = __popcll(__ballot(same));
+  if (in && (!same || lead)) atomicAdd(&hist[bin], lead ? n : 1);
+}
+
+// Whether an eighth of the wave's keys with `in` set equal the first of them (or none is set: not known).
+__device__ __forceinline__ bool wave_tied(uint32_t key, bool in) {
+  const unsigned long long on = __ballot(in);
+  const uint32_t k0 = (uint32_t)__builtin_amdgcn_readlane((int)key, max(__ffsll((long long)on) - 1, 0));
+  const int n = __popcll(__ballot(in && key == k0));
+  return on == 0 || (n > 1 && 8 * n >= __popcll(on));
+}
+
 // The bins of sc.hist in which the first k[q] counts end (q < NK; none for k[q] < 1), to sc.cut[Q0 + q].  Ends behind a
 // barrier.
 template <int THREADS, int NK, int Q0 = 0>
@@ -144,27 +161,41 @@ __device__ __forceinline__ int group_sum(int x) {
   return x;
 }
 
-// What the threshold search needs from before a barrier: every wave's largest key and an empty histogram.
+// A thread's largest and smallest key.
+struct KeyRange {
+  uint32_t largest = 0, smallest = 0xffffffffu;
+  __device__ __forceinline__ void add(uint32_t key) { largest = max(largest, key); smallest = min(smallest, key); }
+  // key 0 where there is none
+  __device__ __forceinline__ void add_or_none(uint32_t key, bool there) { largest = max(largest, key); smallest = min(smallest, there ? key : 0xffffffffu); }
+};
+// What the threshold search needs from before a barrier: every wave's range of keys and an empty histogram.
 template <int THREADS>
-__device__ __forceinline__ void thresholds_begin(uint32_t largest_of_thread, MsScratch &sc) {
+__device__ __forceinline__ void thresholds_begin(const KeyRange &r, MsScratch &sc) {
   const int tid = threadIdx.x;
 #pragma unroll
   for (int i = 0; i < kBins / THREADS; ++i) sc.hist[i * THREADS + tid] = 0;
   if (tid < 2) sc.nsurv[tid] = 0;
-  const uint32_t m = wave_reduce<WMax>(largest_of_thread, 0u);
-  if ((tid & 63) == 0) sc.wmax[tid >> 6] = m;
+  const uint32_t m = wave_reduce<WMax>(r.largest, 0u), n = wave_reduce<WMin>(r.smallest, 0xffffffffu);
+  if ((tid & 63) == 0) sc.wrange[tid >> 6] = make_uint2(m, n);
 }
 
 // Thresholds of the want[q] largest of a workgroup's keys (q < NK; want[q] < 1: not asked for, else at most the number of
 // keys): every thread holds EPT keys, 0 where there is none.  The want[q] largest are the keys above tau[q] and, if
 // krem[q] > 0, the first krem[q] (by position) of those equal to it.  thresholds_begin and a barrier come before.
 // The first histogram takes the distance of a key to the largest one in steps of 2^17 (a float's upper six mantissa bits), up
-// to 32 powers of two below it; the keys of a threshold's bin, if they are no more than kSurvivors and not all needed,
-// are listed and ranked by counting, a few lanes to a key; fuller bins and what lies further below are divided by more
-// histograms.
+// to 32 powers of two below it, or in smaller steps if they reach the smallest; the keys of a threshold's bin, if they are no more than
+// kSurvivors and not all needed, are listed and ranked by counting, a few lanes to a key; fuller bins and what lies further below are
+// divided by more histograms.
+// Equal keys: one atomic per key would send all lanes to one word, so the waves merge such counts.  A head of equal keys needs no
+// search; a bin with an eighth of all keys or more is first cut to the range that its keys really have (which ends the search where they
+// are equal), by the waves whose first keys look tied, and those merge their lanes' counts.  Keys that are not tied pay for the look at one
+// key per thread only.
 // Bound: instruction issue (16 waves on one compute unit) and, with few waves, the length of the chain.  A search from the
-// first bit in which the keys differ (their range first, a histogram per eleven bits and threshold, masks of valid keys)
-// took 3 to 6 us more; keys at odds with the fixed steps (all of a head within a few 2^17) take one histogram more here.
+// first bit in which the keys differ (a histogram per eleven bits and threshold, masks of valid keys) took 3 to 6 us more.  us a
+// selection of 28 layers, that search -> one with an atomic per key and no look at the range -> this: 4 heads of 8160, normal scores 11.7 ->
+// 8.3 -> 8.5, all equal 6.3 -> 22 -> 5.6, 1 % twice the others 14.0 -> 22 -> 7.2, four neighbouring values 9.9 -> 17.6 -> 8.5; head-adaptive, 4 heads of
+// 32 000, normal 56 -> 30 -> 29, all equal 29 -> 145 -> 19, 1 % twice the others 69 -> 94 -> 29, all equal but one far above 64 -> 200 -> 25, four
+// neighbouring values 42 -> 110 -> 28.
 constexpr int kFirstShift = 17;
 template <int THREADS, int EPT, int NK>
 __device__ __forceinline__ void radix_thresholds(const uint32_t (&key)[EPT], const int (&want)[NK], MsScratch &sc, uint32_t (&tau)[NK],
@@ -172,9 +203,19 @@ __device__ __forceinline__ void radix_thresholds(const uint32_t (&key)[EPT], con
   constexpr int NW = THREADS / 64, L = THREADS / kSurvivors;        // L lanes to a listed key
   static_assert(kBins % THREADS == 0 && THREADS % kSurvivors == 0, "whole bins and lanes per thread");
   const int tid = threadIdx.x, lane = tid & 63;
-  const uint32_t kmax = read_lane(row_scan_incl<WMax>((lane & 15) < NW ? sc.wmax[lane & 15] : 0u, 0u), 15);
+  const uint2 wr = (lane & 15) < NW ? sc.wrange[lane & 15] : make_uint2(0u, 0xffffffffu);
+  const uint32_t kmax = read_lane(row_scan_incl<WMax>(wr.x, 0u), 15), kmin = read_lane(row_scan_incl<WMin>(wr.y, 0xffffffffu), 15);
+  if (kmax == kmin) {                                    // equal keys: the first ones
 #pragma unroll
-  for (int e = 0; e < EPT; ++e) hist_add(sc.hist, (int)min((kmax - key[e]) >> kFirstShift, (uint32_t)kBins - 1));
+    for (int q = 0; q < NK; ++q) {
+      tau[q] = want[q] < 1 ? 0xffffffffu : kmax;
+      krem[q] = max(want[q], 0);
+    }
+    return;
+  }
+  const int shift1 = min(kFirstShift, max(0, 32 - __clz((int)(kmax - kmin)) - kDigit));
+#pragma unroll
+  for (int e = 0; e < EPT; ++e) hist_add(sc.hist, (int)min((kmax - key[e]) >> shift1, (uint32_t)kBins - 1));
   __syncthreads();
   find_bins<THREADS, NK>(want, sc);
   uint32_t hi[NK], width[NK];                            // a threshold's bin: the keys from hi - width to hi
@@ -187,19 +228,54 @@ __device__ __forceinline__ void radix_thresholds(const uint32_t (&key)[EPT], con
     krem[q] = 0;
     if (want[q] < 1) continue;
     const int bin = sc.cut[q].bin;
-    hi[q] = kmax - ((uint32_t)bin << kFirstShift);
-    width[q] = min(hi[q] - 1, bin == kBins - 1 ? 0xffffffffu : (1u << kFirstShift) - 1);     // keys are at least 1
+    hi[q] = kmax - ((uint32_t)bin << shift1);
+    width[q] = min(hi[q] - kmin, bin == kBins - 1 ? 0xffffffffu : (1u << shift1) - 1);
     krem[q] = sc.cut[q].k;
     count[q] = sc.cut[q].count;
-    if (bin == kBins - 1) count[q] = 0x7fffffff;         // as wide as it gets, and "no key" is counted here: look again
-    while (width[q] > 0 && count[q] > kSurvivors && count[q] != krem[q]) {        // uniform over the workgroup
-      const int shift = max(0, 32 - __clz((int)width[q]) - kDigit);
+    bool wide = bin == kBins - 1;                        // as wide as it gets, and "no key" is counted here: look again
+    while (width[q] > 0 && (wide || (count[q] > kSurvivors && count[q] != krem[q]))) {        // uniform over the workgroup
+      const bool crowd = count[q] > THREADS * EPT / 8;
+      wide = false;
 #pragma unroll
       for (int i = 0; i < kBins / THREADS; ++i) sc.hist[i * THREADS + tid] = 0;
-      __syncthreads();
+      auto inside = [&](int e) { return hi[q] - key[e] <= width[q]; };
+      const bool tied = crowd && wave_tied(key[0], inside(0));
+      if (crowd) {
+        // the range that the bin's keys really have, if every wave looks for it: equal keys are told apart no further
+        uint32_t near = 0, far = width[q];
+        if (tied) {
+          near = 0xffffffffu;
+          far = 0;
 #pragma unroll
-      for (int e = 0; e < EPT; ++e)
-        if (hi[q] - key[e] <= width[q]) atomicAdd(&sc.hist[(hi[q] - key[e]) >> shift], 1);
+          for (int e = 0; e < EPT; ++e) {
+            const uint32_t d = hi[q] - key[e];
+            near = min(near, d);                         // (a key outside the bin is further than `width`)
+            far = max(far, d <= width[q] ? d : 0u);
+          }
+          near = wave_reduce<WMin>(near, 0xffffffffu);
+          far = wave_reduce<WMax>(far, 0u);
+        }
+        if (lane == 0) sc.bin_range[q][tid >> 6] = make_uint2(far, near);
+        __syncthreads();
+        const uint2 br = (lane & 15) < NW ? sc.bin_range[q][lane & 15] : make_uint2(0u, 0xffffffffu);
+        far = read_lane(row_scan_incl<WMax>(br.x, 0u), 15);
+        near = read_lane(row_scan_incl<WMin>(br.y, 0xffffffffu), 15);
+        hi[q] -= near;
+        width[q] = far - near;
+        if (width[q] == 0) break;
+      } else {
+        __syncthreads();
+      }
+      const int shift = max(0, 32 - __clz((int)width[q]) - kDigit);
+      auto bin_of = [&](int e) { return (int)((hi[q] - key[e]) >> shift); };
+      if (tied) {
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) hist_add(sc.hist, bin_of(e), inside(e));
+      } else {
+#pragma unroll
+        for (int e = 0; e < EPT; ++e)
+          if (inside(e)) atomicAdd(&sc.hist[bin_of(e)], 1);
+      }
       __syncthreads();
       const int k1[1] = {krem[q]};
       if (q == 0) find_bins<THREADS, 1, 0>(k1, sc); else find_bins<THREADS, 1, NK - 1>(k1, sc);

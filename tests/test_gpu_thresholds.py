@@ -76,3 +76,45 @@ def test_thresholds_of_the_head_adaptive_split(kind, Nc, Bp, floor, Hkv):
     np.testing.assert_array_equal(off, np.concatenate([[0], np.cumsum(bp + W)]))
     for h in range(Hkv):
         np.testing.assert_array_equal(idx[off[h]:off[h + 1]], O.select_unit(s[0, h, :Nc].astype(np.float64), int(bp[h]), N, W))
+
+
+# Equal scores meet in one bin of a histogram.  Whatever their share of a head, the selection takes no more than twice what it takes on
+# scores that are spread (measured: at most 1.45 times; 3.4 to 6.6 times if every one of them is counted by an atomic of its own).
+@pytest.mark.parametrize("mode,floor", [("fixed", 0), ("adaptive", 128)])
+def test_equal_scores_take_no_longer_than_spread_ones(mode, floor):
+    L, Hkv, Nc, Bp = 28, 4, 32000, 480
+    N, rng, us = Nc + W, np.random.default_rng(63), {}
+    one = np.full((1, Hkv, Nc), 0.25)
+    far = one.copy()
+    far[..., 3] = 1e30
+    kinds = {"spread": rng.standard_normal((1, Hkv, Nc)), "equal": one, "equal but one": far,
+             "two values": np.where(rng.random((1, Hkv, Nc)) < 0.01, 2.0, 1.0), "halves": np.where(rng.random((1, Hkv, Nc)) < 0.5, 2.0, 1.0),
+             "neighbours": 1.5 + rng.integers(0, 4, (1, Hkv, Nc)) * 2.0 ** -23}
+    p = B.make_params("bf16", 1, Hkv, Hkv, 128, N, W, Bp + W, budget_mode=mode, budget_floor=floor)
+    for kind, s in kinds.items():
+        print(f"[case] tied scores {mode} {kind}", flush=True)
+        s = np.concatenate([s.astype(np.float32), np.full((1, Hkv, W), np.inf, dtype=np.float32)], -1)
+        outs = []
+        for _ in range(L):
+            outs.append(B.alloc_layer_out(p, "cuda:0", redundancy=False, gather=False))
+            outs[-1].scores = torch.from_numpy(s).to("cuda:0")
+        ws = B.alloc_workspace(p, L, "cuda:0")
+        stream, graph, calls = torch.cuda.Stream(), torch.cuda.CUDAGraph(), 10
+        stream.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(stream):
+            B.mixkv_select(p, outs, ws)
+        stream.synchronize()
+        with torch.cuda.graph(graph, stream=stream):
+            for _ in range(calls):
+                B.mixkv_select(p, outs, ws)
+        times = []
+        for _ in range(7):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            graph.replay()
+            end.record()
+            end.synchronize()
+            times.append(start.elapsed_time(end) * 1000 / calls)
+        us[kind] = sorted(times)[3]
+    print(us, flush=True)
+    assert max(us.values()) <= 2 * us["spread"], us
