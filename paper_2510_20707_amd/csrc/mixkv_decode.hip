@@ -410,7 +410,8 @@ __global__ __launch_bounds__(D * 2, 2) void decode_mfma_kernel(DShape s, DecodeT
 // decode_wave_kernel (bf16, up to 16 query heads per KV head): a workgroup of four waves per (layer, batch item, KV
 // head, row range), every wave on 32-row tiles of its own.
 //   * Wave w takes the tiles w, w + 4, ...: rows global -> registers (whole rows, coalesced, a tile ahead) -> a private LDS image,
-//     first the keys, then, once their fragments have been read, the values: no barrier before the end.
+//     first the keys, then, once their fragments have been read, the values: no barrier before the end.  One workgroup reads a
+//     row for all of its query heads: non-temporal loads.
 //   * Scores: keys on the output rows of two 16 x 16 x 32 products, query heads on the columns: lane (g = lane % 16, quad) holds
 //     the scores of head g on rows 16 r + 4 quad + i at register 4 r + i.  That order is the contraction index of the second product, so
 //     the weights, split into a bf16 head and a bf16 remainder, feed it as they stand, and the values come transposed out of
@@ -430,7 +431,7 @@ typedef short s16x8 __attribute__((__vector_size__(16)));
 template <int D>
 __device__ __forceinline__ int value_swz(int r) { return D == 128 ? (2 * r) & 15 : r & 6; }
 
-template <int D, bool ONCE>
+template <int D>
 __global__ __launch_bounds__(kDecWaveThreads, 2) void decode_wave_kernel(DShape s, DecodeTable tab, float *part) {
   constexpr int DT = MIXKV_BF16, RB = D * 2, PPR = RB / 16, TILE = 32 * PPR, NL = TILE / 64, RPL = 64 / PPR, NC = D / 32, NS = D / 16, W = 4;
   __shared__ uint4 img_s[W * TILE];
@@ -472,12 +473,12 @@ __global__ __launch_bounds__(kDecWaveThreads, 2) void decode_wave_kernel(DShape 
       const char *tile = compact + (int64_t)tb * RB;
       const uint32_t off = (uint32_t)(lane * 16);
 #pragma unroll
-      for (int j = 0; j < NL; ++j) r[j] = load_vec<ONCE>(tile + j * 1024 + off);
+      for (int j = 0; j < NL; ++j) r[j] = load_vec<true>(tile + j * 1024 + off);
     } else {
 #pragma unroll
       for (int j = 0; j < NL; ++j) {
         const int row = min(tb + j * RPL + lrow, n - 1);
-        r[j] = load_vec<ONCE>((row < cnt ? compact : tail) + (int64_t)row * RB + lq * 16);
+        r[j] = load_vec<true>((row < cnt ? compact : tail) + (int64_t)row * RB + lq * 16);
       }
     }
   };
@@ -689,7 +690,7 @@ template <int D>
 static void launch_decode_mfma(const DShape &s, const DecodeTable &t, int nunits, float *part, hipStream_t st) {
   const dim3 grid((unsigned)(nunits * s.gchunks * s.nsplit)), block(D * 2);
   if (s.G <= kDecWaveHeads) {
-    hipLaunchKernelGGL((decode_wave_kernel<D, true>), grid, dim3(kDecWaveThreads), 0, st, s, t, part);
+    hipLaunchKernelGGL(decode_wave_kernel<D>, grid, dim3(kDecWaveThreads), 0, st, s, t, part);
   } else {
     auto kern = decode_reads_once(s.G, MIXKV_BF16) ? decode_mfma_kernel<D, true> : decode_mfma_kernel<D, false>;
     hipLaunchKernelGGL(kern, grid, block, 0, st, s, t, part);
