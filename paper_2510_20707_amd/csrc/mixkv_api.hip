@@ -104,7 +104,7 @@ static bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 
 // whole chip: so the launch pays where moved / 40 > 4500 + nunits * moved / 5000 (bytes, ns).  Calls, copied inside -> apart,
 // bf16, D = 128: 4 heads of 256 rows 44.4 -> 44.3 us, of 400 41.4 -> 38.8; 8 of 2048 63.9 -> 44.2; 28 of 1024 98.4 -> 91.3; 56 of 1500 158 ->
 // 142; 112 of 2048 259 -> 235 (240 with the copy inside as it is now).
-static bool gather_apart(const Shape &s, int eb, int max_head_rows, int64_t nunits) {
+bool gather_apart(const Shape &s, int eb, int max_head_rows, int64_t nunits) {
   const int64_t moved = (int64_t)max_head_rows * s.D * eb * 4;
   return moved * (125 - nunits) > (int64_t)4500 * 5000;
 }

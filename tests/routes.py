@@ -1,4 +1,4 @@
-"""Which kernels a call's streaming passes go to: the library's own dispatch rules, asked on the host (no GPU).  They are
+"""Which kernels a call's streaming passes, its gather and a decoding step go to: the library's own dispatch rules, asked on the host (no GPU).  They are
 C++ functions inside libmixkv.so; the shape they take is filled in by the library and never looked into here."""
 import ctypes as C
 
@@ -41,3 +41,9 @@ def decode_reads_once(heads_per_group: int, dtype: str):
 def few_rows_read_once(p: B.MixkvParams, n_layers: int):
     """Whether the two passes for few query rows load keys and values non-temporally."""
     return bool(_function("_ZN5mixkv13keysplit_onceERKNS_5ShapeEii", C.c_void_p, C.c_int, C.c_int)(_shape(p), p.dtype, n_layers * p.batch * p.n_kv_heads))
+
+
+def gathers_apart(p: B.MixkvParams, n_layers: int, most_rows: int):
+    """Whether the rows that a fused selection keeps (of the best-endowed head: `most_rows`) are copied by a kernel behind it."""
+    apart = _function("_ZN5mixkv12gather_apartERKNS_5ShapeEiil", C.c_void_p, C.c_int, C.c_int, C.c_int64)
+    return bool(apart(_shape(p), 2 if p.dtype == B.DTYPE["bf16"] else 4, most_rows, n_layers * p.batch * p.n_kv_heads))

@@ -233,3 +233,28 @@ def test_bf16_split_on_less_than_the_largest_workspace():
         B.mixkv_decode_attention(p, caches, None, [q], 0, workspace=torch.empty(least - 4, dtype=torch.uint8, device="cuda:0"))
     assert e.value.status == B.MIXKV_ERR_WORKSPACE_TOO_SMALL
     assert (outs[0] - outs[1]).abs().max() <= 2.0 ** -7 * outs[0].abs().max()      # one bf16 rounding either side
+
+
+# Rows whose scores are -inf (a masked key: -inf in an element where every query is positive) have no weight, wherever they lie: the first rows of
+# all, whole 32-row tiles, everything that one wave or one row range takes, the tail.
+@pytest.mark.parametrize("dtype,D,G,Bud,tail_len", [("bf16", 128, 4, 200, 9), ("bf16", 64, 16, 300, 40), ("bf16", 128, 3, 1100, 0), ("bf16", 128, 17, 200, 9),
+                                                    ("f32", 64, 4, 200, 9)])
+@pytest.mark.parametrize("masked", ["scattered", "tiles", "front", "all but one"])
+def test_rows_of_no_weight(dtype, D, G, Bud, tail_len, masked):
+    print(f"[case] decode -inf rows {dtype} D={D} G={G} B={Bud} tail={tail_len} {masked}", flush=True)
+    Hkv, n = 2, Bud + tail_len
+    rng = np.random.default_rng([82, D, G, Bud])
+    off = {"scattered": rng.random(n) < 0.3, "tiles": np.arange(n) // 32 % 4 != 2, "front": np.arange(n) < Bud - 3, "all but one": np.arange(n) != n - 5}[masked]
+    t = lambda *shape: torch.from_numpy(rng.standard_normal(shape)).to(B.TORCH_DTYPE[B.DTYPE[dtype]])  # noqa: E731
+    K, V, q = t(1, Hkv, n, D), t(1, Hkv, n, D), t(1, Hkv * G, D)
+    q[..., 7] = q[..., 7].abs() + 0.5
+    K[:, :, torch.from_numpy(off), 7] = -np.inf
+    p = B.make_params(dtype, 1, Hkv * G, Hkv, D, Bud, 8, Bud)
+    dev = lambda x: x.contiguous().to("cuda:0")  # noqa: E731
+    cache = B.LayerOut(counts=torch.full((1, Hkv), Bud, dtype=torch.int32, device="cuda:0"), K_out=dev(K[:, :, :Bud]), V_out=dev(V[:, :, :Bud]))
+    tails = [(dev(K[:, :, Bud:]), dev(V[:, :, Bud:]))] if tail_len else None
+    got = B.mixkv_decode_attention(p, [cache], tails, [dev(q)], tail_len)[0].cpu().double()
+    for h in range(Hkv):
+        want = torch.softmax(p.softmax_scale * (q[0, h * G:(h + 1) * G].double() @ K[0, h].double().t()), -1) @ V[0, h].double()
+        err = (got[0, h * G:(h + 1) * G] - want).abs().amax(-1) / want.abs().amax(-1)
+        assert err.max() <= TOL[dtype], float(err.max())

@@ -13,9 +13,15 @@ pytestmark = pytest.mark.gpu
 WL = synth.WORKLOADS
 
 
-@pytest.mark.parametrize("dtype,D,N,W,Hkv,B", [
-    ("bf16", 128, 700, 8, 2, 8), ("bf16", 128, 700, 8, 2, 64), ("bf16", 64, 700, 8, 2, 129), ("f32", 128, 700, 8, 2, 33),     # inside
-    ("bf16", 128, 900, 8, 2, 900), ("f32", 64, 3000, 16, 1, 2900), ("bf16", 64, 9000, 8, 1, 1031), ("f32", 128, 2500, 8, 3, 511)])   # apart
+# dtype, D, N, W, Hkv, B
+INSIDE = [("bf16", 128, 700, 8, 2, 8), ("bf16", 128, 700, 8, 2, 64), ("bf16", 64, 700, 8, 2, 129), ("f32", 128, 700, 8, 2, 33)]
+APART = [("bf16", 128, 900, 8, 2, 900), ("f32", 64, 3000, 16, 1, 2900), ("bf16", 64, 9000, 8, 1, 1031), ("f32", 128, 2500, 8, 3, 511)]
+# Hkv, B, rows of the best-endowed head
+TABLE_INSIDE = [(3, 40, 90), (66, 30, 400), (66, 30, 60)]
+TABLE_APART = [(3, 900, 1900), (66, 60, 1500)]
+
+
+@pytest.mark.parametrize("dtype,D,N,W,Hkv,B", INSIDE + APART)
 def test_gathered_rows_of_equal_budgets(dtype, D, N, W, Hkv, B):
     print(f"[case] gather {dtype} D={D} N={N} W={W} Hkv={Hkv} B={B}", flush=True)
     wl = WL["c2"].with_(name="gather", dtype=dtype, head_dim=D, seq_len=N, window=W, n_q_heads=Hkv, n_kv_heads=Hkv, budget=B,
@@ -25,7 +31,7 @@ def test_gathered_rows_of_equal_budgets(dtype, D, N, W, Hkv, B):
     H.check_layer(wl, lay, p, outs[0])
 
 
-@pytest.mark.parametrize("Hkv,B,top", [(3, 40, 90), (3, 900, 1900), (66, 30, 400), (66, 30, 60)])
+@pytest.mark.parametrize("Hkv,B,top", TABLE_INSIDE + TABLE_APART)
 def test_gathered_rows_of_unequal_budgets(Hkv, B, top):
     N, W = 2000, 8
     print(f"[case] gather per head Hkv={Hkv} B={B} top={top}", flush=True)

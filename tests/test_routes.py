@@ -4,6 +4,7 @@ import pytest
 
 from paper_2510_20707_amd import binding as B
 from tests import routes
+from tests import test_gpu_gather as gather
 
 UNITS = 1024
 
@@ -60,3 +61,11 @@ def test_keys_that_the_second_pass_reads_again_stay_cached(dtype, d, alone):
         assert routes.few_rows_read_once(make(500, "vnorm"), 8) == (mb > 180), mb
     units = round(200e6 / (400 * row * 8))               # short heads
     assert not routes.few_rows_read_once(B.make_params(dtype, units, 1, 1, d, 400, 32, 64, intrinsic="none"), 8)
+
+
+def test_gather_cases_are_on_the_side_that_they_are_meant_for():
+    for want, cases, tables in ((False, gather.INSIDE, gather.TABLE_INSIDE), (True, gather.APART, gather.TABLE_APART)):
+        for dtype, d, n, w, hkv, budget in cases:
+            assert routes.gathers_apart(B.make_params(dtype, 1, hkv, hkv, d, n, w, budget), 1, budget) == want, (dtype, d, budget)
+        for hkv, budget, top in tables:
+            assert routes.gathers_apart(B.make_params("bf16", 1, hkv, hkv, 64, 2000, 8, budget), 1, top) == want, (hkv, top)
