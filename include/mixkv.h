@@ -270,10 +270,13 @@ mixkv_status mixkv_similarity(const mixkv_params *params, const mixkv_rows_in *i
  * the dtype of the inputs (bf16: rounded to nearest even).  All pointers are DEVICE pointers, rows
  * 16-byte aligned; K_tail / V_tail may be NULL when tail_len is 0, offsets when the layout is fixed.
  * counts / offsets are clamped to the capacity of the layout before use.
- * Workspace: long caches (more than 384 rows per head at params->budget + tail_len) are split over
- * several workgroups per head whose partial results pass through `workspace`:
- * mixkv_decode_workspace_size bytes (0 for short caches, then NULL is accepted), 256-byte aligned,
- * no initialisation.
+ * Workspace: long caches (by the rows per head, params->budget + tail_len: more than 384 in fp32, 512 or
+ * more in bf16 if few heads share the GPU) are split over several workgroups per head whose partial
+ * results pass through `workspace`: mixkv_decode_workspace_size bytes (0 for caches that are not split,
+ * then NULL is accepted), 256-byte aligned, no initialisation.  In bf16 a smaller workspace may be
+ * accepted (MIXKV_ERR_WORKSPACE_TOO_SMALL if not): the rows are then split into fewer ranges, which
+ * takes longer and sums in another order, so that outputs may differ in their last bit from those
+ * with the full workspace.  With the same arguments, sizes included, outputs repeat bit for bit.
  */
 typedef struct {
   const void *K_cache, *V_cache;
