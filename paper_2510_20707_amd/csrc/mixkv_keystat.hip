@@ -15,7 +15,9 @@
 //   * The matrix instructions run half a tile ahead of the weights, an eighth (D = 64: a quarter) of them beside each: fma, exp2 and add of a
 //     half tile are issued while the next half's scores are formed.
 //   * Query rows lie a piece apart in LDS, so that a tile's fragments are one address and immediates.
-// 448 heads of 32768 keys, 7 query tiles, us: queries on the rows, matrix and vector work taking turns 993; keys on the rows 973;
+// Bound: issue, at the clock that the card's power leaves.  448 heads of 32768 keys, 7 query tiles: 1.61 GHz (a copy runs at 2.37); of the
+// SIMDs' clocks the matrix units are busy in 54 %, the vector units in 70 %, one or the other in 90 %; 3.8 GB from memory at 3.9 TB/s.
+// The same launch, us: queries on the rows, matrix and vector work taking turns 993; keys on the rows 973;
 // half a tile ahead 909 (2649 -> 2595 the call: the card holds its power, and the first pass then runs 1 % slower).  28 chunks of
 // 128 keys per compute unit: 8 tiles 88.8 -> 79.4, 7 82.0 -> 78.1, 4 58.7 -> 55.9, 3 54.9 -> 55.2; 64-element heads, 16 tiles 97.5 -> 89.0, 4
 // 40.2 -> 37.9.
@@ -278,26 +280,30 @@ __global__ __launch_bounds__(kKstThreads, 2) void kst_attn_kernel(Shape s, Layer
   }
 }
 
+// The lines below were drawn for an earlier form of this kernel (queries on the output rows); the figures are of the kernel as it is, each of a
+// call for the scores.  Where it is taken it is at most 6 % behind attn_kernel (the shortest heads of a line, 16 to 24 chunks per compute unit); the
+// lines leave up to 9 % at short heads (64 elements, 9 tiles, 384 keys), more only under the limit for the last round.
 // From sixteen 128-key chunks per compute unit on (64 KB of queries are staged per workgroup and run): 7 query tiles, 8192 keys per
-// head, old -> this, us: 3.5 chunks per unit 9.4 -> 11.9, 14 chunks 45 -> 48, 28 chunks 80 -> 73; 4 query tiles: 8 chunks 21.4 -> 21.9, 16
-// chunks 36.7 -> 35.7, 32 chunks 67 -> 64.
+// head, attn_kernel -> this, us: 3.5 chunks per unit 54 -> 55, 8 chunks 71 -> 73, 14 chunks 121 -> 117, 40 chunks 261 -> 257; 4 query tiles: 3.5
+// chunks 47 -> 48, 8 chunks 62 -> 62, 14 chunks 101 -> 98, 40 chunks 224 -> 214.
 // A wave takes whole 64-key blocks: not where the last round of them would leave more than a tenth of the time idle (112 heads of 7013 keys,
-// 6.02 blocks a wave: 170 us a call with attn_kernel, 172 with this).
+// 7 tiles, 6.02 blocks a wave: 175 us with either; 18 chunks per compute unit, 4.5 blocks a wave, heads of 2048 keys and more: 8 tiles 1.06 times
+// as fast as attn_kernel, 2 to 7 tiles 0.99 to 1.05; 64 elements, 9 to 16 tiles 1.10 to 1.22, 3 to 8 tiles 1.02 to 1.09).
 // A run ends with its head, so that short heads pay the staging and a last round of the eight waves again and again: time of a call with
-// attn_kernel over that with this, 16 to 56 chunks per compute unit, by keys per head:
+// attn_kernel over that with this, 16 to 56 chunks per compute unit in whole rounds, by keys per head:
 //   128 elements   512          1024         1536         2048         4096         8192
-//     8 tiles      0.99-1.04    1.02-1.07    1.05-1.09    1.04-1.11    1.08-1.11    1.09-1.10
-//     7            0.89-0.93    0.92-0.97    0.95-0.99    0.95-0.99    0.98-1.01    1.00-1.01
-//     4 to 6       0.91-0.97    0.92-1.01    0.98-1.04    0.98-1.05    1.00-1.08    1.01-1.09
-//     2, 3         0.92-0.98    0.92-1.01    0.96-1.02    0.97-1.04    0.96-1.02    0.97-1.02 (below 24 chunks 0.96-0.98)
+//     8 tiles      0.97-0.98    0.97-1.01    0.99-1.05    1.04-1.05    1.06         1.06-1.08
+//     7            0.88-0.92    0.92-0.95    0.93-1.00    0.99-1.01    1.01-1.02    1.02-1.04
+//     4 to 6       0.88-0.96    0.91-1.00    0.94-1.03    1.00-1.06    0.99-1.07    1.01-1.08
+//     2, 3         0.90-0.96    0.90-1.01    0.95-1.01    0.97-1.03    0.97-1.03    0.97-1.03 (below 24 chunks 0.97-0.98)
 //   64 elements
-//     9 to 16      1.04-1.17    1.05-1.20    1.08-1.22    1.07-1.22    1.09-1.23    1.08-1.23 (384 keys 0.91-1.00)
-//     3 to 8       0.93-0.98    0.97-1.03    1.00-1.05    0.99-1.07    1.02-1.09    1.03-1.10
-// Between those lengths the last round counts (blocks of 64 keys a head; 18, 28, 40, 60 chunks per compute unit):
-//   64 elements, 16 tiles: 8 blocks 1.02 1.06 1.07 1.08; 9 0.92 0.93 0.97 0.97; 10 0.96 0.97 1.00 1.01; 11 1.01 1.00 1.01 1.03; 17 1.04 1.02 1.05 1.06
-//     13 tiles: 9 blocks 0.95 0.97 0.99 1.00; 10 0.98 1.00 1.03 1.03; 12 tiles: 9 blocks 0.97 0.98 1.01 1.03; 9 tiles: 9 blocks 1.04 1.06 1.09 1.10
-//   128 elements, 6 tiles: 25 blocks 0.97 0.96 1.00 1.00; 28 0.99 0.99 1.02 1.03; 30 0.94 0.97 1.02 1.00; 31 1.03 1.01 1.04 1.03
-//     4 and 5 tiles: 24 to 28 blocks 0.98-1.06
+//     9 to 16      1.07-1.17    1.07-1.18    1.07-1.23    1.09-1.24    1.10-1.23    1.11-1.24 (384 keys 0.95-1.09)
+//     3 to 8       0.89-0.96    0.95-1.01    0.94-1.04    1.01-1.07    1.01-1.06    1.02-1.07
+// Between those lengths the last round counts (blocks of 64 keys a head; 20, 28, 40, 56 chunks per compute unit):
+//   64 elements, 16 tiles: 9 blocks 1.02 0.99 1.01 1.01; 10 1.03 1.02 1.03 1.03; 11 1.05 1.02 1.06 1.06; 17 1.07 1.06 1.08 1.08
+//     13 tiles: 9 blocks 1.04 1.01 1.03 1.04; 10 1.05 1.04 1.05 1.05; 12 tiles: 9 blocks 1.06 1.03 1.05 1.05; 9 tiles: 9 blocks 1.13 1.08 1.11 1.12
+//   128 elements, 6 tiles: 25 blocks 1.00 0.99 0.99 1.00; 28 0.98 1.00 1.01 1.01; 30 0.97 0.98 0.99 1.01; 31 0.98 0.99 1.01 1.01
+//     4 and 5 tiles: 25 and 28 blocks 0.98-1.04
 // (attn_kernel computes whole slots of 4, 8 or 16 query tiles, and the mean key costs it extra where none is spare: 4, 8, 16.)
 bool keystat_supported(const Shape &s, int dtype, int nunits, int num_cus) {
   if (dtype != MIXKV_BF16 || s.QT > (s.D == 128 ? 8 : 16)) return false;
