@@ -11,8 +11,8 @@
 // Bound: the instructions of a workgroup's 4 to 16 waves and the length of their chain (112 workgroups use less than half of the
 // chip); past 16 384 candidates the loads of four rows too.  All of a thread's loads in flight together, keys formed as
 // they are dealt, whole groups through LDS, one search of six barriers for both thresholds, us a launch before and now:
-// 2 heads of 504 11.6 -> 8.9, 4 of 4064 13.4 -> 11.1, 112 of 8160 18.5 -> 16.3, 256 of 16 128 49.7 -> 43.3, 448 of 32 736
-// 137 -> 103 (head-adaptive lists).
+// 2 heads of 504 11.6 -> 7.6, 4 of 4064 13.4 -> 10.9, 112 of 8160 18.5 -> 15.9, 256 of 16 128 49.7 -> 40.6, 448 of 32 736
+// 137 -> 97 (head-adaptive lists).
 //
 // Paper: Sec. 3.2 Eq. 2 (importance = attention + scaled value norm), Sec. 3.3 (min-max and mean
 // matching of the diversity, Eq. 5 mix), Sec. 3.1 / Algorithm 1 (TopB with B' = B - W); Sec. 4.3 /
@@ -274,7 +274,7 @@ __global__ __launch_bounds__(THREADS) void mixsel_kernel(Shape s, LayerOutTable 
 // their order keys through the padded LDS row to their consecutive-range owners) and selects from registers as
 // above: the head's final rows in fixed and per-head mode, or with cand_m > 0 its best cand_m
 // candidates with their keys for the head-adaptive split (Sec. 3.1 / Algorithm 1, TopB).  112 heads of 8160, 1536 candidates
-// and a floor each: 14.9 -> 9.0 us with the search of mixkv_topsel.h as it is now.
+// and a floor each: 14.9 -> 9.2 us with the search of mixkv_topsel.h as it is now.
 template <int THREADS, int EPT>
 __global__ __launch_bounds__(THREADS) void topsel_kernel(Shape s, LayerOutTable out, char *ws, CandLists cl, int64_t unit0,
                                                            int cand_m, const int32_t *budgets) {
@@ -364,11 +364,13 @@ __global__ __launch_bounds__(THREADS) void candsplit_kernel(Shape s, LayerOutTab
       floors[j0 / STEP] |= j0 + j < left && flag ? 1u << j : 0u;
       const bool there = j0 + j < left && !flag && rest > 0;
       key[j0 + j] = there ? key[j0 + j] : 0u;
-      range.add_or_none(key[j0 + j], there);
+      if constexpr (HOLD) range.add_or_none(key[j0 + j], there);
+      else range.largest = max(range.largest, key[j0 + j]);
       if constexpr (HOLD) pw[j] = p[j];
     }
     if constexpr (!HOLD) __builtin_amdgcn_sched_barrier(0);
   }
+  if constexpr (!HOLD) range.smallest = 1;              // keys are at least that; the smallest of 64 per thread took 1.9 us of 54 to find
   thresholds_begin<THREADS>(range, sc);
   __syncthreads();
   const int want[1] = {rest};
@@ -487,7 +489,7 @@ hipError_t launch_topsel(const Shape &s, const LayerOutTable &out, char *ws, con
 // item) with all entries in registers, or, past 64 of them per thread, streamed from memory.  As many threads as there
 // are groups of four entries, up to 1024: a wave's instructions are what takes the time (4 lists of 1536 entries: 1024 threads
 // of 8 7.4 us, 512 of 16 8.6; with lists that shared a thread and branches on every entry 13.2).  64 of them against the stream, the
-// selection's whole call: 8 lists of 5344 entries 126 -> 58 us, of 7744 161 -> 68, 28 layers of those 176 -> 88.
+// selection's whole call: 8 lists of 5344 entries 126 -> 58 us, of 7744 161 -> 67, 28 layers of those 176 -> 85.
 template <int THREADS, int EPT>
 static hipError_t launch_candsplit_e(const Shape &s, const LayerOutTable &out, char *ws, const CandLists &cl, int64_t unit0,
                                      int grid, int cand_m, hipStream_t st) {
