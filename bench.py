@@ -42,8 +42,8 @@ MFMA_BF16_PEAK = 2.5e15
 # the profiled command (default workload, budget and variant, three copies) and unchanged sources.
 PROFILED_TRAFFIC = {
     "sources": ["mixkv_stream.hip", "mixkv_stream.h", "mixkv_keystat.hip"],
-    "sources_sha256": "a92bd9a899d02a028fa3a908012497bf2d59ae1921a3eaac1d3baa971b8969f4",
-    "kernels": {"stats": ("stats_kernel<bf16,128,8,1>", 513.8e6), "attn": ("kst_attn_kernel<128,8>", 276.0e6)},
+    "sources_sha256": "007d8d8bbdd77aefee3453c9900b14fdc7ab857a2e26030437718fa526dc3c7b",
+    "kernels": {"stats": ("stats_kernel<bf16,128,8,1>", 513.7e6), "attn": ("kst_attn_kernel<128,8>", 275.9e6)},
 }
 
 

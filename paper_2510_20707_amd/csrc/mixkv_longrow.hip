@@ -12,10 +12,10 @@
 //
 // Bound: HBM (four rows of floats per key, read by the statistics and again by the mix; the diversity and the
 // intrinsic score stay in registers from then on).  One 130 688-token prompt of 28 layers and 4 KV heads (234 MB of
-// rows, budget 128, head-adaptive): statistics 38 us (6.2 TB/s), mix and lists 76, merge 23, split 8.6 (44, 82, 31 and 8.8 before
+// rows, budget 128, head-adaptive): statistics 37 us (6.3 TB/s), mix and lists 65, merge 20, split 5.9 (44, 82, 31 and 8.8 before
 // the loads of a thread were in flight together and the search took six barriers).  One workgroup
 // per head for the mix and one per layer for the selection left most of the chip idle: 784 + 2 583 us.
-// At 32 768 tokens (448 heads) mixsel_kernel, which holds a whole head, takes 103 us, and the three kernels took no less than it.
+// At 32 768 tokens (448 heads) mixsel_kernel, which holds a whole head, takes 97 us, and the three kernels took no less than it.
 //
 // Paper: Sec. 3.2 Eq. 2, Sec. 3.3 Eq. 5, Sec. 3.1 / Algorithm 1 (TopB), as in mixsel_kernel.
 #include <cfloat>
@@ -402,9 +402,9 @@ static int round_group(int keep, int nseg) {
 // (beyond that its one workgroup per head is the longer half); failing that the largest that fit it.  Longer lists, of up
 // to half of what a workgroup holds, are merged in rounds.  Beyond that one workgroup ranks whole rows
 // (select_adaptive_kernel: all heads' rows of a batch item), which took these, too: selection alone, head-adaptive, us before ->
-// after: 130 688 tokens, 4 heads, budget 1200 1856 -> 86, 28 layers of them 2399 -> 146, budget 960 (one merge of 29 696 entries) 2396 -> 100;
-// 8 heads, budget 600 3671 -> 174; 14 layers of 131 072 tokens, 8 heads, budget 2048 4603 -> 884; 60 000 tokens, 8 heads, budget 2048
-// 1691 -> 376.
+// after: 130 688 tokens, 4 heads, budget 1200 1856 -> 84, 28 layers of them 2399 -> 142, budget 960 (one merge of 29 696 entries) 2396 -> 54;
+// 8 heads, budget 600 3671 -> 110; 14 layers of 131 072 tokens, 8 heads, budget 2048 4603 -> 873; 60 000 tokens, 8 heads, budget 2048
+// 1691 -> 372.
 SegPlan plan_segments(const Shape &s, int keep) {
   SegPlan best{0, 0, 0, 0};
   for (int seg : {4096, 8192, 16384}) {
