@@ -420,7 +420,8 @@ __global__ __launch_bounds__(D * 2, 2) void decode_mfma_kernel(DShape s, DecodeT
 // Bound: HBM for long caches, one chain of memory round trips for short ones.  decode_mfma_kernel has all its waves form
 // every score tile and meet at a barrier per tile, and half of its 32 columns are empty up to 16 heads.  us a step, decode_mfma_kernel ->
 // here, with the merge: 4 heads of 81 rows 6.3 -> 5.1, 112 of 81 7.2 -> 5.8, 256 of 1089 31.8 -> 25.3 (5.6 TB/s), of unequal length 36.7 ->
-// 29.5, 384 of 2148 81.9 -> 68 (6.2 TB/s), 112 of 2065 rows of 64 elements 22.4 -> 15.3.  178 registers for rows of 128 elements: two
+// 29.5, 384 of 2148 81.9 -> 68 (6.2 TB/s), 112 of 2065 rows of 64 elements 22.4 -> 15.3; slower only with
+// 16 query heads on some 16 rows, 5.9 -> 6.3.  178 registers for rows of 128 elements: two
 // workgroups per compute unit (three spill, and were 5 % slower).
 // ------------------------------------------------------------------------------------------------
 constexpr int kDecWaveHeads = 16, kDecWaveThreads = 256;
